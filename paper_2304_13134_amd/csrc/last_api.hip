@@ -16,6 +16,8 @@
 #include "fused_kernels.hpp"
 #include "fused_numerator_kernels.hpp"
 #include "probe_kernels.hpp"
+#include "trigram_kernels.hpp"
+#include "marginals_kernels.hpp"
 #include <algorithm>
 
 #include <atomic>
@@ -596,6 +598,147 @@ last_status_t launch_fused_backward(const Shape& s, const FusedPlan& p, const Fu
     return hip_status();
 }
 
+// Geometry of the clustered path for full 2-gram contexts (trigram_kernels.hpp).  It takes every shape its
+// tiles hold (3 to 64 labels), whatever the batch: measured against one workgroup per item with marginals,
+// B=1 T=8 V=3 39 / 53 us, B=8 T=300 V=8 0.31 / 1.9 ms, B=1024 T=50 V=8 (64 items one after the other on
+// every cluster) 0.50 / 1.4 ms, B=8 T=300 V=32 0.71 / 34 ms, distance B=8 T=200 V=50 0.44 / 19 ms.
+// Of two shapes of workgroup the one with fewer rounds over the batch is taken: the wide one handles twice
+// the labels, so that half as many make a cluster, at 2.9 instead of 1.9 us a frame (V=32).
+struct TriPlan {
+    bool ok;
+    int dims;            // index into the instantiations below
+    int nb, K, ncl, G, xs, roles, grid;
+    size_t lds;
+};
+
+// workgroups of 8 waves, two of them exchanging (128 states a workgroup), or of 16 and four (256)
+typedef TriDims<8, 2, 2, 5> Tri0;       // up to 19 labels
+typedef TriDims<8, 2, 3, 9> Tri1;       // up to 35
+typedef TriDims<8, 2, 4, 11> Tri2;      // up to 42 (43: three labels a workgroup no longer fit)
+typedef TriDims<16, 4, 3, 9> Tri3;      // up to 35
+typedef TriDims<16, 4, 6, 17> Tri4;     // up to 64
+
+constexpr size_t kTriRowBytes = (size_t)24 << 20;   // most that the rows of a call without marginals may take
+
+TriPlan tri_plan(const Shape& s, int kind, bool trop)
+{
+    TriPlan best{};
+    if (opt(LAST_OPT_FORCE_SOLO) || !chip_takes_clusters()) return best;
+    if (kind != LAST_WEIGHTS_DENSE || s.order != 2 || s.V < 3 || s.V > kTriMaxV || s.T < 1) return best;
+    long long fewest = 0;
+    auto consider = [&](int dims, auto DD) {
+        typedef decltype(DD) D;
+        if (s.V > D::MaxV) return;
+        TriPlan p{};
+        p.dims = dims;
+        p.roles = trop ? 1 : 2;
+        p.nb = std::min(s.V, D::NCM * kWave / s.V);
+        p.K = (s.V + p.nb - 1) / p.nb;
+        p.nb = (s.V + p.K - 1) / p.K;                       // evenly over the workgroups, each with at least one
+        p.K = (s.V + p.nb - 1) / p.nb;
+        if (p.roles * p.K > 32 || p.K * D::NCM > kWave) return;
+        p.ncl = std::min((s.B + 7) / 8, 32 / (p.roles * p.K));
+        const int cq = (p.nb * s.V1 + 3) / 4;
+        p.G = std::min(std::min(D::CT / cq, s.V1), kTriMaxG);
+        if (p.G < 1 || p.G * D::NR < s.V1) return;          // every row of the frame has a thread
+        if (p.nb * s.V1 + 1 > D::NP * D::CT / 4 || p.nb * s.V1 + 1 > D::States || p.nb >= 32) return;
+        p.xs = s.V * s.V + s.V + p.K * D::NCM;
+        p.grid = 8 * p.ncl * p.roles * p.K;
+        const size_t fwd = (size_t)2 * kTriMaxG * 4 * cq;
+        const size_t bwd = (size_t)(p.nb + 1) * D::BtPitch + 3 + (size_t)s.V1 * 4 * cq + kTriPad;
+        p.lds = std::max(fwd, trop ? (size_t)0 : bwd) * sizeof(float);
+        if (p.lds > kBigLds - 16384) return;
+        p.ok = true;
+        const long long rounds = (s.B + 8 * p.ncl - 1) / (8 * p.ncl);
+        if (!best.ok || rounds < fewest) { best = p; fewest = rounds; }
+    };
+    consider(0, Tri0());
+    if (!best.ok) consider(1, Tri1());
+    if (!best.ok) consider(2, Tri2());
+    consider(3, Tri3());
+    if (!best.ok) consider(4, Tri4());
+    return best;
+}
+
+struct TriWs {
+    float *alpha, *beta;
+    double *offa, *offb, *D2;
+    u64* x;
+    size_t xwords;
+    int* fail;
+};
+
+// keep: rows of all frames (marginals follow); otherwise one row per item.  Tropical: final scores only.
+TriWs carve_tri(Carver& cv, const Shape& s, const TriPlan& p, bool trop, bool keep)
+{
+    TriWs c{};
+    const size_t rows = (size_t)s.B * (keep ? s.T + 1 : 1);
+    c.alpha = cv.take<float>(rows * s.C);
+    c.beta = trop ? nullptr : cv.take<float>(rows * s.C);
+    c.offa = trop ? nullptr : cv.take<double>(rows);
+    c.offb = trop ? nullptr : cv.take<double>(rows);
+    c.D2 = trop ? nullptr : cv.take<double>((size_t)s.B);
+    c.xwords = (size_t)8 * p.ncl * p.roles * 2 * p.xs;
+    c.x = cv.take<u64>(c.xwords);
+    c.fail = cv.take<int>((size_t)s.B);
+    return c;
+}
+
+// the call without marginals: its rows must stay small enough for the static scratch array too
+bool tri_rows_fit(const Shape& s) { return (size_t)s.B * s.C * 2 * sizeof(float) <= kTriRowBytes; }
+
+last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const float* w, const int* lengths,
+                         bool trop, bool keep, int* bp, hipStream_t st)
+{
+    hipLaunchKernelGGL(tri_clear_kernel, dim3(64), dim3(256), 0, st, c.x, c.xwords, c.fail, s.B);
+    TriArgs a;
+    a.w = w; a.len = lengths; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb;
+    a.bp = bp; a.x = c.x; a.fail = c.fail;
+    a.B = s.B; a.T = s.T; a.V = s.V; a.C = s.C;
+    a.nb = p.nb; a.K = p.K; a.ncl = p.ncl; a.G = p.G; a.xs = p.xs; a.roles = p.roles;
+    a.keep = keep; a.spin_limit = opt(LAST_OPT_SPIN_LIMIT);
+    last_status_t rc = LAST_OK;
+    auto go = [&](auto k, int threads) {
+        rc = allow_lds((const void*)k, kBigLds - 16384);
+        if (rc == LAST_OK) hipLaunchKernelGGL(k, dim3(p.grid), dim3(threads), p.lds, st, a);
+    };
+    auto pick = [&](auto DD) {
+        typedef decltype(DD) D;
+        if (trop) go(trigram_kernel<D, true>, D::NW * kWave);
+        else go(trigram_kernel<D, false>, D::NW * kWave);
+    };
+    switch (p.dims) {
+    case 0: pick(Tri0()); break;
+    case 1: pick(Tri1()); break;
+    case 2: pick(Tri2()); break;
+    case 3: pick(Tri3()); break;
+    default: pick(Tri4()); break;
+    }
+    return rc;
+}
+
+// marginals of all frames from the stored rows (marginals_kernels.hpp)
+template <int ORDER>
+last_status_t launch_marginals(const Shape& s, const float* w, const int* lengths, const float* alpha, const float* beta,
+                               const double* offa, const double* offb, const double* D2, const last_grads_t* out,
+                               hipStream_t st)
+{
+    const size_t lds = (size_t)2 * s.C * sizeof(float);
+    int rows = std::max(1, kMgChunk / s.V1);
+    const int parts = (s.C + rows - 1) / rows;
+    rows = (s.C + parts - 1) / parts;
+    last_status_t rc = LAST_OK;
+    auto go = [&](auto k) {
+        if (lds > kMaxLds) rc = allow_lds((const void*)k, kBigLds);
+        if (rc == LAST_OK)
+            hipLaunchKernelGGL(k, dim3(parts, s.T, s.B), dim3(kMgThreads), lds, st, w, lengths, make_ctx(s), s.T, rows,
+                               alpha, beta, offa, offb, D2, out->dw, out->scale);
+    };
+    if (out->accumulate) go(dense_marginals_kernel<ORDER, true>);
+    else go(dense_marginals_kernel<ORDER, false>);
+    return rc;
+}
+
 // streaming tropical kernel for the full 1-gram context dependency (129 <= C <= 264); false: not applicable
 bool launch_bigram_viterbi(const Shape& s, const float* w, const int* lengths, int* bp, int* final_state,
                            float* score, int* item_status, hipStream_t st)
@@ -796,8 +939,9 @@ int32_t last_kernel_variant(const last_weights_t* weights, const last_context_t*
         return (op_ok && fused_plan(s, weights).ok) ? 2 : -1;
     }
     if (op == LAST_OP_SHORTEST_DISTANCE || op == LAST_OP_ARC_POSTERIORS)
-        return cluster_plan(s, weights->kind).ok ? 1 : 0;
-    if (op == LAST_OP_SHORTEST_PATH) return viterbi_plan(s, weights->kind).ok ? 1 : 0;
+        return cluster_plan(s, weights->kind).ok || tri_plan(s, weights->kind, false).ok ? 1 : 0;
+    if (op == LAST_OP_SHORTEST_PATH)
+        return viterbi_plan(s, weights->kind).ok || tri_plan(s, weights->kind, true).ok ? 1 : 0;
     return 0;
 }
 
@@ -830,14 +974,23 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
     carve_table_flag(cv, s);
     const ClusterPlan plan = cluster_plan(s, weights->kind);
     const ViterbiPlan vplan = viterbi_plan(s, weights->kind);
+    const TriPlan tplan = tri_plan(s, weights->kind, false), tvplan = tri_plan(s, weights->kind, true);
     switch (op) {
     case LAST_OP_SHORTEST_DISTANCE:
         if (plan.ok) carve_cluster(cv, s, plan);
         else cv.take<double>(1);
         if (vplan.ok) cv.take<u64>(vplan.xwords);        // tropical semiring: exchange buffer
+        if (tri_rows_fit(s) && (tplan.ok || tvplan.ok)) {
+            // one semiring or the other: the larger of the two
+            Carver log(nullptr), trop(nullptr);
+            if (tplan.ok) carve_tri(log, s, tplan, false, false);
+            if (tvplan.ok) carve_tri(trop, s, tvplan, true, false);
+            cv.take<char>(std::max(log.used, trop.used));
+        }
         break;
     case LAST_OP_ARC_POSTERIORS:
         if (plan.ok) carve_cluster(cv, s, plan);
+        else if (tplan.ok) carve_tri(cv, s, tplan, false, true);
         else carve_posteriors(cv, s);
         break;
     case LAST_OP_INTERSECT_REFERENCE:
@@ -855,6 +1008,7 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
     }
     case LAST_OP_SHORTEST_PATH:
         carve_path(cv, s, vplan.ok ? vplan.xwords : 0);
+        if (tvplan.ok) carve_tri(cv, s, tvplan, true, false);
         break;
     default:
         return 0;
@@ -901,6 +1055,20 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         Carver cv(ws);
         const ClusterWs cw = carve_cluster(cv, s, plan);
         launch_cluster<false>(s, plan, cw, weights->w, lengths, dist, item_status, nullptr, 1.f, 0, st);
+    } else if (const TriPlan tp = tri_plan(s, weights->kind, semiring == LAST_TROPICAL); tp.ok && tri_rows_fit(s)) {
+        const bool trop = semiring == LAST_TROPICAL;
+        Carver cv(ws);
+        cv.take<double>(1);
+        const TriWs tw = carve_tri(cv, s, tp, trop, false);
+        rc = launch_tri(s, tp, tw, weights->w, lengths, trop, false, nullptr, st);
+        if (rc != LAST_OK) return rc;
+        if (trop)
+            hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, lengths,
+                               (const int*)tw.fail, s.T, s.C, (int*)nullptr, dist, item_status);
+        else
+            hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, (const float*)tw.beta,
+                               (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, s.T, s.C, 0,
+                               (double*)nullptr, dist, item_status);
     } else if (semiring == LAST_LOG) {
         if (l.lds_forward > kMaxLds) return LAST_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(solo_forward_log, dim3(s.B), dim3(1024), l.lds_forward, st,
@@ -955,6 +1123,17 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
         launch_cluster<true>(s, plan, cw, weights->w, lengths, dist, item_status, out->dw, out->scale,
                              out->accumulate, st);
         return hip_status();
+    }
+    if (const TriPlan tp = tri_plan(s, weights->kind, false); tp.ok) {
+        Carver cvt(ws);
+        const TriWs tw = carve_tri(cvt, s, tp, false, true);
+        rc = launch_tri(s, tp, tw, weights->w, lengths, false, true, nullptr, st);
+        if (rc != LAST_OK) return rc;
+        hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, (const float*)tw.beta,
+                           (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, s.T, s.C, 1,
+                           tw.D2, dist, item_status);
+        rc = launch_marginals<2>(s, weights->w, lengths, tw.alpha, tw.beta, tw.offa, tw.offb, tw.D2, out, st);
+        return rc != LAST_OK ? rc : hip_status();
     }
     const SoloLayout l = solo_layout(s);
     if (l.lds_forward > (s.order == 0 ? kBigLds : kMaxLds)) return LAST_ERR_UNSUPPORTED;
@@ -1275,7 +1454,8 @@ last_status_t last_shortest_path(const last_weights_t* weights, const int32_t* l
     hipStream_t st = (hipStream_t)hip_stream;
     const SoloLayout l = solo_layout(s);
     const ViterbiPlan vp = viterbi_plan(s, weights->kind);
-    if (!vp.ok && l.lds_viterbi > (s.order == 0 ? kBigLds : kMaxLds)) return LAST_ERR_UNSUPPORTED;
+    const TriPlan tp = tri_plan(s, weights->kind, true);
+    if (!vp.ok && !tp.ok && l.lds_viterbi > (s.order == 0 ? kBigLds : kMaxLds)) return LAST_ERR_UNSUPPORTED;
     const Ctx c = make_ctx(s);
     Carver cv(ws);
     int* flag = carve_table_flag(cv, s);
@@ -1286,7 +1466,13 @@ last_status_t last_shortest_path(const last_weights_t* weights, const int32_t* l
         if (rc != LAST_OK) return rc;
     } else if (vp.ok)
         launch_cluster_viterbi(s, vp, p.xv, weights->w, lengths, p.bp, p.final_state, score, item_status, st);
-    else if (!launch_bigram_viterbi(s, weights->w, lengths, p.bp, p.final_state, score, item_status, st))
+    else if (tp.ok) {
+        const TriWs tw = carve_tri(cv, s, tp, true, false);
+        rc = launch_tri(s, tp, tw, weights->w, lengths, true, false, p.bp, st);
+        if (rc != LAST_OK) return rc;
+        hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, lengths,
+                           (const int*)tw.fail, s.T, s.C, p.final_state, score, item_status);
+    } else if (!launch_bigram_viterbi(s, weights->w, lengths, p.bp, p.final_state, score, item_status, st))
         hipLaunchKernelGGL(solo_viterbi, dim3(s.B), dim3(1024), l.lds_viterbi, st, weights->w, lengths,
                            c, s.T, l.CPAD, l.R, p.bp, p.final_state, score, item_status);
     const int cthreads = s.C < 256 ? (s.C + 63) / 64 * 64 : 256;

@@ -1,0 +1,94 @@
+// Arc marginals (Eq. 1 of arXiv 2304.13134) of the complete lattice from stored
+// state vectors, for any context dependency: the whole chip streams over the
+// frames, nothing is serial.
+//   alpha, beta [B][T+1][C] base-2 logs, relative to the float64 offsets
+//   offa, offb  [B][T+1];  D2 [B] base-2 log of the partition sum
+//   dw[b][t][q][y] (+)= scale 2^(alpha_t[q] + w log2 e + beta_{t+1}[next(q,y)] + (offa_t + offb_{t+1} - D2))
+// Bound: HBM, 4 bytes read and 4 written per arc.  A workgroup takes a stretch of rows of one frame, keeps
+// its two state vectors in LDS (the row offset of the destinations with them) and goes through the stretch with
+// 16-byte accesses on 16-byte boundaries of memory; rows are V+1 floats, so a piece may span rows.
+#pragma once
+#include "cluster_kernels.hpp"
+#include "common.hpp"
+
+namespace last {
+
+constexpr int kMgThreads = 256;
+constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
+
+// ORDER 1, 2: closed form; 0: next-state table.  LDS: float[C] alpha + exponent | float[C] beta.
+template <int ORDER, bool ACC>
+__global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
+    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int rows,
+    const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
+    const double* __restrict__ offb, const double* __restrict__ D2, float* __restrict__ dw, float scale)
+{
+    extern __shared__ float mg_s[];
+    float* al = mg_s;
+    float* be = mg_s + c.C;
+    const int t = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int q0 = blockIdx.x * rows, q1 = min(q0 + rows, c.C);
+    const size_t first = (((size_t)b * T + t) * c.C + q0) * c.V1;
+    const int n = (q1 - q0) * c.V1;
+    const int L = len[b];
+    float* g = dw + first;
+    const float* wt = w + first;
+    // pieces of four that start on a 16-byte boundary of dw; up to three arcs before them
+    const int lead = min((int)((4 - ((size_t)g >> 2)) & 3), n);
+    const int n4 = (n - lead) / 4;
+    if (L < 0 || L > T || t >= L) {
+        if (ACC) return;
+        for (int i = tid; i < n4; i += kMgThreads) *(float4*)(g + lead + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (tid < lead) g[tid] = 0.f;
+        for (int i = lead + 4 * n4 + tid; i < n; i += kMgThreads) g[i] = 0.f;
+        return;
+    }
+    {
+        const size_t ra = (size_t)b * (T + 1) + t;
+        const float K = (float)(offa[ra] + offb[ra + 1] - D2[b]);
+        for (int q = tid; q < c.C; q += kMgThreads) {
+            if (q >= q0 && q < q1) al[q] = alpha[ra * c.C + q] + K;
+            be[q] = beta[(ra + 1) * c.C + q];
+        }
+    }
+    __syncthreads();
+    auto arc = [&](int q, int y, float x) __attribute__((always_inline)) {
+        int d = q;
+        if (y > 0) {
+            if (ORDER == 1) d = y;
+            else if (ORDER == 2) d = (q == 0 ? 0 : ((q - 1) % c.V + 1) * c.V) + y;
+            else d = ctx_next(c, q, y);
+        }
+        return scale * fast_exp2(fmaf(x, kLog2e, al[q] + be[d]));
+    };
+    for (int i = tid; i < n4; i += kMgThreads) {
+        const int e = lead + 4 * i;
+        struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
+        const f4 x = *(const f4*)(wt + e);
+        int q = q0 + e / c.V1, y = e - (q - q0) * c.V1;
+        float o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            o[k] = arc(q, y, x.v[k]);
+            const bool wrap = ++y == c.V1;
+            q += wrap;
+            y = wrap ? 0 : y;
+        }
+        float4* p = (float4*)(g + e);
+        if (ACC) {
+            const float4 old = *p;
+            *p = make_float4(old.x + o[0], old.y + o[1], old.z + o[2], old.w + o[3]);
+        } else {
+            *p = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    }
+    const int rest = n - lead - 4 * n4;
+    if (tid < lead + rest) {
+        const int e = tid < lead ? tid : lead + 4 * n4 + (tid - lead);
+        const int q = q0 + e / c.V1, y = e - (q - q0) * c.V1;
+        const float o = arc(q, y, wt[e]);
+        if (ACC) g[e] += o; else g[e] = o;
+    }
+}
+
+}  // namespace last

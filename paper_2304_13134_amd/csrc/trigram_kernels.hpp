@@ -1,0 +1,741 @@
+// Full 2-gram contexts with dense weights: the recursions of Eq. 2 (arXiv
+// 2304.13134) in both directions and the tropical one (Section 4.2.3), each
+// item and direction on a cluster of K workgroups of one XCD.
+//
+// With the states written as q = a V + b (b the last label 1..V, a the label
+// before it, a = 0 for a history of one label, q = 0 the empty history) the
+// label arcs out of the V+1 states with last label b lead to b V + y and
+// nowhere else.  Workgroup k owns nb last labels, i.e. for every a a
+// contiguous run of nb rows (nb (V+1) floats) of each frame:
+//   forward : new[b V + y] = (+)_a cur[a V + b] w[a V + b][y] needs own rows only;
+//   backward: new[a V + b] = (+)_y w[a V + b][y] nxt[b V + y] likewise;
+// and the V x V transpose between "produced for (b, y)" and "owned by y" is
+// the one exchange per frame, through the XCD's L2 (tagged 64-bit words, see
+// cluster_kernels.hpp).  The empty label keeps the state and needs none.
+//
+// Everything is in the log domain (base 2, float32 relative to a float64
+// offset per frame, the offset being the largest entry of the frame), so there is no limit on
+// the dynamic range of the weights; the tropical recursion adds float32 scores
+// and keeps (score, source) exactly as solo_viterbi does.
+//
+// What bounds it: the chain of a frame.  Own rows -> partial sums (compute
+// waves) -> barrier -> combine and publish (exchange waves) -> L2 round trip
+// -> own states -> barrier.  Weights are requested four rows' worth at a time with
+// 16-byte loads two frames (backward: three) ahead by waves that never wait
+// for an exchange; the exchange waves issue no weight loads, because a wave's
+// loads return in order and a look at the exchange would queue behind them.
+// Forward and backward pass run at the same time on different compute units.
+// Arc marginals are formed afterwards from the stored state vectors by
+// dense_marginals_kernel, which streams at memory speed on the whole chip;
+// forming them inside the recursion would put the stores on the chain to save
+// 4 of 16 bytes per arc.
+//
+// Measured (8 items, 300 frames, 32 labels): forward and backward pass 1.9 us a
+// frame, marginals at 5.6 TB/s; last_arc_posteriors 0.71 ms against 34 ms with
+// one workgroup per item (solo_kernels.hpp), shortest path 0.53 against 4.2 ms.
+// What made the difference between 3.0 and 1.9 us a frame is that every weight
+// request and store is issued on every path (the waits for the weights can then
+// be counted; a condition around one of them turns them into waits for all) and
+// that the exchange waves read all partial results in one batch.
+#pragma once
+#include "cluster_kernels.hpp"
+#include "common.hpp"
+#include "numerator_kernels.hpp"
+#include "solo_kernels.hpp"
+
+namespace last {
+
+struct TriArgs {
+    const float* w;
+    const int* len;
+    float* alpha;        // log: rows of C floats (base-2 logs); tropical: final scores [B][C]
+    float* beta;
+    double* offa;        // offsets of the rows
+    double* offb;
+    int* bp;             // tropical: [B][T][C] flat arc indices (may be null)
+    u64* x;              // exchange slots [clusters][roles][2][xs]
+    int* fail;           // [B] set when a workgroup gave up waiting
+    int B, T, V, C;
+    int nb, K, ncl, G, xs;
+    int roles;           // 2: forward and backward, 1: forward only
+    int keep;            // 1: every row is stored at [b][T+1][C]; 0: only the meeting row at [b][C]
+    int spin_limit;
+};
+
+// row of the state vectors at which the two directions are joined into the distance
+__host__ __device__ inline int tri_meet(int L, bool keep) { return keep ? L : L / 2; }
+
+constexpr int kTriMaxV = 64;
+constexpr int kTriPad = 72;      // floats behind the tile that a row's lanes may read
+constexpr int kTriMaxG = 12;     // row groups whose partial results the exchange waves combine
+
+// NW waves of which NCM exchange and the rest compute, nb V <= 64 NCM; NR: 16-byte pieces of a frame per
+// compute thread; EPL: elements of a row per lane in the backward direction (four lanes a row, two rows a lane)
+template <int NW_, int NCM_, int NR_, int EPL_>
+struct TriDims {
+    static constexpr int NW = NW_, NCM = NCM_, NR = NR_, EPL = EPL_;
+    static constexpr int CT = (NW - NCM) * kWave;              // compute threads
+    static constexpr int NP = 2;
+    static constexpr int MaxV = 4 * EPL - 1 < kTriMaxV ? 4 * EPL - 1 : kTriMaxV;
+    static constexpr int States = NCM * kWave + 32;            // own states, the start state
+    static constexpr int BtPitch = (4 * EPL) | 1;              // odd: neighbouring labels start in other banks
+};
+
+__device__ __forceinline__ float tri_lse2(float x, float y)     // log2(2^x + 2^y)
+{
+    const float m = fmaxf(x, y), lo = fminf(x, y);
+    const float d = m == LAST_NEG_INF ? 0.f : lo - m;
+    return m + __builtin_amdgcn_logf(1.f + fast_exp2(d));
+}
+
+__device__ __forceinline__ float4 tri_load4(buf_t r, unsigned voff, unsigned soff)      // 4-byte aligned
+{
+    typedef decltype(__builtin_amdgcn_raw_buffer_load_b128(r, 0, 0, 0)) b128_t;
+    return __builtin_bit_cast(float4, (b128_t)__builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+
+template <int CTRL>
+__device__ __forceinline__ float tri_quad(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float tri_quad_max(float v)
+{
+    v = fmaxf(v, tri_quad<0xB1>(v));     // lanes 1,0,3,2
+    return fmaxf(v, tri_quad<0x4E>(v));  // lanes 2,3,0,1
+}
+__device__ __forceinline__ float tri_quad_sum(float v)
+{
+    v += tri_quad<0xB1>(v);
+    return v + tri_quad<0x4E>(v);
+}
+
+// One look after the other at this lane's word (and, with HEAD, at one header word) until the tags are
+// right in every lane of the wave; false when the bound is reached.
+template <bool HEAD, bool TAG16>
+__device__ __forceinline__ bool tri_poll(const u64* wp, const u64* hp, bool act, unsigned tag, int limit,
+                                         u64& word, u64& head)
+{
+    for (int n = 0; n <= limit; ++n) {
+        word = xload(wp);
+        if (HEAD) head = xload(hp);
+        bool ok = TAG16 ? (unsigned)(word >> 48) == (tag & 0xffffu) : (unsigned)(word >> 32) == tag;
+        ok = ok || !act;
+        if (HEAD) ok = ok && (unsigned)(head >> 32) == tag;
+        if (__all(ok)) return true;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
+}
+
+// what the two directions share: which part of the lattice a workgroup owns, and its pieces of a frame
+struct TriOwn {
+    int V, V1, k, b0, nbk;       // own last labels b0 .. b0 + nbk - 1
+    int W, CQ, G;                // floats and 16-byte pieces of a row run, row groups
+    int rows;                    // own states with at least one label: (V + 1) nbk
+};
+
+// static LDS of either direction
+template <typename D>
+struct TriLds {
+    float own[D::States + 32];                 // own states, [a nbk + i]; the start state at [rows]; then nbk times -inf
+    float bl[D::States];                       // forward: empty-label candidates; backward: the new states
+    float strow[2][4 * 17 + 4];                // the start state's row of weights
+    float xl[D::NCM * kWave + kTriMaxV];       // exchange of a single workgroup (K = 1)
+    int xa[D::NCM * kWave];
+    int flat[D::States];                       // tropical: backpointers of the frame
+    double off;                                // offset of the own states
+    float hd[8];
+    int dead;
+};
+
+// a lane that must not store gets an offset outside the descriptor; every store is issued on every path, so that
+// the waits for prefetched weights can be counted
+constexpr unsigned kTriOut = 0xfffffff0u;
+
+template <typename D, bool TROP>
+__device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, int b, int L, unsigned& gstep,
+                                            u64* xbase, TriLds<D>& s, float* dyn)
+{
+    constexpr int NCM = D::NCM;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));     // (what one direction derives from it is not kept in registers through the other)
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool comm = wave < NCM;
+    const int V = o.V, V1 = o.V1, nbk = o.nbk, P = 4 * o.CQ;
+    float* pm = dyn;                            // [kTriMaxG][P] partial maxima (tropical: scores)
+    float* ps = dyn + kTriMaxG * P;             // [kTriMaxG][P] partial sums   (tropical: source a, as int)
+    const size_t fr = (size_t)o.V1 * a.C;
+    const float* wi = a.w + (size_t)b * a.T * fr;
+    const int steps = TROP || a.keep ? L : tri_meet(L, false);
+
+    for (int r = tid; r < D::States + 32; r += D::NW * kWave) s.own[r] = r == o.rows ? 0.f : LAST_NEG_INF;
+    for (int i = tid; i < kTriMaxG * P; i += D::NW * kWave) {      // groups that do not exist stay neutral
+        pm[i] = LAST_NEG_INF;
+        ps[i] = TROP ? __int_as_float(0xffff) : 0.f;
+    }
+    if (tid == 0) { s.dead = 0; s.off = 0.0; }
+    __syncthreads();
+
+    if (!comm) {
+        const int ct = tid - NCM * kWave;
+        const int g = ct / o.CQ, cq = ct - g * o.CQ;
+        const bool act = g < o.G;
+        const int gc = act ? g : 0;
+        const int col0 = min(4 * cq, o.W - 4);
+        int iC[4], cB = 0, iB = 0;
+        bool hasB = false;                                     // one of the four columns is an empty label's (V >= 3)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            iC[c] = (col0 + c) / V1;
+            if (act && col0 + c == iC[c] * V1) { hasB = true; cB = c; iB = iC[c]; }
+        }
+        // pieces n = 0 .. nl - 1 of a thread are rows g + G n of every frame, piece nl may be past the last row
+        // (its states then read -inf), pieces beyond nl repeat it
+        const int nl = V / o.G, rl = gc + o.G * nl;
+        const unsigned off0 = 4u * (unsigned)((gc * V + o.b0) * V1 + col0), offL = 4u * (unsigned)((min(rl, V) * V + o.b0) * V1 + col0);
+        const unsigned stoff = 4u * (unsigned)min(lane, V), frb = 4u * (unsigned)fr;
+        const int dOff = 4 * o.G * V * V1;
+        const int base0 = gc * nbk, dBase = o.G * nbk, baseN = o.rows + 1;
+        const int baseL = rl <= V ? rl * nbk : baseN;
+        auto base = [&](int n) __attribute__((always_inline)) { return n < nl ? base0 + n * dBase : n == nl ? baseL : baseN; };
+        // own states -> a row in memory: compute thread <-> own state, the start state from the first workgroup
+        const bool rok = ct < o.rows || (ct == o.rows && o.k == 0);
+        const int rS = min(ct, o.rows);
+        const unsigned rq = rok ? 4u * (unsigned)(ct < o.rows ? (ct / nbk) * V + o.b0 + ct % nbk : 0) : kTriOut;
+        const unsigned oq = ct == 0 && o.k == 0 ? 0u : kTriOut;
+        const unsigned rowb = (unsigned)a.C * 4u;
+        auto store_row = [&](int t, bool on) __attribute__((always_inline)) {
+            const size_t row = !TROP && a.keep ? (size_t)b * (a.T + 1) + t : (size_t)b;
+            buf_store(s.own[rS], make_buf(a.alpha + row * a.C, on ? rowb : 0u), rq, 0);
+            if (!TROP) nw_store64(s.off, make_buf(a.offa + row, on ? 8u : 0u), oq, 0);
+        };
+        float4 wv[2][D::NR];
+        float st[2] = {0.f, 0.f}, st64[2] = {0.f, 0.f};
+        auto issue = [&](auto S, int t) __attribute__((always_inline)) {
+            const buf_t rs = make_buf(wi + (size_t)min(t, L - 1) * fr, frb);
+#pragma unroll
+            for (int n = 0; n < D::NR; ++n)
+                wv[decltype(S)::value][n] = tri_load4(rs, n < nl ? off0 : offL, (unsigned)(n < nl ? n * dOff : 0));
+            st[decltype(S)::value] = buf_load(rs, stoff, 0);
+            if (D::MaxV == 64) st64[decltype(S)::value] = buf_load(rs, 4u * (unsigned)V, 0);
+        };
+        auto start_row = [&](auto S) __attribute__((always_inline)) {
+            constexpr int Z = decltype(S)::value;
+            if (wave == D::NW - 1) {
+                if (lane <= V) s.strow[Z][lane] = st[Z];
+                if (D::MaxV == 64) s.strow[Z][V] = st64[Z];
+            }
+        };
+        if (steps > 0) {
+            issue(std::integral_constant<int, 0>(), 0);
+            issue(std::integral_constant<int, 1>(), 1);
+            start_row(std::integral_constant<int, 0>());
+        }
+        __syncthreads();
+        auto frame = [&](auto S, int t) __attribute__((always_inline)) {
+            constexpr int Z = decltype(S)::value;
+            if (!TROP) store_row(t, a.keep);
+            else if (t > 0) buf_store(__int_as_float(s.flat[rS]), make_buf(a.bp + ((size_t)b * a.T + t - 1) * a.C, a.bp ? rowb : 0u), rq, 0);
+            float m[4], z[4];
+            int src[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { m[c] = LAST_NEG_INF; z[c] = 0.f; src[c] = 0xffff; }
+            // at most three rows at a time (registers)
+#pragma unroll
+            for (int n0 = 0; n0 < D::NR; n0 += 3) {
+                constexpr int N3 = D::NR < 3 ? D::NR : 3;
+                float q[N3][4], mo[4];
+#pragma unroll
+                for (int n = 0; n < N3; ++n)
+                    if (n0 + n < D::NR) {
+                        const int bs = base(n0 + n);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) q[n][c] = s.own[bs + iC[c]];
+                    }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) mo[c] = m[c];
+#pragma unroll
+                for (int n = 0; n < N3; ++n) {
+                    if (n0 + n >= D::NR) continue;
+                    const float4 w4 = wv[Z][n0 + n];
+                    const float wc[4] = {w4.x, w4.y, w4.z, w4.w};
+                    float xB = LAST_NEG_INF;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float x = TROP ? __fadd_rn(q[n][c], wc[c]) : fmaf(wc[c], kLog2e, q[n][c]);
+                        q[n][c] = x;
+                        xB = c == cB ? x : xB;
+                        if (TROP) {
+                            const bool up = x > m[c];          // (ascending a: the first maximum stays)
+                            m[c] = up ? x : m[c];
+                            src[c] = up ? gc + o.G * (n0 + n) : src[c];
+                        } else {
+                            m[c] = fmaxf(m[c], x);
+                        }
+                    }
+                    const int bs = base(n0 + n);
+                    if (hasB && bs <= o.rows) s.bl[bs + iB] = xB;
+                }
+                if (!TROP) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float mm = m[c] == LAST_NEG_INF ? 0.f : m[c];
+                        if (n0 > 0) z[c] *= fast_exp2(mo[c] - mm);
+#pragma unroll
+                        for (int n = 0; n < N3; ++n)
+                            if (n0 + n < D::NR) z[c] += fast_exp2(q[n][c] - mm);
+                    }
+                }
+            }
+            if (act) {
+                *(float4*)(pm + g * P + 4 * cq) = make_float4(m[0], m[1], m[2], m[3]);
+                if (TROP) *(int4*)(ps + g * P + 4 * cq) = make_int4(src[0], src[1], src[2], src[3]);
+                else *(float4*)(ps + g * P + 4 * cq) = make_float4(z[0], z[1], z[2], z[3]);
+            }
+            lds_only_barrier();                                                   // B
+            if (a.K == 1) lds_only_barrier();
+            // (the exchange is under way) start row of the next frame, weights of the frame after it
+            start_row(std::integral_constant<int, Z ^ 1>());
+            issue(S, t + 2);
+            lds_only_barrier();                                                   // A
+        };
+        for (int t = 0; t < steps; t += 2) {
+            frame(std::integral_constant<int, 0>(), t);
+            if (t + 1 < steps) frame(std::integral_constant<int, 1>(), t + 1);
+        }
+        store_row(steps, true);
+        if (TROP && steps > 0)
+            buf_store(__int_as_float(s.flat[rS]), make_buf(a.bp + ((size_t)b * a.T + steps - 1) * a.C, a.bp ? rowb : 0u), rq, 0);
+    } else {
+        // published state (b0 + i, y) of this lane and the word of its own state (ga, b0 + gi)
+        const int lidx = wave * kWave + lane;
+        const bool act = lidx < nbk * V;
+        const int pi = act ? lidx / V : 0, py = act ? lidx - pi * V + 1 : 1;
+        const int col = pi * V1 + py;
+        const int slot = col + (col >= 4 * (o.CQ - 1) ? P - o.W : 0);
+        const int ga = act ? lidx / nbk + 1 : 1, gi = act ? lidx - (ga - 1) * nbk : 0;
+        const int grow = ga * nbk + gi;                                           // own row of the gathered state
+        const int gidx = (ga - 1) * V + (o.b0 - 1 + gi);
+        const bool second = wave == 0 && lane <= nbk;                             // histories of one label, the start state
+        const bool single = wave == 0 && lane < nbk;
+        const int nh = a.K * NCM;
+        const int hidx = V * V + V + (lane < nh ? lane : 0);
+        bool dead = false;
+        double A = 0.0;
+        __syncthreads();
+        for (int t = 0; t < steps; ++t) {
+            u64* xs = xbase + (size_t)(gstep & 1) * a.xs;
+            const unsigned tag = gstep + 1;
+            gstep += 1;
+            lds_only_barrier();                                                   // B
+            float val = LAST_NEG_INF, m[kTriMaxG], z[kTriMaxG];
+            int src = 0xffff;
+#pragma unroll
+            for (int g = 0; g < kTriMaxG; ++g) m[g] = pm[g * P + slot];
+#pragma unroll
+            for (int g = 0; g < kTriMaxG; ++g) z[g] = ps[g * P + slot];
+            const float blr = s.bl[grow];
+            const float w0 = s.strow[t & 1][single ? o.b0 + lane : 0], start = s.own[o.rows], sbr = s.bl[single ? lane : 0];
+#pragma unroll
+            for (int g = 0; g < kTriMaxG; ++g) val = fmaxf(val, m[g]);
+            if (TROP) {
+#pragma unroll
+                for (int g = 0; g < kTriMaxG; ++g) src = min(src, m[g] == val ? __float_as_int(z[g]) : 0xffff);
+                if (val == LAST_NEG_INF) src = 0xffff;
+            } else {
+                const float mm = val == LAST_NEG_INF ? 0.f : val;
+                float zz = 0.f;
+#pragma unroll
+                for (int g = 0; g < kTriMaxG; ++g) zz += z[g] * fast_exp2(m[g] - mm);
+                val = val == LAST_NEG_INF ? LAST_NEG_INF : val + __builtin_amdgcn_logf(zz);
+            }
+            const float blg = act ? blr : LAST_NEG_INF;
+            // histories of one label: from the start state, or kept by the empty label; the start state: kept
+            const float sn = !second ? LAST_NEG_INF : TROP ? __fadd_rn(start, w0) : fmaf(w0, kLog2e, start);
+            const float sb = single ? sbr : LAST_NEG_INF;
+            float head = LAST_NEG_INF;
+            u64 word = 0, hw = 0;
+            if (a.K == 1) {
+                if (!TROP) head = wave_max_dpp(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), fmaxf(sn, sb)));
+                if (act) { s.xl[lidx] = val; s.xa[lidx] = src; }
+                if (lane == 0) s.hd[wave] = head;
+                lds_only_barrier();
+                const int wl = (ga - 1) * V + gi;                                 // (b0 = 1)
+                val = s.xl[act ? wl : 0];
+                src = s.xa[act ? wl : 0];
+                head = s.hd[lane < NCM ? lane : 0];
+            } else {
+                u64* mine = xs + (size_t)(o.b0 - 1) * V + lidx;
+                if (act) xpublish(mine, TROP ? (u64)__float_as_uint(val) | ((u64)(unsigned)src << 32) | ((u64)(tag & 0xffffu) << 48)
+                                             : pack_word(val, tag));
+                if (!TROP) {
+                    head = wave_max_dpp(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), fmaxf(sn, sb)));
+                    if (lane == 0) xpublish(xs + V * V + V + o.k * NCM + wave, pack_word(head, tag));
+                }
+                if (!dead) dead = !tri_poll<!TROP, TROP>(xs + gidx, xs + hidx, act, tag, a.spin_limit, word, hw);
+                val = __uint_as_float((unsigned)word);
+                src = (int)((word >> 32) & 0xffffu);
+                head = __uint_as_float((unsigned)hw);
+            }
+            if (TROP) {
+                // the label candidate against the empty label: higher score, then lower arc
+                auto keep = [&](float x, int fx, float y, int fy, int row) __attribute__((always_inline)) {
+                    if (x == LAST_NEG_INF) fx = 0x7fffffff;
+                    if (y == LAST_NEG_INF) fy = 0x7fffffff;
+                    const bool first = x > y || (x == y && fx < fy);
+                    const int flat = first ? fx : fy;
+                    s.own[row] = first ? x : y;
+                    s.flat[row] = flat == 0x7fffffff ? -1 : flat;
+                };
+                if (act) {
+                    const int q = ga * V + o.b0 + gi;
+                    keep(dead ? LAST_NEG_INF : val, (src * V + ga) * V1 + o.b0 + gi, blg, q * V1, grow);
+                }
+                if (single) keep(sn, o.b0 + lane, sb, (o.b0 + lane) * V1, lane);
+                if (second && !single) keep(sn, 0, LAST_NEG_INF, 0, o.rows);
+            } else {
+                float mx = wave_max_dpp(head);
+                if (mx == LAST_NEG_INF) mx = 0.f;              // no state reachable: keep -inf everywhere
+                A += (double)mx;
+                if (act) s.own[grow] = tri_lse2(val, blg) - mx;
+                if (second) s.own[single ? lane : o.rows] = tri_lse2(sn, sb) - mx;
+                if (tid == 0) s.off = A;
+            }
+            if (dead) s.dead = 1;
+            lds_only_barrier();                                                   // A
+        }
+    }
+    __syncthreads();
+    if (tid == 0 && s.dead) a.fail[b] = 1;
+    __syncthreads();
+}
+
+template <typename D>
+__device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, int b, int L, unsigned& gstep,
+                                             u64* xbase, TriLds<D>& s, float* dyn)
+{
+    constexpr int NCM = D::NCM;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));     // (what one direction derives from it is not kept in registers through the other)
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool comm = wave < NCM;
+    const int V = o.V, V1 = o.V1, nbk = o.nbk, P = 4 * o.CQ;
+    constexpr int BP = D::BtPitch;
+    const int epl = (V1 + 3) / 4;
+    float* bt = dyn;                              // [nbk + 1][BP] states (b0 + i, y) by i; [nbk]: histories of one label
+    float* tile = dyn + ((a.nb + 1) * BP + 3) / 4 * 4;   // [V + 1][P] weights of a frame
+    const size_t fr = (size_t)V1 * a.C;
+    const float* wi = a.w + (size_t)b * a.T * fr;
+    const int low = a.keep ? 1 : tri_meet(L, false);       // the last row this direction makes
+    const int steps = max(L - low, 0);
+    const int rows = o.rows + (o.k == 0 ? 1 : 0);          // the first workgroup also has the start state
+
+    for (int r = tid; r <= o.rows; r += D::NW * kWave) s.own[r] = 0.f;
+    // (four lanes read at least V + 1 elements of a row; what they read past it counts for nothing)
+    for (int i = tid; i < (nbk + 1) * BP; i += D::NW * kWave) bt[i] = i % BP < V1 ? 0.f : LAST_NEG_INF;
+    for (int i = tid; i < V1 * P + kTriPad; i += D::NW * kWave) tile[i] = 0.f;
+    if (tid < 72) s.strow[0][tid] = 0.f;
+    if (tid == 0) { s.dead = 0; s.off = 0.0; }
+    __syncthreads();
+
+    if (!comm) {
+        const int ct = tid - NCM * kWave;
+        const int g = ct / o.CQ, cq = ct - g * o.CQ;
+        const bool act = g < o.G;
+        const int gc = act ? g : 0;
+        const int col0 = min(4 * cq, o.W - 4);
+        const int nl = V / o.G, rl = gc + o.G * nl;             // as in the forward direction
+        const unsigned off0 = 4u * (unsigned)((gc * V + o.b0) * V1 + col0), offL = 4u * (unsigned)((min(rl, V) * V + o.b0) * V1 + col0);
+        const unsigned stoff = 4u * (unsigned)min(lane, V), frb = 4u * (unsigned)fr;
+        const int dOff = 4 * o.G * V * V1;
+        const bool rok = ct < o.rows || (ct == o.rows && o.k == 0);
+        const int rS = min(ct, o.rows);
+        const unsigned rq = rok ? 4u * (unsigned)(ct < o.rows ? (ct / nbk) * V + o.b0 + ct % nbk : 0) : kTriOut;
+        const unsigned oq = ct == 0 && o.k == 0 ? 0u : kTriOut;
+        const unsigned rowb = (unsigned)a.C * 4u;
+        auto store_row = [&](int t, bool on) __attribute__((always_inline)) {
+            const size_t row = a.keep ? (size_t)b * (a.T + 1) + t : (size_t)b;
+            buf_store(s.own[rS], make_buf(a.beta + row * a.C, on ? rowb : 0u), rq, 0);
+            nw_store64(s.off, make_buf(a.offb + row, on ? 8u : 0u), oq, 0);
+        };
+        float4 wv[2][D::NR];
+        float st[2] = {0.f, 0.f}, st64[2] = {0.f, 0.f};
+        // step n works on frame L - 1 - n
+        auto issue = [&](auto S, int n) __attribute__((always_inline)) {
+            const buf_t rs = make_buf(wi + (size_t)max(L - 1 - n, 0) * fr, frb);
+#pragma unroll
+            for (int x = 0; x < D::NR; ++x)
+                wv[decltype(S)::value][x] = tri_load4(rs, x < nl ? off0 : offL, (unsigned)(x < nl ? x * dOff : 0));
+            st[decltype(S)::value] = buf_load(rs, stoff, 0);
+            if (D::MaxV == 64) st64[decltype(S)::value] = buf_load(rs, 4u * (unsigned)V, 0);
+        };
+        auto spread = [&](auto S) __attribute__((always_inline)) {                 // registers -> tile
+            constexpr int Z = decltype(S)::value;
+#pragma unroll
+            for (int x = 0; x < D::NR; ++x)
+                if (act && g + o.G * x <= V) {
+                    float* d = tile + (g + o.G * x) * P + col0;
+                    const float4 v = wv[Z][x];
+                    if (col0 & 3) { d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w; }
+                    else *(float4*)d = v;
+                }
+            if (wave == D::NW - 1) {
+                if (lane <= V) s.strow[0][lane] = st[Z];
+                if (D::MaxV == 64) s.strow[0][V] = st64[Z];
+            }
+        };
+        // four lanes a row: elements y = l epl .. l epl + epl - 1
+        const int l = ct & 3;
+        const float* rowP[D::NP];
+        const float* btP[D::NP];
+        int rP[D::NP];
+#pragma unroll
+        for (int p = 0; p < D::NP; ++p) {
+            rP[p] = min((ct >> 2) + p * (D::CT / 4), rows - 1);
+            const int ra = rP[p] / nbk, ri = rP[p] - ra * nbk;
+            rowP[p] = (rP[p] == o.rows ? s.strow[0] : tile + ra * P + ri * V1) + l * epl;
+            btP[p] = bt + (rP[p] == o.rows ? nbk : ri) * BP + l * epl;
+        }
+        if (steps > 0) {
+            issue(std::integral_constant<int, 0>(), 0);
+            issue(std::integral_constant<int, 1>(), 1);
+            spread(std::integral_constant<int, 0>());
+            issue(std::integral_constant<int, 0>(), 2);
+        }
+        __syncthreads();
+        auto frame = [&](auto S, int n) __attribute__((always_inline)) {
+            constexpr int Z = decltype(S)::value;
+#pragma unroll
+            for (int p = 0; p < D::NP; ++p) {
+                const int r = (ct >> 2) + p * (D::CT / 4);
+                if (r < rows) {
+                    float v[D::EPL], x[D::EPL], m = LAST_NEG_INF;
+                    const float keep = s.own[r];                                   // the empty label keeps the state
+                    constexpr int EH = D::EPL > 11 ? 9 : D::EPL;                   // (registers)
+#pragma unroll
+                    for (int e0 = 0; e0 < D::EPL; e0 += EH) {
+#pragma unroll
+                        for (int e = e0; e < e0 + EH && e < D::EPL; ++e) { x[e] = rowP[p][e]; v[e] = btP[p][e]; }
+                        if (e0 == 0) v[0] = l == 0 ? keep : v[0];
+#pragma unroll
+                        for (int e = e0; e < e0 + EH && e < D::EPL; ++e) {
+                            v[e] = e < epl ? fmaf(x[e], kLog2e, v[e]) : LAST_NEG_INF;
+                            m = fmaxf(m, v[e]);
+                        }
+                        if (D::EPL > 11) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    m = tri_quad_max(m);
+                    const float mm = m == LAST_NEG_INF ? 0.f : m;
+                    float z = 0.f;
+#pragma unroll
+                    for (int e = 0; e < D::EPL; ++e) z += fast_exp2(v[e] - mm);
+                    z = tri_quad_sum(z);
+                    if (l == 0) s.bl[r] = m == LAST_NEG_INF ? LAST_NEG_INF : m + __builtin_amdgcn_logf(z);
+                }
+                if (D::EPL > 11) __builtin_amdgcn_sched_barrier(0);                // (one row's elements in registers at a time)
+            }
+            store_row(L - n, a.keep);
+            lds_only_barrier();                                                    // B
+            if (a.K == 1) lds_only_barrier();
+            // (the exchange is under way) the next frame into the tile, the requests for the frame two after it
+            spread(std::integral_constant<int, Z ^ 1>());
+            issue(std::integral_constant<int, Z ^ 1>(), n + 3);
+            lds_only_barrier();                                                    // A
+        };
+        for (int n = 0; n < steps; n += 2) {
+            frame(std::integral_constant<int, 0>(), n);
+            if (n + 1 < steps) frame(std::integral_constant<int, 1>(), n + 1);
+        }
+        store_row(L - steps, true);
+    } else {
+        const int lidx = wave * kWave + lane;
+        const bool act = lidx < nbk * V;
+        const int pa = act ? lidx / nbk + 1 : 1, pi = act ? lidx - (pa - 1) * nbk : 0;   // published own state
+        const int prow = pa * nbk + pi;
+        const int gi = act ? lidx / V : 0, gy = act ? lidx - gi * V + 1 : 1;             // gathered state (b0 + gi, gy)
+        const bool single = wave == 0 && lane < nbk;
+        const bool second = wave == 0 && lane <= nbk;
+        const bool starter = o.k == 0 && wave == 0;                                      // gathers the histories of one label
+        const int nh = a.K * NCM;
+        const int hidx = V * V + V + (lane < nh ? lane : 0);
+        bool dead = false;
+        double A = 0.0;
+        __syncthreads();
+        for (int n = 0; n < steps; ++n) {
+            u64* xs = xbase + (size_t)(gstep & 1) * a.xs;
+            const unsigned tag = gstep + 1;
+            gstep += 1;
+            lds_only_barrier();                                                    // B
+            const float val = act ? s.bl[prow] : LAST_NEG_INF;
+            const float sv = second && (single || o.k == 0) ? s.bl[single ? lane : o.rows] : LAST_NEG_INF;
+            float head = LAST_NEG_INF;
+            u64 word = 0, hw = 0;
+            float got, gots = LAST_NEG_INF;
+            if (a.K == 1) {
+                head = wave_max_dpp(fmaxf(val, sv));
+                if (act) s.xl[(pa - 1) * V + pi] = val;
+                if (single) s.xl[V * V + lane] = sv;
+                if (lane == 0) s.hd[wave] = head;
+                lds_only_barrier();
+                got = s.xl[act ? lidx : 0];
+                if (starter && lane < V) gots = s.xl[V * V + lane];
+                head = s.hd[lane < NCM ? lane : 0];
+            } else {
+                if (act) xpublish(xs + (size_t)(pa - 1) * V + (o.b0 - 1 + pi), pack_word(val, tag));
+                if (single) xpublish(xs + V * V + (o.b0 - 1 + lane), pack_word(sv, tag));
+                head = wave_max_dpp(fmaxf(val, sv));
+                if (lane == 0) xpublish(xs + V * V + V + o.k * NCM + wave, pack_word(head, tag));
+                if (!dead) dead = !tri_poll<true, false>(xs + (size_t)(o.b0 - 1) * V + (act ? lidx : 0), xs + hidx, act, tag,
+                                                         a.spin_limit, word, hw);
+                got = __uint_as_float((unsigned)word);
+                head = __uint_as_float((unsigned)hw);
+                if (starter) {
+                    if (!dead) dead = !tri_poll<false, false>(xs + V * V + (lane < V ? lane : 0), xs, lane < V, tag,
+                                                              a.spin_limit, word, hw);
+                    gots = __uint_as_float((unsigned)word);
+                }
+            }
+            float mx = wave_max_dpp(head);
+            if (mx == LAST_NEG_INF) mx = 0.f;
+            A += (double)mx;
+            if (act) {
+                bt[gi * BP + gy] = got - mx;
+                s.own[prow] = val - mx;
+            }
+            if (starter && lane < V) bt[nbk * BP + 1 + lane] = gots - mx;
+            if (second && (single || o.k == 0)) s.own[single ? lane : o.rows] = sv - mx;
+            if (tid == 0) s.off = A;
+            if (dead) s.dead = 1;
+            lds_only_barrier();                                                    // A
+        }
+    }
+    __syncthreads();
+    if (tid == 0 && s.dead) a.fail[b] = 1;
+    __syncthreads();
+}
+
+template <typename D, bool TROP>
+__global__ __launch_bounds__(D::NW * kWave) void trigram_kernel(TriArgs a)
+{
+    extern __shared__ __align__(16) float tri_dyn[];
+    __shared__ __align__(16) TriLds<D> s;
+    // workgroups with equal id % 8 sit on one XCD; a cluster takes K of them per direction
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int cl = slot / (a.roles * a.K), rk = slot - cl * a.roles * a.K;
+    const int role = rk / a.K;
+    const int cg = xcd + 8 * cl;
+    TriOwn o;
+    o.k = rk - role * a.K;
+    o.V = a.V;
+    o.V1 = a.V + 1;
+    o.b0 = 1 + o.k * a.nb;
+    o.nbk = min(a.nb, a.V - (o.b0 - 1));
+    o.W = o.nbk * o.V1;
+    o.CQ = (o.W + 3) / 4;
+    o.G = a.G;
+    o.rows = o.V1 * o.nbk;
+    u64* xbase = a.x + (size_t)(cg * a.roles + role) * 2 * a.xs;
+    unsigned gstep = 0;
+    for (int b = cg; b < a.B; b += 8 * a.ncl) {
+        const int L = a.len[b];
+        if (L < 0 || L > a.T) continue;
+        if (TROP || role == 0) tri_forward<D, TROP>(a, o, b, L, gstep, xbase, s, tri_dyn);
+        else tri_backward<D>(a, o, b, L, gstep, xbase, s, tri_dyn);
+    }
+}
+
+// D = log (+)_q alpha_m[q] beta_m[q] of every item from the rows at which the two directions meet (beta = 0 at the
+// last frame), one workgroup per item.  alpha, beta: base-2 logs with offsets.
+__global__ __launch_bounds__(256) void tri_join_kernel(
+    const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
+    const double* __restrict__ offb, const int* __restrict__ len, const int* __restrict__ fail, int T, int C, int keep,
+    double* __restrict__ D2, float* __restrict__ dist, int* __restrict__ item_status)
+{
+    __shared__ float red[32];
+    __shared__ double redd[4];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int L = len[b];
+    const bool bad = L < 0 || L > T, tmo = fail[b] != 0;
+    if (bad || tmo) {
+        if (tid == 0) {
+            dist[b] = __builtin_nanf("");
+            if (D2) D2[b] = __builtin_nan("");
+            if (item_status) item_status[b] = bad ? kItemBadLength : kItemTimeout;
+        }
+        return;
+    }
+    const size_t ra = keep ? ((size_t)b * (T + 1) + L) : (size_t)b;
+    const float* al = alpha + ra * C;
+    const float* be = beta + ra * C;
+    float mx = LAST_NEG_INF;
+    for (int q = tid; q < C; q += 256) mx = fmaxf(mx, keep ? al[q] : al[q] + be[q]);
+    mx = block_max(mx, red);
+    const float mm = mx == LAST_NEG_INF ? 0.f : mx;
+    double z = 0.0;
+    for (int q = tid; q < C; q += 256) z += (double)fast_exp2((keep ? al[q] : al[q] + be[q]) - mm);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
+    if ((tid & 63) == 0) redd[tid >> 6] = z;
+    __syncthreads();
+    if (tid == 0) {
+        z = redd[0] + redd[1] + redd[2] + redd[3];
+        const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF
+                                             : offa[ra] + (keep ? 0.0 : offb[ra]) + (double)mm + log2(z);
+        dist[b] = (float)(d2 * 0.6931471805599453);
+        if (D2) D2[b] = d2;
+        if (item_status) item_status[b] = kItemOk;
+    }
+}
+
+// best final state of every item (lowest index among equals) from its final scores
+__global__ __launch_bounds__(256) void tri_final_kernel(
+    const float* __restrict__ fin, const int* __restrict__ len, const int* __restrict__ fail, int T, int C,
+    int* __restrict__ final_state, float* __restrict__ score, int* __restrict__ item_status)
+{
+    __shared__ float redv[4];
+    __shared__ int redi[4];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int L = len[b];
+    const bool bad = L < 0 || L > T, tmo = fail[b] != 0;
+    if (bad || tmo) {
+        if (tid == 0) {
+            score[b] = __builtin_nanf("");
+            if (final_state) final_state[b] = -1;
+            if (item_status) item_status[b] = bad ? kItemBadLength : kItemTimeout;
+        }
+        return;
+    }
+    float best = LAST_NEG_INF;
+    int idx = 0x7fffffff;
+    for (int q = tid; q < C; q += 256) {
+        const float v = fin[(size_t)b * C + q];
+        if (v > best || (v == best && q < idx)) { best = v; idx = q; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(best, o, kWave);
+        const int oi = __shfl_xor(idx, o, kWave);
+        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
+    }
+    if ((tid & 63) == 0) { redv[tid >> 6] = best; redi[tid >> 6] = idx; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int k = 1; k < 4; ++k)
+            if (redv[k] > best || (redv[k] == best && redi[k] < idx)) { best = redv[k]; idx = redi[k]; }
+        score[b] = best;
+        if (final_state) final_state[b] = idx;
+        if (item_status) item_status[b] = kItemOk;
+    }
+}
+
+__global__ void tri_clear_kernel(u64* __restrict__ x, size_t n, int* __restrict__ fail, int B)
+{
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = i0; i < n; i += (size_t)gridDim.x * blockDim.x) x[i] = ~0ull;
+    for (size_t i = i0; i < (size_t)B; i += (size_t)gridDim.x * blockDim.x) fail[i] = 0;
+}
+
+}  // namespace last

@@ -1,0 +1,114 @@
+"""Full 2-gram contexts with dense weights on the clustered kernels (trigram_kernels.hpp): every
+instantiation and the edges of its range against the float64 oracle.  Tolerances are those of
+test_gpu_parity: distances 1e-5 relative, marginals 1e-5 absolute, paths bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2304_13134_amd import binding as lb
+from paper_2304_13134_amd import workloads
+from gpu_util import TOL_POST_ABS, announce, assert_dist_close, dev, library_option
+from test_gpu_parity import check_path, check_posteriors, forbid_arcs
+
+pytestmark = pytest.mark.gpu
+
+
+# V: 3 is the smallest label set taken; 11, 12 the last with one workgroup an item and the first with two;
+# 19/20, 35/36, 42/43, 64 the edges of the instantiations; 32 and 28 whole and ragged shares of the labels;
+# B = 20 at V = 32 takes the wide workgroups, B = 140 more items than clusters
+@pytest.mark.parametrize("V,T,B", [(3, 9, 2), (11, 9, 3), (12, 8, 3), (19, 7, 2), (20, 7, 2), (28, 9, 5), (32, 20, 3),
+                                   (32, 6, 20), (35, 5, 2), (36, 5, 2), (42, 5, 2), (43, 4, 2), (64, 4, 3),
+                                   (20, 5, 140)])
+def test_every_instantiation(V, T, B):
+    announce("clustered trigram", V, T, B)
+    cfg = workloads.dense(B=B, T=T, V=V, order=2, sigma=1.5, seed=100 + V, len_lo=max(1, T - 3), len_hi=T)
+    check_posteriors(cfg, order=2)
+    check_path(cfg, order=2)
+    dist = lb.last_shortest_distance(dev(cfg["w"]), dev(cfg["lengths"]), order=2)
+    assert_dist_close(dist.cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 2)[1])
+
+
+@pytest.mark.parametrize("V", [2, 7, 65])
+def test_one_workgroup_kernels_keep_the_rest(V):
+    announce("trigram, one workgroup per item, V", V)
+    cfg = workloads.dense(B=2, T=5, V=V, order=2, sigma=1.0, seed=V, len_lo=3, len_hi=5)
+    with library_option(lb.OPT_FORCE_SOLO, 1):
+        check_posteriors(cfg, order=2)
+        check_path(cfg, order=2)
+    if V != 7:
+        check_posteriors(cfg, order=2)
+        check_path(cfg, order=2)
+
+
+@pytest.mark.parametrize("V", [5, 32, 44])
+def test_lengths_status_scale_and_accumulate(V):
+    announce("trigram: lengths 0, 1, 2, T, invalid; scale and accumulate, V", V)
+    T = 7
+    cfg = workloads.dense(B=6, T=T, V=V, order=2, sigma=1.0, seed=9 + V)
+    cfg["lengths"] = np.array([0, 1, 2, T, T + 1, -1], np.int32)
+    cfg["w"][1, 1:] = np.nan                                   # frames past the length are not read into a result
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    status = torch.full((6,), -1, dtype=torch.int32, device="cuda")
+    D, g = lb.last_arc_posteriors(w, lengths, order=2, item_status=status)
+    assert status.cpu().tolist() == [0, 0, 0, 0, 1, 1]
+    ok = dict(w=cfg["w"][:4], lengths=cfg["lengths"][:4])
+    _, D_o = oracle.forward(ok["w"], ok["lengths"], 2)
+    g_o = oracle.posteriors(ok["w"], ok["lengths"], 2)
+    assert_dist_close(D.cpu().numpy()[:4], D_o)
+    assert np.all(np.isnan(D.cpu().numpy()[4:])) and torch.all(g[4:] == 0)
+    assert np.max(np.abs(g.cpu().numpy()[:4] - g_o)) <= TOL_POST_ABS
+    dist = lb.last_shortest_distance(w, lengths, order=2).cpu().numpy()
+    assert_dist_close(dist[:4], D_o)
+    assert np.all(np.isnan(dist[4:]))
+    labels, states, score = lb.last_shortest_path(w, lengths, order=2)
+    l_o, s_o, sc_o = oracle.viterbi(ok["w"], ok["lengths"], 2, "f32")
+    assert np.array_equal(labels.cpu().numpy()[:4], l_o) and np.array_equal(states.cpu().numpy()[:4], s_o)
+    assert torch.all(labels[4:] == -1) and torch.all(states[4:] == -1)
+    base = torch.full_like(w, 0.5)
+    lb.last_arc_posteriors(w, lengths, order=2, dw=base, scale=-2.0, accumulate=True)
+    want = 0.5 - 2.0 * g
+    for b in range(6):
+        n = int(cfg["lengths"][b])
+        want[b, n if 0 <= n <= T else 0:] = 0.5
+    assert torch.max(torch.abs(base - want)).item() < 1e-6
+
+
+@pytest.mark.parametrize("V", [9, 21, 46])
+def test_ties_and_forbidden_arcs(V):
+    announce("trigram: integer weights with ties, forbidden arcs, V", V)
+    rng = np.random.default_rng(V)
+    C = workloads.num_states(V, 2)
+    wc = rng.integers(-1, 2, size=(2, 7, C, V + 1)).astype(np.float32)
+    check_path(dict(w=wc, lengths=np.array([7, 4], np.int32), B=2), order=2)
+    check_path(dict(w=np.zeros((1, 4, C, V + 1), np.float32), lengths=np.array([4], np.int32), B=1), order=2)
+    # (sigma 4: scores of up to 30 in base 2, three float32 roundings of at most 1e-6 each in a marginal's exponent)
+    cfg = workloads.dense(B=2, T=6, V=V, order=2, sigma=4.0, seed=V)
+    check_path(forbid_arcs(cfg, 5), order=2)
+    check_posteriors(cfg, order=2)
+    cfg["w"][rng.random(cfg["w"].shape) < 0.3] = -np.inf       # arcs that do not exist
+    check_path(cfg, order=2)
+    check_posteriors(cfg, order=2)
+
+
+def test_bounded_waits_end_and_flag():
+    announce("trigram: a spin limit of one poll")
+    cfg = workloads.dense(B=3, T=30, V=24, order=2, sigma=1.0, seed=4)
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    _, D_o = oracle.forward(cfg["w"], cfg["lengths"], 2)
+    status = torch.full((3,), -1, dtype=torch.int32, device="cuda")
+    with library_option(lb.OPT_SPIN_LIMIT, 1):
+        D, _ = lb.last_arc_posteriors(w, lengths, order=2, item_status=status)
+        torch.cuda.synchronize()
+        D, st = D.cpu().numpy(), status.cpu().numpy()
+        for b in range(3):
+            assert st[b] in (0, 5)
+            if st[b] == 5:
+                assert np.isnan(D[b])
+            else:
+                assert abs(D[b] - D_o[b]) <= 1e-5 * abs(D_o[b])
+        lb.last_shortest_path(w, lengths, order=2, item_status=status)
+        torch.cuda.synchronize()
+        assert all(s in (0, 5) for s in status.cpu().tolist())
+    check_posteriors(cfg, order=2)
+    check_path(cfg, order=2)
