@@ -18,6 +18,8 @@
 #include "probe_kernels.hpp"
 #include "trigram_kernels.hpp"
 #include "marginals_kernels.hpp"
+#include "bigram_kernels.hpp"
+#include "table_chain_kernels.hpp"
 #include <algorithm>
 
 #include <atomic>
@@ -718,10 +720,10 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
 }
 
 // marginals of all frames from the stored rows (marginals_kernels.hpp)
-template <int ORDER>
+template <int ORDER, bool LINEAR>
 last_status_t launch_marginals(const Shape& s, const float* w, const int* lengths, const float* alpha, const float* beta,
                                const double* offa, const double* offb, const double* D2, const last_grads_t* out,
-                               hipStream_t st)
+                               const int* badtab, int* item_status, hipStream_t st)
 {
     const size_t lds = (size_t)2 * s.C * sizeof(float);
     int rows = std::max(1, kMgChunk / s.V1);
@@ -732,10 +734,107 @@ last_status_t launch_marginals(const Shape& s, const float* w, const int* length
         if (lds > kMaxLds) rc = allow_lds((const void*)k, kBigLds);
         if (rc == LAST_OK)
             hipLaunchKernelGGL(k, dim3(parts, s.T, s.B), dim3(kMgThreads), lds, st, w, lengths, make_ctx(s), s.T, rows,
-                               alpha, beta, offa, offb, D2, out->dw, out->scale);
+                               alpha, beta, offa, offb, D2, out->dw, out->scale, badtab, item_status);
     };
-    if (out->accumulate) go(dense_marginals_kernel<ORDER, true>);
-    else go(dense_marginals_kernel<ORDER, false>);
+    if (out->accumulate) go(dense_marginals_kernel<ORDER, true, LINEAR>);
+    else go(dense_marginals_kernel<ORDER, false, LINEAR>);
+    return rc;
+}
+
+// Table contexts whose frame is small enough to be owned by the threads of one workgroup (table_chain_kernels.hpp):
+// 16384 arcs, the registers of 1024 threads with two frames requested ahead.  It is the faster one wherever it fits,
+// with marginals against the kernels that fetch arcs where they are used: 585 states, 8 labels, B=8 T=200 0.53 / 6.1 ms;
+// 300 states, 50 labels, B=8 T=100 0.60 / 6.1 ms; 200 states, 12 labels, B=300 T=40 0.27 / 1.0 ms.
+bool tab_ok(const Shape& s, bool trop)
+{
+    const size_t n = (size_t)s.C * s.V1;
+    return s.order == 0 && !opt(LAST_OPT_FORCE_SOLO) && s.T >= 1 && n >= 4 && n <= (size_t)kTabMaxQ * 4 * kTabThreads
+           && tab_lds(s.C, s.V1, trop) <= kBigLds - 1024;
+}
+
+struct BiWs {
+    float *alpha, *beta;
+    double *offa, *offb, *D2;
+};
+last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep,
+                         int* bp, int* final_state, float* dist, int* item_status, const int* flag, hipStream_t st);
+
+// Full 1-gram contexts, one workgroup per item and direction (bigram_kernels.hpp).  From 97 states on a compute
+// unit takes longer over a frame than a cluster over its exchange: forward-backward at T=200 and 71 states
+// B=16 0.41 / 0.54 ms, B=64 0.48 / 1.17 ms against the cluster; at 101 states (measured with wider tiles) B=16 0.71 / 0.56 ms;
+// shortest path at 71 states B=32 0.33 / 0.37 ms, at 101 0.44 / 0.37 ms.  Below 4 states a row is no 16-byte piece.
+bool bi_ok(const Shape& s, int kind, bool trop)
+{
+    if (opt(LAST_OPT_FORCE_SOLO) || kind != LAST_WEIGHTS_DENSE || s.order != 1 || s.T < 1) return false;
+    if (trop ? opt(LAST_OPT_CLUSTER_VITERBI) != 1 : opt(LAST_OPT_CLUSTER_GENERATION) != 0) return false;
+    return s.C >= 4 && s.C <= kBiMaxC;
+}
+
+
+BiWs carve_bi(Carver& cv, const Shape& s, bool keep)
+{
+    BiWs c;
+    const size_t rows = (size_t)s.B * (keep ? s.T + 1 : 1);
+    c.alpha = cv.take<float>(rows * s.C);
+    c.beta = cv.take<float>(rows * s.C);
+    c.offa = cv.take<double>(rows);
+    c.offb = cv.take<double>(rows);
+    c.D2 = cv.take<double>((size_t)s.B);
+    return c;
+}
+
+last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep,
+                         int* bp, int* final_state, float* dist, int* item_status, const int* flag, hipStream_t st)
+{
+    TabArgs a;
+    a.w = w; a.len = lengths; a.bad = flag; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb;
+    a.D2 = c.D2; a.dist = dist; a.item_status = item_status; a.bp = bp; a.final_state = final_state;
+    a.T = s.T; a.keep = keep;
+    a.lpr = 1;                                   // lanes per row: as many as the workgroup has for its rows
+    while (a.lpr < 64 && a.lpr * 2 * s.C <= 2 * kTabThreads && a.lpr * 4 < s.V1) a.lpr *= 2;
+    const size_t lds = tab_lds(s.C, s.V1, trop);
+    last_status_t rc = LAST_OK;
+    auto go = [&](auto NQ) {
+        auto launch = [&](auto k, int roles) {
+            if (lds > kMaxLds) rc = allow_lds((const void*)k, kBigLds - 1024);
+            if (rc == LAST_OK) hipLaunchKernelGGL(k, dim3(s.B, roles), dim3(kTabThreads), lds, st, a, make_ctx(s));
+        };
+        if (trop) launch(table_chain_kernel<decltype(NQ)::value, true>, 1);
+        else launch(table_chain_kernel<decltype(NQ)::value, false>, 2);
+    };
+    const size_t n = (size_t)s.C * s.V1;
+    if (n <= 4 * kTabThreads) go(std::integral_constant<int, 1>());
+    else if (n <= 8 * kTabThreads) go(std::integral_constant<int, 2>());
+    else go(std::integral_constant<int, kTabMaxQ>());
+    return rc;
+}
+
+constexpr size_t kBiBigLds = 2 * kBiMaxC * kBiMaxC * sizeof(float);
+last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep, int* bp,
+               int* final_state, float* dist, int* item_status, hipStream_t st)
+{
+    BiArgs a;
+    a.w = w; a.len = lengths; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb; a.D2 = c.D2;
+    a.dist = dist; a.item_status = item_status; a.bp = bp; a.final_state = final_state;
+    a.T = s.T; a.C = s.C; a.keep = keep;
+    last_status_t rc = LAST_OK;
+    a.P = (s.C + 3) / 4 * 4;
+    auto go = [&](auto DD) {
+        typedef decltype(DD) D;
+        a.rc = (s.C + D::NC - 1) / D::NC;
+        a.rp = (s.C + D::NP - 1) / D::NP;
+        const size_t lds = (size_t)2 * s.C * a.P * sizeof(float);
+        auto launch = [&](auto k, int roles) {
+            if (D::N > 64) rc = allow_lds((const void*)k, kBiBigLds);
+            if (rc == LAST_OK) hipLaunchKernelGGL(k, dim3(s.B, roles), dim3((D::NC + D::NP) * kWave), lds, st, a);
+        };
+        if (trop) launch(bigram_kernel<D, true>, 1);
+        else launch(bigram_kernel<D, false>, 2);
+    };
+    if (s.C <= 32) go(BiDims<8, 1, 4, 4, 8, 1, 2>());
+    else if (s.C <= 48) go(BiDims<16, 1, 4, 4, 12, 3, 2>());
+    else if (s.C <= 64) go(BiDims<16, 1, 4, 4, 16, 4, 2>());
+    else go(BiDims<32, 2, 8, 8, 12, 6, 1>());
     return rc;
 }
 
@@ -939,9 +1038,9 @@ int32_t last_kernel_variant(const last_weights_t* weights, const last_context_t*
         return (op_ok && fused_plan(s, weights).ok) ? 2 : -1;
     }
     if (op == LAST_OP_SHORTEST_DISTANCE || op == LAST_OP_ARC_POSTERIORS)
-        return cluster_plan(s, weights->kind).ok || tri_plan(s, weights->kind, false).ok ? 1 : 0;
+        return bi_ok(s, weights->kind, false) || cluster_plan(s, weights->kind).ok || tri_plan(s, weights->kind, false).ok ? 1 : 0;
     if (op == LAST_OP_SHORTEST_PATH)
-        return viterbi_plan(s, weights->kind).ok || tri_plan(s, weights->kind, true).ok ? 1 : 0;
+        return bi_ok(s, weights->kind, true) || viterbi_plan(s, weights->kind).ok || tri_plan(s, weights->kind, true).ok ? 1 : 0;
     return 0;
 }
 
@@ -977,9 +1076,10 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
     const TriPlan tplan = tri_plan(s, weights->kind, false), tvplan = tri_plan(s, weights->kind, true);
     switch (op) {
     case LAST_OP_SHORTEST_DISTANCE:
-        if (plan.ok) carve_cluster(cv, s, plan);
+        if (bi_ok(s, weights->kind, false) || (tab_ok(s, false) && tri_rows_fit(s))) carve_bi(cv, s, false);
+        else if (plan.ok) carve_cluster(cv, s, plan);
         else cv.take<double>(1);
-        if (vplan.ok) cv.take<u64>(vplan.xwords);        // tropical semiring: exchange buffer
+        if (vplan.ok && !bi_ok(s, weights->kind, true)) cv.take<u64>(vplan.xwords);        // tropical semiring: exchange buffer
         if (tri_rows_fit(s) && (tplan.ok || tvplan.ok)) {
             // one semiring or the other: the larger of the two
             Carver log(nullptr), trop(nullptr);
@@ -989,7 +1089,8 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
         }
         break;
     case LAST_OP_ARC_POSTERIORS:
-        if (plan.ok) carve_cluster(cv, s, plan);
+        if (bi_ok(s, weights->kind, false) || tab_ok(s, false)) carve_bi(cv, s, true);
+        else if (plan.ok) carve_cluster(cv, s, plan);
         else if (tplan.ok) carve_tri(cv, s, tplan, false, true);
         else carve_posteriors(cv, s);
         break;
@@ -1044,6 +1145,19 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         Carver cv(ws);
         int* flag = carve_table_flag(cv, s);
         launch_table_check(s, flag, st);
+        if (semiring == LAST_TROPICAL && tab_ok(s, true)) {
+            rc = launch_tab(s, BiWs{}, weights->w, lengths, true, false, nullptr, nullptr, dist, item_status, flag, st);
+            return rc != LAST_OK ? rc : hip_status();
+        }
+        if (semiring == LAST_LOG && tab_ok(s, false) && tri_rows_fit(s)) {
+            const BiWs bw = carve_bi(cv, s, false);
+            rc = launch_tab(s, bw, weights->w, lengths, false, false, nullptr, nullptr, dist, item_status, flag, st);
+            if (rc != LAST_OK) return rc;
+            hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)bw.alpha, (const float*)bw.beta,
+                               (const double*)bw.offa, (const double*)bw.offb, lengths, (const int*)nullptr, (const int*)flag,
+                               s.T, s.C, 0, (double*)nullptr, dist, item_status);
+            return hip_status();
+        }
         rc = semiring == LAST_LOG
                  ? launch_table_forward(s, l, weights->w, lengths, nullptr, nullptr, nullptr, dist, item_status, flag, st)
                  : launch_table_viterbi(s, l, weights->w, lengths, nullptr, nullptr, dist, item_status, flag, st);
@@ -1051,7 +1165,17 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
     }
     const Ctx c = make_ctx(s);
     const ClusterPlan plan = cluster_plan(s, weights->kind);
-    if (semiring == LAST_LOG && plan.ok) {
+    if (bi_ok(s, weights->kind, semiring == LAST_TROPICAL)) {
+        const bool trop = semiring == LAST_TROPICAL;
+        Carver cv(ws);
+        BiWs bw{};
+        if (!trop) bw = carve_bi(cv, s, false);
+        rc = launch_bi(s, bw, weights->w, lengths, trop, false, nullptr, nullptr, dist, item_status, st);
+        if (rc != LAST_OK) return rc;
+        if (!trop)
+            hipLaunchKernelGGL(bigram_join_kernel, dim3(s.B), dim3(64), 0, st, (const float*)bw.alpha, (const float*)bw.beta,
+                               (const double*)bw.offa, (const double*)bw.offb, lengths, s.T, s.C, dist, item_status);
+    } else if (semiring == LAST_LOG && plan.ok) {
         Carver cv(ws);
         const ClusterWs cw = carve_cluster(cv, s, plan);
         launch_cluster<false>(s, plan, cw, weights->w, lengths, dist, item_status, nullptr, 1.f, 0, st);
@@ -1067,7 +1191,7 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
                                (const int*)tw.fail, s.T, s.C, (int*)nullptr, dist, item_status);
         else
             hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, (const float*)tw.beta,
-                               (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, s.T, s.C, 0,
+                               (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, (const int*)nullptr, s.T, s.C, 0,
                                (double*)nullptr, dist, item_status);
     } else if (semiring == LAST_LOG) {
         if (l.lds_forward > kMaxLds) return LAST_ERR_UNSUPPORTED;
@@ -1076,8 +1200,6 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
                            (float*)nullptr, (double*)nullptr, (double*)nullptr, dist, item_status);
     } else if (const ViterbiPlan vp = viterbi_plan(s, weights->kind); vp.ok) {
         Carver cv(ws);
-        if (plan.ok) carve_cluster(cv, s, plan);
-        else cv.take<double>(1);
         u64* xv = cv.take<u64>(vp.xwords);
         launch_cluster_viterbi(s, vp, xv, weights->w, lengths, nullptr, nullptr, dist, item_status, st);
     } else {
@@ -1116,6 +1238,14 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     rc = check_ws(ws, ws_bytes, last_workspace_bytes(weights, context, LAST_OP_ARC_POSTERIORS, 0));
     if (rc != LAST_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
+    if (bi_ok(s, weights->kind, false)) {
+        Carver cvb(ws);
+        const BiWs bw = carve_bi(cvb, s, true);
+        rc = launch_bi(s, bw, weights->w, lengths, false, true, nullptr, nullptr, dist, item_status, st);
+        if (rc != LAST_OK) return rc;
+        rc = launch_marginals<1, true>(s, weights->w, lengths, bw.alpha, bw.beta, bw.offa, bw.offb, bw.D2, out, nullptr, item_status, st);
+        return rc != LAST_OK ? rc : hip_status();
+    }
     const ClusterPlan plan = cluster_plan(s, weights->kind);
     if (plan.ok) {
         Carver cvc(ws);
@@ -1130,9 +1260,9 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
         rc = launch_tri(s, tp, tw, weights->w, lengths, false, true, nullptr, st);
         if (rc != LAST_OK) return rc;
         hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, (const float*)tw.beta,
-                           (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, s.T, s.C, 1,
+                           (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, (const int*)nullptr, s.T, s.C, 1,
                            tw.D2, dist, item_status);
-        rc = launch_marginals<2>(s, weights->w, lengths, tw.alpha, tw.beta, tw.offa, tw.offb, tw.D2, out, st);
+        rc = launch_marginals<2, false>(s, weights->w, lengths, tw.alpha, tw.beta, tw.offa, tw.offb, tw.D2, out, nullptr, item_status, st);
         return rc != LAST_OK ? rc : hip_status();
     }
     const SoloLayout l = solo_layout(s);
@@ -1140,6 +1270,15 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     const Ctx c = make_ctx(s);
     Carver cv(ws);
     int* flag = carve_table_flag(cv, s);
+    if (tab_ok(s, false)) {
+        const BiWs bw = carve_bi(cv, s, true);
+        launch_table_check(s, flag, st);
+        rc = launch_tab(s, bw, weights->w, lengths, false, true, nullptr, nullptr, dist, item_status, flag, st);
+        if (rc != LAST_OK) return rc;
+        rc = launch_marginals<0, false>(s, weights->w, lengths, bw.alpha, bw.beta, bw.offa, bw.offb, bw.D2, out, flag,
+                                        item_status, st);
+        return rc != LAST_OK ? rc : hip_status();
+    }
     PosteriorWs p = carve_posteriors(cv, s);
     if (s.order == 0) {
         launch_table_check(s, flag, st);
@@ -1455,14 +1594,20 @@ last_status_t last_shortest_path(const last_weights_t* weights, const int32_t* l
     const SoloLayout l = solo_layout(s);
     const ViterbiPlan vp = viterbi_plan(s, weights->kind);
     const TriPlan tp = tri_plan(s, weights->kind, true);
-    if (!vp.ok && !tp.ok && l.lds_viterbi > (s.order == 0 ? kBigLds : kMaxLds)) return LAST_ERR_UNSUPPORTED;
+    const bool bi = bi_ok(s, weights->kind, true);
+    if (!bi && !vp.ok && !tp.ok && l.lds_viterbi > (s.order == 0 ? kBigLds : kMaxLds)) return LAST_ERR_UNSUPPORTED;
     const Ctx c = make_ctx(s);
     Carver cv(ws);
     int* flag = carve_table_flag(cv, s);
     PathWs p = carve_path(cv, s, vp.ok ? vp.xwords : 0);
     if (s.order == 0) {
         launch_table_check(s, flag, st);
-        rc = launch_table_viterbi(s, l, weights->w, lengths, p.bp, p.final_state, score, item_status, flag, st);
+        rc = tab_ok(s, true)
+                 ? launch_tab(s, BiWs{}, weights->w, lengths, true, false, p.bp, p.final_state, score, item_status, flag, st)
+                 : launch_table_viterbi(s, l, weights->w, lengths, p.bp, p.final_state, score, item_status, flag, st);
+        if (rc != LAST_OK) return rc;
+    } else if (bi) {
+        rc = launch_bi(s, BiWs{}, weights->w, lengths, true, false, p.bp, p.final_state, score, item_status, st);
         if (rc != LAST_OK) return rc;
     } else if (vp.ok)
         launch_cluster_viterbi(s, vp, p.xv, weights->w, lengths, p.bp, p.final_state, score, item_status, st);

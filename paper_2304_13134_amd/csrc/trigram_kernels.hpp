@@ -648,22 +648,23 @@ __global__ __launch_bounds__(D::NW * kWave) void trigram_kernel(TriArgs a)
 }
 
 // D = log (+)_q alpha_m[q] beta_m[q] of every item from the rows at which the two directions meet (beta = 0 at the
-// last frame), one workgroup per item.  alpha, beta: base-2 logs with offsets.
+// last frame), one workgroup per item.  alpha, beta: base-2 logs with offsets.  fail, badtab may be null.
 __global__ __launch_bounds__(256) void tri_join_kernel(
     const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
-    const double* __restrict__ offb, const int* __restrict__ len, const int* __restrict__ fail, int T, int C, int keep,
-    double* __restrict__ D2, float* __restrict__ dist, int* __restrict__ item_status)
+    const double* __restrict__ offb, const int* __restrict__ len, const int* __restrict__ fail,
+    const int* __restrict__ badtab, int T, int C, int keep, double* __restrict__ D2, float* __restrict__ dist,
+    int* __restrict__ item_status)
 {
     __shared__ float red[32];
     __shared__ double redd[4];
     const int b = blockIdx.x, tid = threadIdx.x;
     const int L = len[b];
-    const bool bad = L < 0 || L > T, tmo = fail[b] != 0;
-    if (bad || tmo) {
+    const bool bad = L < 0 || L > T, tmo = fail && fail[b] != 0, tab = badtab && badtab[0] != 0;
+    if (bad || tmo || tab) {
         if (tid == 0) {
             dist[b] = __builtin_nanf("");
             if (D2) D2[b] = __builtin_nan("");
-            if (item_status) item_status[b] = bad ? kItemBadLength : kItemTimeout;
+            if (item_status) item_status[b] = tab ? kItemBadTable : bad ? kItemBadLength : kItemTimeout;
         }
         return;
     }

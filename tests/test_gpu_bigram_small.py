@@ -1,0 +1,103 @@
+"""Full 1-gram contexts of 4 to 96 states (bigram_kernels.hpp) against the float64 oracle, at the edges
+of its tiles; tolerances of test_gpu_parity."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2304_13134_amd import binding as lb
+from paper_2304_13134_amd import workloads
+from gpu_util import TOL_POST_ABS, announce, assert_dist_close, dev, library_option
+from test_gpu_parity import check_path, check_posteriors
+
+pytestmark = pytest.mark.gpu
+
+
+# V = C - 1: 2 and 96 lie just outside, 3 is the smallest taken; 31/32, 47/48, 63/64, 95 the edges of the
+# instantiations; 34 and 61 rows that no 16-byte piece divides
+@pytest.mark.parametrize("V", [2, 3, 4, 7, 31, 32, 34, 47, 48, 61, 63, 64, 95, 96])
+def test_sizes_and_lengths(V):
+    announce("small bigram, V", V)
+    cfg = workloads.dense(B=8, T=9, V=V, order=1, sigma=1.5, seed=200 + V)
+    cfg["lengths"] = np.array([0, 1, 2, 3, 4, 7, 8, 9], np.int32)
+    cfg["w"][1, 1:] = np.nan                                   # frames past the length are not read into a result
+    check_posteriors(cfg)
+    check_path(cfg)
+    dist = lb.last_shortest_distance(dev(cfg["w"]), dev(cfg["lengths"]))
+    assert_dist_close(dist.cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 1)[1])
+
+
+@pytest.mark.parametrize("V", [3, 32, 70])
+def test_long_batch_and_older_kernels(V):
+    announce("small bigram, 40 items of 60 frames, V", V)
+    cfg = workloads.dense(B=40, T=60, V=V, order=1, sigma=1.0, seed=V, len_lo=40, len_hi=60)
+    check_posteriors(cfg)
+    check_path(cfg)
+    for generation in (1, 2):                                  # the clustered kernels stay selectable here
+        with library_option(lb.OPT_CLUSTER_GENERATION, generation):
+            check_posteriors(cfg)
+    for mode in (0, 2):
+        with library_option(lb.OPT_CLUSTER_VITERBI, mode):
+            check_path(cfg)
+
+
+@pytest.mark.parametrize("V", [5, 33, 80])
+def test_status_scale_and_accumulate(V):
+    announce("small bigram: invalid lengths, scale, accumulate, V", V)
+    T = 7
+    cfg = workloads.dense(B=4, T=T, V=V, order=1, seed=9 + V)
+    cfg["lengths"] = np.array([T, T + 1, -1, 3], np.int32)
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    status = torch.full((4,), -1, dtype=torch.int32, device="cuda")
+    D, g = lb.last_arc_posteriors(w, lengths, item_status=status)
+    assert status.cpu().tolist() == [0, 1, 1, 0]
+    assert torch.isnan(D[1:3]).all() and torch.all(g[1:3] == 0)
+    assert torch.isnan(lb.last_shortest_distance(w, lengths, item_status=status)[1:3]).all()
+    assert status.cpu().tolist() == [0, 1, 1, 0]
+    labels, states, score = lb.last_shortest_path(w, lengths, item_status=status)
+    assert status.cpu().tolist() == [0, 1, 1, 0]
+    assert torch.all(labels[1:3] == -1) and torch.all(states[1:3] == -1) and torch.isnan(score[1:3]).all()
+    base = torch.full_like(w, 0.5)
+    lb.last_arc_posteriors(w, lengths, dw=base, scale=-2.0, accumulate=True)
+    want = 0.5 - 2.0 * g
+    want[3, 3:] = 0.5
+    want[1:3] = 0.5
+    assert torch.max(torch.abs(base - want)).item() < 1e-6
+
+
+@pytest.mark.parametrize("V", [4, 40, 90])
+def test_ties_missing_arcs_and_range(V):
+    announce("small bigram: ties, arcs of weight -inf and -1e4, wide range, V", V)
+    rng = np.random.default_rng(V)
+    C = V + 1
+    check_path(dict(w=rng.integers(-1, 2, size=(3, 15, C, C)).astype(np.float32), lengths=np.array([15, 8, 1], np.int32), B=3))
+    check_path(dict(w=np.zeros((1, 6, C, C), np.float32), lengths=np.array([6], np.int32), B=1))
+    # weights of up to about +-50 (all within the range the distance and the marginals are exact for)
+    cfg = workloads.dense(B=2, T=14, V=V, order=1, sigma=12.0, seed=V)
+    cfg["w"][rng.random(cfg["w"].shape) < 0.3] = -1.0e4
+    cfg["w"][:, :, 2, :] = -1.0e4
+    check_path(cfg)
+    check_posteriors(cfg)
+    cfg = workloads.dense(B=2, T=10, V=V, order=1, sigma=2.0, seed=V + 1)
+    cfg["w"][rng.random(cfg["w"].shape) < 0.3] = -np.inf
+    cfg["w"][:, 1:, 0, :] = np.finfo(np.float32).min           # the start state may not be left after the first frame
+    check_posteriors(cfg)
+    check_path(cfg)
+    # no path at all: the distance is -inf and no marginal is anything but 0
+    cfg["w"][:, 4] = -np.inf
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    D, g = lb.last_arc_posteriors(w, lengths)
+    assert torch.all(D == -np.inf) and torch.all(g == 0)
+    assert torch.all(lb.last_shortest_distance(w, lengths) == -np.inf)
+    # far beyond scaled float32: right distance, and either right marginals or status 6
+    cfg = workloads.dense(B=2, T=11, V=V, order=1, sigma=40.0, seed=4000 + V)
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    status = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+    D, g = lb.last_arc_posteriors(w, lengths, item_status=status)
+    assert_dist_close(D.cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 1)[1])
+    go = oracle.posteriors(cfg["w"], cfg["lengths"], 1)
+    assert not torch.isnan(g).any()
+    for b in range(2):
+        assert int(status[b]) in (0, 6)
+        if int(status[b]) == 0:
+            assert np.max(np.abs(g[b].cpu().numpy() - go[b])) <= TOL_POST_ABS
