@@ -188,7 +188,7 @@ NumWs carve_num(Carver& cv, const Shape& s, int Umax, bool local)
     p.ctxs = cv.take<int>((size_t)s.B * U1);
     p.link = cv.take<int>((size_t)s.B * U1 * 2);
     p.lz = local ? cv.take<double>((size_t)s.B * (s.T > 0 ? s.T : 1) * U1) : nullptr;
-    p.wi = cv.take<float2>((size_t)s.B * (s.T > 0 ? s.T : 1) * U1);
+    p.wi = cv.take<float2>((size_t)s.B * (s.T > 0 ? s.T : 1) * U1 * (local ? 2 : 1));   // local: pairs of float64
     p.a = cv.take<double>((size_t)s.B * (s.T + 1) * U1);
     p.bk = cv.take<double>((size_t)s.B * (s.T + 1) * U1);
     p.N = cv.take<double>((size_t)s.B);
@@ -1306,15 +1306,21 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
 // The (t,u) recursion with one wavefront per item and direction (references of up to 511 labels);
 // false when the shape needs the workgroup kernel.
 static bool launch_num_wave(const Shape& s, int Umax, const NumWs& p, const int* lengths, const int* ref_lengths,
-                            float* numerator, int* item_status, hipStream_t st)
+                            float* numerator, int* item_status, bool local, hipStream_t st)
 {
     const int U1 = Umax + 1;
     const int cpl = (U1 + kWave - 1) / kWave;
-    if (cpl > 8 || s.T < 1 || (size_t)(s.T + 1) * U1 * 8 >= 0xfffffff0ull) return false;
+    if (cpl > 8 || s.T < 1 || (size_t)(s.T + 1) * U1 * (local ? 16 : 8) >= 0xfffffff0ull) return false;
     auto go = [&](auto CPL, auto CH) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(num_wave_kernel<decltype(CPL)::value, decltype(CH)::value>),
-                           dim3(s.B, 2), dim3(kWave), 0, st, (const float2*)p.wi, lengths, ref_lengths,
-                           (const int*)p.status, s.T, Umax, p.a, p.bk, p.N, numerator, item_status);
+        constexpr int cpl_ = decltype(CPL)::value, ch = decltype(CH)::value;
+        if (local)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(num_wave_kernel<cpl_, ch, double>), dim3(s.B, 2), dim3(kWave), 0, st,
+                               (const double*)p.wi, lengths, ref_lengths, (const int*)p.status, s.T, Umax, p.a, p.bk,
+                               p.N, numerator, item_status);
+        else
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(num_wave_kernel<cpl_, ch, float>), dim3(s.B, 2), dim3(kWave), 0, st,
+                               (const float*)p.wi, lengths, ref_lengths, (const int*)p.status, s.T, Umax, p.a, p.bk,
+                               p.N, numerator, item_status);
     };
     using std::integral_constant;
     // frames per prefetch chunk: a wavefront can keep count of 63 memory operations in flight, and a
@@ -1372,9 +1378,9 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
             hipLaunchKernelGGL(fnum_gather_kernel, dim3(ugrid, (s.T + kFnStrip - 1) / kFnStrip, s.B), block, 0, st,
                                f, e, (const float*)Wt, lengths, refs, ref_lengths, (const int*)p.status,
                                (const int*)p.ctxs, s.T, Umax, H, p.wi);
-        if (!launch_num_wave(s, Umax, p, lengths, ref_lengths, numerator, item_status, st))
-            hipLaunchKernelGGL(num_recursion_kernel, dim3(s.B, 2), dim3(256), lds, st,
-                               (const float2*)p.wi, (const double*)nullptr, lengths, ref_lengths,
+        if (!launch_num_wave(s, Umax, p, lengths, ref_lengths, numerator, item_status, false, st))
+            hipLaunchKernelGGL(num_recursion_kernel<float2>, dim3(s.B, 2), dim3(256), lds, st,
+                               (const float2*)p.wi, lengths, ref_lengths,
                                (const int*)p.status, s.T, Umax, p.a, p.bk, p.N, numerator, item_status);
         }
         if (out && scatter) {
@@ -1399,9 +1405,7 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
     }
     if (weights->kind != LAST_WEIGHTS_DENSE) return LAST_ERR_UNSUPPORTED;
     if (out && !out->dw) return LAST_ERR_NULL;
-    constexpr int kLocalWaves = 4;
-    const size_t lds_scatter = (size_t)kLocalWaves * s.V1 * sizeof(float);
-    if (local && lds_scatter > kMaxLds) return LAST_ERR_UNSUPPORTED;
+    if (local && (size_t)4 * s.V1 * sizeof(float) > kMaxLds) return LAST_ERR_UNSUPPORTED;
     rc = check_ws(ws, ws_bytes,
                   last_workspace_bytes(weights, context,
                                        local ? LAST_OP_LOCAL_LOG_LIKELIHOOD : LAST_OP_INTERSECT_REFERENCE, Umax));
@@ -1413,44 +1417,65 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
     NumWs p = carve_num(cv, s, Umax, local);
     const int U1 = Umax + 1;
     const dim3 pgrid((U1 + 127) / 128, s.T > 0 ? s.T : 1, s.B);
-    const dim3 wgrid((U1 + kLocalWaves - 1) / kLocalWaves, s.T > 0 ? s.T : 1, s.B);   // a wavefront per cell
+    // 16-byte pieces of a row per lane of the locally normalised kernels; 0: a loop over single weights
+    const int pieces = s.V1 < 4 || s.V1 > 512 ? 0 : s.V1 <= 256 ? 1 : 2;
+    auto with_pieces = [&](auto&& f) {
+        if (pieces == 1) f(std::integral_constant<int, 1>());
+        else if (pieces == 2) f(std::integral_constant<int, 2>());
+        else f(std::integral_constant<int, 0>());
+    };
     if (prepare) {
     if (flag) launch_table_check(s, flag, st);
     hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(256), 0, st, lengths, refs, ref_lengths,
                        c, s.T, Umax, p.status, p.ctxs, p.link, (const int*)flag);
     if (s.T > 0) {
         if (local)
-            hipLaunchKernelGGL(num_gather_local_kernel, wgrid, dim3(kLocalWaves * kWave), 0, st, weights->w,
-                               lengths, refs, ref_lengths, (const int*)p.status, (const int*)p.ctxs, c,
-                               s.T, Umax, p.wi, p.lz);
+            with_pieces([&](auto QL) {
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(num_gather_local_kernel<decltype(QL)::value>),
+                                   dim3((U1 + 3) / 4, (s.T + kNlFrames - 1) / kNlFrames, s.B), dim3(256), 0, st, weights->w,
+                                   lengths, refs, ref_lengths, (const int*)p.status, (const int*)p.ctxs, c,
+                                   s.T, Umax, (double2*)p.wi, p.lz);
+            });
         else
             hipLaunchKernelGGL(num_gather_kernel, pgrid, dim3(128), 0, st, weights->w, lengths, refs,
                                ref_lengths, (const int*)p.status, (const int*)p.ctxs, c, s.T, Umax, p.wi);
     }
-    if (!local && launch_num_wave(s, Umax, p, lengths, ref_lengths, numerator, item_status, st)) {
+    if (launch_num_wave(s, Umax, p, lengths, ref_lengths, numerator, item_status, local, st)) {
         // one wavefront per item and direction has run the recursion
+    } else if (local) {
+        hipLaunchKernelGGL(num_recursion_kernel<double2>, dim3(s.B, 2), dim3(256), lds, st,
+                           (const double2*)p.wi, lengths, ref_lengths,
+                           (const int*)p.status, s.T, Umax, p.a, p.bk, p.N, numerator, item_status);
     } else {
-        hipLaunchKernelGGL(num_recursion_kernel, dim3(s.B, 2), dim3(256), lds, st,
-                           (const float2*)p.wi, (const double*)p.lz, lengths, ref_lengths,
+        hipLaunchKernelGGL(num_recursion_kernel<float2>, dim3(s.B, 2), dim3(256), lds, st,
+                           (const float2*)p.wi, lengths, ref_lengths,
                            (const int*)p.status, s.T, Umax, p.a, p.bk, p.N, numerator, item_status);
     }
     }
     if (out && s.T > 0 && scatter) {
-        if (!out->accumulate) {
+        const bool zeroed = !out->accumulate && (!local || s.C > kNsMaxC);
+        if (zeroed) {
             const size_t n = (size_t)s.B * s.T * s.C * s.V1;
             hipLaunchKernelGGL(zero_fill_kernel, dim3(2048), dim3(256), 0, st, out->dw, n);
         }
         if (local)
-            hipLaunchKernelGGL(num_scatter_local_kernel, wgrid, dim3(kLocalWaves * kWave), lds_scatter, st,
-                               weights->w, (const float2*)p.wi, (const double*)p.lz, lengths, refs,
-                               ref_lengths, (const int*)p.status, (const int*)p.ctxs, (const int*)p.link,
-                               c, s.T, Umax, (const double*)p.a, (const double*)p.bk, (const double*)p.N,
-                               out->dw, out->scale, out->accumulate);
+            with_pieces([&](auto QL) {
+                auto k = num_scatter_local_kernel<decltype(QL)::value>;
+                const size_t need = (size_t)U1 * (sizeof(float2) + 3 * sizeof(int)) + (s.C <= kNsMaxC ? s.C : 0);
+                if (need > kMaxLds) rc = allow_lds((const void*)k, kBigLds - 1024);
+                if (rc == LAST_OK)
+                    hipLaunchKernelGGL(k, dim3(s.T, s.B), dim3(kNsThreads), need, st,
+                                       weights->w, (const double2*)p.wi, (const double*)p.lz, lengths, refs,
+                                       ref_lengths, (const int*)p.status, (const int*)p.ctxs, (const int*)p.link,
+                                       c, s.T, Umax, (const double*)p.a, (const double*)p.bk, (const double*)p.N,
+                                       out->dw, out->scale, out->accumulate, (int)zeroed);
+            });
         else
             hipLaunchKernelGGL(num_scatter_kernel, pgrid, dim3(128), 0, st, (const float2*)p.wi,
                                lengths, refs, ref_lengths, (const int*)p.status, (const int*)p.ctxs, c,
                                s.T, Umax, (const double*)p.a, (const double*)p.bk, (const double*)p.N,
                                out->dw, out->scale);
+        if (rc != LAST_OK) return rc;
     }
     return hip_status();
 }
