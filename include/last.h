@@ -95,7 +95,7 @@ typedef enum {
  * is order 1), or a next-state table.  next_table: dev int32 [C][V], read by
  * every call that uses the struct, never written; it must stay valid until the
  * work enqueued by the call has finished.  With a table, the weights must be
- * dense, every call runs one workgroup per item, C is limited by the 160 KiB of
+ * dense, every call runs one workgroup per item (and direction), C is limited by the 160 KiB of
  * LDS of a compute unit (about 10000 states for the log semiring, 13000 for the
  * tropical one) and C*V by 2^24 (LAST_ERR_UNSUPPORTED beyond), and each call validates the table
  * on the device (item_status 7). */
@@ -246,12 +246,13 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
  *   LAST_OPT_FORCE_SOLO (0/1, default 0): 1 = always the one-workgroup-per-item kernels (log domain,
  *     no limit on the dynamic range of the weights).
  *   LAST_OPT_CLUSTER_GENERATION (0..3, default 0): which cooperating-workgroup forward-backward kernel
- *     dense bigram lattices take; 0 = the newest that supports the shape, 3 = sixteen workgroups per
+ *     dense bigram lattices take (with 0 those of 5 to 96 states have a kernel of their own, one workgroup
+ *     per item and direction); 0 = the newest that supports the shape, 3 = sixteen workgroups per
  *     direction and item (256 labels only), 2 = eight (5..264 states), 1 = the oldest (one exchange per
  *     frame).  A generation that does not support the shape falls back to the next older one.
  *   LAST_OPT_CLUSTER_VITERBI (0..2, default 1): shortest path of dense bigram lattices: 0 = one workgroup
- *     per item; 1 = cooperating workgroups, the newest kernel that takes the shape; 2 = cooperating
- *     workgroups, the older kernel also where the newer one (256 labels only) would run.
+ *     per item; 1 = the kernel of their own for 4 to 96 states, beyond that cooperating workgroups, the newest
+ *     kernel that takes the shape; 2 = cooperating workgroups, the older kernel also where a newer one would run.
  *   LAST_OPT_SPIN_LIMIT (>= 1, default 2^20): polls a cooperating workgroup makes before it gives up
  *     waiting for the others (the item then gets status 5 and dist = NaN; every kernel still ends).
  *   LAST_OPT_FUSED_FRAMES_PER_TILE (1 or 2, default 2): frames whose on-the-fly weights the forward
@@ -313,8 +314,8 @@ const char* last_status_string(last_status_t status);
 const char* last_hip_error_string(void);
 
 /* Library version and the kernel variant a call would use, for diagnostics:
- * 0 = one workgroup per item, 1 = cooperating workgroups per item (dense
- * weights, context size 1), 2 = on-the-fly weights (shared_emb), -1 = the
+ * 0 = one workgroup per item, 1 = several workgroups per item (dense
+ * weights, context size 1 or 2), 2 = on-the-fly weights (shared_emb), -1 = the
  * combination is not supported (the call would return LAST_ERR_UNSUPPORTED or
  * an argument error). */
 int32_t last_version(void);

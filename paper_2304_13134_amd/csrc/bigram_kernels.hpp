@@ -1,4 +1,4 @@
-// Full 1-gram contexts of 4 to 96 states (C = V + 1) with dense weights: one
+// Full 1-gram contexts of 5 (tropical: 4) to 96 states with dense weights: one
 // workgroup per item and direction, no exchange between compute units.
 //
 // A frame is a C x C matrix; at these sizes one compute unit can stream it and

@@ -748,7 +748,8 @@ last_status_t launch_marginals(const Shape& s, const float* w, const int* length
 bool tab_ok(const Shape& s, bool trop)
 {
     const size_t n = (size_t)s.C * s.V1;
-    return s.order == 0 && !opt(LAST_OPT_FORCE_SOLO) && s.T >= 1 && n >= 4 && n <= (size_t)kTabMaxQ * 4 * kTabThreads
+    // (also bigram lattices of fewer than 5 states, log semiring: log domain, so no limit on the range of the weights)
+    return (s.order == 0 || (!trop && s.order == 1 && s.C < 5)) && !opt(LAST_OPT_FORCE_SOLO) && s.T >= 1 && n >= 4 && n <= (size_t)kTabMaxQ * 4 * kTabThreads
            && tab_lds(s.C, s.V1, trop) <= kBigLds - 1024;
 }
 
@@ -762,12 +763,13 @@ last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const in
 // Full 1-gram contexts, one workgroup per item and direction (bigram_kernels.hpp).  From 97 states on a compute
 // unit takes longer over a frame than a cluster over its exchange: forward-backward at T=200 and 71 states
 // B=16 0.41 / 0.54 ms, B=64 0.48 / 1.17 ms against the cluster; at 101 states (measured with wider tiles) B=16 0.71 / 0.56 ms;
-// shortest path at 71 states B=32 0.33 / 0.37 ms, at 101 0.44 / 0.37 ms.  Below 4 states a row is no 16-byte piece.
+// shortest path at 71 states B=32 0.33 / 0.37 ms, at 101 0.44 / 0.37 ms.  Below 4 states a row is no 16-byte piece;
+// with 4 the log semiring stays in the log domain (tab_ok), whose marginals hold for any range of weights.
 bool bi_ok(const Shape& s, int kind, bool trop)
 {
     if (opt(LAST_OPT_FORCE_SOLO) || kind != LAST_WEIGHTS_DENSE || s.order != 1 || s.T < 1) return false;
     if (trop ? opt(LAST_OPT_CLUSTER_VITERBI) != 1 : opt(LAST_OPT_CLUSTER_GENERATION) != 0) return false;
-    return s.C >= 4 && s.C <= kBiMaxC;
+    return s.C >= (trop ? 4 : 5) && s.C <= kBiMaxC;
 }
 
 
@@ -1140,6 +1142,18 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
     rc = check_ws(ws, ws_bytes, last_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0));
     if (rc != LAST_OK) return rc;
     const SoloLayout l = solo_layout(s);
+    if (semiring == LAST_LOG && tab_ok(s, false) && tri_rows_fit(s)) {
+        Carver cv(ws);
+        int* flag = carve_table_flag(cv, s);
+        if (flag) launch_table_check(s, flag, st);
+        const BiWs bw = carve_bi(cv, s, false);
+        rc = launch_tab(s, bw, weights->w, lengths, false, false, nullptr, nullptr, dist, item_status, flag, st);
+        if (rc != LAST_OK) return rc;
+        hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)bw.alpha, (const float*)bw.beta,
+                           (const double*)bw.offa, (const double*)bw.offb, lengths, (const int*)nullptr, (const int*)flag,
+                           s.T, s.C, 0, (double*)nullptr, dist, item_status);
+        return hip_status();
+    }
     if (s.order == 0) {
         if ((semiring == LAST_LOG ? l.lds_forward : l.lds_viterbi) > kBigLds) return LAST_ERR_UNSUPPORTED;
         Carver cv(ws);
@@ -1148,15 +1162,6 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         if (semiring == LAST_TROPICAL && tab_ok(s, true)) {
             rc = launch_tab(s, BiWs{}, weights->w, lengths, true, false, nullptr, nullptr, dist, item_status, flag, st);
             return rc != LAST_OK ? rc : hip_status();
-        }
-        if (semiring == LAST_LOG && tab_ok(s, false) && tri_rows_fit(s)) {
-            const BiWs bw = carve_bi(cv, s, false);
-            rc = launch_tab(s, bw, weights->w, lengths, false, false, nullptr, nullptr, dist, item_status, flag, st);
-            if (rc != LAST_OK) return rc;
-            hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)bw.alpha, (const float*)bw.beta,
-                               (const double*)bw.offa, (const double*)bw.offb, lengths, (const int*)nullptr, (const int*)flag,
-                               s.T, s.C, 0, (double*)nullptr, dist, item_status);
-            return hip_status();
         }
         rc = semiring == LAST_LOG
                  ? launch_table_forward(s, l, weights->w, lengths, nullptr, nullptr, nullptr, dist, item_status, flag, st)
@@ -1272,7 +1277,7 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     int* flag = carve_table_flag(cv, s);
     if (tab_ok(s, false)) {
         const BiWs bw = carve_bi(cv, s, true);
-        launch_table_check(s, flag, st);
+        if (flag) launch_table_check(s, flag, st);
         rc = launch_tab(s, bw, weights->w, lengths, false, true, nullptr, nullptr, dist, item_status, flag, st);
         if (rc != LAST_OK) return rc;
         rc = launch_marginals<0, false>(s, weights->w, lengths, bw.alpha, bw.beta, bw.offa, bw.offb, bw.D2, out, flag,

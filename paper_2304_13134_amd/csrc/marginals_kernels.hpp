@@ -22,7 +22,7 @@ constexpr float kMgRangeBits = 80.f;
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
 
-// ORDER 1, 2: closed form; 0: next-state table.  LDS: float[C] alpha + exponent | float[C] beta.
+// ORDER 1, 2: closed form; 0: any context (badtab: flag of a bad next-state table, may be null).  LDS: float[C] alpha + exponent | float[C] beta.
 template <int ORDER, bool ACC, bool LINEAR>
 __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int rows,
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     // pieces of four that start on a 16-byte boundary of dw; up to three arcs before them
     const int lead = min((int)((4 - ((size_t)g >> 2)) & 3), n);
     const int n4 = (n - lead) / 4;
-    if (L < 0 || L > T || t >= L || (ORDER == 0 && badtab[0] != 0)) {
+    if (L < 0 || L > T || t >= L || (ORDER == 0 && badtab && badtab[0] != 0)) {
         if (ACC) return;
         for (int i = tid; i < n4; i += kMgThreads) *(float4*)(g + lead + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
         if (tid < lead) g[tid] = 0.f;

@@ -26,7 +26,7 @@ namespace last {
 struct TabArgs {
     const float* w;
     const int* len;
-    const int* bad;      // set by table_check_kernel
+    const int* bad;      // set by table_check_kernel; null for a closed-form context
     float* alpha;        // rows of C floats; tropical: unused
     float* beta;
     double* offa;
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kTabThreads) void table_chain_kernel(TabArgs a, Ctx
     const bool back = !TROP && blockIdx.y == 1;
     const int C = c.C, V1 = c.V1, n = C * V1;
     const int L = a.len[b];
-    const bool badtab = a.bad[0] != 0;
+    const bool badtab = a.bad && a.bad[0] != 0;
     if (L < 0 || L > a.T || badtab) {
         if ((TROP || a.keep) && !back && tid == 0) {
             a.dist[b] = __builtin_nanf("");

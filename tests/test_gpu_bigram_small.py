@@ -13,9 +13,9 @@ from test_gpu_parity import check_path, check_posteriors
 pytestmark = pytest.mark.gpu
 
 
-# V = C - 1: 2 and 96 lie just outside, 3 is the smallest taken; 31/32, 47/48, 63/64, 95 the edges of the
+# V = C - 1: up to 3 labels stay in the log domain, 96 lies just outside; 31/32, 47/48, 63/64, 95 the edges of the
 # instantiations; 34 and 61 rows that no 16-byte piece divides
-@pytest.mark.parametrize("V", [2, 3, 4, 7, 31, 32, 34, 47, 48, 61, 63, 64, 95, 96])
+@pytest.mark.parametrize("V", [1, 2, 3, 4, 7, 31, 32, 34, 47, 48, 61, 63, 64, 95, 96])
 def test_sizes_and_lengths(V):
     announce("small bigram, V", V)
     cfg = workloads.dense(B=8, T=9, V=V, order=1, sigma=1.5, seed=200 + V)
@@ -101,3 +101,17 @@ def test_ties_missing_arcs_and_range(V):
         assert int(status[b]) in (0, 6)
         if int(status[b]) == 0:
             assert np.max(np.abs(g[b].cpu().numpy() - go[b])) <= TOL_POST_ABS
+
+
+@pytest.mark.parametrize("V", [1, 2, 3])
+def test_fewest_states_have_no_range_limit(V):
+    announce("bigram of fewer than five states, weights of up to +-180: right marginals, status 0, V", V)
+    cfg = workloads.dense(B=3, T=12, V=V, order=1, sigma=40.0, seed=4000 + V, len_lo=9, len_hi=12)
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    status = torch.full((3,), -1, dtype=torch.int32, device="cuda")
+    D, g = lb.last_arc_posteriors(w, lengths, item_status=status)
+    assert status.cpu().tolist() == [0, 0, 0]
+    assert_dist_close(D.cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 1)[1])
+    # float32 scores of a few hundred in base 2 resolve 1.5e-5: a handful of roundings in an exponent
+    assert np.max(np.abs(g.cpu().numpy() - oracle.posteriors(cfg["w"], cfg["lengths"], 1))) <= 5.0e-5
+    assert_dist_close(lb.last_shortest_distance(w, lengths).cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 1)[1])
