@@ -204,6 +204,7 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
         prep(I0(), 0);
         prep(std::integral_constant<int, DS - 1>(), 1);
         lds_only_barrier();
+        lds_only_barrier();                                     // (the consumers have E of step 0: step 2 goes to its place)
         for (int t = 0; t < steps; t += 2) {
             prep(I0(), t + 2);
             lds_only_barrier();
@@ -272,6 +273,7 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
     if (steps > 0) {
         lds_only_barrier();
         fetch(0);
+        lds_only_barrier();
     }
 
     if (TROP) {
