@@ -7,7 +7,7 @@
 // LINEAR: alpha, beta are linear relative to 2^offset and dw (+)= scale alpha 2^(w log2 e + offsets - D2) beta.
 // There an entry more than 2^126 below the largest of its frame is zero; the marginal it would have had is below
 // 2^-46 as long as the product of the frame's three maxima is below 2^80, and beyond that the item is
-// flagged (kItemRange) and the exponent capped so that it stays finite.
+// flagged (kItemRange) and the exponent capped so that it stays finite (kMgExpCap).
 // Bound: HBM, 4 bytes read and 4 written per arc.  A workgroup takes a stretch of rows of one frame, keeps
 // its two state vectors in LDS (the row offset of the destinations with them) and goes through the stretch with
 // 16-byte accesses on 16-byte boundaries of memory; rows are V+1 floats, so a piece may span rows.
@@ -19,6 +19,9 @@ namespace last {
 
 constexpr int kMgThreads = 256;
 constexpr float kMgRangeBits = 80.f;
+// The forward weights are sums of at most 97 products below 2 each, times 2^(fraction) <= 2^(1/2): below 2^8.2; 2^f with
+// |f| <= 1/2 adds half a bit and the backward weights, below 2, one: with this cap every product stays below 2^127.
+constexpr float kMgExpCap = 117.f;
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
 
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
             // the largest error of a marginal
             const float y = fmaf(x, kLog2e, K), h = rintf(x * kLog2e);
             const float f = fmaf(x, kLog2eLow, fmaf(x, kLog2e, -h));
-            const float e = y > -200.f ? __builtin_ldexpf(fast_exp2(f), (int)fminf(h + K, 126.f)) : 0.f;
+            const float e = y > -200.f ? __builtin_ldexpf(fast_exp2(f), (int)fminf(h + K, kMgExpCap)) : 0.f;
             return scale * (al[q] * e * be[d]);
         }
         return scale * fast_exp2(fmaf(x, kLog2e, al[q] + be[d]));

@@ -115,3 +115,22 @@ def test_fewest_states_have_no_range_limit(V):
     # float32 scores of a few hundred in base 2 resolve 1.5e-5: a handful of roundings in an exponent
     assert np.max(np.abs(g.cpu().numpy() - oracle.posteriors(cfg["w"], cfg["lengths"], 1))) <= 5.0e-5
     assert_dist_close(lb.last_shortest_distance(w, lengths).cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 1)[1])
+
+
+@pytest.mark.parametrize("V", [8, 32, 59, 95])
+def test_marginals_beyond_the_range_stay_finite(V):
+    announce("small bigram: a frame that only an arc of a vanished state can leave, V", V)
+    C = V + 1
+    w = np.zeros((1, 4, C, C), np.float32)
+    w[0, 1:3] = -1000.0
+    w[0, 1, :, 1] = 0.0                      # every state leads to state 1: its forward weight is the sum of C others
+    w[0, 2, 1, 2] = 0.0                      # from there only to state 2,
+    w[0, 3, 2] = -500.0                      # whose backward weight is far below the smallest float
+    wd, lengths = dev(w), torch.tensor([4], dtype=torch.int32, device="cuda")
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    D, g = lb.last_arc_posteriors(wd, lengths, item_status=status)
+    assert_dist_close(D.cpu().numpy(), oracle.forward(w, np.array([4], np.int32), 1)[1])
+    assert torch.isfinite(g).all() and int(status[0]) in (0, 6)
+    base = torch.full_like(wd, 0.25)
+    lb.last_arc_posteriors(wd, lengths, dw=base, scale=1.0, accumulate=True)
+    assert torch.isfinite(base).all()
