@@ -732,9 +732,10 @@ last_status_t launch_marginals(const Shape& s, const float* w, const int* length
     last_status_t rc = LAST_OK;
     auto go = [&](auto k) {
         if (lds > kMaxLds) rc = allow_lds((const void*)k, kBigLds);
-        if (rc == LAST_OK)
-            hipLaunchKernelGGL(k, dim3(parts, s.T, s.B), dim3(kMgThreads), lds, st, w, lengths, make_ctx(s), s.T, rows,
-                               alpha, beta, offa, offb, D2, out->dw, out->scale, badtab, item_status);
+        // (a grid has at most 65535 blocks in y; B is checked against the same bound)
+        for (int t0 = 0; rc == LAST_OK && t0 < s.T; t0 += 65535)
+            hipLaunchKernelGGL(k, dim3(parts, std::min(s.T - t0, 65535), s.B), dim3(kMgThreads), lds, st, w, lengths, make_ctx(s),
+                               s.T, t0, rows, alpha, beta, offa, offb, D2, out->dw, out->scale, badtab, item_status);
     };
     if (out->accumulate) go(dense_marginals_kernel<ORDER, true, LINEAR>);
     else go(dense_marginals_kernel<ORDER, false, LINEAR>);

@@ -25,10 +25,10 @@ constexpr float kMgExpCap = 117.f;
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
 
-// ORDER 1, 2: closed form; 0: any context (badtab: flag of a bad next-state table, may be null).  LDS: float[C] alpha + exponent | float[C] beta.
+// grid (stretches, frames t0 ..., items).  ORDER 1, 2: closed form; 0: any context (badtab: flag of a bad next-state table, may be null).  LDS: float[C] alpha + exponent | float[C] beta.
 template <int ORDER, bool ACC, bool LINEAR>
 __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
-    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int rows,
+    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int t0, int rows,
     const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
     const double* __restrict__ offb, const double* __restrict__ D2, float* __restrict__ dw, float scale,
     const int* __restrict__ badtab, int* __restrict__ item_status)
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     __shared__ float red[3][kMgThreads / kWave];
     float* al = mg_s;
     float* be = mg_s + c.C;
-    const int t = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int t = t0 + blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int q0 = blockIdx.x * rows, q1 = min(q0 + rows, c.C);
     const size_t first = (((size_t)b * T + t) * c.C + q0) * c.V1;
     const int n = (q1 - q0) * c.V1;

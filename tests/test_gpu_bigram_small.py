@@ -134,3 +134,16 @@ def test_marginals_beyond_the_range_stay_finite(V):
     base = torch.full_like(wd, 0.25)
     lb.last_arc_posteriors(wd, lengths, dw=base, scale=1.0, accumulate=True)
     assert torch.isfinite(base).all()
+
+
+@pytest.mark.parametrize("V", [3, 4])
+def test_more_frames_than_a_grid_has_rows(V):
+    announce("small bigram: 66000 frames, V", V)
+    T, C = 66000, V + 1
+    w = np.full((1, T, C, C), -np.inf, np.float32)
+    w[:, :, 0, 0] = 0.0                      # up to the last 60 frames only the empty label: nothing is rounded there
+    w[:, -60:] = np.random.default_rng(V).normal(size=(1, 60, C, C))
+    lengths = np.array([T], np.int32)
+    D, g = lb.last_arc_posteriors(dev(w), dev(lengths))
+    assert_dist_close(D.cpu().numpy(), oracle.forward(w, lengths, 1)[1])
+    assert np.max(np.abs(g.cpu().numpy() - oracle.posteriors(w, lengths, 1))) <= TOL_POST_ABS
