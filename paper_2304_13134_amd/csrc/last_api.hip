@@ -719,11 +719,33 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
     return rc;
 }
 
+TriRedo tri_redo(const Shape& s, const float* w, const last_grads_t* out)
+{
+    const SoloLayout l = solo_layout(s);
+    return TriRedo{w, make_ctx(s), l.CPAD, l.R, out && s.T > 0 ? out->dw : nullptr, out ? out->scale : 0.f, out ? out->accumulate : 0};
+}
+
+// distance of every item (out: of the call with marginals)
+void launch_tri_join(const Shape& s, const TriWs& c, const float* w, const int* lengths, const last_grads_t* out, float* dist,
+                     int* item_status, hipStream_t st)
+{
+    hipLaunchKernelGGL(tri_join_kernel<true>, dim3(s.B), dim3(1024), solo_layout(s).lds_forward, st, c.alpha, (const float*)c.beta,
+                       c.offa, (const double*)c.offb, lengths, (const int*)c.fail, (const int*)nullptr, s.T, s.C, out ? 1 : 0,
+                       out ? c.D2 : nullptr, dist, item_status, tri_redo(s, w, out));
+}
+
+void launch_tri_final(const Shape& s, const TriWs& c, const float* w, const int* lengths, int* bp, int* final_state, float* score,
+                      int* item_status, hipStream_t st)
+{
+    hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(1024), solo_layout(s).lds_viterbi, st, (const float*)c.alpha, lengths,
+                       (const int*)c.fail, s.T, s.C, bp, final_state, score, item_status, tri_redo(s, w, nullptr));
+}
+
 // marginals of all frames from the stored rows (marginals_kernels.hpp)
 template <int ORDER, bool LINEAR>
 last_status_t launch_marginals(const Shape& s, const float* w, const int* lengths, const float* alpha, const float* beta,
                                const double* offa, const double* offb, const double* D2, const last_grads_t* out,
-                               const int* badtab, int* item_status, hipStream_t st)
+                               const int* badtab, const int* skip, int* item_status, hipStream_t st)
 {
     const size_t lds = (size_t)2 * s.C * sizeof(float);
     int rows = std::max(1, kMgChunk / s.V1);
@@ -735,7 +757,7 @@ last_status_t launch_marginals(const Shape& s, const float* w, const int* length
         // (a grid has at most 65535 blocks in y; B is checked against the same bound)
         for (int t0 = 0; rc == LAST_OK && t0 < s.T; t0 += 65535)
             hipLaunchKernelGGL(k, dim3(parts, std::min(s.T - t0, 65535), s.B), dim3(kMgThreads), lds, st, w, lengths, make_ctx(s),
-                               s.T, t0, rows, alpha, beta, offa, offb, D2, out->dw, out->scale, badtab, item_status);
+                               s.T, t0, rows, alpha, beta, offa, offb, D2, out->dw, out->scale, badtab, skip, item_status);
     };
     if (out->accumulate) go(dense_marginals_kernel<ORDER, true, LINEAR>);
     else go(dense_marginals_kernel<ORDER, false, LINEAR>);
@@ -1150,9 +1172,9 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         const BiWs bw = carve_bi(cv, s, false);
         rc = launch_tab(s, bw, weights->w, lengths, false, false, nullptr, nullptr, dist, item_status, flag, st);
         if (rc != LAST_OK) return rc;
-        hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)bw.alpha, (const float*)bw.beta,
-                           (const double*)bw.offa, (const double*)bw.offb, lengths, (const int*)nullptr, (const int*)flag,
-                           s.T, s.C, 0, (double*)nullptr, dist, item_status);
+        hipLaunchKernelGGL(tri_join_kernel<false>, dim3(s.B), dim3(256), 0, st, bw.alpha, (const float*)bw.beta,
+                           bw.offa, (const double*)bw.offb, lengths, (const int*)nullptr, (const int*)flag,
+                           s.T, s.C, 0, (double*)nullptr, dist, item_status, TriRedo{});
         return hip_status();
     }
     if (s.order == 0) {
@@ -1192,13 +1214,8 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         const TriWs tw = carve_tri(cv, s, tp, trop, false);
         rc = launch_tri(s, tp, tw, weights->w, lengths, trop, false, nullptr, st);
         if (rc != LAST_OK) return rc;
-        if (trop)
-            hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, lengths,
-                               (const int*)tw.fail, s.T, s.C, (int*)nullptr, dist, item_status);
-        else
-            hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, (const float*)tw.beta,
-                               (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, (const int*)nullptr, s.T, s.C, 0,
-                               (double*)nullptr, dist, item_status);
+        if (trop) launch_tri_final(s, tw, weights->w, lengths, nullptr, nullptr, dist, item_status, st);
+        else launch_tri_join(s, tw, weights->w, lengths, nullptr, dist, item_status, st);
     } else if (semiring == LAST_LOG) {
         if (l.lds_forward > kMaxLds) return LAST_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(solo_forward_log, dim3(s.B), dim3(1024), l.lds_forward, st,
@@ -1249,7 +1266,8 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
         const BiWs bw = carve_bi(cvb, s, true);
         rc = launch_bi(s, bw, weights->w, lengths, false, true, nullptr, nullptr, dist, item_status, st);
         if (rc != LAST_OK) return rc;
-        rc = launch_marginals<1, true>(s, weights->w, lengths, bw.alpha, bw.beta, bw.offa, bw.offb, bw.D2, out, nullptr, item_status, st);
+        rc = launch_marginals<1, true>(s, weights->w, lengths, bw.alpha, bw.beta, bw.offa, bw.offb, bw.D2, out, nullptr, nullptr,
+                                       item_status, st);
         return rc != LAST_OK ? rc : hip_status();
     }
     const ClusterPlan plan = cluster_plan(s, weights->kind);
@@ -1265,10 +1283,9 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
         const TriWs tw = carve_tri(cvt, s, tp, false, true);
         rc = launch_tri(s, tp, tw, weights->w, lengths, false, true, nullptr, st);
         if (rc != LAST_OK) return rc;
-        hipLaunchKernelGGL(tri_join_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, (const float*)tw.beta,
-                           (const double*)tw.offa, (const double*)tw.offb, lengths, (const int*)tw.fail, (const int*)nullptr, s.T, s.C, 1,
-                           tw.D2, dist, item_status);
-        rc = launch_marginals<2, false>(s, weights->w, lengths, tw.alpha, tw.beta, tw.offa, tw.offb, tw.D2, out, nullptr, item_status, st);
+        launch_tri_join(s, tw, weights->w, lengths, out, dist, item_status, st);
+        rc = launch_marginals<2, false>(s, weights->w, lengths, tw.alpha, tw.beta, tw.offa, tw.offb, tw.D2, out, nullptr,
+                                        tw.fail, item_status, st);
         return rc != LAST_OK ? rc : hip_status();
     }
     const SoloLayout l = solo_layout(s);
@@ -1282,7 +1299,7 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
         rc = launch_tab(s, bw, weights->w, lengths, false, true, nullptr, nullptr, dist, item_status, flag, st);
         if (rc != LAST_OK) return rc;
         rc = launch_marginals<0, false>(s, weights->w, lengths, bw.alpha, bw.beta, bw.offa, bw.offb, bw.D2, out, flag,
-                                        item_status, st);
+                                        nullptr, item_status, st);
         return rc != LAST_OK ? rc : hip_status();
     }
     PosteriorWs p = carve_posteriors(cv, s);
@@ -1646,8 +1663,7 @@ last_status_t last_shortest_path(const last_weights_t* weights, const int32_t* l
         const TriWs tw = carve_tri(cv, s, tp, true, false);
         rc = launch_tri(s, tp, tw, weights->w, lengths, true, false, p.bp, st);
         if (rc != LAST_OK) return rc;
-        hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(256), 0, st, (const float*)tw.alpha, lengths,
-                           (const int*)tw.fail, s.T, s.C, p.final_state, score, item_status);
+        launch_tri_final(s, tw, weights->w, lengths, p.bp, p.final_state, score, item_status, st);
     } else if (!launch_bigram_viterbi(s, weights->w, lengths, p.bp, p.final_state, score, item_status, st))
         hipLaunchKernelGGL(solo_viterbi, dim3(s.B), dim3(1024), l.lds_viterbi, st, weights->w, lengths,
                            c, s.T, l.CPAD, l.R, p.bp, p.final_state, score, item_status);

@@ -25,13 +25,15 @@ constexpr float kMgExpCap = 117.f;
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
 
-// grid (stretches, frames t0 ..., items).  ORDER 1, 2: closed form; 0: any context (badtab: flag of a bad next-state table, may be null).  LDS: float[C] alpha + exponent | float[C] beta.
+// grid (stretches, frames t0 ..., items).  ORDER 1, 2: closed form; 0: any context (badtab: flag of a bad next-state
+// table, may be null).  skip: items whose marginals have been written already (may be null).
+// LDS: float[C] alpha + exponent | float[C] beta.
 template <int ORDER, bool ACC, bool LINEAR>
 __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int t0, int rows,
     const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
     const double* __restrict__ offb, const double* __restrict__ D2, float* __restrict__ dw, float scale,
-    const int* __restrict__ badtab, int* __restrict__ item_status)
+    const int* __restrict__ badtab, const int* __restrict__ skip, int* __restrict__ item_status)
 {
     extern __shared__ float mg_s[];
     __shared__ float red[3][kMgThreads / kWave];
@@ -41,6 +43,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     const int q0 = blockIdx.x * rows, q1 = min(q0 + rows, c.C);
     const size_t first = (((size_t)b * T + t) * c.C + q0) * c.V1;
     const int n = (q1 - q0) * c.V1;
+    if (skip && skip[b] != 0) return;
     const int L = len[b];
     float* g = dw + first;
     const float* wt = w + first;

@@ -31,28 +31,18 @@ __device__ __forceinline__ void lse_acc(float v, float& m, float& s)
 //   alpha_ws [B][T+1][C] rescaled forward weights (may be null: not stored)
 //   offs     [B][T+1]    A_t (may be null)
 //   Dws      [B]         D in float64 (may be null);  dist [B] float32
-__global__ __launch_bounds__(1024) void solo_forward_log(
-    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int CPAD, int R,
-    float* __restrict__ alpha_ws, double* __restrict__ offs, double* __restrict__ Dws,
-    float* __restrict__ dist, int* __restrict__ item_status)
+// One item of length L by the whole workgroup (any number of waves with R * CPAD threads); smem: LDS of
+// 2C + 2 R CPAD + 32 floats.
+__device__ __forceinline__ void solo_forward_item(
+    int b, int L, float* smem, const float* w, const Ctx& c, int T, int CPAD, int R, float* alpha_ws, double* offs,
+    double* Dws, float* dist)
 {
-    extern __shared__ float smem[];
     float* cur = smem;
     float* nxt = cur + c.C;
     float* pm = nxt + c.C;
     float* ps = pm + R * CPAD;
     float* red = ps + R * CPAD;
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int L = len[b];
-    if (L < 0 || L > T) {
-        if (tid == 0) {
-            if (item_status) item_status[b] = kItemBadLength;
-            dist[b] = __builtin_nanf("");
-            if (Dws) Dws[b] = __builtin_nan("");
-        }
-        return;
-    }
-    if (tid == 0 && item_status) item_status[b] = kItemOk;
+    const int tid = threadIdx.x;
     const int g = tid / CPAD, dl = tid - g * CPAD;
     const size_t fr = (size_t)c.C * c.V1;
     float* al = alpha_ws ? alpha_ws + (size_t)b * (T + 1) * c.C : nullptr;
@@ -123,24 +113,42 @@ __global__ __launch_bounds__(1024) void solo_forward_log(
     }
 }
 
+__global__ __launch_bounds__(1024) void solo_forward_log(
+    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int CPAD, int R,
+    float* __restrict__ alpha_ws, double* __restrict__ offs, double* __restrict__ Dws,
+    float* __restrict__ dist, int* __restrict__ item_status)
+{
+    extern __shared__ float smem[];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int L = len[b];
+    if (L < 0 || L > T) {
+        if (tid == 0) {
+            if (item_status) item_status[b] = kItemBadLength;
+            dist[b] = __builtin_nanf("");
+            if (Dws) Dws[b] = __builtin_nan("");
+        }
+        return;
+    }
+    if (tid == 0 && item_status) item_status[b] = kItemOk;
+    solo_forward_item(b, L, smem, w, c, T, CPAD, R, alpha_ws, offs, Dws, dist);
+}
+
 // Backward weights and arc marginals (Eq. 1; Section 4.2.2).  A group of G
 // lanes owns one source state (a row of the frame, contiguous in memory) and
 // strides over its V+1 arcs.  gamma = exp(alpha~_t[q] + w + beta~_{t+1}[next]
 // + (A_t + B_{t+1} - D)), the bracket formed in float64.
+// smem: LDS of 2C + 32 floats.
 template <int G>
-__global__ __launch_bounds__(1024) void solo_backward_log(
-    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T,
-    const float* __restrict__ alpha_ws, const double* __restrict__ offs,
-    const double* __restrict__ Dws, float* __restrict__ dw, float scale, int accumulate)
+__device__ __forceinline__ void solo_backward_item(
+    int b, int L, float* smem, const float* w, const Ctx& c, int T, const float* alpha_ws, const double* offs,
+    const double* Dws, float* dw, float scale, int accumulate)
 {
-    extern __shared__ float smem[];
     float* bn = smem;          // beta~_{t+1}
     float* bc = bn + c.C;      // beta_t before rescaling
     float* red = bc + c.C;
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const size_t fr = (size_t)c.C * c.V1;
     float* gw = dw + (size_t)b * T * fr;
-    int L = len[b];
     const bool bad = (L < 0 || L > T);
     if (bad) L = 0;
     if (!accumulate)
@@ -190,6 +198,17 @@ __global__ __launch_bounds__(1024) void solo_backward_log(
     }
 }
 
+template <int G>
+__global__ __launch_bounds__(1024) void solo_backward_log(
+    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T,
+    const float* __restrict__ alpha_ws, const double* __restrict__ offs,
+    const double* __restrict__ Dws, float* __restrict__ dw, float scale, int accumulate)
+{
+    extern __shared__ float smem[];
+    const int b = blockIdx.x;
+    solo_backward_item<G>(b, len[b], smem, w, c, T, alpha_ws, offs, Dws, dw, scale, accumulate);
+}
+
 // zero the gradient of items whose length is invalid (used by the clustered path too)
 // workgroup barrier that orders LDS traffic only: global loads issued before it stay in flight
 __device__ __forceinline__ void lds_only_barrier()
@@ -212,29 +231,17 @@ __device__ __forceinline__ void trop_acc(float v, int flat, float& best, int& bf
     if (v > best || (v == best && v != LAST_NEG_INF && flat < bflat)) { best = v; bflat = flat; }
 }
 
-__global__ __launch_bounds__(1024) void solo_viterbi(
-    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int CPAD, int R,
-    int* __restrict__ bp, int* __restrict__ final_state, float* __restrict__ score,
-    int* __restrict__ item_status)
+// One item of length L by the whole workgroup; smem: LDS of 2C + 2 R CPAD + 64 floats.
+__device__ __forceinline__ void solo_viterbi_item(
+    int b, int L, float* smem, const float* w, const Ctx& c, int T, int CPAD, int R, int* bp, int* final_state, float* score)
 {
-    extern __shared__ float smem[];
     float* cur = smem;
     float* nxt = cur + c.C;
     float* pv = nxt + c.C;
     int* pi = (int*)(pv + R * CPAD);
     float* redv = (float*)(pi + R * CPAD);
     int* redi = (int*)(redv + 32);
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int L = len[b];
-    if (L < 0 || L > T) {
-        if (tid == 0) {
-            if (item_status) item_status[b] = kItemBadLength;
-            score[b] = __builtin_nanf("");
-            if (final_state) final_state[b] = -1;
-        }
-        return;
-    }
-    if (tid == 0 && item_status) item_status[b] = kItemOk;
+    const int tid = threadIdx.x;
     const int g = tid / CPAD, dl = tid - g * CPAD;
     const size_t fr = (size_t)c.C * c.V1;
     for (int d = tid; d < c.C; d += blockDim.x) cur[d] = d == 0 ? 0.f : LAST_NEG_INF;
@@ -289,6 +296,26 @@ __global__ __launch_bounds__(1024) void solo_viterbi(
         score[b] = best;
         if (final_state) final_state[b] = bidx;
     }
+}
+
+__global__ __launch_bounds__(1024) void solo_viterbi(
+    const float* __restrict__ w, const int* __restrict__ len, Ctx c, int T, int CPAD, int R,
+    int* __restrict__ bp, int* __restrict__ final_state, float* __restrict__ score,
+    int* __restrict__ item_status)
+{
+    extern __shared__ float smem[];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int L = len[b];
+    if (L < 0 || L > T) {
+        if (tid == 0) {
+            if (item_status) item_status[b] = kItemBadLength;
+            score[b] = __builtin_nanf("");
+            if (final_state) final_state[b] = -1;
+        }
+        return;
+    }
+    if (tid == 0 && item_status) item_status[b] = kItemOk;
+    solo_viterbi_item(b, L, smem, w, c, T, CPAD, R, bp, final_state, score);
 }
 
 // Tropical recursion for the full 1-gram context dependency (state = last label,

@@ -647,71 +647,101 @@ __global__ __launch_bounds__(D::NW * kWave) void trigram_kernel(TriArgs a)
     }
 }
 
+// What the general kernels need to take over an item whose workgroups gave up waiting for each other (their
+// partners had no compute unit: other launches of cooperating workgroups share the chip).
+struct TriRedo {
+    const float* w;
+    Ctx c;
+    int CPAD, R;         // thread layout of solo_kernels.hpp
+    float* dw;           // marginals (may be null)
+    float scale;
+    int accumulate;
+};
+
 // D = log (+)_q alpha_m[q] beta_m[q] of every item from the rows at which the two directions meet (beta = 0 at the
-// last frame), one workgroup per item.  alpha, beta: base-2 logs with offsets.  fail, badtab may be null.
-__global__ __launch_bounds__(256) void tri_join_kernel(
-    const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
-    const double* __restrict__ offb, const int* __restrict__ len, const int* __restrict__ fail,
-    const int* __restrict__ badtab, int T, int C, int keep, double* __restrict__ D2, float* __restrict__ dist,
-    int* __restrict__ item_status)
+// last frame), one workgroup per item.  alpha, beta: base-2 logs with offsets.  badtab may be null.
+// REDO: an item marked in `fail` is computed here once more by this workgroup alone, gradient included
+// (dense_marginals_kernel leaves it out); dynamic LDS of solo_layout.
+template <bool REDO>
+__global__ __launch_bounds__(REDO ? 1024 : 256) void tri_join_kernel(
+    float* alpha, const float* __restrict__ beta, double* offa, const double* __restrict__ offb,
+    const int* __restrict__ len, const int* __restrict__ fail, const int* __restrict__ badtab, int T, int C, int keep,
+    double* D2, float* dist, int* __restrict__ item_status, TriRedo redo)
 {
+    extern __shared__ float tri_redo_s[];
     __shared__ float red[32];
-    __shared__ double redd[4];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    __shared__ double redd[16];
+    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int L = len[b];
-    const bool bad = L < 0 || L > T, tmo = fail && fail[b] != 0, tab = badtab && badtab[0] != 0;
-    if (bad || tmo || tab) {
+    const bool bad = L < 0 || L > T, tab = badtab && badtab[0] != 0;
+    if (bad || tab) {
         if (tid == 0) {
             dist[b] = __builtin_nanf("");
             if (D2) D2[b] = __builtin_nan("");
-            if (item_status) item_status[b] = tab ? kItemBadTable : bad ? kItemBadLength : kItemTimeout;
+            if (item_status) item_status[b] = tab ? kItemBadTable : kItemBadLength;
         }
+        return;
+    }
+    if (tid == 0 && item_status) item_status[b] = kItemOk;
+    if (REDO && fail[b] != 0) {
+        solo_forward_item(b, L, tri_redo_s, redo.w, redo.c, T, redo.CPAD, redo.R, keep ? alpha : nullptr,
+                          keep ? offa : nullptr, D2, dist);
+        __syncthreads();
+        if (redo.dw)
+            solo_backward_item<16>(b, L, tri_redo_s, redo.w, redo.c, T, alpha, offa, D2, redo.dw, redo.scale, redo.accumulate);
         return;
     }
     const size_t ra = keep ? ((size_t)b * (T + 1) + L) : (size_t)b;
     const float* al = alpha + ra * C;
     const float* be = beta + ra * C;
     float mx = LAST_NEG_INF;
-    for (int q = tid; q < C; q += 256) mx = fmaxf(mx, keep ? al[q] : al[q] + be[q]);
+    for (int q = tid; q < C; q += nt) mx = fmaxf(mx, keep ? al[q] : al[q] + be[q]);
     mx = block_max(mx, red);
     const float mm = mx == LAST_NEG_INF ? 0.f : mx;
     double z = 0.0;
-    for (int q = tid; q < C; q += 256) z += (double)fast_exp2((keep ? al[q] : al[q] + be[q]) - mm);
+    for (int q = tid; q < C; q += nt) z += (double)fast_exp2((keep ? al[q] : al[q] + be[q]) - mm);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
     if ((tid & 63) == 0) redd[tid >> 6] = z;
     __syncthreads();
     if (tid == 0) {
-        z = redd[0] + redd[1] + redd[2] + redd[3];
+        z = redd[0];
+        for (int k = 1; k < nt / kWave; ++k) z += redd[k];
         const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF
                                              : offa[ra] + (keep ? 0.0 : offb[ra]) + (double)mm + log2(z);
         dist[b] = (float)(d2 * 0.6931471805599453);
         if (D2) D2[b] = d2;
-        if (item_status) item_status[b] = kItemOk;
     }
 }
 
-// best final state of every item (lowest index among equals) from its final scores
-__global__ __launch_bounds__(256) void tri_final_kernel(
+// best final state of every item (lowest index among equals) from its final scores; an item marked in `fail` is
+// computed here once more by this workgroup alone (dynamic LDS of solo_layout)
+__global__ __launch_bounds__(1024) void tri_final_kernel(
     const float* __restrict__ fin, const int* __restrict__ len, const int* __restrict__ fail, int T, int C,
-    int* __restrict__ final_state, float* __restrict__ score, int* __restrict__ item_status)
+    int* __restrict__ bp, int* __restrict__ final_state, float* __restrict__ score, int* __restrict__ item_status,
+    TriRedo redo)
 {
-    __shared__ float redv[4];
-    __shared__ int redi[4];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    extern __shared__ float tri_redo_s[];
+    __shared__ float redv[16];
+    __shared__ int redi[16];
+    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int L = len[b];
-    const bool bad = L < 0 || L > T, tmo = fail[b] != 0;
-    if (bad || tmo) {
+    if (L < 0 || L > T) {
         if (tid == 0) {
             score[b] = __builtin_nanf("");
             if (final_state) final_state[b] = -1;
-            if (item_status) item_status[b] = bad ? kItemBadLength : kItemTimeout;
+            if (item_status) item_status[b] = kItemBadLength;
         }
+        return;
+    }
+    if (tid == 0 && item_status) item_status[b] = kItemOk;
+    if (fail[b] != 0) {
+        solo_viterbi_item(b, L, tri_redo_s, redo.w, redo.c, T, redo.CPAD, redo.R, bp, final_state, score);
         return;
     }
     float best = LAST_NEG_INF;
     int idx = 0x7fffffff;
-    for (int q = tid; q < C; q += 256) {
+    for (int q = tid; q < C; q += nt) {
         const float v = fin[(size_t)b * C + q];
         if (v > best || (v == best && q < idx)) { best = v; idx = q; }
     }
@@ -724,11 +754,10 @@ __global__ __launch_bounds__(256) void tri_final_kernel(
     if ((tid & 63) == 0) { redv[tid >> 6] = best; redi[tid >> 6] = idx; }
     __syncthreads();
     if (tid == 0) {
-        for (int k = 1; k < 4; ++k)
+        for (int k = 1; k < nt / kWave; ++k)
             if (redv[k] > best || (redv[k] == best && redi[k] < idx)) { best = redv[k]; idx = redi[k]; }
         score[b] = best;
         if (final_state) final_state[b] = idx;
-        if (item_status) item_status[b] = kItemOk;
     }
 }
 

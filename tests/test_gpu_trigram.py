@@ -112,3 +112,53 @@ def test_bounded_waits_end_and_flag():
         assert all(s in (0, 5) for s in status.cpu().tolist())
     check_posteriors(cfg, order=2)
     check_path(cfg, order=2)
+
+
+# V: one, two, fourteen and sixteen workgroups an item and direction
+@pytest.mark.parametrize("V", [5, 24, 42, 64])
+def test_items_whose_waits_ran_out_are_computed_all_the_same(V):
+    announce("trigram: a spin limit of one poll, results and status as ever, V", V)
+    T = 8 if V > 40 else 20
+    cfg = workloads.dense(B=4, T=T, V=V, order=2, sigma=1.0, seed=40 + V, len_lo=T - 3, len_hi=T)
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    _, D_o = oracle.forward(cfg["w"], cfg["lengths"], 2)
+    g_o = oracle.posteriors(cfg["w"], cfg["lengths"], 2)
+    status = torch.full((4,), -1, dtype=torch.int32, device="cuda")
+    with library_option(lb.OPT_SPIN_LIMIT, 1):
+        check_posteriors(cfg, order=2)
+        check_path(cfg, order=2)
+        base = torch.full_like(w, 0.5)
+        D, _ = lb.last_arc_posteriors(w, lengths, order=2, dw=base, scale=-2.0, accumulate=True, item_status=status)
+        assert status.cpu().tolist() == [0] * 4
+        assert_dist_close(D.cpu().numpy(), D_o)
+        assert np.max(np.abs(base.cpu().numpy() - (0.5 - 2.0 * g_o))) <= 2.0 * TOL_POST_ABS
+        assert_dist_close(lb.last_shortest_distance(w, lengths, order=2, item_status=status).cpu().numpy(), D_o)
+        assert status.cpu().tolist() == [0] * 4
+        best = lb.last_shortest_distance(w, lengths, order=2, semiring="tropical", item_status=status)
+        assert status.cpu().tolist() == [0] * 4
+        assert np.array_equal(best.cpu().numpy(), oracle.viterbi(cfg["w"], cfg["lengths"], 2, "f32")[2])
+
+
+@pytest.mark.parametrize("V,B", [(24, 8), (50, 20)])
+def test_calls_on_several_streams_share_the_chip(V, B):
+    announce("trigram: three calls at a time on streams of their own, V, B", V, B)
+    cfg = workloads.dense(B=B, T=12, V=V, order=2, sigma=1.0, seed=V, len_lo=9, len_hi=12)
+    w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+    D, g = lb.last_arc_posteriors(w, lengths, order=2)
+    labels, states, score = lb.last_shortest_path(w, lengths, order=2)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for _ in range(2):
+        status = [torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in streams]
+        torch.cuda.synchronize()
+        out = []
+        for i, stream in enumerate(streams):
+            with torch.cuda.stream(stream):
+                out.append(lb.last_shortest_path(w, lengths, order=2, item_status=status[i]) if i == 1
+                           else lb.last_arc_posteriors(w, lengths, order=2, item_status=status[i]))
+        torch.cuda.synchronize()
+        assert all(torch.all(x == 0) for x in status)
+        for i in (0, 2):                     # (an item that another kernel had to take agrees within the tolerance)
+            assert_dist_close(out[i][0].cpu().numpy(), D.cpu().numpy())
+            assert torch.max(torch.abs(out[i][1] - g)).item() <= TOL_POST_ABS
+        assert torch.equal(out[1][0], labels) and torch.equal(out[1][1], states) and torch.equal(out[1][2], score)
