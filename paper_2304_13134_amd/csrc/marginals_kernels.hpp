@@ -1,26 +1,35 @@
 // Arc marginals (Eq. 1 of arXiv 2304.13134) of the complete lattice from stored
 // state vectors, for any context dependency: the whole chip streams over the
 // frames, nothing is serial.
-//   alpha, beta [B][T+1][C] base-2 logs, relative to the float64 offsets
-//   offa, offb  [B][T+1];  D2 [B] base-2 log of the partition sum
-//   dw[b][t][q][y] (+)= scale 2^(alpha_t[q] + w log2 e + beta_{t+1}[next(q,y)] + (offa_t + offb_{t+1} - D2))
-// LINEAR: alpha, beta are linear relative to 2^offset and dw (+)= scale alpha 2^(w log2 e + offsets - D2) beta.
-// There an entry more than 2^126 below the largest of its frame is zero; the marginal it would have had is below
-// 2^-46 as long as the product of the frame's three maxima is below 2^80, and beyond that the item is
-// flagged (kItemRange) and the exponent capped so that it stays finite (kMgExpCap).
+//   alpha, beta [B][T+1][C] natural logs, relative to the float64 offsets
+//   offa, offb  [B][T+1];  D2 [B] log of the partition sum
+//   dw[b][t][q][y] (+)= scale exp(alpha_t[q] + w + beta_{t+1}[next(q,y)] + offa_t + offb_{t+1}) / Z_{t+1}
+// with Z_{t+1} = sum_q exp(alpha_{t+1}[q] + beta_{t+1}[q] + offsets), formed here.  It is the partition sum, but from
+// the two vectors at hand: what the roundings of some hundred frames have moved the vectors by
+// as a whole is in the numerator and in Z alike.  Divided by exp(D2), which has the roundings of the forward pass, it
+// stayed in the marginals (their relative error together, against 64 bits, 61 frames, sigma 1.5: 5 states 2.7e-7 against
+// 0.8e-7, a table of 200 states with 12 labels 1.2e-6 against 2.1e-7).  One more vector is read for each stretch of
+// rows, 1 to 3 % of a call (loss at 8 items, 300 frames, 32 labels of order 2 0.737 -> 0.747 ms).
+// LINEAR: alpha, beta are linear relative to 2^offset, offsets and D2 in base 2, and dw (+)= scale alpha 2^(w log2 e) beta
+// 2^offsets / Z.  There an entry more than 2^126 below the largest of its frame is zero; the marginal it would have had is
+// below 2^-46 as long as the product of the frame's three maxima is below 2^80 Z, and beyond that the item is
+// flagged (kItemRange) and the exponent capped so that it stays finite (kMgExpCap).  It is flagged, too, where
+// Z is not the partition sum: then one of the directions has lost a part of it.
 // Bound: HBM, 4 bytes read and 4 written per arc.  A workgroup takes a stretch of rows of one frame, keeps
 // its two state vectors in LDS (the row offset of the destinations with them) and goes through the stretch with
 // 16-byte accesses on 16-byte boundaries of memory; rows are V+1 floats, so a piece may span rows.
 #pragma once
 #include "cluster_kernels.hpp"
 #include "common.hpp"
+#include "trigram_kernels.hpp"
 
 namespace last {
 
 constexpr int kMgThreads = 256;
 constexpr float kMgRangeBits = 80.f;
-// The forward weights are sums of at most 97 products below 2 each, times 2^(fraction) <= 2^(1/2): below 2^8.2; 2^f with
-// |f| <= 1/2 adds half a bit and the backward weights, below 2, one: with this cap every product stays below 2^127.
+constexpr double kMgLostBits = 0.01;         // difference of two logarithms of the partition sum that no rounding makes
+// The forward weights are sums of at most 97 products below 2 each: below 2^7.6; 2^f with |f| <= 1/2 adds half a bit, the
+// backward weights, below 2, one, and 1 / Z's mantissa one at most: with this cap every product stays below 2^128.
 constexpr float kMgExpCap = 117.f;
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
@@ -37,6 +46,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
 {
     extern __shared__ float mg_s[];
     __shared__ float red[3][kMgThreads / kWave];
+    __shared__ double redz[kMgThreads / kWave];
     float* al = mg_s;
     float* be = mg_s + c.C;
     const int t = t0 + blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
@@ -57,25 +67,63 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
         for (int i = lead + 4 * n4 + tid; i < n; i += kMgThreads) g[i] = 0.f;
         return;
     }
-    float K, amax = 0.f, bmax = 0.f, wmax = LAST_NEG_INF;
-    {
-        const size_t ra = (size_t)b * (T + 1) + t;
-        const double d2 = D2[b];                      // (-inf: no path, every product below is zero)
-        const double kd = d2 == (double)LAST_NEG_INF ? 0.0 : offa[ra] + offb[ra + 1] - d2;
-        // linear: the whole part goes into the exponent of 2^w, the fraction into the forward weights
-        K = LINEAR ? (float)rint(fmin(fmax(kd, -1.0e9), 1.0e9)) : (float)kd;
-        const float scaleK = LINEAR ? fast_exp2((float)(kd - (double)K)) : 1.f;
+    float K = 0.f, amax = 0.f, bmax = 0.f, wmax = LAST_NEG_INF, sc = scale;
+    bool lost = false;
+    const size_t ra = (size_t)b * (T + 1) + t;
+    const int wv = tid / kWave;
+    if (LINEAR) {
+        double z = 0.0;
         for (int q = tid; q < c.C; q += kMgThreads) {
             const float x = alpha[ra * c.C + q], y = beta[(ra + 1) * c.C + q];
-            if (LINEAR) {
-                al[q] = x * scaleK;
-                amax = fmaxf(amax, x);
-                bmax = fmaxf(bmax, y);
-            } else if (q >= q0 && q < q1) {
-                al[q] = x + K;
-            }
+            z += (double)alpha[(ra + 1) * c.C + q] * (double)y;
+            al[q] = x;
+            be[q] = y;
+            amax = fmaxf(amax, x);
+            bmax = fmaxf(bmax, y);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
+        if ((tid & (kWave - 1)) == 0) redz[wv] = z;
+        __syncthreads();
+        z = redz[0];
+#pragma unroll
+        for (int k = 1; k < kMgThreads / kWave; ++k) z += redz[k];
+        // 1 / Z: the exponent goes into that of 2^w (offsets are whole numbers), the mantissa into the scale
+        const double d2 = D2[b];                  // (-inf: no path, every product below is zero)
+        if (z > 0.0) {
+            int e;
+            const double m = frexp(z, &e);        // in [1/2, 1)
+            K = (float)(offa[ra] - offa[ra + 1] - (double)e);
+            sc = scale * (float)(1.0 / m);
+            lost = !(fabs(offa[ra + 1] + offb[ra + 1] + log2(z) - d2) < kMgLostBits);
+        } else {
+            lost = d2 != (double)LAST_NEG_INF;
+        }
+    } else {
+        float m = LAST_NEG_INF, z = 0.f;
+        for (int q = tid; q < c.C; q += kMgThreads) {
+            const float x = alpha[ra * c.C + q], y = beta[(ra + 1) * c.C + q];
+            const float v = alpha[(ra + 1) * c.C + q] + y;
+            const float n = fmaxf(m, v), nn = n == LAST_NEG_INF ? 0.f : n;
+            z = fmaf(z, tri_exp(m - nn), tri_exp(v - nn));
+            m = n;
+            if (q >= q0 && q < q1) al[q] = x;
             be[q] = y;
         }
+        const float mw = wave_max_dpp(m), mn = mw == LAST_NEG_INF ? 0.f : mw;
+        z = wave_sum_dpp(z * tri_exp(m - mn));
+        if ((tid & (kWave - 1)) == 0) { red[0][wv] = mw; red[1][wv] = z; }
+        __syncthreads();
+        float M = red[0][0];
+#pragma unroll
+        for (int k = 1; k < kMgThreads / kWave; ++k) M = fmaxf(M, red[0][k]);
+        const float MM = M == LAST_NEG_INF ? 0.f : M;     // (no path: every exponential below is zero)
+        z = 0.f;
+#pragma unroll
+        for (int k = 0; k < kMgThreads / kWave; ++k) z += red[1][k] * tri_exp(red[0][k] - MM);
+        sc = M == LAST_NEG_INF ? scale : scale / z;
+        const double kd = offa[ra] - offa[ra + 1] - (double)MM;
+        for (int q = q0 + tid; q < q1; q += kMgThreads) al[q] = (float)((double)al[q] + kd);
     }
     __syncthreads();
     auto arc = [&](int q, int y, float x) __attribute__((always_inline)) {
@@ -92,9 +140,9 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
             const float y = fmaf(x, kLog2e, K), h = rintf(x * kLog2e);
             const float f = fmaf(x, kLog2eLow, fmaf(x, kLog2e, -h));
             const float e = y > -200.f ? __builtin_ldexpf(fast_exp2(f), (int)fminf(h + K, kMgExpCap)) : 0.f;
-            return scale * (al[q] * e * be[d]);
+            return sc * (al[q] * e * be[d]);
         }
-        return scale * fast_exp2(fmaf(x, kLog2e, al[q] + be[d]));
+        return sc * tri_exp(al[q] + be[d] + x);
     };
     for (int i = tid; i < n4; i += kMgThreads) {
         const int e = lead + 4 * i;
@@ -125,7 +173,6 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
         if (ACC) g[e] += o; else g[e] = o;
     }
     if (LINEAR && item_status) {
-        const int wv = tid / kWave;
         amax = wave_max(amax);
         bmax = wave_max(bmax);
         wmax = wave_max(wmax);
@@ -137,7 +184,8 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
                 bmax = fmaxf(bmax, red[1][k]);
                 wmax = fmaxf(wmax, red[2][k]);
             }
-            if (amax > 0.f && bmax > 0.f && K + wmax * kLog2e + __builtin_amdgcn_logf(amax) + __builtin_amdgcn_logf(bmax) > kMgRangeBits)
+            if (lost || (amax > 0.f && bmax > 0.f
+                         && K + wmax * kLog2e + __builtin_amdgcn_logf(amax) + __builtin_amdgcn_logf(bmax) > kMgRangeBits))
                 atomicMax(item_status + b, (int)kItemRange);
         }
     }

@@ -14,7 +14,7 @@
 // the table's entries as 16-bit numbers, and LPR lanes take a row.
 // Measured (8 items, 200 frames, 585 states, 8 labels): both directions 2.3 us a
 // frame, last_arc_posteriors 0.53 ms against 6.1 ms, shortest path 0.22 against 1.4 ms.
-// Base-2 logs relative to a float64 offset per frame; marginals are formed from the
+// Natural logs relative to a float64 offset per frame, rounded as in table_kernels.hpp; marginals are formed from the
 // stored vectors by dense_marginals_kernel.
 #pragma once
 #include "common.hpp"
@@ -49,6 +49,21 @@ __host__ __device__ inline size_t tab_lds(int C, int V1, bool trop)
     const size_t fwd = (size_t)C * (trop ? 12 : 16) + 64 * sizeof(float);
     const size_t bwd = ((n + 7) & ~(size_t)3) * 4 + ((n + 3) & ~(size_t)3) * 2 + (size_t)C * 8 + 64 * sizeof(float);
     return trop || fwd > bwd ? fwd : bwd;
+}
+
+// log(sum 2^-40) of a fixed-point sum: exponent, mantissa in [0.7, 1.4) and what the mantissa was rounded by apart, so
+// that the result is as good as the double-precision logarithm rounded to float32 (which took a fifth of a frame here)
+__device__ __forceinline__ float tab_ln(tk_u64 sum)
+{
+    const double d = (double)sum * kTkUnfix;
+    const float f = (float)d;
+    int e = __builtin_amdgcn_frexp_expf(f);
+    float m = __builtin_amdgcn_frexp_mantf(f);
+    const bool low = m < 0.70710678f;
+    m = low ? 2.f * m : m;
+    e -= low;
+    const float r = (float)(d - (double)f) * __builtin_amdgcn_rcpf(f);
+    return fmaf((float)e, kLn2, fmaf(__builtin_amdgcn_logf(m), kLn2, r));
 }
 
 // largest value of the workgroup's 16 waves; ends with the barrier after which red is readable
@@ -141,7 +156,7 @@ __global__ __launch_bounds__(kTabThreads) void table_chain_kernel(TabArgs a, Ctx
                     const bool on = arc[j][k] != 0xffffffffu;
                     const float x = on ? cur[arc[j][k] >> 16] : LAST_NEG_INF;
                     // (an arc out of an unreachable state does not count, whatever its weight)
-                    v[j][k] = x == LAST_NEG_INF ? LAST_NEG_INF : TROP ? __fadd_rn(x, wv[k]) : fmaf(wv[k], kLog2e, x);
+                    v[j][k] = x == LAST_NEG_INF ? LAST_NEG_INF : __fadd_rn(x, wv[k]);
                 }
             }
 #pragma unroll
@@ -175,13 +190,13 @@ __global__ __launch_bounds__(kTabThreads) void table_chain_kernel(TabArgs a, Ctx
                 for (int k = 0; k < 4; ++k)
                     if (v[j][k] != LAST_NEG_INF) {
                         const int d = arc[j][k] & 0xffffu;
-                        atomicAdd(&sm[d], (tk_u64)(fast_exp2(v[j][k] - tk_sval(mk[d])) * kTkFix));
+                        atomicAdd(&sm[d], (tk_u64)(tri_exp(v[j][k] - tk_sval(mk[d])) * kTkFix));
                     }
             lds_only_barrier();
             float mx = LAST_NEG_INF;
             for (int d = tid; d < C; d += kTabThreads) {
                 const float m = tk_sval(mk[d]);
-                const float x = m == LAST_NEG_INF ? m : m + __builtin_amdgcn_logf((float)sm[d] * (float)kTkUnfix);
+                const float x = m == LAST_NEG_INF ? m : m + tab_ln(sm[d]);
                 cur[d] = x;
                 mk[d] = kneg;
                 sm[d] = 0;
@@ -237,7 +252,7 @@ __global__ __launch_bounds__(kTabThreads) void table_chain_kernel(TabArgs a, Ctx
             mx = tab_block_max(mx, red);
             const float mm = mx == LAST_NEG_INF ? 0.f : mx;
             double z = 0.0;
-            for (int d = tid; d < C; d += kTabThreads) z += (double)fast_exp2(cur[d] - mm);
+            for (int d = tid; d < C; d += kTabThreads) z += (double)tri_exp(cur[d] - mm);
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
             __syncthreads();
@@ -247,9 +262,9 @@ __global__ __launch_bounds__(kTabThreads) void table_chain_kernel(TabArgs a, Ctx
             if (tid == 0) {
                 z = 0.0;
                 for (int k = 0; k < kTabThreads / kWave; ++k) z += redd[k];
-                const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF : A + (double)mm + log2(z);
+                const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF : A + (double)mm + log(z);
                 a.D2[b] = d2;
-                a.dist[b] = (float)(d2 * 0.6931471805599453);
+                a.dist[b] = (float)d2;
                 if (a.item_status) a.item_status[b] = kItemOk;
             }
         }
@@ -305,24 +320,24 @@ __global__ __launch_bounds__(kTabThreads) void table_chain_kernel(TabArgs a, Ctx
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int e = q * V1 + min(y + i, e1 - 1);
-                        x[i] = fmaf(tile[e], kLog2e, be[nxs[e]]);
+                        x[i] = tile[e] + be[nxs[e]];
                         if (y + i >= e1) x[i] = LAST_NEG_INF;
                         mn = fmaxf(mn, x[i]);
                     }
                     const float mm = mn == LAST_NEG_INF ? 0.f : mn;
-                    s *= fast_exp2(m - mm);
+                    s *= tri_exp(m - mm);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) s += fast_exp2(x[i] - mm);
+                    for (int i = 0; i < 4; ++i) s += tri_exp(x[i] - mm);
                     m = mn;
                 }
             }
             for (int o = 1; o < lpr; o <<= 1) {
                 const float om = __shfl_xor(m, o, kWave), os = __shfl_xor(s, o, kWave);
                 const float mn = fmaxf(m, om), mm = mn == LAST_NEG_INF ? 0.f : mn;
-                s = s * fast_exp2(m - mm) + os * fast_exp2(om - mm);
+                s = s * tri_exp(m - mm) + os * tri_exp(om - mm);
                 m = mn;
             }
-            const float x = m == LAST_NEG_INF ? m : m + __builtin_amdgcn_logf(s);
+            const float x = ln_sum(m, s);
             if (q < C && l == 0) bc[q] = x;
             mx = fmaxf(mx, q < C ? x : LAST_NEG_INF);
         }

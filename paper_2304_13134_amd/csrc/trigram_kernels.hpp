@@ -13,9 +13,10 @@
 // the one exchange per frame, through the XCD's L2 (tagged 64-bit words, see
 // cluster_kernels.hpp).  The empty label keeps the state and needs none.
 //
-// Everything is in the log domain (base 2, float32 relative to a float64
+// Everything is in the log domain (natural logarithms, float32 relative to a float64
 // offset per frame, the offset being the largest entry of the frame), so there is no limit on
-// the dynamic range of the weights; the tropical recursion adds float32 scores
+// the dynamic range of the weights, and scores are rounded as in solo_kernels.hpp (in
+// base 2 they would be 1.44 times larger, and so would their roundings).  The tropical recursion adds float32 scores
 // and keeps (score, source) exactly as solo_viterbi does.
 //
 // What bounds it: the chain of a frame.  Own rows -> partial sums (compute
@@ -48,7 +49,7 @@ namespace last {
 struct TriArgs {
     const float* w;
     const int* len;
-    float* alpha;        // log: rows of C floats (base-2 logs); tropical: final scores [B][C]
+    float* alpha;        // log: rows of C floats (natural logs); tropical: final scores [B][C]
     float* beta;
     double* offa;        // offsets of the rows
     double* offb;
@@ -81,11 +82,19 @@ struct TriDims {
     static constexpr int BtPitch = (4 * EPL) | 1;              // odd: neighbouring labels start in other banks
 };
 
-__device__ __forceinline__ float tri_lse2(float x, float y)     // log2(2^x + 2^y)
+constexpr float kLn2 = 0.6931471805599453f;
+
+// log of a sum of e^x from the largest x and the sum of e^(x - m); -inf for m = -inf
+__device__ __forceinline__ float ln_sum(float m, float z)
+{
+    return m == LAST_NEG_INF ? LAST_NEG_INF : fmaf(__builtin_amdgcn_logf(z), kLn2, m);
+}
+__device__ __forceinline__ float tri_exp(float d) { return fast_exp2(d * kLog2e); }
+__device__ __forceinline__ float tri_lse2(float x, float y)     // log(e^x + e^y)
 {
     const float m = fmaxf(x, y), lo = fminf(x, y);
     const float d = m == LAST_NEG_INF ? 0.f : lo - m;
-    return m + __builtin_amdgcn_logf(1.f + fast_exp2(d));
+    return fmaf(__builtin_amdgcn_logf(1.f + tri_exp(d)), kLn2, m);
 }
 
 __device__ __forceinline__ float4 tri_load4(buf_t r, unsigned voff, unsigned soff)      // 4-byte aligned
@@ -264,7 +273,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                     float xB = LAST_NEG_INF;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float x = TROP ? __fadd_rn(q[n][c], wc[c]) : fmaf(wc[c], kLog2e, q[n][c]);
+                        const float x = __fadd_rn(q[n][c], wc[c]);
                         q[n][c] = x;
                         xB = c == cB ? x : xB;
                         if (TROP) {
@@ -282,10 +291,10 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         const float mm = m[c] == LAST_NEG_INF ? 0.f : m[c];
-                        if (n0 > 0) z[c] *= fast_exp2(mo[c] - mm);
+                        if (n0 > 0) z[c] *= tri_exp(mo[c] - mm);
 #pragma unroll
                         for (int n = 0; n < N3; ++n)
-                            if (n0 + n < D::NR) z[c] += fast_exp2(q[n][c] - mm);
+                            if (n0 + n < D::NR) z[c] += tri_exp(q[n][c] - mm);
                     }
                 }
             }
@@ -348,12 +357,12 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 const float mm = val == LAST_NEG_INF ? 0.f : val;
                 float zz = 0.f;
 #pragma unroll
-                for (int g = 0; g < kTriMaxG; ++g) zz += z[g] * fast_exp2(m[g] - mm);
-                val = val == LAST_NEG_INF ? LAST_NEG_INF : val + __builtin_amdgcn_logf(zz);
+                for (int g = 0; g < kTriMaxG; ++g) zz += z[g] * tri_exp(m[g] - mm);
+                val = ln_sum(val, zz);
             }
             const float blg = act ? blr : LAST_NEG_INF;
             // histories of one label: from the start state, or kept by the empty label; the start state: kept
-            const float sn = !second ? LAST_NEG_INF : TROP ? __fadd_rn(start, w0) : fmaf(w0, kLog2e, start);
+            const float sn = !second ? LAST_NEG_INF : __fadd_rn(start, w0);
             const float sb = single ? sbr : LAST_NEG_INF;
             float head = LAST_NEG_INF;
             u64 word = 0, hw = 0;
@@ -522,7 +531,7 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
                         if (e0 == 0) v[0] = l == 0 ? keep : v[0];
 #pragma unroll
                         for (int e = e0; e < e0 + EH && e < D::EPL; ++e) {
-                            v[e] = e < epl ? fmaf(x[e], kLog2e, v[e]) : LAST_NEG_INF;
+                            v[e] = e < epl ? x[e] + v[e] : LAST_NEG_INF;
                             m = fmaxf(m, v[e]);
                         }
                         if (D::EPL > 11) __builtin_amdgcn_sched_barrier(0);
@@ -531,9 +540,9 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
                     const float mm = m == LAST_NEG_INF ? 0.f : m;
                     float z = 0.f;
 #pragma unroll
-                    for (int e = 0; e < D::EPL; ++e) z += fast_exp2(v[e] - mm);
+                    for (int e = 0; e < D::EPL; ++e) z += tri_exp(v[e] - mm);
                     z = tri_quad_sum(z);
-                    if (l == 0) s.bl[r] = m == LAST_NEG_INF ? LAST_NEG_INF : m + __builtin_amdgcn_logf(z);
+                    if (l == 0) s.bl[r] = ln_sum(m, z);
                 }
                 if (D::EPL > 11) __builtin_amdgcn_sched_barrier(0);                // (one row's elements in registers at a time)
             }
@@ -659,7 +668,7 @@ struct TriRedo {
 };
 
 // D = log (+)_q alpha_m[q] beta_m[q] of every item from the rows at which the two directions meet (beta = 0 at the
-// last frame), one workgroup per item.  alpha, beta: base-2 logs with offsets.  badtab may be null.
+// last frame), one workgroup per item.  alpha, beta: natural logs with offsets.  badtab may be null.
 // REDO: an item marked in `fail` is computed here once more by this workgroup alone, gradient included
 // (dense_marginals_kernel leaves it out); dynamic LDS of solo_layout.
 template <bool REDO>
@@ -699,7 +708,7 @@ __global__ __launch_bounds__(REDO ? 1024 : 256) void tri_join_kernel(
     mx = block_max(mx, red);
     const float mm = mx == LAST_NEG_INF ? 0.f : mx;
     double z = 0.0;
-    for (int q = tid; q < C; q += nt) z += (double)fast_exp2((keep ? al[q] : al[q] + be[q]) - mm);
+    for (int q = tid; q < C; q += nt) z += (double)tri_exp((keep ? al[q] : al[q] + be[q]) - mm);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
     if ((tid & 63) == 0) redd[tid >> 6] = z;
@@ -708,8 +717,8 @@ __global__ __launch_bounds__(REDO ? 1024 : 256) void tri_join_kernel(
         z = redd[0];
         for (int k = 1; k < nt / kWave; ++k) z += redd[k];
         const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF
-                                             : offa[ra] + (keep ? 0.0 : offb[ra]) + (double)mm + log2(z);
-        dist[b] = (float)(d2 * 0.6931471805599453);
+                                             : offa[ra] + (keep ? 0.0 : offb[ra]) + (double)mm + log(z);
+        dist[b] = (float)d2;
         if (D2) D2[b] = d2;
     }
 }
