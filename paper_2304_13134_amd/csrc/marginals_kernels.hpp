@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
         float m = LAST_NEG_INF, z = 0.f;
         for (int q = tid; q < c.C; q += kMgThreads) {
             const float x = alpha[ra * c.C + q], y = beta[(ra + 1) * c.C + q];
-            const float v = alpha[(ra + 1) * c.C + q] + y;
+            const float a1 = alpha[(ra + 1) * c.C + q], v = a1 == LAST_NEG_INF ? a1 : a1 + y;
             const float n = fmaxf(m, v), nn = n == LAST_NEG_INF ? 0.f : n;
             z = fmaf(z, tri_exp(m - nn), tri_exp(v - nn));
             m = n;
@@ -142,7 +142,8 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
             const float e = y > -200.f ? __builtin_ldexpf(fast_exp2(f), (int)fminf(h + K, kMgExpCap)) : 0.f;
             return sc * (al[q] * e * be[d]);
         }
-        return sc * tri_exp(al[q] + be[d] + x);
+        // (an arc out of an unreachable state does not count, whatever its weight)
+        return al[q] == LAST_NEG_INF ? 0.f : sc * tri_exp(al[q] + be[d] + x);
     };
     for (int i = tid; i < n4; i += kMgThreads) {
         const int e = lead + 4 * i;

@@ -5,9 +5,10 @@ import pytest
 import torch
 
 import oracle
+from oracle import brute_force as bf
 from paper_2304_13134_amd import binding as lb
 from paper_2304_13134_amd import workloads
-from gpu_util import announce, dev, library_option
+from gpu_util import TOL_POST_ABS, announce, assert_dist_close, dev, library_option
 from test_gpu_tables_local import both_orders, check_table_lattice
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +59,24 @@ def test_bad_table_is_reported_by_every_call():
     assert status.cpu().tolist() == [7, 7]
     labels, _, score = lb.last_shortest_path(w, lengths, order=g0, item_status=status)
     assert status.cpu().tolist() == [7, 7] and torch.isnan(score).all() and torch.all(labels == -1)
+
+
+@pytest.mark.parametrize("V", [2, 5])
+def test_weights_of_unreachable_states_do_not_matter(V):
+    announce("table chain: NaN and +inf on arcs out of states that no path has reached yet, V", V)
+    table, _ = bf.history_table(V, 3)
+    C = table.shape[0]
+    cfg = workloads.dense(B=2, T=9, V=V, sigma=1.0, seed=V, len_lo=6, len_hi=9, C=C)
+    o0, g0 = both_orders(table)
+    lengths = dev(cfg["lengths"])
+    _, D_o = oracle.forward(cfg["w"], cfg["lengths"], o0)
+    g_o = oracle.posteriors(cfg["w"], cfg["lengths"], o0)
+    cfg["w"][:, 0, 1:] = np.nan                                # only the start state
+    cfg["w"][:, 1, 1 + V:, ::2] = np.inf                       # histories of at most one label
+    cfg["w"][:, 1, 1 + V:, 1::2] = np.nan
+    w = dev(cfg["w"])
+    for solo in (0, 1):
+        with library_option(lb.OPT_FORCE_SOLO, solo):
+            D, g = lb.last_arc_posteriors(w, lengths, order=g0)
+            assert_dist_close(D.cpu().numpy(), D_o)
+            assert np.max(np.abs(g.cpu().numpy() - g_o)) <= TOL_POST_ABS
