@@ -1485,9 +1485,13 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
             with_pieces([&](auto QL) {
                 auto k = num_scatter_local_kernel<decltype(QL)::value>;
                 const size_t need = (size_t)U1 * (sizeof(float2) + 3 * sizeof(int)) + (s.C <= kNsMaxC ? s.C : 0);
-                if (need > kMaxLds) rc = allow_lds((const void*)k, kBigLds - 1024);
+                if (need + 64 > kMaxLds) rc = allow_lds((const void*)k, kBigLds - 1024);
+                // eight workgroups a compute unit, as long as each still has 16 KiB of the frame to write, or 128 KiB where
+                // the frames alone are two a compute unit (800 frames of 601 labels 393 -> 333 us, of 131 labels 60 -> 64)
+                const size_t frames = (size_t)s.T * s.B, bytes = (size_t)s.C * s.V1 * sizeof(float);
+                const int parts = (int)std::max((size_t)1, std::min((2048 + frames - 1) / frames, bytes >> (frames < 512 ? 14 : 17)));
                 if (rc == LAST_OK)
-                    hipLaunchKernelGGL(k, dim3(s.T, s.B), dim3(kNsThreads), need, st,
+                    hipLaunchKernelGGL(k, dim3(s.T, s.B, parts), dim3(kNsThreads), need, st,
                                        weights->w, (const double2*)p.wi, (const double*)p.lz, lengths, refs,
                                        ref_lengths, (const int*)p.status, (const int*)p.ctxs, (const int*)p.link,
                                        c, s.T, Umax, (const double*)p.a, (const double*)p.bk, (const double*)p.N,

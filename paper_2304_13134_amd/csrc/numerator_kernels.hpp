@@ -130,11 +130,12 @@ template <int QL>
 struct NumPieces {
     int at[QL];          // first column of the piece
     int skip[QL];        // leading columns that do not count (4: the whole piece)
-    __device__ __forceinline__ NumPieces(int V1, int lane)
+    // c0: first column (a row of more than 256 QL weights goes by stretches of that many)
+    __device__ __forceinline__ NumPieces(int V1, int lane, int c0 = 0)
     {
 #pragma unroll
         for (int j = 0; j < QL; ++j) {
-            const int c = 4 * (lane + kWave * j);
+            const int c = c0 + 4 * (lane + kWave * j);
             at[j] = min(c, V1 - 4);
             skip[j] = min(c - at[j], 4);
         }
@@ -160,7 +161,8 @@ __device__ __forceinline__ NumRow<QL> num_load_row(const float* __restrict__ row
 // weights (their forward or backward weight is -inf, whatever the arc weights).
 // Bound: HBM, one row of the frame per cell.  Rows are read once, with 16-byte loads into registers, those of the
 // wave's frames in flight together: B=16, T=500, V=256, 50 to 150 labels 0.58 -> 0.25 ms against one cell per
-// wave whose row was read twice, 4 bytes a lane.  Rows of more than 512 weights go through a loop.
+// wave whose row was read twice, 4 bytes a lane.  Rows of more than 512 weights (QL = 0) are read twice, in stretches
+// of 256, the second time from cache.
 constexpr int kNlFrames = 4;
 template <int QL>
 __global__ __launch_bounds__(256) void num_gather_local_kernel(
@@ -220,6 +222,37 @@ __global__ __launch_bounds__(256) void num_gather_local_kernel(
                 for (int k = 0; k < 4; ++k) si += k >= p.skip[j] ? expf(r[i].w[j][k] - mm) : 0.f;
             s[i] = lanes((double)si);
         }
+    } else if (c.V1 >= 4) {
+        float mi[kNlFrames], si[kNlFrames];
+#pragma unroll
+        for (int i = 0; i < kNlFrames; ++i) {
+            const float* row = one(in[i] ? i : 0);
+            mi[i] = LAST_NEG_INF;
+            si[i] = 0.f;
+            w0[i] = row[0];
+            w1[i] = row[y1];
+        }
+        auto stretch = [&](int c0, auto&& f) __attribute__((always_inline)) {
+            const NumPieces<1> p(c.V1, lane, c0);
+            NumRow<1> r[kNlFrames];
+#pragma unroll
+            for (int i = 0; i < kNlFrames; ++i) r[i] = num_load_row<1>(one(in[i] ? i : 0), p);
+#pragma unroll
+            for (int i = 0; i < kNlFrames; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) f(i, r[i].w[0][k], k >= p.skip[0]);
+        };
+        for (int c0 = 0; c0 < c.V1; c0 += 4 * kWave)
+            stretch(c0, [&](int i, float x, bool) __attribute__((always_inline)) { mi[i] = fmaxf(mi[i], x); });
+#pragma unroll
+        for (int i = 0; i < kNlFrames; ++i) {
+            m[i] = wave_max(mi[i]);
+            mi[i] = m[i] == LAST_NEG_INF ? 0.f : m[i];
+        }
+        for (int c0 = 0; c0 < c.V1; c0 += 4 * kWave)
+            stretch(c0, [&](int i, float x, bool counts) __attribute__((always_inline)) { si[i] += counts ? expf(x - mi[i]) : 0.f; });
+#pragma unroll
+        for (int i = 0; i < kNlFrames; ++i) s[i] = lanes((double)si[i]);
     } else {
 #pragma unroll 1
         for (int i = 0; i < kNlFrames; ++i) {
@@ -548,7 +581,9 @@ __global__ void num_scatter_kernel(const float2* __restrict__ wi, const int* __r
 // Gradient of the locally normalised log-likelihood (Section 2.1) with respect to the weights,
 // dw[b][t][q][y] (+)= scale * ( [marginals of the intersected lattice riding on arc (t,q,y)]
 //                              - [their sum over the arcs leaving (t,q)] * softmax(w[b][t][q])[y] ).
-// One workgroup per frame: the marginals of its cells first (thread <-> cell, into LDS), then row by row one
+// One workgroup per frame, several where the frames are large and few (each forms the marginals of all cells and takes
+// its share of the rows: one item, 10 frames, 2001 labels 247 -> 47 us, 50 frames of 1201 labels 161 -> 71 us): the
+// marginals of its cells first (thread <-> cell, into LDS), then row by row one
 // wavefront per chain of cells with the same context q (see num_check_kernel): it alone writes row (t,q), so no
 // atomics are needed and the result does not depend on timing.  Rows that no path visits are zero (accumulate:
 // left alone) and are written by the same workgroup, every element of the tensor once.
@@ -568,14 +603,14 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     const double* __restrict__ Nws, float* __restrict__ dw, float scale, int accumulate, int zeroed)
 {
     extern __shared__ float2 nsl_p[];
-    __shared__ int count;
+    __shared__ int count, visited;
     const int U1 = Umax + 1;
     int* heads = (int*)(nsl_p + U1);
     int* next = heads + U1;                     // next cell of the chain, -1: none
     int* label = next + U1;                     // label of the cell's label arc, -1: none
     unsigned char* seen = (unsigned char*)(label + U1);
     const bool zeros = !accumulate && !zeroed;  // rows no path visits are written here
-    const int b = blockIdx.y, t = blockIdx.x, tid = threadIdx.x;
+    const int b = blockIdx.y, t = blockIdx.x, tid = threadIdx.x, part = blockIdx.z, parts = gridDim.z;
     const int wv = tid / kWave, lane = tid & (kWave - 1);
     constexpr int NW = kNsThreads / kWave;
     const int L = len[b], U = ulen[b];
@@ -589,7 +624,7 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     const size_t cell0 = ((size_t)b * T + t) * U1;
     if (zeros)
         for (int q = tid; q < c.C; q += kNsThreads) seen[q] = 0;
-    if (tid == 0) count = 0;
+    if (tid == 0) { count = 0; visited = 0; }
     if (live) {
         const double* at = a + ((size_t)b * (T + 1) + t) * U1;
         const double* bn = bk + ((size_t)b * (T + 1) + t + 1) * U1;
@@ -619,7 +654,8 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             bool any = false;
             for (int v = u; v >= 0 && !any; v = next[v]) any = nsl_p[v].x >= 0.f;
             if (!any) continue;
-            heads[atomicAdd(&count, 1)] = u;            // (the order of the rows does not matter)
+            if (u % parts == part) heads[atomicAdd(&count, 1)] = u;     // (the order of the rows does not matter)
+            visited = 1;
             if (zeros) seen[cx[u]] = 1;
         }
     __syncthreads();
@@ -627,14 +663,16 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     // rows no path visits
     if (zeros) {
         float* g = dw + fo;
-        if (n == 0) {
+        if (!live || !visited) {
             const int total = c.C * c.V1, lead = min((int)((4 - ((size_t)g >> 2)) & 3), total), n4 = (total - lead) / 4;
-            for (int i = tid; i < n4; i += kNsThreads) *(float4*)(g + lead + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (size_t i = (size_t)part * kNsThreads + tid; i < (size_t)n4; i += (size_t)parts * kNsThreads)
+                *(float4*)(g + lead + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (part > 0) return;
             if (tid < lead) g[tid] = 0.f;
             for (int i = lead + 4 * n4 + tid; i < total; i += kNsThreads) g[i] = 0.f;
             return;
         }
-        for (int q = wv; q < c.C; q += NW) {
+        for (int q = part * NW + wv; q < c.C; q += parts * NW) {
             if (seen[q]) continue;
             float* grow = g + (size_t)q * c.V1;
             struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
@@ -644,7 +682,7 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
                     for (int k = y; k < c.V1; ++k) grow[k] = 0.f;
         }
     }
-    constexpr int Q = QL > 0 ? QL : 1;
+    constexpr int Q = QL > 0 ? QL : 2;
     const NumPieces<Q> p(c.V1, lane);
     auto row_of = [&](int i) __attribute__((always_inline)) { return fo + (size_t)cx[heads[min(i, n - 1)]] * c.V1; };
     NumRow<Q> nx;
@@ -655,43 +693,60 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
         const NumRow<Q> x = nx;
         if (QL > 0) nx = num_load_row<Q>(w + row_of(i + NW), p);
         float occ = 0.f, pbs = 0.f, lab[Q][4];
-#pragma unroll
-        for (int j = 0; j < Q; ++j)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) lab[j][k] = 0.f;
         int first = -1;
-        for (int v = u; v >= 0; v = next[v]) {                 // chain order: deterministic
-            const float2 pv = nsl_p[v];
-            const int y = label[v];
-            if (pv.x < 0.f) continue;
-            if (first < 0) first = v;
-            occ += pv.x + pv.y;
-            pbs += pv.x;
+        // the chain's label marginals by column, in chain order (deterministic), and once per row their sums
+        auto walk = [&](const NumPieces<Q>& at, bool sums) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < Q; ++j)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) lab[j][k] += p.at[j] + k == y ? pv.y : 0.f;
-        }
+                for (int k = 0; k < 4; ++k) lab[j][k] = 0.f;
+            for (int v = u; v >= 0; v = next[v]) {
+                const float2 pv = nsl_p[v];
+                const int y = label[v];
+                if (pv.x < 0.f) continue;
+                if (sums) {
+                    if (first < 0) first = v;
+                    occ += pv.x + pv.y;
+                    pbs += pv.x;
+                }
+#pragma unroll
+                for (int j = 0; j < Q; ++j)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) lab[j][k] += at.at[j] + k == y ? pv.y : 0.f;
+            }
+        };
+        walk(p, true);
         const double z = lz[cell0 + first];                    // the same for every cell of the chain
         float* grow = dw + ro;
         auto grad = [&](int y, float wy, float l) __attribute__((always_inline)) {
             const float g = l - occ * __expf((float)((double)wy - z));
             return scale * (y == 0 ? g + pbs : g);
         };
-        if (QL > 0) {
+        auto put = [&](const NumPieces<Q>& at, const NumRow<Q>& r) __attribute__((always_inline)) {
             struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-                if (p.skip[j] >= 4) continue;
+                if (at.skip[j] >= 4) continue;
                 f4 o;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) o.v[k] = grad(p.at[j] + k, x.w[j][k], lab[j][k]);
-                float* d = grow + p.at[j];
+                for (int k = 0; k < 4; ++k) o.v[k] = grad(at.at[j] + k, r.w[j][k], lab[j][k]);
+                float* d = grow + at.at[j];
                 if (!accumulate) *(f4*)d = o;
                 else
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
-                        if (k >= p.skip[j]) d[k] += o.v[k];
+                        if (k >= at.skip[j]) d[k] += o.v[k];
+            }
+        };
+        if (QL > 0) {
+            put(p, x);
+        } else if (c.V1 >= 4) {
+            // (one walk along the chain per stretch: with one per 64 columns 4000 labels took 3 times as long)
+            for (int c0 = 0; c0 < c.V1; c0 += 4 * kWave * Q) {
+                const NumPieces<Q> at(c.V1, lane, c0);
+                const NumRow<Q> r = num_load_row<Q>(w + ro, at);
+                if (c0 > 0) walk(at, false);
+                put(at, r);
             }
         } else {
             for (int y = lane; y < c.V1; y += kWave) {

@@ -8,14 +8,16 @@ import oracle
 from paper_2304_13134_amd import binding as lb
 from paper_2304_13134_amd import workloads
 from gpu_util import TOL_POST_ABS, announce, assert_dist_close, dev
+from test_gpu_tables_local import both_orders
 
 pytestmark = pytest.mark.gpu
 
 
-# V + 1 floats a row: 3 (no 16-byte piece), 4, 5, 256/257 (one or two pieces a lane), 512/513 (two, or a loop);
+# V + 1 floats a row: 3 (no 16-byte piece), 4, 5, 256/257 (one or two pieces a lane), 512/513 (two, or a loop), 800
+# (frames of 2.5 MB, several workgroups each);
 # order 2 with 33 931 states: more than the marks of a frame hold, the tensor is filled by another kernel
 @pytest.mark.parametrize("V,order,T,U", [(2, 1, 9, 4), (3, 1, 9, 6), (4, 1, 9, 5), (255, 1, 7, 5), (256, 1, 7, 6),
-                                         (511, 1, 6, 4), (512, 1, 6, 4), (184, 2, 3, 2), (9, 2, 12, 7)])
+                                         (511, 1, 6, 4), (512, 1, 6, 4), (799, 1, 5, 4), (184, 2, 3, 2), (9, 2, 12, 7)])
 def test_rows(V, order, T, U):
     announce("local rows: V, order, T, U", V, order, T, U)
     cfg = workloads.config(3, B=4 if order == 1 or V < 100 else 1, T=T, V=V, order=order, Umax=U, u_lo=1, u_hi=U)
@@ -31,4 +33,27 @@ def test_rows(V, order, T, U):
     assert np.max(np.abs(g.cpu().numpy() - lo["grad"])) <= TOL_POST_ABS
     base = torch.full_like(w, 0.25)
     lb.last_local_log_likelihood(w, lengths, refs, ulen, order=order, dw=base, scale=-2.0, accumulate=True)
+    assert torch.max(torch.abs(base - (0.25 - 2.0 * g))).item() < 1e-6
+
+
+# rows of 513, 515, 1024, 1025 and 3000 weights, all cells of a frame in one or two chains
+@pytest.mark.parametrize("V,C", [(512, 1), (514, 2), (1023, 1), (1024, 1), (2999, 2)])
+def test_long_rows_and_chains(V, C):
+    announce("local rows of more than 512 weights, long chains: V, C", V, C)
+    T, U = 21, 12
+    cfg = workloads.dense(B=3, T=T, V=V, sigma=1.5, seed=V, C=C)
+    refs, ulen = workloads.references(np.random.default_rng(V), 3, V, U, 0, U)
+    refs[0, 1::2] = refs[0, 0]                                  # one label several times
+    cfg["lengths"] = np.array([T, T - 1, 13], np.int32)
+    ulen[0] = U
+    cfg["w"][np.random.default_rng(V).random(cfg["w"].shape) < 0.1] = -1.0e4
+    o0, g0 = both_orders(workloads.random_table(C, V, seed=C))
+    w, lengths, r, n = dev(cfg["w"]), dev(cfg["lengths"]), dev(refs), dev(ulen)
+    lo = oracle.numerator_local(cfg["w"], cfg["lengths"], refs, ulen, o0)
+    g = torch.full_like(w, 7.0)
+    ll = lb.last_local_log_likelihood(w, lengths, r, n, order=g0, dw=g)
+    assert_dist_close(ll.cpu().numpy(), lo["N"])
+    assert np.max(np.abs(g.cpu().numpy() - lo["grad"])) <= TOL_POST_ABS
+    base = torch.full_like(w, 0.25)
+    lb.last_local_log_likelihood(w, lengths, r, n, order=g0, dw=base, scale=-2.0, accumulate=True)
     assert torch.max(torch.abs(base - (0.25 - 2.0 * g))).item() < 1e-6
