@@ -48,13 +48,16 @@
  *   the number of frames: numerator = -inf, its marginals are 0);
  *   5 the cooperating workgroups of an item timed out waiting for each other
  *   (results of that item are undefined; never expected in normal operation);
- *   6 the weights of the item span more dynamic range than the bandwidth path
- *   for dense bigram lattices guarantees for marginals (it keeps state vectors
- *   in scaled float32: entries more than 2^126 below the largest of a frame
- *   are zero there).  dist is still exact; marginals of arcs that leave such
- *   states may be lost.  Not raised for weights within about +-50; setting the
- *   environment variable LAST_FORCE_SOLO=1 selects the log-domain kernels,
- *   which have no such limit.
+ *   6 the weights of the item span more dynamic range than the kernels for
+ *   dense bigram lattices of 5 to 264 states guarantee for marginals (they keep
+ *   state vectors in scaled float32: entries more than 2^126 below the largest
+ *   of a frame may be zero there): paths through such states may be missing
+ *   from the marginals and from dist.  Never raised for weights within +-27;
+ *   setting the environment variable LAST_FORCE_SOLO=1 selects the log-domain
+ *   kernels, which have no such limit.  last_shortest_distance does not raise
+ *   it: up to 96 states it computes such items in the log domain (weights more
+ *   than 1040 below the largest of their row count as absent arcs), from 97 to
+ *   264 states dist may miss such paths.
  * Items with status 1..3 get dist = NaN and zero gradients.
  * Frames t >= len[b] do not exist for item b: their weights are never read
  * into a result, their marginals are 0 and their path entries are -1.

@@ -19,9 +19,23 @@
 //             rows at a time (three steps that merge two rows each, three adds), row sums -> LDS;
 //   tropical: as forward with (score, source row) and first-maximum rules.
 // Arithmetic is scaled linear float32: the state vector is brought to
-// 2^(s_q - S) state_q with S the largest exponent present, so the largest term
-// of every sum is near 1 whatever the range of the weights; the exponents S add up
-// in a float64 offset per frame.
+// 2^(s_q - S + 100) state_q with S the largest exponent present, the exponents S - 100 add up
+// in a float64 offset per frame, and a sum of 97 products stays below 2^108.  What is lost is what
+// lies 2^126 below the largest weight of its row or 2^226 below the largest state of its
+// frame: nothing to a sum, unless paths make up for it elsewhere.  With marginals an item that may have
+// lost a part is flagged (marginals_kernels.hpp).  Without them the consumers note
+//  - whether a frame with a state so small that lost weights could have been a part of it (below kBiThin; they are
+//    below 2^-18 together) was followed by one that does not bury them again: in which a state is not above
+//    kBiThick, or a row's weights are more than 2^20 above those of the states that matter;
+//  - whether states that may be lost as a factor (kBiSmall) came before a frame that does not bury them.
+// bigram_join_kernel looks through the weights of the former items for some that are far below their row's largest,
+// computes those and the latter in the log domain, and so the distance is exact but for two things
+// that count as absent: weights more than 1040 below the largest of their row, and paths that stay in the
+// start state (which nothing leads back to, so that it always falls behind) until they are 2^226
+// behind and make up for that later.
+// (What was tried instead: E with a span of 2^176, 7 vector instructions a weight instead of 2, the loss at 8
+// items, 200 frames, 32 labels 193 us instead of 177; the weights tested by the producers, the distance 95
+// instead of 84 us.  The producers are the longer half of a frame.)
 // Marginals are formed afterwards from the stored vectors (marginals_kernels.hpp).
 //
 // Measured: last_arc_posteriors at B=8, T=200, V=32 0.16 ms (0.73 us a frame)
@@ -45,17 +59,24 @@ struct BiArgs {
     float* beta;
     double* offa;
     double* offb;
-    double* D2;          // keep: base-2 logarithm of the partition sum
+    double* D2;          // KEEP: base-2 logarithm of the partition sum
     float* dist;
     int* item_status;
     int* bp;             // tropical: [B][T][C] flat arc indices (may be null)
     int* final_state;
     int T, C, P;         // P: pitch of E in LDS, C rounded up to 4
     int rc, rp;          // rows per consumer, rows per producer
-    int keep;            // 1: every row at [b][T+1][C], distance written; 0: the meeting row at [b][C]
+    int* wide;           // not KEEP: [B][2], 1: weights may have been lost, 2: states may have been
 };
 
 constexpr int kBiMaxC = 96;
+constexpr int kBiCentre = 100;           // exponent of the largest state
+constexpr float kBiThin = 1024.f;                    // 2^10
+constexpr float kBiThick = 1.1529215e18f;            // 2^60: what a thin state has lost is 2^-51 of the states after it
+constexpr int kBiOver = 20;
+constexpr unsigned kBiAbsent = 1500, kBiSmall = 1340;    // states 2^160 to 2^1500 below the largest (kBiAbsent less is the unit)
+constexpr float kBiFar = 60.f;                       // weights that may be lost against such a state: 2^60 to 2^1500 below
+                                                     // their row's largest; beyond 2^1500 they are meant to
 
 // Sum or maximum over the 64 lanes of R = 8 or 4 rows at a time; lane l ends with row bi_row<R>(l).
 template <int R>
@@ -121,7 +142,8 @@ struct BiLds {
 };
 
 // grid (B, roles): blockIdx.y = 0 forward, 1 backward.  Dynamic LDS: E [2][C][P].
-template <typename D, bool TROP>
+// KEEP: every row at [b][T+1][C], distance written; else the meeting row at [b][C].
+template <typename D, bool TROP, bool KEEP>
 __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
 {
     constexpr int CB = D::CB, NC = D::NC, RC = D::RC, PP = D::PP, LPR = D::LPR, RPP = 64 / LPR, DS = D::DS;
@@ -132,7 +154,7 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
     const bool back = !TROP && blockIdx.y == 1;
     const int C = a.C, P = a.P, L = a.len[b];
     if (L < 0 || L > a.T) {
-        if ((TROP || a.keep) && !back && tid == 0) {
+        if ((TROP || KEEP) && !back && tid == 0) {
             a.dist[b] = __builtin_nanf("");
             if (!TROP) a.D2[b] = __builtin_nan("");
             if (TROP && a.final_state) a.final_state[b] = -1;
@@ -140,8 +162,8 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
         }
         return;
     }
-    const int low = a.keep ? 1 : L / 2;
-    const int steps = TROP ? L : back ? max(L - low, 0) : a.keep ? L : L / 2;
+    const int low = KEEP ? 1 : L / 2;
+    const int steps = TROP ? L : back ? max(L - low, 0) : KEEP ? L : L / 2;
     const int esz = C * P;
     typedef std::integral_constant<int, 0> I0;
     typedef std::integral_constant<int, 1> I1;
@@ -239,9 +261,42 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
     };
     float v[CB];                                     // the state vector, lane <-> state
     double A = 0.0;
+    // not KEEP: exponents of the positive states below the largest one's, from kBiAbsent down; a lane without a state, and
+    // the start state in the forward direction, do not count
+    unsigned small[CB];
+    bool was_thin = false, unburied = false, unburied_small = false;
+    float not_thin[CB];
+    unsigned not_small[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        const bool out = !ok[c] || (!back && c == 0 && lane == 0);
+        not_thin[c] = out ? __builtin_inff() : 0.f;
+        not_small[c] = out ? ~0u : 0u;
+        small[c] = ~0u;
+    }
+    auto look = [&]() __attribute__((always_inline)) {                  // at the new states
+        float least = v[0] + not_thin[0];
+#pragma unroll
+        for (int c = 1; c < CB; ++c) least = fminf(least, v[c] + not_thin[c]);
+        if (!__any(least < kBiThick)) {
+            was_thin = false;
+            return;
+        }
+        unsigned s0 = small[0];
+#pragma unroll
+        for (int c = 1; c < CB; ++c) s0 = min(s0, small[c]);
+        unburied = unburied || was_thin;
+        unburied_small = unburied_small || __any(s0 < kBiSmall);
+        was_thin = __any(least < kBiThin);
+    };
+    auto note = [&]() __attribute__((always_inline)) {
+        if (KEEP || wave != 0) return;
+        const int f = (unburied ? 1 : 0) | (unburied_small ? 2 : 0);
+        if (lane == 0) a.wide[(size_t)b * 2 + (back ? 1 : 0)] = f;
+    };
     auto put_row = [&](float* base, double* off, int t) __attribute__((always_inline)) {
         if (wave != 0) return;
-        const size_t row = a.keep ? (size_t)b * (a.T + 1) + t : (size_t)b;
+        const size_t row = KEEP ? (size_t)b * (a.T + 1) + t : (size_t)b;
 #pragma unroll
         for (int c = 0; c < CB; ++c)
             if (ok[c]) base[row * C + 64 * c + lane] = v[c];
@@ -260,14 +315,27 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
     };
     // 2^(s_q - S) v_q with S the largest exponent present; returns S
     auto normalise = [&](const int (&sh)[CB], float (&x)[CB]) __attribute__((always_inline)) {
-        int top = -0x40000000;
+        int top = -0x40000000, ex[CB];
 #pragma unroll
-        for (int c = 0; c < CB; ++c) top = max(top, v[c] > 0.f ? float_exponent(v[c]) + sh[c] : -0x40000000);
+        for (int c = 0; c < CB; ++c) {
+            ex[c] = v[c] > 0.f ? float_exponent(v[c]) + sh[c] : -0x40000000;
+            top = max(top, ex[c]);
+        }
         top = wave_max_dpp(top);
         if (top == -0x40000000) top = 0;             // no state reachable
 #pragma unroll
-        for (int c = 0; c < CB; ++c) x[c] = __builtin_ldexpf(v[c], sh[c] - top);
-        return top;
+        for (int c = 0; c < CB; ++c) x[c] = __builtin_ldexpf(v[c], sh[c] - top + kBiCentre);
+        if (!KEEP) {
+#pragma unroll
+            for (int c = 0; c < CB; ++c) small[c] = (unsigned)(ex[c] - (top - (int)kBiAbsent)) | not_small[c];
+            if (was_thin) {
+                int most = sh[0];
+#pragma unroll
+                for (int c = 1; c < CB; ++c) most = max(most, sh[c]);
+                unburied = unburied || __any(most - top + kBiCentre > kBiOver);
+            }
+        }
+        return top - kBiCentre;
     };
 
     if (steps > 0) {
@@ -367,7 +435,7 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
                 eb[c] = s.e0[t & 3][col[c]];
                 acc[c] = 0.f;
             }
-            if (a.keep) put_row(a.alpha, a.offa, t);
+            if (KEEP) put_row(a.alpha, a.offa, t);
             const int top = normalise(sh, x);
             A += (double)top;
 #pragma unroll
@@ -393,13 +461,15 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
                 if (c == 0 && lane == 0) y = 0.f;                  // (column 0 is the empty label)
                 v[c] = ok[c] ? y + eb[c] : 0.f;
             }
+            if (!KEEP) look();
         };
         for (int t = 0; t < steps; t += 2) {
             frame(I0(), t);
             if (t + 1 < steps) frame(I1(), t + 1);
         }
         put_row(a.alpha, a.offa, steps);
-        if (a.keep && wave == 0) {
+        note();
+        if (KEEP && wave == 0) {
             // all states of the last frame are final with weight 0
             double z = 0.0;
 #pragma unroll
@@ -416,8 +486,9 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
         return;
     }
 #pragma unroll
-    for (int c = 0; c < CB; ++c) v[c] = ok[c] ? 1.f : 0.f;
-    if (a.keep || steps == 0) put_row(a.beta, a.offb, L);
+    for (int c = 0; c < CB; ++c) v[c] = ok[c] ? __builtin_ldexpf(1.f, kBiCentre) : 0.f;
+    A = -(double)kBiCentre;
+    if (KEEP || steps == 0) put_row(a.beta, a.offb, L);
     auto frame = [&](auto PAR, int n) __attribute__((always_inline)) {
         constexpr int Z = decltype(PAR)::value;
         float p[RC];
@@ -446,41 +517,90 @@ __global__ __launch_bounds__((D::NC + D::NP) * 64) void bigram_kernel(BiArgs a)
             v[c] = s.rs[Z][col[c]];
             v[c] = ok[c] ? v[c] : 0.f;
         }
+        if (!KEEP) look();
         const int top = normalise(sh, x);
         A += (double)top;
 #pragma unroll
         for (int c = 0; c < CB; ++c) v[c] = x[c];
-        if (a.keep || n + 1 == steps) put_row(a.beta, a.offb, L - 1 - n);
+        if (KEEP || n + 1 == steps) put_row(a.beta, a.offb, L - 1 - n);
     };
     for (int n = 0; n < steps; n += 2) {
         frame(I0(), n);
         if (n + 1 < steps) frame(I1(), n + 1);
     }
+    note();
 }
 
-// D = log2 sum_q alpha_m[q] beta_m[q] of every item at the frame where the two directions meet (the call without marginals)
-__global__ __launch_bounds__(64) void bigram_join_kernel(
-    const float* __restrict__ alpha, const float* __restrict__ beta, const double* __restrict__ offa,
-    const double* __restrict__ offb, const int* __restrict__ len, int T, int C, float* __restrict__ dist,
-    int* __restrict__ item_status)
+// D = log2 sum_q alpha_m[q] beta_m[q] of every item at the frame where the two directions meet (the call without
+// marginals).  An item some part of which may have been lost (`wide`, after a look through its weights; or the sum more than
+// 2^60 below the product of the two maxima, so that states lost from one vector may matter in the other)
+// is computed with the general recursion (dynamic LDS of solo_layout).
+__global__ __launch_bounds__(1024) void bigram_join_kernel(
+    const float* __restrict__ w, Ctx c, int CPAD, int R, const float* __restrict__ alpha, const float* __restrict__ beta,
+    const double* __restrict__ offa, const double* __restrict__ offb, const int* __restrict__ wide,
+    const int* __restrict__ len, int T, float* __restrict__ dist, int* __restrict__ item_status)
 {
-    const int b = blockIdx.x, lane = threadIdx.x;
+    extern __shared__ float bi_join_s[];
+    __shared__ int apart, thin, found;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
     const int L = len[b];
     if (L < 0 || L > T) {
-        if (lane == 0) {
+        if (tid == 0) {
             dist[b] = __builtin_nanf("");
             if (item_status) item_status[b] = kItemBadLength;
         }
         return;
     }
-    double z = 0.0;
-    for (int q = lane; q < C; q += 64) z += (double)alpha[(size_t)b * C + q] * (double)beta[(size_t)b * C + q];
+    if (tid < kWave) {
+        double z = 0.0;
+        float am = 0.f, bm = 0.f;
+        for (int q = tid; q < c.C; q += kWave) {
+            const float x = alpha[(size_t)b * c.C + q], y = beta[(size_t)b * c.C + q];
+            z += (double)x * (double)y;
+            am = fmaxf(am, x);
+            bm = fmaxf(bm, y);
+        }
+        const int f = wide[(size_t)b * 2] | wide[(size_t)b * 2 + 1];
+        am = wave_max_dpp(am);
+        bm = wave_max_dpp(bm);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
-    if (lane == 0) {
-        dist[b] = (float)((offa[b] + offb[b] + log2(z)) * 0.6931471805599453);
-        if (item_status) item_status[b] = kItemOk;
+        for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
+        if (tid == 0) {
+            const double lz = log2(z);
+            dist[b] = (float)((offa[b] + offb[b] + lz) * 0.6931471805599453);
+            if (item_status) item_status[b] = kItemOk;
+            apart = (f & 2) || (am > 0.f && bm > 0.f
+                                && (double)(__builtin_amdgcn_logf(am) + __builtin_amdgcn_logf(bm)) - lz > 60.0);
+            thin = f & 1;
+            found = 0;
+        }
     }
+    __syncthreads();
+    if (!apart && thin) {
+        // (a row per wave, eight rows in flight; rows are at most 128 long)
+        const float* wi = w + (size_t)b * T * c.C * c.V1;
+        const int rows = L * c.C, last = c.V1 - 1, c0 = min(lane, last), c1 = min(lane + kWave, last);
+        constexpr int NW = 1024 / kWave, U = 8;
+        bool far = false;
+        for (int r0 = tid / kWave; r0 < rows; r0 += NW * U) {
+            float x[U], y[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float* row = wi + (size_t)min(r0 + NW * u, rows - 1) * c.V1;
+                x[u] = row[c0];
+                y[u] = row[c1];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float ns = -(float)shift_for(wave_max_dpp(fmaxf(x[u], y[u])));
+                const float p = fmaf(x[u], kLog2e, ns), q = fmaf(y[u], kLog2e, ns);
+                far = far || (p < -kBiFar && p > -(float)kBiAbsent) || (q < -kBiFar && q > -(float)kBiAbsent);
+            }
+        }
+        if (far) found = 1;
+        __syncthreads();
+    }
+    if (apart || found) solo_forward_item(b, L, bi_join_s, w, c, T, CPAD, R, nullptr, nullptr, nullptr, dist);
 }
 
 }  // namespace last

@@ -779,6 +779,7 @@ bool tab_ok(const Shape& s, bool trop)
 struct BiWs {
     float *alpha, *beta;
     double *offa, *offb, *D2;
+    int* wide;           // call without marginals
 };
 last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep,
                          int* bp, int* final_state, float* dist, int* item_status, const int* flag, hipStream_t st);
@@ -805,6 +806,7 @@ BiWs carve_bi(Carver& cv, const Shape& s, bool keep)
     c.offa = cv.take<double>(rows);
     c.offb = cv.take<double>(rows);
     c.D2 = cv.take<double>((size_t)s.B);
+    c.wide = keep ? nullptr : cv.take<int>((size_t)s.B * 2);
     return c;
 }
 
@@ -841,7 +843,7 @@ last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int
     BiArgs a;
     a.w = w; a.len = lengths; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb; a.D2 = c.D2;
     a.dist = dist; a.item_status = item_status; a.bp = bp; a.final_state = final_state;
-    a.T = s.T; a.C = s.C; a.keep = keep;
+    a.T = s.T; a.C = s.C; a.wide = c.wide;
     last_status_t rc = LAST_OK;
     a.P = (s.C + 3) / 4 * 4;
     auto go = [&](auto DD) {
@@ -853,8 +855,9 @@ last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int
             if (D::N > 64) rc = allow_lds((const void*)k, kBiBigLds);
             if (rc == LAST_OK) hipLaunchKernelGGL(k, dim3(s.B, roles), dim3((D::NC + D::NP) * kWave), lds, st, a);
         };
-        if (trop) launch(bigram_kernel<D, true>, 1);
-        else launch(bigram_kernel<D, false>, 2);
+        if (trop) launch(bigram_kernel<D, true, false>, 1);
+        else if (keep) launch(bigram_kernel<D, false, true>, 2);
+        else launch(bigram_kernel<D, false, false>, 2);
     };
     if (s.C <= 32) go(BiDims<8, 1, 4, 4, 8, 1, 2>());
     else if (s.C <= 48) go(BiDims<16, 1, 4, 4, 12, 3, 2>());
@@ -1201,8 +1204,9 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         rc = launch_bi(s, bw, weights->w, lengths, trop, false, nullptr, nullptr, dist, item_status, st);
         if (rc != LAST_OK) return rc;
         if (!trop)
-            hipLaunchKernelGGL(bigram_join_kernel, dim3(s.B), dim3(64), 0, st, (const float*)bw.alpha, (const float*)bw.beta,
-                               (const double*)bw.offa, (const double*)bw.offb, lengths, s.T, s.C, dist, item_status);
+            hipLaunchKernelGGL(bigram_join_kernel, dim3(s.B), dim3(1024), l.lds_forward, st, weights->w, c, l.CPAD, l.R,
+                               (const float*)bw.alpha, (const float*)bw.beta, (const double*)bw.offa, (const double*)bw.offb,
+                               (const int*)bw.wide, lengths, s.T, dist, item_status);
     } else if (semiring == LAST_LOG && plan.ok) {
         Carver cv(ws);
         const ClusterWs cw = carve_cluster(cv, s, plan);

@@ -10,11 +10,11 @@
 // stayed in the marginals (their relative error together, against 64 bits, 61 frames, sigma 1.5: 5 states 2.7e-7 against
 // 0.8e-7, a table of 200 states with 12 labels 1.2e-6 against 2.1e-7).  One more vector is read for each stretch of
 // rows, 1 to 3 % of a call (loss at 8 items, 300 frames, 32 labels of order 2 0.737 -> 0.747 ms).
-// LINEAR: alpha, beta are linear relative to 2^offset, offsets and D2 in base 2, and dw (+)= scale alpha 2^(w log2 e) beta
-// 2^offsets / Z.  There an entry more than 2^126 below the largest of its frame is zero; the marginal it would have had is
-// below 2^-46 as long as the product of the frame's three maxima is below 2^80 Z, and beyond that the item is
-// flagged (kItemRange) and the exponent capped so that it stays finite (kMgExpCap).  It is flagged, too, where
-// Z is not the partition sum: then one of the directions has lost a part of it.
+// LINEAR (bigram_kernels.hpp): alpha, beta are linear relative to 2^offset, offsets and D2 in base 2, and dw (+)= scale
+// alpha 2^(w log2 e) beta 2^offsets / Z.  There an entry more than 2^126 below the largest of its frame may be zero; the
+// marginal it would have had is below 2^-46 as long as the product of the frame's three maxima is below 2^80 Z,
+// and beyond that the item is flagged (kItemRange).  It is flagged, too, where Z is not the partition sum: then one of the
+// directions has lost a part of it.
 // Bound: HBM, 4 bytes read and 4 written per arc.  A workgroup takes a stretch of rows of one frame, keeps
 // its two state vectors in LDS (the row offset of the destinations with them) and goes through the stretch with
 // 16-byte accesses on 16-byte boundaries of memory; rows are V+1 floats, so a piece may span rows.
@@ -27,10 +27,10 @@ namespace last {
 
 constexpr int kMgThreads = 256;
 constexpr float kMgRangeBits = 80.f;
-constexpr double kMgLostBits = 0.01;         // difference of two logarithms of the partition sum that no rounding makes
-// The forward weights are sums of at most 97 products below 2 each: below 2^7.6; 2^f with |f| <= 1/2 adds half a bit, the
-// backward weights, below 2, one, and 1 / Z's mantissa one at most: with this cap every product stays below 2^128.
-constexpr float kMgExpCap = 117.f;
+// difference of two logarithms of the partition sum that no rounding makes: this much, and per frame
+constexpr double kMgLostBits = 0.01, kMgLostBitsPerFrame = 1.0e-7;
+constexpr int kMgAlphaExp = 46, kMgBetaExp = 40;      // alpha is below 2^108, beta below 2^101: taken down for their product
+constexpr float kMgMax = 1.8e19f;            // 2^64: no marginal exceeds 1 but those of items that are flagged
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
 
@@ -74,7 +74,8 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     if (LINEAR) {
         double z = 0.0;
         for (int q = tid; q < c.C; q += kMgThreads) {
-            const float x = alpha[ra * c.C + q], y = beta[(ra + 1) * c.C + q];
+            const float x = __builtin_ldexpf(alpha[ra * c.C + q], -kMgAlphaExp);
+            const float y = __builtin_ldexpf(beta[(ra + 1) * c.C + q], -kMgBetaExp);
             z += (double)alpha[(ra + 1) * c.C + q] * (double)y;
             al[q] = x;
             be[q] = y;
@@ -93,9 +94,10 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
         if (z > 0.0) {
             int e;
             const double m = frexp(z, &e);        // in [1/2, 1)
-            K = (float)(offa[ra] - offa[ra + 1] - (double)e);
-            sc = scale * (float)(1.0 / m);
-            lost = !(fabs(offa[ra + 1] + offb[ra + 1] + log2(z) - d2) < kMgLostBits);
+            K = (float)(offa[ra] - offa[ra + 1] - (double)(e - kMgAlphaExp));          // (z has beta's factor, too)
+            sc = scale / (float)m;
+            lost = !(fabs(offa[ra + 1] + offb[ra + 1] + (double)((float)(e + kMgBetaExp) + __builtin_amdgcn_logf((float)m)) - d2)
+                     < kMgLostBits + kMgLostBitsPerFrame * L);
         } else {
             lost = d2 != (double)LAST_NEG_INF;
         }
@@ -139,8 +141,8 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
             // the largest error of a marginal
             const float y = fmaf(x, kLog2e, K), h = rintf(x * kLog2e);
             const float f = fmaf(x, kLog2eLow, fmaf(x, kLog2e, -h));
-            const float e = y > -200.f ? __builtin_ldexpf(fast_exp2(f), (int)fminf(h + K, kMgExpCap)) : 0.f;
-            return sc * (al[q] * e * be[d]);
+            const float e = y > -300.f ? fast_exp2(f) : 0.f;               // (the product of the vectors is below 2^123)
+            return sc * fminf(__builtin_ldexpf(al[q] * be[d] * e, (int)(h + K)), kMgMax);
         }
         // (an arc out of an unreachable state does not count, whatever its weight)
         return al[q] == LAST_NEG_INF ? 0.f : sc * tri_exp(al[q] + be[d] + x);

@@ -147,3 +147,52 @@ def test_more_frames_than_a_grid_has_rows(V):
     D, g = lb.last_arc_posteriors(dev(w), dev(lengths))
     assert_dist_close(D.cpu().numpy(), oracle.forward(w, lengths, 1)[1])
     assert np.max(np.abs(g.cpu().numpy() - oracle.posteriors(w, lengths, 1))) <= TOL_POST_ABS
+
+
+def far_apart(kind, V, B=12, T=24):
+    """weights whose differences within a row, between rows or between columns leave scaled float32"""
+    C = V + 1
+    rng = np.random.default_rng(1000 * V + len(kind))
+    w = rng.normal(size=(B, T, C, C)).astype(np.float32)
+    if kind == "one way up, the others later":
+        # all but the way through state 1 fall behind by 2R, and make up for it in the next frame
+        for b, R in enumerate([30, 40, 50, 60, 80, 200] * (B // 6)):
+            p = [0, 3, 11, 12, 17, 22][b % 6]
+            w[b, p], w[b, p + 1] = -R, R
+            w[b, p, :, 1], w[b, p + 1, 1] = R, -R
+    elif kind == "sigma 60":
+        w *= 60.0
+    elif kind == "rows and columns":
+        w += 60.0 * rng.normal(size=(B, T, C, 1)).astype(np.float32) + 60.0 * rng.normal(size=(B, T, 1, C)).astype(np.float32)
+    elif kind == "a column of -100":
+        w[:, :, :, 1] = -100.0
+        w[:, T // 2, 2:, :] = -300.0
+    elif kind == "rows of -200":
+        w[:, :, 1:3] = -200.0
+        w[:, T // 3:T // 3 + 2, :, 3:] = -250.0
+    lengths = np.full(B, T, np.int32)
+    lengths[::4] = rng.integers(2, T, size=len(lengths[::4]))
+    return w, lengths
+
+
+@pytest.mark.parametrize("V", [4, 33, 60, 95])
+@pytest.mark.parametrize("kind", ["one way up, the others later", "sigma 60", "rows and columns", "a column of -100",
+                                  "rows of -200"])
+def test_weights_far_apart(kind, V):
+    announce("small bigram: right distances without marginals; with them right ones or status 6:", kind, V)
+    w, lengths = far_apart(kind, V)
+    wd, ld = dev(w), dev(lengths)
+    B = len(lengths)
+    status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    _, D_o = oracle.forward(w, lengths, 1)
+    assert_dist_close(lb.last_shortest_distance(wd, ld, item_status=status).cpu().numpy(), D_o)
+    assert status.cpu().tolist() == [0] * B
+    D, g = lb.last_arc_posteriors(wd, ld, item_status=status)
+    g_o = oracle.posteriors(w, lengths, 1)
+    assert torch.isfinite(g).all()
+    # (scores of a thousand: their float32 roundings are 3e-5 in an exponent)
+    for b in range(B):
+        assert int(status[b]) in (0, 6)
+        if int(status[b]) == 0:
+            assert_dist_close(D[b:b + 1].cpu().numpy(), D_o[b:b + 1])
+            assert np.max(np.abs(g[b].cpu().numpy() - g_o[b])) <= 5.0e-5
