@@ -686,8 +686,14 @@ TriWs carve_tri(Carver& cv, const Shape& s, const TriPlan& p, bool trop, bool ke
     return c;
 }
 
-// the call without marginals: its rows must stay small enough for the static scratch array too
-bool tri_rows_fit(const Shape& s) { return (size_t)s.B * s.C * 2 * sizeof(float) <= kTriRowBytes; }
+// The call without marginals goes through the batch in slices whose rows fit kTriRowBytes (the static scratch array has
+// 32 MiB): 756 items at 4161 states, the most there are, so that a slice still fills the chip many times over.
+Shape tri_slice(const Shape& s)
+{
+    Shape r = s;
+    r.B = (int)std::min((size_t)s.B, kTriRowBytes / ((size_t)s.C * 2 * sizeof(float)));
+    return r;
+}
 
 last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const float* w, const int* lengths,
                          bool trop, bool keep, int* bp, hipStream_t st)
@@ -1104,15 +1110,18 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
     const TriPlan tplan = tri_plan(s, weights->kind, false), tvplan = tri_plan(s, weights->kind, true);
     switch (op) {
     case LAST_OP_SHORTEST_DISTANCE:
-        if (bi_ok(s, weights->kind, false) || (tab_ok(s, false) && tri_rows_fit(s))) carve_bi(cv, s, false);
+        if (bi_ok(s, weights->kind, false)) carve_bi(cv, s, false);
+        else if (tab_ok(s, false)) carve_bi(cv, tri_slice(s), false);
         else if (plan.ok) carve_cluster(cv, s, plan);
         else cv.take<double>(1);
         if (vplan.ok && !bi_ok(s, weights->kind, true)) cv.take<u64>(vplan.xwords);        // tropical semiring: exchange buffer
-        if (tri_rows_fit(s) && (tplan.ok || tvplan.ok)) {
+        if (tplan.ok || tvplan.ok) {
             // one semiring or the other: the larger of the two
+            const Shape sl = tri_slice(s);
+            const TriPlan p = tri_plan(sl, weights->kind, false), vp = tri_plan(sl, weights->kind, true);
             Carver log(nullptr), trop(nullptr);
-            if (tplan.ok) carve_tri(log, s, tplan, false, false);
-            if (tvplan.ok) carve_tri(trop, s, tvplan, true, false);
+            if (p.ok) carve_tri(log, sl, p, false, false);
+            if (vp.ok) carve_tri(trop, sl, vp, true, false);
             cv.take<char>(std::max(log.used, trop.used));
         }
         break;
@@ -1168,16 +1177,23 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
     rc = check_ws(ws, ws_bytes, last_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0));
     if (rc != LAST_OK) return rc;
     const SoloLayout l = solo_layout(s);
-    if (semiring == LAST_LOG && tab_ok(s, false) && tri_rows_fit(s)) {
+    const size_t item = (size_t)s.T * s.C * s.V1;              // weights of an item
+    if (semiring == LAST_LOG && tab_ok(s, false)) {
         Carver cv(ws);
         int* flag = carve_table_flag(cv, s);
         if (flag) launch_table_check(s, flag, st);
-        const BiWs bw = carve_bi(cv, s, false);
-        rc = launch_tab(s, bw, weights->w, lengths, false, false, nullptr, nullptr, dist, item_status, flag, st);
-        if (rc != LAST_OK) return rc;
-        hipLaunchKernelGGL(tri_join_kernel<false>, dim3(s.B), dim3(256), 0, st, bw.alpha, (const float*)bw.beta,
-                           bw.offa, (const double*)bw.offb, lengths, (const int*)nullptr, (const int*)flag,
-                           s.T, s.C, 0, (double*)nullptr, dist, item_status, TriRedo{});
+        Shape sl = tri_slice(s);
+        const BiWs bw = carve_bi(cv, sl, false);
+        const int per = sl.B;
+        for (int b0 = 0; b0 < s.B; b0 += per) {
+            sl.B = std::min(per, s.B - b0);
+            int* status = item_status ? item_status + b0 : nullptr;
+            rc = launch_tab(sl, bw, weights->w + b0 * item, lengths + b0, false, false, nullptr, nullptr, dist + b0, status, flag, st);
+            if (rc != LAST_OK) return rc;
+            hipLaunchKernelGGL(tri_join_kernel<false>, dim3(sl.B), dim3(256), 0, st, bw.alpha, (const float*)bw.beta,
+                               bw.offa, (const double*)bw.offb, lengths + b0, (const int*)nullptr, (const int*)flag,
+                               s.T, s.C, 0, (double*)nullptr, dist + b0, status, TriRedo{});
+        }
         return hip_status();
     }
     if (s.order == 0) {
@@ -1211,15 +1227,21 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
         Carver cv(ws);
         const ClusterWs cw = carve_cluster(cv, s, plan);
         launch_cluster<false>(s, plan, cw, weights->w, lengths, dist, item_status, nullptr, 1.f, 0, st);
-    } else if (const TriPlan tp = tri_plan(s, weights->kind, semiring == LAST_TROPICAL); tp.ok && tri_rows_fit(s)) {
+    } else if (const TriPlan tp = tri_plan(tri_slice(s), weights->kind, semiring == LAST_TROPICAL); tp.ok) {
         const bool trop = semiring == LAST_TROPICAL;
+        Shape sl = tri_slice(s);
         Carver cv(ws);
         cv.take<double>(1);
-        const TriWs tw = carve_tri(cv, s, tp, trop, false);
-        rc = launch_tri(s, tp, tw, weights->w, lengths, trop, false, nullptr, st);
-        if (rc != LAST_OK) return rc;
-        if (trop) launch_tri_final(s, tw, weights->w, lengths, nullptr, nullptr, dist, item_status, st);
-        else launch_tri_join(s, tw, weights->w, lengths, nullptr, dist, item_status, st);
+        const TriWs tw = carve_tri(cv, sl, tp, trop, false);
+        const int per = sl.B;
+        for (int b0 = 0; b0 < s.B; b0 += per) {
+            sl.B = std::min(per, s.B - b0);
+            int* status = item_status ? item_status + b0 : nullptr;
+            rc = launch_tri(sl, tp, tw, weights->w + b0 * item, lengths + b0, trop, false, nullptr, st);
+            if (rc != LAST_OK) return rc;
+            if (trop) launch_tri_final(sl, tw, weights->w + b0 * item, lengths + b0, nullptr, nullptr, dist + b0, status, st);
+            else launch_tri_join(sl, tw, weights->w + b0 * item, lengths + b0, nullptr, dist + b0, status, st);
+        }
     } else if (semiring == LAST_LOG) {
         if (l.lds_forward > kMaxLds) return LAST_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(solo_forward_log, dim3(s.B), dim3(1024), l.lds_forward, st,

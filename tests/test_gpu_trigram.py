@@ -9,6 +9,7 @@ import oracle
 from paper_2304_13134_amd import binding as lb
 from paper_2304_13134_amd import workloads
 from gpu_util import TOL_POST_ABS, announce, assert_dist_close, dev, library_option
+from test_gpu_tables_local import both_orders
 from test_gpu_parity import check_path, check_posteriors, forbid_arcs
 
 pytestmark = pytest.mark.gpu
@@ -162,3 +163,28 @@ def test_calls_on_several_streams_share_the_chip(V, B):
             assert_dist_close(out[i][0].cpu().numpy(), D.cpu().numpy())
             assert torch.max(torch.abs(out[i][1] - g)).item() <= TOL_POST_ABS
         assert torch.equal(out[1][0], labels) and torch.equal(out[1][1], states) and torch.equal(out[1][2], score)
+
+
+# 4161 states: slices of 755 items; 4096 states of a table: of 768
+@pytest.mark.parametrize("order,V,C,B", [(2, 64, 4161, 800), (0, 3, 4096, 1600)])
+def test_distance_of_a_batch_in_slices(order, V, C, B):
+    announce("distance of a batch whose vectors take more than 24 MiB: order, V, B", order, V, B)
+    T = 2 if order else 3
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V)
+    w = torch.randn((B, T, C, V + 1), generator=g, device="cuda")
+    lengths = torch.randint(0, T + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lengths[-2] = T + 1
+    o_order, g_order = (order, order) if order else both_orders(workloads.random_table(C, V, seed=C))
+    some = [0, 1, B // 2, 700, 754, 755, 756, 767, 768, 769, B - 1]
+    status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    D = lb.last_shortest_distance(w, lengths, order=g_order, item_status=status)
+    best = lb.last_shortest_distance(w, lengths, order=g_order, semiring="tropical")
+    assert status.cpu().tolist() == [0] * (B - 2) + [1, 0]
+    assert torch.isnan(D[-2]) and torch.isfinite(D[:-2]).all()
+    w_o, l_o = w[some].cpu().numpy(), lengths[some].cpu().numpy()
+    assert_dist_close(D[some].cpu().numpy(), oracle.forward(w_o, l_o, o_order)[1])
+    assert np.array_equal(best[some].cpu().numpy(), oracle.viterbi(w_o, l_o, o_order, "f32")[2])
+    with library_option(lb.OPT_FORCE_SOLO, 1):                 # the general kernels on the whole batch
+        again = lb.last_shortest_distance(w, lengths, order=g_order)
+    assert_dist_close(D.cpu().numpy()[:-2], again.cpu().numpy()[:-2])
