@@ -725,26 +725,33 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
     return rc;
 }
 
-TriRedo tri_redo(const Shape& s, const float* w, const last_grads_t* out)
+// LDS bytes of the general recursions in a workgroup of kTriJoin threads, and what they need besides
+constexpr int kTriJoin = 256;
+TriRedo tri_redo(const Shape& s, const float* w, const last_grads_t* out, size_t* lds)
 {
-    const SoloLayout l = solo_layout(s);
-    return TriRedo{w, make_ctx(s), l.CPAD, l.R, out && s.T > 0 ? out->dw : nullptr, out ? out->scale : 0.f, out ? out->accumulate : 0};
+    const int cpad = std::min((s.C + 63) / 64 * 64, kTriJoin), r = kTriJoin / cpad;
+    *lds = (size_t)(2 * s.C + 2 * r * cpad + 64) * sizeof(float);
+    return TriRedo{w, make_ctx(s), cpad, r, out && s.T > 0 ? out->dw : nullptr, out ? out->scale : 0.f, out ? out->accumulate : 0};
 }
 
 // distance of every item (out: of the call with marginals)
 void launch_tri_join(const Shape& s, const TriWs& c, const float* w, const int* lengths, const last_grads_t* out, float* dist,
                      int* item_status, hipStream_t st)
 {
-    hipLaunchKernelGGL(tri_join_kernel<true>, dim3(s.B), dim3(1024), solo_layout(s).lds_forward, st, c.alpha, (const float*)c.beta,
+    size_t lds;
+    const TriRedo redo = tri_redo(s, w, out, &lds);
+    hipLaunchKernelGGL(tri_join_kernel<true>, dim3(s.B), dim3(kTriJoin), lds, st, c.alpha, (const float*)c.beta,
                        c.offa, (const double*)c.offb, lengths, (const int*)c.fail, (const int*)nullptr, s.T, s.C, out ? 1 : 0,
-                       out ? c.D2 : nullptr, dist, item_status, tri_redo(s, w, out));
+                       out ? c.D2 : nullptr, dist, item_status, redo);
 }
 
 void launch_tri_final(const Shape& s, const TriWs& c, const float* w, const int* lengths, int* bp, int* final_state, float* score,
                       int* item_status, hipStream_t st)
 {
-    hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(1024), solo_layout(s).lds_viterbi, st, (const float*)c.alpha, lengths,
-                       (const int*)c.fail, s.T, s.C, bp, final_state, score, item_status, tri_redo(s, w, nullptr));
+    size_t lds;
+    const TriRedo redo = tri_redo(s, w, nullptr, &lds);
+    hipLaunchKernelGGL(tri_final_kernel, dim3(s.B), dim3(kTriJoin), lds, st, (const float*)c.alpha, lengths,
+                       (const int*)c.fail, s.T, s.C, bp, final_state, score, item_status, redo);
 }
 
 // marginals of all frames from the stored rows (marginals_kernels.hpp)
@@ -754,7 +761,10 @@ last_status_t launch_marginals(const Shape& s, const float* w, const int* length
                                const int* badtab, const int* skip, int* item_status, hipStream_t st)
 {
     const size_t lds = (size_t)2 * s.C * sizeof(float);
-    int rows = std::max(1, kMgChunk / s.V1);
+    // stretches of about kMgChunk arcs, shorter ones (down to an eighth) where these are fewer than four workgroups a compute
+    // unit: 190 frames of 651 states, 25 labels 63 -> 55 us a call
+    const size_t stretches = (size_t)s.T * s.B * (((size_t)s.C * s.V1 + kMgChunk - 1) / kMgChunk);
+    int rows = std::max(1, (int)(kMgChunk / std::min((size_t)8, std::max((size_t)1, 1024 / stretches)) / s.V1));
     const int parts = (s.C + rows - 1) / rows;
     rows = (s.C + parts - 1) / parts;
     last_status_t rc = LAST_OK;
@@ -787,8 +797,6 @@ struct BiWs {
     double *offa, *offb, *D2;
     int* wide;           // call without marginals
 };
-last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep,
-                         int* bp, int* final_state, float* dist, int* item_status, const int* flag, hipStream_t st);
 
 // Full 1-gram contexts, one workgroup per item and direction (bigram_kernels.hpp).  From 97 states on a compute
 // unit takes longer over a frame than a cluster over its exchange: forward-backward at T=200 and 71 states

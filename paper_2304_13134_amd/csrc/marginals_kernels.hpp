@@ -128,11 +128,15 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
         for (int q = q0 + tid; q < q1; q += kMgThreads) al[q] = (float)((double)al[q] + kd);
     }
     __syncthreads();
-    auto arc = [&](int q, int y, float x) __attribute__((always_inline)) {
+    // ORDER 2: the label arcs of state q lead to the states after row_base(q), those of q + 1 to V states further on (after
+    // the last label from the first again)
+    auto row_base = [&](int q) __attribute__((always_inline)) { return ORDER == 2 && q > 0 ? ((q - 1) % c.V + 1) * c.V : 0; };
+    auto next_base = [&](int base) __attribute__((always_inline)) { return base == c.V * c.V ? c.V : base + c.V; };
+    auto arc = [&](int q, int y, int base, float x) __attribute__((always_inline)) {
         int d = q;
         if (y > 0) {
             if (ORDER == 1) d = y;
-            else if (ORDER == 2) d = (q == 0 ? 0 : ((q - 1) % c.V + 1) * c.V) + y;
+            else if (ORDER == 2) d = base + y;
             else d = ctx_next(c, q, y);
         }
         if (LINEAR) {
@@ -152,13 +156,15 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
         struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
         const f4 x = *(const f4*)(wt + e);
         int q = q0 + e / c.V1, y = e - (q - q0) * c.V1;
+        int base = row_base(q);
         float o[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            o[k] = arc(q, y, x.v[k]);
+            o[k] = arc(q, y, base, x.v[k]);
             const bool wrap = ++y == c.V1;
             q += wrap;
             y = wrap ? 0 : y;
+            if (ORDER == 2) base = wrap ? next_base(base) : base;
         }
         float4* p = (float4*)(g + e);
         if (ACC) {
@@ -172,7 +178,7 @@ __global__ __launch_bounds__(kMgThreads) void dense_marginals_kernel(
     if (tid < lead + rest) {
         const int e = tid < lead ? tid : lead + 4 * n4 + (tid - lead);
         const int q = q0 + e / c.V1, y = e - (q - q0) * c.V1;
-        const float o = arc(q, y, wt[e]);
+        const float o = arc(q, y, row_base(q), wt[e]);
         if (ACC) g[e] += o; else g[e] = o;
     }
     if (LINEAR && item_status) {

@@ -670,17 +670,17 @@ struct TriRedo {
 // D = log (+)_q alpha_m[q] beta_m[q] of every item from the rows at which the two directions meet (beta = 0 at the
 // last frame), one workgroup per item.  alpha, beta: natural logs with offsets.  badtab may be null.
 // REDO: an item marked in `fail` is computed here once more by this workgroup alone, gradient included
-// (dense_marginals_kernel leaves it out); dynamic LDS of solo_layout.
+// (dense_marginals_kernel leaves it out); dynamic LDS for solo_kernels.hpp.
 template <bool REDO>
-__global__ __launch_bounds__(REDO ? 1024 : 256) void tri_join_kernel(
+__global__ __launch_bounds__(256) void tri_join_kernel(
     float* alpha, const float* __restrict__ beta, double* offa, const double* __restrict__ offb,
     const int* __restrict__ len, const int* __restrict__ fail, const int* __restrict__ badtab, int T, int C, int keep,
     double* D2, float* dist, int* __restrict__ item_status, TriRedo redo)
 {
     extern __shared__ float tri_redo_s[];
     __shared__ float red[32];
-    __shared__ double redd[16];
-    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+    __shared__ double redd[4];
+    const int b = blockIdx.x, tid = threadIdx.x;
     const int L = len[b];
     const bool bad = L < 0 || L > T, tab = badtab && badtab[0] != 0;
     if (bad || tab) {
@@ -704,18 +704,18 @@ __global__ __launch_bounds__(REDO ? 1024 : 256) void tri_join_kernel(
     const float* al = alpha + ra * C;
     const float* be = beta + ra * C;
     float mx = LAST_NEG_INF;
-    for (int q = tid; q < C; q += nt) mx = fmaxf(mx, keep ? al[q] : al[q] + be[q]);
+    for (int q = tid; q < C; q += 256) mx = fmaxf(mx, keep ? al[q] : al[q] + be[q]);
     mx = block_max(mx, red);
     const float mm = mx == LAST_NEG_INF ? 0.f : mx;
     double z = 0.0;
-    for (int q = tid; q < C; q += nt) z += (double)tri_exp((keep ? al[q] : al[q] + be[q]) - mm);
+    for (int q = tid; q < C; q += 256) z += (double)tri_exp((keep ? al[q] : al[q] + be[q]) - mm);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
     if ((tid & 63) == 0) redd[tid >> 6] = z;
     __syncthreads();
     if (tid == 0) {
         z = redd[0];
-        for (int k = 1; k < nt / kWave; ++k) z += redd[k];
+        for (int k = 1; k < 4; ++k) z += redd[k];
         const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF
                                              : offa[ra] + (keep ? 0.0 : offb[ra]) + (double)mm + log(z);
         dist[b] = (float)d2;
@@ -724,16 +724,16 @@ __global__ __launch_bounds__(REDO ? 1024 : 256) void tri_join_kernel(
 }
 
 // best final state of every item (lowest index among equals) from its final scores; an item marked in `fail` is
-// computed here once more by this workgroup alone (dynamic LDS of solo_layout)
-__global__ __launch_bounds__(1024) void tri_final_kernel(
+// computed here once more by this workgroup alone (dynamic LDS for solo_kernels.hpp)
+__global__ __launch_bounds__(256) void tri_final_kernel(
     const float* __restrict__ fin, const int* __restrict__ len, const int* __restrict__ fail, int T, int C,
     int* __restrict__ bp, int* __restrict__ final_state, float* __restrict__ score, int* __restrict__ item_status,
     TriRedo redo)
 {
     extern __shared__ float tri_redo_s[];
-    __shared__ float redv[16];
-    __shared__ int redi[16];
-    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+    __shared__ float redv[4];
+    __shared__ int redi[4];
+    const int b = blockIdx.x, tid = threadIdx.x;
     const int L = len[b];
     if (L < 0 || L > T) {
         if (tid == 0) {
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(1024) void tri_final_kernel(
     }
     float best = LAST_NEG_INF;
     int idx = 0x7fffffff;
-    for (int q = tid; q < C; q += nt) {
+    for (int q = tid; q < C; q += 256) {
         const float v = fin[(size_t)b * C + q];
         if (v > best || (v == best && q < idx)) { best = v; idx = q; }
     }
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(1024) void tri_final_kernel(
     if ((tid & 63) == 0) { redv[tid >> 6] = best; redi[tid >> 6] = idx; }
     __syncthreads();
     if (tid == 0) {
-        for (int k = 1; k < nt / kWave; ++k)
+        for (int k = 1; k < 4; ++k)
             if (redv[k] > best || (redv[k] == best && redi[k] < idx)) { best = redv[k]; idx = redi[k]; }
         score[b] = best;
         if (final_state) final_state[b] = idx;
