@@ -47,7 +47,13 @@
  *   3 reference length outside [0,Umax]; 4 infeasible (reference longer than
  *   the number of frames: numerator = -inf, its marginals are 0);
  *   5 the cooperating workgroups of an item timed out waiting for each other
- *   (results of that item are undefined; never expected in normal operation);
+ *   (results of that item are undefined).  Possible for dense bigrams of 97 to
+ *   264 states and for shared_emb weights, where a launch wants all its
+ *   workgroups resident at once: not expected as long as no more than two
+ *   such calls run on one GPU at a time (streams, threads, processes).  Dense
+ *   trigrams of 3 to 64 labels wait for each other, too, but an item whose
+ *   waits ran out is computed by one workgroup afterwards: right, late, and
+ *   with status 0.  LAST_OPT_FORCE_SOLO takes every dense call off the waits;
  *   6 the weights of the item span more dynamic range than the kernels for
  *   dense bigram lattices of 5 to 264 states guarantee for marginals (they keep
  *   state vectors in scaled float32: entries more than 2^126 below the largest
@@ -159,7 +165,10 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
 
 /* Log-semiring shortest distance and its gradient, the arc marginals of
  * Eq. 1, by forward-backward (Section 4.2.2: only alpha and beta are kept,
- * O(|Q|) extra space).  dist: dev float32 [B].  out: see last_grads_t. */
+ * O(|Q|) extra space).  dist: dev float32 [B].  out: see last_grads_t.
+ * Workspace: the vectors of all frames, both directions' where the marginals
+ * are formed afterwards (dense bigrams of up to 96 states, trigrams of 3 to 64
+ * labels, tables of up to 16384 arcs a frame), else one direction's. */
 last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* lengths,
                                   const last_context_t* context, float* dist,
                                   const last_grads_t* out, int32_t* item_status,
@@ -257,7 +266,8 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
  *     per item; 1 = the kernel of their own for 4 to 96 states, beyond that cooperating workgroups, the newest
  *     kernel that takes the shape; 2 = cooperating workgroups, the older kernel also where a newer one would run.
  *   LAST_OPT_SPIN_LIMIT (>= 1, default 2^20): polls a cooperating workgroup makes before it gives up
- *     waiting for the others (the item then gets status 5 and dist = NaN; every kernel still ends).
+ *     waiting for the others (the item then gets status 5 and dist = NaN, or is
+ *     computed by one workgroup, see status 5; every kernel still ends).
  *   LAST_OPT_FUSED_FRAMES_PER_TILE (1 or 2, default 2): frames whose on-the-fly weights the forward
  *     kernel of the shared_emb path computes at a time (Section 5 discusses evaluating the weight
  *     function for several frames at once).  2 shares the rows of e and the phase barriers between
@@ -317,8 +327,8 @@ const char* last_status_string(last_status_t status);
 const char* last_hip_error_string(void);
 
 /* Library version and the kernel variant a call would use, for diagnostics:
- * 0 = one workgroup per item, 1 = several workgroups per item (dense
- * weights, context size 1 or 2), 2 = on-the-fly weights (shared_emb), -1 = the
+ * 0 = one workgroup per item, 1 = several workgroups per item, or one for each
+ * direction (dense weights, context size 1 or 2), 2 = on-the-fly weights (shared_emb), -1 = the
  * combination is not supported (the call would return LAST_ERR_UNSUPPORTED or
  * an argument error). */
 int32_t last_version(void);

@@ -603,9 +603,11 @@ last_status_t launch_fused_backward(const Shape& s, const FusedPlan& p, const Fu
 // Geometry of the clustered path for full 2-gram contexts (trigram_kernels.hpp).  It takes every shape its
 // tiles hold (3 to 64 labels), whatever the batch: measured against one workgroup per item with marginals,
 // B=1 T=8 V=3 39 / 53 us, B=8 T=300 V=8 0.31 / 1.9 ms, B=1024 T=50 V=8 (64 items one after the other on
-// every cluster) 0.50 / 1.4 ms, B=8 T=300 V=32 0.71 / 34 ms, distance B=8 T=200 V=50 0.44 / 19 ms.
+// every cluster) 0.50 / 1.4 ms, B=8 T=300 V=32 0.73 / 34 ms, distance B=8 T=200 V=50 0.44 / 19 ms.
 // Of two shapes of workgroup the one with fewer rounds over the batch is taken: the wide one handles twice
-// the labels, so that half as many make a cluster, at 2.9 instead of 1.9 us a frame (V=32).
+// the labels, so that half as many make a cluster, at 2.9 instead of 1.9 us a frame (V=32).  A round
+// of the wide one counted one and a half times was slower where it changed the choice: marginals of 40 and 48 items
+// at V=32 207 -> 230, 229 -> 253 us, of 60 and 72 at V=24 176 -> 211, 183 -> 215, elsewhere the same.
 struct TriPlan {
     bool ok;
     int dims;            // index into the instantiations below
@@ -798,10 +800,11 @@ struct BiWs {
     int* wide;           // call without marginals
 };
 
-// Full 1-gram contexts, one workgroup per item and direction (bigram_kernels.hpp).  From 97 states on a compute
-// unit takes longer over a frame than a cluster over its exchange: forward-backward at T=200 and 71 states
-// B=16 0.41 / 0.54 ms, B=64 0.48 / 1.17 ms against the cluster; at 101 states (measured with wider tiles) B=16 0.71 / 0.56 ms;
-// shortest path at 71 states B=32 0.33 / 0.37 ms, at 101 0.44 / 0.37 ms.  Below 4 states a row is no 16-byte piece;
+// Full 1-gram contexts, one workgroup per item and direction (bigram_kernels.hpp), against the cluster at 96 states,
+// the most the tiles hold, 75 to 100 frames, B=1 / 16 / 64 / 128, us: marginals 184 / 223 / 279 / 384 against
+// 247 / 285 / 667 / 1346, distance 102 / 125 / 126 / 164 against 114 / 133 / 311 / 761, path 148 / 168 / 171 / 175 against
+// 170 / 193 / 195 / 397.  With tiles for 101 states the registers no longer hold the pieces in flight: 16 items of 200 frames
+// 0.71 against 0.56 ms, path 0.44 against 0.37.  Below 4 states a row is no 16-byte piece;
 // with 4 the log semiring stays in the log domain (tab_ok), whose marginals hold for any range of weights.
 bool bi_ok(const Shape& s, int kind, bool trop)
 {
