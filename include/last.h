@@ -268,16 +268,17 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
  *   LAST_OPT_SPIN_LIMIT (>= 1, default 2^20): polls a cooperating workgroup makes before it gives up
  *     waiting for the others (the item then gets status 5 and dist = NaN, or is
  *     computed by one workgroup, see status 5; every kernel still ends).
+ *   LAST_OPT_FUSED_KEEP_MARGINALS (0/1, default 1): 1 = the shared_emb path lays the weights of the frames
+ *     out in the workspace (and partial sums of the gradients, together at most 8 GiB at a time: larger batches
+ *     go through in slices of items); 0 = it never holds more than the weights of a frame or two, in the kernels
+ *     that single items of more than 8 GiB and contexts of fewer than three labels take, too.
+ *     last_workspace_bytes follows the setting: ask again after changing it.  A call whose workspace only holds
+ *     what the kernels without weights need takes these.
  *   LAST_OPT_FUSED_FRAMES_PER_TILE (1 or 2, default 2): frames whose on-the-fly weights the forward
- *     kernel of the shared_emb path computes at a time (Section 5 discusses evaluating the weight
+ *     kernel that holds no weights computes at a time (Section 5 discusses evaluating the weight
  *     function for several frames at once).  2 shares the rows of e and the phase barriers between
  *     two frames and doubles the hidden tile in LDS; a shape whose tiles then no longer fit uses 1.
  *     The shortest distance does not depend on it bit for bit.
- *   LAST_OPT_FUSED_KEEP_MARGINALS (0/1, default 1): 1 = the backward pass of the shared_emb path keeps
- *     the arc marginals of every frame (two bfloat16 halves each) in the workspace for the kernel that
- *     forms dW, which then does not evaluate the weight function a third time; as long as they take
- *     at most 8 GiB (B T V (V+2) (V+1 rounded up to 8) 4 bytes), else and with 0 they are recomputed.
- *     last_workspace_bytes follows the setting: ask again after changing it.
  * last_set_option returns LAST_ERR_UNSUPPORTED for an unknown option or value; last_get_option
  * returns -1 for an unknown option. */
 typedef enum {

@@ -20,6 +20,7 @@
 #include "marginals_kernels.hpp"
 #include "bigram_kernels.hpp"
 #include "table_chain_kernels.hpp"
+#include "emb.hpp"
 #include <algorithm>
 
 #include <atomic>
@@ -736,15 +737,15 @@ TriRedo tri_redo(const Shape& s, const float* w, const last_grads_t* out, size_t
     return TriRedo{w, make_ctx(s), cpad, r, out && s.T > 0 ? out->dw : nullptr, out ? out->scale : 0.f, out ? out->accumulate : 0};
 }
 
-// distance of every item (out: of the call with marginals)
+// distance of every item (out: of the call with marginals; rows: the rows of all frames are kept)
 void launch_tri_join(const Shape& s, const TriWs& c, const float* w, const int* lengths, const last_grads_t* out, float* dist,
-                     int* item_status, hipStream_t st)
+                     int* item_status, hipStream_t st, bool rows = false)
 {
     size_t lds;
     const TriRedo redo = tri_redo(s, w, out, &lds);
-    hipLaunchKernelGGL(tri_join_kernel<true>, dim3(s.B), dim3(kTriJoin), lds, st, c.alpha, (const float*)c.beta,
-                       c.offa, (const double*)c.offb, lengths, (const int*)c.fail, (const int*)nullptr, s.T, s.C, out ? 1 : 0,
-                       out ? c.D2 : nullptr, dist, item_status, redo);
+    hipLaunchKernelGGL(tri_join_kernel<true>, dim3(s.B), dim3(kTriJoin), lds, st, c.alpha, c.beta,
+                       c.offa, c.offb, lengths, (const int*)c.fail, (const int*)nullptr, s.T, s.C, out ? 1 : rows ? 2 : 0,
+                       out || rows ? c.D2 : nullptr, dist, item_status, redo);
 }
 
 void launch_tri_final(const Shape& s, const TriWs& c, const float* w, const int* lengths, int* bp, int* final_state, float* score,
@@ -792,6 +793,133 @@ bool tab_ok(const Shape& s, bool trop)
     // (also bigram lattices of fewer than 5 states, log semiring: log domain, so no limit on the range of the weights)
     return (s.order == 0 || (!trop && s.order == 1 && s.C < 5)) && !opt(LAST_OPT_FORCE_SOLO) && s.T >= 1 && n >= 4 && n <= (size_t)kTabMaxQ * 4 * kTabThreads
            && tab_lds(s.C, s.V1, trop) <= kBigLds - 1024;
+}
+
+// ---- on-the-fly weights of two-label contexts, laid out in memory (emb_kernels.hip) ----
+// The items that are in the workspace at a time: as many as keep their weights and partial gradients within
+// kFusedKeepBytes.  Shapes of which one item does not (64 labels: more than 6200 frames), contexts of fewer than three
+// labels and calls with LAST_OPT_FUSED_KEEP_MARGINALS = 0 take the kernels that never hold the weights (fused_kernels.hpp).
+bool emb_slice(const Shape& s, const last_weights_t* wt, Shape* sl)
+{
+    *sl = s;
+    if (!opt(LAST_OPT_FUSED_KEEP_MARGINALS) || !fused_plan(s, wt).ok || s.T < 1) return false;
+    const EmbPlan p = emb_plan(1, s.T, s.C, s.V, wt->hidden);
+    const size_t item = (size_t)s.T * (p.row + (size_t)p.tiles * wt->hidden * sizeof(float));
+    if (!p.ok || item > kFusedKeepBytes) return false;
+    sl->B = (int)std::min((size_t)s.B, kFusedKeepBytes / item);
+    return tri_plan(*sl, LAST_WEIGHTS_DENSE, false).ok;
+}
+
+struct EmbWs {
+    EmbArgs a;
+    EmbGradArgs g;
+    TriWs tri;
+};
+
+EmbWs carve_emb(Carver& cv, const Shape& sl, const EmbPlan& p, const last_weights_t* wt, bool grads)
+{
+    EmbWs c{};
+    const size_t H = wt->hidden, BT = (size_t)sl.B * sl.T, tiles = p.tiles;
+    c.a.B = sl.B; c.a.T = sl.T; c.a.C = sl.C; c.a.V = sl.V; c.a.H = wt->hidden;
+    c.a.tiles = p.tiles; c.a.nch = p.nch;
+    c.a.w = cv.take<float>(BT * sl.C * sl.V1);
+    c.a.Ef = cv.take<float>(BT * H);
+    c.a.Ee = cv.take<float>(tiles * kEmTile * H);
+    c.a.Wn = cv.take<char>(H / 32 * kEmMaxLabelTiles * 1024);
+    c.a.Wt = grads ? cv.take<char>(H / 32 * 4 * 1024) : nullptr;
+    c.a.frames = cv.take<int2>(BT);
+    c.a.count = cv.take<int>(1);
+    c.a.big = cv.take<int>(kEmScan);
+    c.a.wide = cv.take<int>(1);
+    c.tri = carve_tri(cv, sl, tri_plan(sl, LAST_WEIGHTS_DENSE, false), false, grads);
+    if (grads) {
+        c.g.alpha = c.tri.alpha; c.g.beta = c.tri.beta; c.g.offa = c.tri.offa; c.g.offb = c.tri.offb;
+        c.g.norm = cv.take<EmbNorm>(BT);
+        c.g.ngr = p.ngr;
+        c.g.pdf = cv.take<float>(tiles * BT * H);
+        c.g.pde = cv.take<float>((size_t)p.ngr * tiles * kEmTile * H);
+        c.g.pdw = cv.take<float>((size_t)p.ngr * tiles * H * sl.V1);
+    }
+    return c;
+}
+
+// 0: the call does not go through the weights in memory
+size_t emb_workspace(const Shape& s, const last_weights_t* wt, bool grads)
+{
+    Shape sl;
+    if (!emb_slice(s, wt, &sl)) return 0;
+    Carver cv(nullptr);
+    carve_emb(cv, sl, emb_plan(sl.B, sl.T, sl.C, sl.V, wt->hidden), wt, grads);
+    return cv.used;
+}
+
+// cells of the intersected lattice by tile, for a loss
+size_t emb_cells_workspace(const Shape& s, const last_weights_t* wt, int Umax, EmbNumArgs* n, void* base)
+{
+    Carver cv(base);
+    EmbNumArgs a{};
+    a.cells = cv.take<int>((size_t)s.B * (Umax + 1));
+    a.starts = cv.take<int>((size_t)s.B * (emb_plan(1, 1, s.C, s.V, wt->hidden).tiles + 1));
+    if (n) { n->cells = a.cells; n->starts = a.starts; }
+    return cv.used;
+}
+
+// Distances, and with `out` the gradients of scale (distance - numerator), the numerator of `num` (may be null: none)
+// being ready on the stream after the event `num_ready`.
+last_status_t emb_run(const Shape& s, const last_weights_t* wt, const int* lengths, float* dist, const last_grads_t* out,
+                      int* item_status, void* ws, hipStream_t st, const EmbNumArgs* num, hipEvent_t num_ready)
+{
+    Shape sl;
+    emb_slice(s, wt, &sl);
+    const int per = sl.B;
+    const EmbPlan p = emb_plan(sl.B, sl.T, sl.C, sl.V, wt->hidden);
+    const TriPlan tp = tri_plan(sl, LAST_WEIGHTS_DENSE, false);
+    Carver cv(ws);
+    EmbWs c = carve_emb(cv, sl, p, wt, out != nullptr);
+    auto hip = [](hipError_t e) {
+        if (e != hipSuccess) g_last_hip_error = e;
+        return e == hipSuccess ? LAST_OK : LAST_ERR_HIP;
+    };
+    for (int b0 = 0; b0 < s.B; b0 += per) {
+        sl.B = c.a.B = std::min(per, s.B - b0);
+        c.a.f = (const __bf16*)wt->f + (size_t)b0 * s.T * wt->hidden;
+        c.a.e = wt->e;
+        c.a.W = wt->W;
+        c.a.len = lengths + b0;
+        last_status_t rc = hip(emb_launch_weights(c.a, p, st));
+        if (rc == LAST_OK) rc = launch_tri(sl, tp, c.tri, c.a.w, lengths + b0, false, out != nullptr, nullptr, st);
+        if (rc != LAST_OK) return rc;
+        launch_tri_join(sl, c.tri, c.a.w, lengths + b0, nullptr, dist + b0, item_status ? item_status + b0 : nullptr, st, out != nullptr);
+        if (!out) continue;
+        if (num) {
+            if (b0 == 0) rc = hip(hipStreamWaitEvent(st, num_ready, 0));
+            EmbNumArgs n = *num;
+            const size_t rows = (size_t)b0 * s.T * n.U1, rows1 = (size_t)b0 * (s.T + 1) * n.U1;
+            n.wi += rows;
+            n.a += rows1;
+            n.bk += rows1;
+            n.N += b0;
+            n.status += b0;
+            n.ulen += b0;
+            n.ctxs += (size_t)b0 * n.U1;
+            n.refs += (size_t)b0 * (n.U1 - 1);
+            if (rc == LAST_OK) rc = hip(emb_launch_numerator(c.a, n, st));
+            if (rc != LAST_OK) return rc;
+            c.g.pn = n.wi;
+            c.g.cells = n.cells;
+            c.g.starts = n.starts;
+            c.g.U1 = n.U1;
+        }
+        c.g.df = out->df + (size_t)b0 * s.T * wt->hidden;
+        c.g.de = out->de;
+        c.g.dW = out->dW;
+        c.g.scale = out->scale;
+        c.g.acc_df = out->accumulate;
+        c.g.acc_rest = out->accumulate || b0 > 0;
+        rc = hip(emb_launch_gradient(c.a, c.g, st));
+        if (rc != LAST_OK) return rc;
+    }
+    return hip_status();
 }
 
 struct BiWs {
@@ -1100,7 +1228,7 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
         if (op == LAST_OP_LOSS) {
             const size_t den = last_workspace_bytes(weights, context, LAST_OP_ARC_POSTERIORS, 0);
             const size_t num = last_workspace_bytes(weights, context, LAST_OP_INTERSECT_REFERENCE, Umax);
-            return den && num ? den + num : 0;
+            return den && num ? den + num + emb_cells_workspace(s, weights, Umax, nullptr, nullptr) : 0;
         }
         if (op == LAST_OP_INTERSECT_REFERENCE) {
             // the numerator evaluates single arcs: no limit on the vocabulary, any closed-form context
@@ -1110,10 +1238,13 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
             return cv.used;
         }
         if (!fp.ok) return 0;
-        if (op == LAST_OP_SHORTEST_DISTANCE) carve_fused(cv, s, fp, false);
-        else if (op == LAST_OP_ARC_POSTERIORS) carve_fused(cv, s, fp, true);
-        else return 0;
-        return cv.used;
+        if (op == LAST_OP_SHORTEST_DISTANCE) {
+            carve_fused(cv, s, fp, false);
+            return std::max(cv.used, emb_workspace(s, weights, false));
+        }
+        if (op != LAST_OP_ARC_POSTERIORS) return 0;
+        carve_fused(cv, s, fp, true);
+        return std::max(cv.used, emb_workspace(s, weights, true));
     }
     carve_table_flag(cv, s);
     const ClusterPlan plan = cluster_plan(s, weights->kind);
@@ -1179,9 +1310,15 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
     if (weights->kind == LAST_WEIGHTS_SHARED_EMB) {
         const FusedPlan fp = fused_plan(s, weights);
         if (!fp.ok || semiring != LAST_LOG) return LAST_ERR_UNSUPPORTED;
-        rc = check_ws(ws, ws_bytes, last_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0));
+        const size_t need = emb_workspace(s, weights, false);
+        if (need && check_ws(ws, ws_bytes, need) == LAST_OK)
+            return emb_run(s, weights, lengths, dist, nullptr, item_status, ws, st, nullptr, nullptr);
+        // a smaller workspace (the static one among them) holds what the kernels need that keep no weights
+        Carver cvf(nullptr);
+        carve_fused(cvf, s, fp, false);
+        rc = check_ws(ws, ws_bytes, cvf.used);
         if (rc != LAST_OK) return rc;
-        Carver cvf(ws);
+        cvf = Carver(ws);
         const FusedWs fw = carve_fused(cvf, s, fp, false);
         return launch_fused_forward(s, fp, fw, weights, lengths, dist, item_status, false, st);
     }
@@ -1201,8 +1338,8 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
             int* status = item_status ? item_status + b0 : nullptr;
             rc = launch_tab(sl, bw, weights->w + b0 * item, lengths + b0, false, false, nullptr, nullptr, dist + b0, status, flag, st);
             if (rc != LAST_OK) return rc;
-            hipLaunchKernelGGL(tri_join_kernel<false>, dim3(sl.B), dim3(256), 0, st, bw.alpha, (const float*)bw.beta,
-                               bw.offa, (const double*)bw.offb, lengths + b0, (const int*)nullptr, (const int*)flag,
+            hipLaunchKernelGGL(tri_join_kernel<false>, dim3(sl.B), dim3(256), 0, st, bw.alpha, bw.beta,
+                               bw.offa, bw.offb, lengths + b0, (const int*)nullptr, (const int*)flag,
                                s.T, s.C, 0, (double*)nullptr, dist + b0, status, TriRedo{});
         }
         return hip_status();
@@ -1285,9 +1422,14 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
         const FusedPlan fp = fused_plan(s, weights);
         if (!fp.ok) return LAST_ERR_UNSUPPORTED;
         if (!out->df || !out->de || !out->dW) return LAST_ERR_NULL;
-        rc = check_ws(ws, ws_bytes, last_workspace_bytes(weights, context, LAST_OP_ARC_POSTERIORS, 0));
+        const size_t need = emb_workspace(s, weights, true);
+        if (need && check_ws(ws, ws_bytes, need) == LAST_OK)
+            return emb_run(s, weights, lengths, dist, out, item_status, ws, (hipStream_t)hip_stream, nullptr, nullptr);
+        Carver cvf(nullptr);
+        carve_fused(cvf, s, fp, true);
+        rc = check_ws(ws, ws_bytes, cvf.used);
         if (rc != LAST_OK) return rc;
-        Carver cvf(ws);
+        cvf = Carver(ws);
         const FusedWs fw = carve_fused(cvf, s, fp, true);
         rc = launch_fused_forward(s, fp, fw, weights, lengths, dist, item_status, true, (hipStream_t)hip_stream);
         if (rc != LAST_OK) return rc;
@@ -1611,16 +1753,27 @@ last_status_t last_globally_normalized_loss(const last_weights_t* weights, const
                                              int32_t* item_status, void* ws, size_t ws_bytes, void* hip_stream)
 {
     if (!weights || !context || !out) return LAST_ERR_NULL;
-    const size_t need_den = last_workspace_bytes(weights, context, LAST_OP_ARC_POSTERIORS, 0);
+    size_t need_den = last_workspace_bytes(weights, context, LAST_OP_ARC_POSTERIORS, 0);
     const size_t need_num = last_workspace_bytes(weights, context, LAST_OP_INTERSECT_REFERENCE, Umax);
     if (need_den == 0 || need_num == 0) {
         Shape s;
         const last_status_t rc = check_common(weights, context, &s);
         return rc != LAST_OK ? rc : LAST_ERR_UNSUPPORTED;
     }
+    Shape s;
+    check_common(weights, context, &s);
+    // on-the-fly weights in memory: the numerator's gradient goes through the weight function with the denominator's
+    EmbNumArgs num{};
+    bool emb = weights->kind == LAST_WEIGHTS_SHARED_EMB && emb_workspace(s, weights, true) != 0;
+    if (emb && check_ws(ws, ws_bytes, need_den + need_num + emb_cells_workspace(s, weights, Umax, nullptr, nullptr)) != LAST_OK) {
+        emb = false;                                // (a smaller workspace holds what the kernels need that keep no weights)
+        Carver cv(nullptr);
+        carve_fused(cv, s, fused_plan(s, weights), true);
+        need_den = cv.used;
+    }
     last_status_t rc = check_ws(ws, ws_bytes, need_den + need_num);
     if (rc != LAST_OK) return rc;
-    if (!dist || !numerator) return LAST_ERR_NULL;
+    if (!lengths || !dist || !numerator) return LAST_ERR_NULL;
     void* ws_num = (char*)ws + need_den;            // (both sizes are multiples of the alignment)
     hipStream_t st = (hipStream_t)hip_stream;
     std::lock_guard<std::mutex> lock(g_side_mu);
@@ -1642,6 +1795,20 @@ last_status_t last_globally_normalized_loss(const last_weights_t* weights, const
                         ws_num, need_num, sd->stream, false, kNumPrepare);
     // the fork is always joined, also after an error, so that the caller's stream never loses the side work
     e = hipEventRecord(sd->join, sd->stream);
+    if (emb) {
+        Carver cv(ws_num);
+        const NumWs p = carve_num(cv, s, Umax, false);
+        emb_cells_workspace(s, weights, Umax, &num, (char*)ws_num + need_num);
+        num.wi = p.wi; num.a = p.a; num.bk = p.bk; num.N = p.N;
+        num.status = p.status; num.ctxs = p.ctxs; num.refs = refs; num.ulen = ref_lengths; num.U1 = Umax + 1;
+        last_status_t rc_den = rc != LAST_OK ? rc : emb_run(s, weights, lengths, dist, out, item_status, ws, st, &num, sd->join);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, sd->join, 0);
+        if (e != hipSuccess) { g_last_hip_error = e; return LAST_ERR_HIP; }
+        if (rc_den != LAST_OK) return rc_den;
+        if (item_status)
+            hipLaunchKernelGGL(merge_status_kernel, dim3((s.B + 255) / 256), dim3(256), 0, st, (const int*)p.status, item_status, s.B);
+        return hip_status();
+    }
     g_numerator_beside = true;
     const last_status_t rc_den = last_arc_posteriors(weights, lengths, context, dist, out, item_status, ws,
                                                      need_den, hip_stream);
@@ -1655,8 +1822,6 @@ last_status_t last_globally_normalized_loss(const last_weights_t* weights, const
     if (rc != LAST_OK) return rc;
     if (item_status) {
         // the numerator's per-item status sits at a fixed place of its workspace
-        Shape s;
-        check_common(weights, context, &s);
         Carver cv(ws_num);
         carve_table_flag(cv, s);
         const NumWs p = carve_num(cv, s, Umax, false);
@@ -1751,6 +1916,14 @@ last_status_t static_scratch(void** out)
     return LAST_OK;
 }
 
+size_t smallest_distance_workspace(const Shape& s, const last_weights_t* wt, const last_context_t* cx)
+{
+    if (wt->kind != LAST_WEIGHTS_SHARED_EMB) return last_workspace_bytes(wt, cx, LAST_OP_SHORTEST_DISTANCE, 0);
+    Carver cv(nullptr);
+    carve_fused(cv, s, fused_plan(s, wt), false);
+    return cv.used;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1764,9 +1937,8 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
     if (rc != LAST_OK) return rc;
     if (!lengths || !dist) return LAST_ERR_NULL;
     if (semiring != LAST_LOG && semiring != LAST_TROPICAL) return LAST_ERR_SEMIRING;
-    const size_t need = last_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0);
-    if (need == 0) return LAST_ERR_UNSUPPORTED;
-    if (need > (size_t)LAST_STATIC_SCRATCH_BYTES) return LAST_ERR_WORKSPACE;
+    if (last_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0) == 0) return LAST_ERR_UNSUPPORTED;
+    if (smallest_distance_workspace(s, weights, context) > (size_t)LAST_STATIC_SCRATCH_BYTES) return LAST_ERR_WORKSPACE;
     void* ws = nullptr;
     rc = static_scratch(&ws);
     if (rc != LAST_OK) return rc;

@@ -138,10 +138,11 @@ __global__ __launch_bounds__(1024) void solo_forward_log(
 // strides over its V+1 arcs.  gamma = exp(alpha~_t[q] + w + beta~_{t+1}[next]
 // + (A_t + B_{t+1} - D)), the bracket formed in float64.
 // smem: LDS of 2C + 32 floats.
-template <int G>
+// ROWS: the backward weights beta [B][T+1][C] and their offsets are stored instead of marginals.
+template <int G, bool ROWS = false>
 __device__ __forceinline__ void solo_backward_item(
     int b, int L, float* smem, const float* w, const Ctx& c, int T, const float* alpha_ws, const double* offs,
-    const double* Dws, float* dw, float scale, int accumulate)
+    const double* Dws, float* dw, float scale, int accumulate, float* beta = nullptr, double* boffs = nullptr)
 {
     float* bn = smem;          // beta~_{t+1}
     float* bc = bn + c.C;      // beta_t before rescaling
@@ -151,13 +152,19 @@ __device__ __forceinline__ void solo_backward_item(
     float* gw = dw + (size_t)b * T * fr;
     const bool bad = (L < 0 || L > T);
     if (bad) L = 0;
-    if (!accumulate)
+    if (!ROWS && !accumulate)
         for (size_t i = (size_t)L * fr + tid; i < (size_t)T * fr; i += blockDim.x) gw[i] = 0.f;
     if (bad) return;
     for (int d = tid; d < c.C; d += blockDim.x) bn[d] = 0.f;
     const double D = Dws[b];
     double Boff = 0.0;
     const int NR = blockDim.x / G, r = tid / G, l = tid - r * G;
+    auto store_row = [&](int t) __attribute__((always_inline)) {      // (every thread its own states of bn)
+        const size_t row = (size_t)b * (T + 1) + t;
+        for (int d = tid; d < c.C; d += blockDim.x) beta[row * c.C + d] = bn[d];
+        if (tid == 0) boffs[row] = Boff;
+    };
+    if (ROWS) store_row(L);
     __syncthreads();
     for (int t = L - 1; t >= 0; --t) {
         const float* wt = w + ((size_t)b * T + t) * fr;
@@ -178,6 +185,7 @@ __device__ __forceinline__ void solo_backward_item(
             s = group_sum<G>(s);
             if (valid) {
                 if (l == 0) bc[q] = (m == LAST_NEG_INF) ? LAST_NEG_INF : m + logf(s);
+                if (ROWS) continue;
                 const float a = at[q];
                 float* grow = gt + (size_t)q * c.V1;
                 for (int y = l; y < c.V1; y += G) {
@@ -194,6 +202,7 @@ __device__ __forceinline__ void solo_backward_item(
         if (mx == LAST_NEG_INF) mx = 0.f;
         Boff += (double)mx;
         for (int d = tid; d < c.C; d += blockDim.x) bn[d] = bc[d] - mx;
+        if (ROWS) store_row(t);
         __syncthreads();
     }
 }

@@ -65,7 +65,7 @@ struct TriArgs {
 };
 
 // row of the state vectors at which the two directions are joined into the distance
-__host__ __device__ inline int tri_meet(int L, bool keep) { return keep ? L : L / 2; }
+__host__ __device__ inline int tri_meet(int L, bool keep) { return keep ? L : (L + 1) / 2; }
 
 constexpr int kTriMaxV = 64;
 constexpr int kTriPad = 72;      // floats behind the tile that a row's lanes may read
@@ -670,11 +670,13 @@ struct TriRedo {
 
 // D = log (+)_q alpha_m[q] beta_m[q] of every item from the rows at which the two directions meet (beta = 0 at the
 // last frame), one workgroup per item.  alpha, beta: natural logs with offsets.  badtab may be null.
+// keep: 0: one row per item; 1: rows of all frames, joined at the last one; 2: rows of all frames, joined where
+// keep = 0 joins them, so that the two return the same bits.
 // REDO: an item marked in `fail` is computed here once more by this workgroup alone, gradient included
-// (dense_marginals_kernel leaves it out); dynamic LDS for solo_kernels.hpp.
+// (dense_marginals_kernel leaves it out; keep = 2: the rows of both directions); dynamic LDS for solo_kernels.hpp.
 template <bool REDO>
 __global__ __launch_bounds__(256) void tri_join_kernel(
-    float* alpha, const float* __restrict__ beta, double* offa, const double* __restrict__ offb,
+    float* alpha, float* beta, double* offa, double* offb,
     const int* __restrict__ len, const int* __restrict__ fail, const int* __restrict__ badtab, int T, int C, int keep,
     double* D2, float* dist, int* __restrict__ item_status, TriRedo redo)
 {
@@ -699,17 +701,20 @@ __global__ __launch_bounds__(256) void tri_join_kernel(
         __syncthreads();
         if (redo.dw)
             solo_backward_item<16>(b, L, tri_redo_s, redo.w, redo.c, T, alpha, offa, D2, redo.dw, redo.scale, redo.accumulate);
+        else if (keep == 2)
+            solo_backward_item<16, true>(b, L, tri_redo_s, redo.w, redo.c, T, alpha, offa, D2, nullptr, 0.f, 0, beta, offb);
         return;
     }
-    const size_t ra = keep ? ((size_t)b * (T + 1) + L) : (size_t)b;
+    const size_t ra = keep ? (size_t)b * (T + 1) + tri_meet(L, keep == 1) : (size_t)b;
+    const bool last = keep == 1;             // (beta is 0 there)
     const float* al = alpha + ra * C;
     const float* be = beta + ra * C;
     float mx = LAST_NEG_INF;
-    for (int q = tid; q < C; q += 256) mx = fmaxf(mx, keep ? al[q] : al[q] + be[q]);
+    for (int q = tid; q < C; q += 256) mx = fmaxf(mx, last ? al[q] : al[q] + be[q]);
     mx = block_max(mx, red);
     const float mm = mx == LAST_NEG_INF ? 0.f : mx;
     double z = 0.0;
-    for (int q = tid; q < C; q += 256) z += (double)tri_exp((keep ? al[q] : al[q] + be[q]) - mm);
+    for (int q = tid; q < C; q += 256) z += (double)tri_exp((last ? al[q] : al[q] + be[q]) - mm);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
     if ((tid & 63) == 0) redd[tid >> 6] = z;
@@ -718,7 +723,7 @@ __global__ __launch_bounds__(256) void tri_join_kernel(
         z = redd[0];
         for (int k = 1; k < 4; ++k) z += redd[k];
         const double d2 = mx == LAST_NEG_INF ? (double)LAST_NEG_INF
-                                             : offa[ra] + (keep ? 0.0 : offb[ra]) + (double)mm + log(z);
+                                             : offa[ra] + (last ? 0.0 : offb[ra]) + (double)mm + log(z);
         dist[b] = (float)d2;
         if (D2) D2[b] = d2;
     }

@@ -1,0 +1,133 @@
+"""GPU parity of the on-the-fly weights that are laid out in memory (emb_kernels.hip): inputs beyond the range of the
+exponentials, batches in slices, references whose cells crowd one tile, items computed by one workgroup, and
+workspaces that only hold the kernels without weights in memory; against the float64 oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2304_13134_amd import binding as lb
+from paper_2304_13134_amd import workloads
+from gpu_util import announce, assert_dist_close, library_option
+from test_gpu_fused import assert_grad_close, fused_inputs, run_fused_grads, run_fused_loss
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("case", ["f", "e", "both", "infinite"])
+def test_values_beyond_the_range_of_the_exponentials(case):
+    """tanh(f + e) from e^2f e^2e: f or e alone far outside (saturated whatever the other is), both outside with sums
+    of a few units, and infinities."""
+    announce("wide inputs", case)
+    s = workloads.shared_emb(B=3, T=9, V=5, order=2, H=128, seed=5, len_lo=6, len_hi=9)
+    rng = np.random.default_rng(5)
+    big = rng.choice([-1.0, 1.0], size=128) * rng.uniform(31.0, 90.0, size=128)
+    f, e = (oracle_float(s[k]).copy() for k in "fe")
+    on = rng.random(128) < 0.3
+    if case in ("f", "both"):
+        f[:, :, on] = big[on]
+    if case == "e":
+        e[:, on] = big[on]
+    if case == "both":
+        e[:, on] = -workloads_round(big)[on] + rng.standard_normal((e.shape[0], int(on.sum())))
+    if case == "infinite":
+        f[:, ::2, on] = np.inf
+        f[:, 1::2, on] = -np.inf
+    s["f"], s["e"] = workloads.to_bf16_bits(f.astype(np.float32)), workloads.to_bf16_bits(e.astype(np.float32))
+    run_fused_grads(s)
+
+
+def oracle_float(bits):
+    return (bits.astype(np.uint32) << 16).view(np.float32)
+
+
+def workloads_round(x):
+    return oracle_float(workloads.to_bf16_bits(x.astype(np.float32)))
+
+
+def test_batch_in_slices_returns_what_its_items_return_alone():
+    """Three items of which two fit the weights kept at a time: distances and df bit for bit those of calls with one
+    item each, de and dW their sum."""
+    B, T, V, H = 3, 3500, 64, 128
+    announce("slices", B, T, V, H)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    C = 1 + V + V * V
+    f = torch.randn((B, T, H), generator=g, device="cuda").bfloat16()
+    e = (0.5 * torch.randn((C, H), generator=g, device="cuda")).bfloat16()
+    W = (torch.randn((H, V + 1), generator=g, device="cuda") / H ** 0.5).bfloat16()
+    lengths = torch.tensor([T, T - 77, T - 1200], dtype=torch.int32, device="cuda")
+    d0 = lb.last_shortest_distance(lb.SharedEmb(f, e, W), lengths, order=2)
+    dist, (df, de, dW) = lb.last_arc_posteriors(lb.SharedEmb(f, e, W), lengths, order=2)
+    assert torch.equal(d0, dist)
+    de1, dW1 = torch.zeros_like(de), torch.zeros_like(dW)
+    for b in range(B):
+        d1, (df1, x, y) = lb.last_arc_posteriors(lb.SharedEmb(f[b:b + 1].contiguous(), e, W), lengths[b:b + 1], order=2)
+        assert torch.equal(d1, dist[b:b + 1])
+        # (stretches of frames differ with the batch, sums over the states of a frame do not)
+        assert torch.equal(df1[0], df[b])
+        de1 += x
+        dW1 += y
+    assert_grad_close("de", de.cpu().numpy(), de1.cpu().numpy())
+    assert_grad_close("dW", dW.cpu().numpy(), dW1.cpu().numpy())
+
+
+@pytest.mark.parametrize("H,V,U", [(128, 3, 200), (512, 33, 40), (256, 32, 0)])
+def test_loss_with_many_cells_in_one_tile(H, V, U):
+    """References of one label over and over: all cells of the intersected lattice in one tile of states, more of them
+    than a workgroup has threads (H = 128); no label at all; accumulated with a scale."""
+    B, T = 2, max(30, U + 40)
+    announce("cells of one tile", H, V, U)
+    s = workloads.shared_emb(B=B, T=T, V=V, order=2, H=H, seed=9, len_lo=T - 5, len_hi=T)
+    s["refs"] = np.full((B, max(U, 1)), 2, dtype=np.int32)
+    s["ref_lengths"] = np.asarray([U, U // 2], dtype=np.int32)
+    se = fused_inputs(s)
+    st = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    grads = tuple(torch.full(t.shape, 3.0, dtype=torch.float32, device="cuda") for t in se)
+    D, N, _ = lb.last_globally_normalized_loss(se, torch.from_numpy(s["lengths"]).cuda(), torch.from_numpy(s["refs"]).cuda(),
+                                               torch.from_numpy(s["ref_lengths"]).cuda(), order=2, dw=grads, scale=0.5,
+                                               accumulate=True, item_status=st)
+    torch.cuda.synchronize()
+    den = oracle.fused_forward_backward(s["f"], s["e"], s["W"], s["lengths"], 2, round_h=True, grads=True)
+    num = oracle.fused_numerator(s["f"], s["e"], s["W"], s["lengths"], s["refs"], s["ref_lengths"], 2)
+    assert st.cpu().tolist() == [0] * B
+    assert_dist_close(D.cpu().numpy(), den["D"])
+    assert_dist_close(N.cpu().numpy(), num["N"], "numerator")
+    for name, got in zip(("df", "de", "dW"), grads):
+        a, b = den[name].astype(np.float64), num[name].astype(np.float64)
+        tol = 1e-4 * max(1.0, np.max(np.abs(a)) + np.max(np.abs(b)))      # a difference of two such terms
+        assert np.max(np.abs(got.cpu().numpy() - (3.0 + 0.5 * (a - b)))) <= tol, name
+
+
+def test_items_whose_waits_ran_out_have_their_gradient():
+    announce("spin limit 1, weights in memory")
+    with library_option(lb.OPT_SPIN_LIMIT, 1):
+        run_fused_grads(workloads.shared_emb(B=4, T=13, V=24, order=2, H=128, seed=78, len_lo=5, len_hi=13))
+
+
+@pytest.mark.parametrize("V,lens", [(3, [1, 0, 2]), (31, [40, 0, 33]), (47, [7, 7, 1]), (64, [9, 2, 5])])
+def test_lengths_labels_and_smaller_workspaces(V, lens):
+    """Lengths of nothing and of one frame, tiles of labels with remainders; the entry point with the static workspace
+    and the smallest workspace that the call takes, which holds no weights."""
+    announce("lengths and workspaces", V, lens)
+    s = workloads.shared_emb(B=3, T=max(lens), V=V, order=2, H=256, seed=V)
+    s["lengths"] = np.asarray(lens, dtype=np.int32)
+    o, _ = run_fused_grads(s)
+    se, lengths = fused_inputs(s), torch.from_numpy(s["lengths"]).cuda()
+    dist = torch.empty(3, dtype=torch.float32, device="cuda")
+    lb.last_shortest_distance_static(se, lengths, dist, order=2)
+    torch.cuda.synchronize()
+    assert_dist_close(dist.cpu().numpy(), o["D"])
+    wt, cx, _, _ = lb._weights_and_context(se, 2)
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0):
+        small = lb.last_workspace_bytes(wt, cx, lb.OP_SHORTEST_DISTANCE)
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    dist2 = torch.empty_like(dist)
+    for nbytes, code in ((small, 0), (small - 1, 5)):
+        assert lb.load_library().last_shortest_distance(
+            ctypes.byref(wt), lb._ptr(lengths), ctypes.byref(cx), lb.LAST_LOG, lb._ptr(dist2), None, lb._ptr(ws), nbytes,
+            lb._stream()) == code
+    torch.cuda.synchronize()
+    assert_dist_close(dist2.cpu().numpy(), o["D"])
