@@ -364,17 +364,18 @@ struct EmGradLds {
     static constexpr int S1 = 16 * KY + 8;         // row strides (bf16): 16-byte reads of 8 lanes fall on different banks
     static constexpr int S2 = 40;
     static constexpr int NT = KY / 2;              // tiles of 32 labels
-    __bf16 g1[2][2][32 * S1];                      // [buffer][half][state][label - 1]
-    __bf16 g2[2][2][32 * NT * S2];                 // [buffer][half][label - 1][state in operand order]
-    float g0[2][32];                               // empty label
-    float num[2][32 * (16 * KY + 1)];              // marginals of the intersected lattice [state][label]
+    static constexpr int FP = KY == 2 ? 2 : 1;     // frames between two barriers
+    __bf16 g1[2 * FP][2][32 * S1];                 // [buffer][half][state][label - 1]
+    __bf16 g2[2 * FP][2][32 * NT * S2];            // [buffer][half][label - 1][state in operand order]
+    float g0[2 * FP][32];                          // empty label
+    float num[2 * FP][32 * (16 * KY + 1)];         // marginals of the intersected lattice [state][label]
 };
 
 template <int NW, int KY, bool NUM>
 __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArgs& g, EmGradLds<NW, KY>& s, int tile, int grp, int lo, int hi)
 {
     typedef EmGradLds<NW, KY> S;
-    constexpr int NT = S::NT, S1 = S::S1, S2 = S::S2;
+    constexpr int NT = S::NT, S1 = S::S1, S2 = S::S2, FP = S::FP;
     constexpr int LPR = 2 * NW;                             // lanes of a row when the marginals are formed
     constexpr int NS = (16 * KY + 1 + LPR - 1) / LPR;       // labels of such a lane
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -439,8 +440,8 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         x.f[1] = f[32];
     };
     // marginals of a frame -> LDS
-    auto put = [&](const Frame& x, int buf) __attribute__((always_inline)) {
-        const bool live = rok && x.a != LAST_NEG_INF;       // (an arc out of an unreachable state does not count, whatever its weight)
+    auto put = [&](const Frame& x, int i, int buf) __attribute__((always_inline)) {
+        const bool live = i < hi && rok && x.a != LAST_NEG_INF;       // (an arc out of an unreachable state does not count, whatever its weight)
         const float al = (float)((double)x.a + x.n.k);
 #pragma unroll
         for (int n = 0; n < NS; ++n) {
@@ -483,10 +484,10 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         if (e & 127) unsafeAtomicAdd(d + (e & 127), p.y);
     };
     struct Num { float2 p; int ent, n; const int* cp; };
-    auto request_cells = [&](Num& x, int2 v) __attribute__((always_inline)) {
+    auto request_cells = [&](Num& x, int2 v, int i) __attribute__((always_inline)) {
         cells_of(v.y);
         x.ent = ent;
-        x.n = ncell;
+        x.n = i < hi ? ncell : 0;
         x.cp = cp;
         x.p = g.pn[(size_t)v.x * g.U1 + (ent >> 12)];       // (no condition: the waits for what was requested are counted)
     };
@@ -495,7 +496,7 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         for (int i = tid + 64 * NW; i < x.n; i += 64 * NW) add_cell(x.cp[i], g.pn[(size_t)v.x * g.U1 + (x.cp[i] >> 12)], buf);
     };
 
-    auto compute = [&](const float (&f)[2], int2 v, int buf) __attribute__((always_inline)) {
+    auto compute = [&](const float (&f)[2], int2 v, bool live, int buf) __attribute__((always_inline)) {
         float cs[2];
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
@@ -552,7 +553,7 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         // sum over the 32 states: lanes of the other half hold the other 16; half 0 stores k0, half 1 k0 + 32
         const float send = half ? cs[0] : cs[1], keep = half ? cs[1] : cs[0];
         const float sum = keep + __shfl_xor(send, 32);
-        g.pdf[((size_t)tile * a.B * a.T + v.x) * H + k0 + 32 * half] = sum;
+        if (live) g.pdf[((size_t)tile * a.B * a.T + v.x) * H + k0 + 32 * half] = sum;
     };
 
     // dW so far -> the partial sums of this workgroup
@@ -580,53 +581,81 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
     };
 
     if (lo < hi) {
-        Frame x[2];
-        Num m[2];
-        int2 v0 = uniform(raw_frame(lo)), v1 = uniform(raw_frame(lo + 1)), v2 = uniform(raw_frame(lo + 2));
-        int2 nv = raw_frame(lo + 3);
-        request(x[0], v0);
-        request_f(x[0], v0);
-        if (NUM) {
-            request_cells(m[0], v0);
-            request_cells(m[1], v1);
-            add_cells(m[0], v0, 0);
-            em_lds_barrier();
-        }
-        put(x[0], 0);
-        if (NUM) {
-            add_cells(m[1], v1, 1);
-            request_cells(m[0], v2);
-        }
-        float f[2] = {bf_lo(x[0].f[0]), bf_lo(x[0].f[1])};
-        request(x[0], v1);
-        request_f(x[0], v1);
-        em_lds_barrier();
-        // frame i is used; its successor's marginals are formed, the requests for the one after it go out; the
-        // cells of the frame after the successor are added up
-        // a sum over a thousand frames of values of which a few are near 1 and most near 1e-4 loses 2.4e-6 of dW: it is
-        // put away every 64 frames
-        for (int i = lo; i < hi;) {
-        for (const int end = min(i + 64, hi); i < end; ++i) {
-            const int buf = (i - lo) & 1;
-            const int2 v3 = uniform(nv);                    // (requested a frame ago)
-            nv = raw_frame(i + 4);
-            compute(f, v0, buf);
-            put(x[0], buf ^ 1);
-            f[0] = bf_lo(x[0].f[0]);
-            f[1] = bf_lo(x[0].f[1]);
-            asm volatile("" : "+v"(f[0]), "+v"(f[1]));           // (read before the registers are requested into again)
-            request(x[0], v2);
-            request_f(x[0], v2);
-            if (NUM) {
-                add_cells(m[0], v2, buf);
-                request_cells(m[0], v3);
+        Frame x[FP];
+        Num m[FP];
+        int2 v0[FP], v1[FP], v2[FP], nv[FP];
+        float f[FP][2];
+        auto used_f = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < FP; ++j) {
+                f[j][0] = bf_lo(x[j].f[0]);
+                f[j][1] = bf_lo(x[j].f[1]);
+                asm volatile("" : "+v"(f[j][0]), "+v"(f[j][1]));      // (read before the registers are requested into again)
             }
-            v0 = v1;
-            v1 = v2;
-            v2 = v3;
+        };
+#pragma unroll
+        for (int j = 0; j < FP; ++j) {
+            v0[j] = uniform(raw_frame(lo + j));
+            v1[j] = uniform(raw_frame(lo + FP + j));
+            v2[j] = uniform(raw_frame(lo + 2 * FP + j));
+            nv[j] = raw_frame(lo + 3 * FP + j);
+            request(x[j], v0[j]);
+            request_f(x[j], v0[j]);
+        }
+        if (NUM) {
+#pragma unroll
+            for (int j = 0; j < FP; ++j) {
+                request_cells(m[j], v0[j], lo + j);
+                add_cells(m[j], v0[j], j);
+                request_cells(m[j], v1[j], lo + FP + j);
+                add_cells(m[j], v1[j], FP + j);
+                request_cells(m[j], v2[j], lo + 2 * FP + j);
+            }
             em_lds_barrier();
         }
-        flush(i <= lo + 64);
+#pragma unroll
+        for (int j = 0; j < FP; ++j) put(x[j], lo + j, j);
+        used_f();
+#pragma unroll
+        for (int j = 0; j < FP; ++j) {
+            request(x[j], v1[j]);
+            request_f(x[j], v1[j]);
+        }
+        em_lds_barrier();
+        // the frames from i on are used; the marginals of those after them are formed, the requests for the next ones
+        // go out and their cells are added up.  dW is put away every 64 frames: a sum over a thousand frames of values
+        // of which a few are near 1 and most near 1e-4 loses 2.4e-6 of it.
+        for (int i = lo; i < hi;) {
+            for (const int end = min(i + 64, hi); i < end; i += FP) {
+                const int cur = (i - lo) & FP ? FP : 0, nxt = FP - cur;
+                int2 v3[FP];
+#pragma unroll
+                for (int j = 0; j < FP; ++j) {
+                    v3[j] = uniform(nv[j]);                 // (requested FP frames ago)
+                    nv[j] = raw_frame(i + 4 * FP + j);
+                }
+#pragma unroll
+                for (int j = 0; j < FP; ++j) compute(f[j], v0[j], i + j < hi, cur + j);
+#pragma unroll
+                for (int j = 0; j < FP; ++j) put(x[j], i + FP + j, nxt + j);
+                used_f();
+#pragma unroll
+                for (int j = 0; j < FP; ++j) {
+                    request(x[j], v2[j]);
+                    request_f(x[j], v2[j]);
+                }
+                if (NUM) {
+#pragma unroll
+                    for (int j = 0; j < FP; ++j) {
+                        add_cells(m[j], v2[j], cur + j);
+                        request_cells(m[j], v3[j], i + 3 * FP + j);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < FP; ++j) { v0[j] = v1[j]; v1[j] = v2[j]; v2[j] = v3[j]; }
+                em_lds_barrier();
+            }
+            flush(i <= lo + 64);
         }
     }
     if (lo >= hi) flush(true);
