@@ -612,7 +612,7 @@ last_status_t launch_fused_backward(const Shape& s, const FusedPlan& p, const Fu
 struct TriPlan {
     bool ok;
     int dims;            // index into the instantiations below
-    int nb, K, ncl, G, xs, roles, grid;
+    int nb, K, ncl, G, xs, roles, across, grid;
     size_t lds;
 };
 
@@ -622,6 +622,7 @@ typedef TriDims<8, 2, 3, 9> Tri1;       // up to 35
 typedef TriDims<8, 2, 4, 11> Tri2;      // up to 42 (43: three labels a workgroup no longer fit)
 typedef TriDims<16, 4, 3, 9> Tri3;      // up to 35
 typedef TriDims<16, 4, 6, 17> Tri4;     // up to 64
+typedef TriDims<8, 2, 6, 17> Tri5;      // up to 64, two labels a workgroup
 
 constexpr size_t kTriRowBytes = (size_t)24 << 20;   // most that the rows of a call without marginals may take
 
@@ -641,27 +642,33 @@ TriPlan tri_plan(const Shape& s, int kind, bool trop)
         p.K = (s.V + p.nb - 1) / p.nb;
         p.nb = (s.V + p.K - 1) / p.K;                       // evenly over the workgroups, each with at least one
         p.K = (s.V + p.nb - 1) / p.nb;
-        if (p.roles * p.K > 32 || p.K * D::NCM > kWave) return;
-        p.ncl = std::min((s.B + 7) / 8, 32 / (p.roles * p.K));
+        if (p.K > 32 || p.K * D::NCM > kWave) return;
+        p.across = p.roles * p.K > 32 ? 1 : 0;
+        const int xcds = 8 >> p.across, each = p.K * (p.roles >> p.across);      // XCDs an item may start on, workgroups there
+        p.ncl = std::min((s.B + xcds - 1) / xcds, 32 / each);
         const int cq = (p.nb * s.V1 + 3) / 4;
         p.G = std::min(std::min(D::CT / cq, s.V1), kTriMaxG);
         if (p.G < 1 || p.G * D::NR < s.V1) return;          // every row of the frame has a thread
         if (p.nb * s.V1 + 1 > D::NP * D::CT / 4 || p.nb * s.V1 + 1 > D::States || p.nb >= 32) return;
         p.xs = s.V * s.V + s.V + p.K * D::NCM;
-        p.grid = 8 * p.ncl * p.roles * p.K;
+        p.grid = 8 * p.ncl * each;
         const size_t fwd = (size_t)2 * kTriMaxG * 4 * cq;
         const size_t bwd = (size_t)(p.nb + 1) * D::BtPitch + 3 + (size_t)s.V1 * 4 * cq + kTriPad;
         p.lds = std::max(fwd, trop ? (size_t)0 : bwd) * sizeof(float);
         if (p.lds > kBigLds - 16384) return;
         p.ok = true;
-        const long long rounds = (s.B + 8 * p.ncl - 1) / (8 * p.ncl);
+        const long long rounds = (s.B + xcds * p.ncl - 1) / (xcds * p.ncl);
         if (!best.ok || rounds < fewest) { best = p; fewest = rounds; }
     };
     consider(0, Tri0());
     if (!best.ok) consider(1, Tri1());
     if (!best.ok) consider(2, Tri2());
     consider(3, Tri3());
-    if (!best.ok) consider(4, Tri4());
+    // two labels a workgroup, one direction of an item on an XCD, against four, both directions on it: 2.3 to 4.3 against 3.1 to
+    // 5.2 us a frame with 45 to 60 labels (posteriors of 4 items, 60 labels, 200 frames 1043 -> 898 us, distance 389 -> 309),
+    // but half as many items at a time (8 items 1431 / 1754 us, 24 items of 64 labels, 100 frames 2494 / 2969)
+    if (!best.ok) consider(5, Tri5());
+    if (!best.ok || best.dims == 5) consider(4, Tri4());
     return best;
 }
 
@@ -683,7 +690,7 @@ TriWs carve_tri(Carver& cv, const Shape& s, const TriPlan& p, bool trop, bool ke
     c.offa = trop ? nullptr : cv.take<double>(rows);
     c.offb = trop ? nullptr : cv.take<double>(rows);
     c.D2 = trop ? nullptr : cv.take<double>((size_t)s.B);
-    c.xwords = (size_t)8 * p.ncl * p.roles * 2 * p.xs;
+    c.xwords = (size_t)(8 >> p.across) * p.ncl * p.roles * 2 * p.xs;
     c.x = cv.take<u64>(c.xwords);
     c.fail = cv.take<int>((size_t)s.B);
     return c;
@@ -706,7 +713,7 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
     a.w = w; a.len = lengths; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb;
     a.bp = bp; a.x = c.x; a.fail = c.fail;
     a.B = s.B; a.T = s.T; a.V = s.V; a.C = s.C;
-    a.nb = p.nb; a.K = p.K; a.ncl = p.ncl; a.G = p.G; a.xs = p.xs; a.roles = p.roles;
+    a.nb = p.nb; a.K = p.K; a.ncl = p.ncl; a.G = p.G; a.xs = p.xs; a.roles = p.roles; a.across = p.across;
     a.keep = keep; a.spin_limit = opt(LAST_OPT_SPIN_LIMIT);
     last_status_t rc = LAST_OK;
     auto go = [&](auto k, int threads) {
@@ -723,7 +730,8 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
     case 1: pick(Tri1()); break;
     case 2: pick(Tri2()); break;
     case 3: pick(Tri3()); break;
-    default: pick(Tri4()); break;
+    case 4: pick(Tri4()); break;
+    default: pick(Tri5()); break;
     }
     return rc;
 }

@@ -31,9 +31,10 @@
 // forming them inside the recursion would put the stores on the chain to save
 // 4 of 16 bytes per arc.
 //
-// Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.73 ms against
+// Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.68 ms against
 // 34 ms with one workgroup per item (solo_kernels.hpp), 1.9 us a frame and
-// marginals in 0.11 ms; 6 items, 120 to 250 frames, 28 labels, shortest path 0.39
+// marginals in 0.11 ms; distance of 4 items, 1000 frames, 64 labels (weights in memory) 1.6 ms on 32 workgroups a direction,
+// 2.1 on 16 that own twice the labels; 6 items, 120 to 250 frames, 28 labels, shortest path 0.39
 // against 3.7 ms.
 // What made the difference between 3.0 and 1.9 us a frame is that every weight
 // request and store is issued on every path (the waits for the weights can then
@@ -60,6 +61,7 @@ struct TriArgs {
     int B, T, V, C;
     int nb, K, ncl, G, xs;
     int roles;           // 2: forward and backward, 1: forward only
+    int across;          // 1: the directions of an item on two XCDs
     int keep;            // 1: every row is stored at [b][T+1][C]; 0: only the meeting row at [b][C]
     int spin_limit;
 };
@@ -137,6 +139,17 @@ __device__ __forceinline__ bool tri_poll(const u64* wp, const u64* hp, bool act,
     }
     return false;
 }
+
+// A lane's place in an exchange slot as a byte offset in a register of its own: the scalar registers are all taken, and an
+// address put together from uniform parts that were put away costs their reads from a vector register's lanes
+// on the chain of every frame.
+__device__ __forceinline__ unsigned tri_place(int word)
+{
+    unsigned off = 8u * (unsigned)word;
+    asm volatile("" : "+v"(off));
+    return off;
+}
+__device__ __forceinline__ u64* tri_at(u64* slot, unsigned off) { return (u64*)((char*)slot + off); }
 
 // what the two directions share: which part of the lattice a workgroup owns, and its pieces of a frame
 struct TriOwn {
@@ -331,7 +344,8 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
         const bool second = wave == 0 && lane <= nbk;                             // histories of one label, the start state
         const bool single = wave == 0 && lane < nbk;
         const int nh = a.K * NCM;
-        const int hidx = V * V + V + (lane < nh ? lane : 0);
+        const unsigned oMine = tri_place((o.b0 - 1) * V + lidx), oGot = tri_place(gidx);
+        const unsigned oHead = tri_place(V * V + V + o.k * NCM + wave), oHeads = tri_place(V * V + V + (lane < nh ? lane : 0));
         bool dead = false;
         double A = 0.0;
         __syncthreads();
@@ -377,14 +391,13 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 src = s.xa[act ? wl : 0];
                 head = s.hd[lane < NCM ? lane : 0];
             } else {
-                u64* mine = xs + (size_t)(o.b0 - 1) * V + lidx;
-                if (act) xpublish(mine, TROP ? (u64)__float_as_uint(val) | ((u64)(unsigned)src << 32) | ((u64)(tag & 0xffffu) << 48)
+                if (act) xpublish(tri_at(xs, oMine), TROP ? (u64)__float_as_uint(val) | ((u64)(unsigned)src << 32) | ((u64)(tag & 0xffffu) << 48)
                                              : pack_word(val, tag));
                 if (!TROP) {
                     head = wave_max_dpp(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), fmaxf(sn, sb)));
-                    if (lane == 0) xpublish(xs + V * V + V + o.k * NCM + wave, pack_word(head, tag));
+                    if (lane == 0) xpublish(tri_at(xs, oHead), pack_word(head, tag));
                 }
-                if (!dead) dead = !tri_poll<!TROP, TROP>(xs + gidx, xs + hidx, act, tag, a.spin_limit, word, hw);
+                if (!dead) dead = !tri_poll<!TROP, TROP>(tri_at(xs, oGot), tri_at(xs, oHeads), act, tag, a.spin_limit, word, hw);
                 val = __uint_as_float((unsigned)word);
                 src = (int)((word >> 32) & 0xffffu);
                 head = __uint_as_float((unsigned)hw);
@@ -570,7 +583,9 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
         const bool second = wave == 0 && lane <= nbk;
         const bool starter = o.k == 0 && wave == 0;                                      // gathers the histories of one label
         const int nh = a.K * NCM;
-        const int hidx = V * V + V + (lane < nh ? lane : 0);
+        const unsigned oMine = tri_place((pa - 1) * V + (o.b0 - 1 + pi)), oGot = tri_place((o.b0 - 1) * V + (act ? lidx : 0));
+        const unsigned oHead = tri_place(V * V + V + o.k * NCM + wave), oHeads = tri_place(V * V + V + (lane < nh ? lane : 0));
+        const unsigned oSingle = tri_place(V * V + (o.b0 - 1 + lane)), oSingles = tri_place(V * V + (lane < V ? lane : 0));
         bool dead = false;
         double A = 0.0;
         __syncthreads();
@@ -594,16 +609,16 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
                 if (starter && lane < V) gots = s.xl[V * V + lane];
                 head = s.hd[lane < NCM ? lane : 0];
             } else {
-                if (act) xpublish(xs + (size_t)(pa - 1) * V + (o.b0 - 1 + pi), pack_word(val, tag));
-                if (single) xpublish(xs + V * V + (o.b0 - 1 + lane), pack_word(sv, tag));
+                if (act) xpublish(tri_at(xs, oMine), pack_word(val, tag));
+                if (single) xpublish(tri_at(xs, oSingle), pack_word(sv, tag));
                 head = wave_max_dpp(fmaxf(val, sv));
-                if (lane == 0) xpublish(xs + V * V + V + o.k * NCM + wave, pack_word(head, tag));
-                if (!dead) dead = !tri_poll<true, false>(xs + (size_t)(o.b0 - 1) * V + (act ? lidx : 0), xs + hidx, act, tag,
+                if (lane == 0) xpublish(tri_at(xs, oHead), pack_word(head, tag));
+                if (!dead) dead = !tri_poll<true, false>(tri_at(xs, oGot), tri_at(xs, oHeads), act, tag,
                                                          a.spin_limit, word, hw);
                 got = __uint_as_float((unsigned)word);
                 head = __uint_as_float((unsigned)hw);
                 if (starter) {
-                    if (!dead) dead = !tri_poll<false, false>(xs + V * V + (lane < V ? lane : 0), xs, lane < V, tag,
+                    if (!dead) dead = !tri_poll<false, false>(tri_at(xs, oSingles), xs, lane < V, tag,
                                                               a.spin_limit, word, hw);
                     gots = __uint_as_float((unsigned)word);
                 }
@@ -627,18 +642,21 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
     __syncthreads();
 }
 
+// (four waves a SIMD: a cluster of 32 workgroups, a whole XCD, leaves room for that of another launch)
 template <typename D, bool TROP>
-__global__ __launch_bounds__(D::NW * kWave) void trigram_kernel(TriArgs a)
+__global__ __launch_bounds__(D::NW * kWave, 4) void trigram_kernel(TriArgs a)
 {
     extern __shared__ __align__(16) float tri_dyn[];
     __shared__ __align__(16) TriLds<D> s;
-    // workgroups with equal id % 8 sit on one XCD; a cluster takes K of them per direction
+    // workgroups with equal id % 8 sit on one XCD; a cluster takes K of them per direction.  The directions do not meet
+    // in this kernel: those of a cluster with more than 16 workgroups sit on two neighbouring XCDs (across = 1).
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int cl = slot / (a.roles * a.K), rk = slot - cl * a.roles * a.K;
-    const int role = rk / a.K;
-    const int cg = xcd + 8 * cl;
+    const int rx = a.roles >> a.across;
+    const int cl = slot / (rx * a.K), rk = slot - cl * rx * a.K;
+    const int role = a.across ? xcd & 1 : rk / a.K;
+    const int cg = (xcd >> a.across) + (8 >> a.across) * cl;
     TriOwn o;
-    o.k = rk - role * a.K;
+    o.k = rk % a.K;
     o.V = a.V;
     o.V1 = a.V + 1;
     o.b0 = 1 + o.k * a.nb;
@@ -649,7 +667,7 @@ __global__ __launch_bounds__(D::NW * kWave) void trigram_kernel(TriArgs a)
     o.rows = o.V1 * o.nbk;
     u64* xbase = a.x + (size_t)(cg * a.roles + role) * 2 * a.xs;
     unsigned gstep = 0;
-    for (int b = cg; b < a.B; b += 8 * a.ncl) {
+    for (int b = cg; b < a.B; b += (8 >> a.across) * a.ncl) {
         const int L = a.len[b];
         if (L < 0 || L > a.T) continue;
         if (TROP || role == 0) tri_forward<D, TROP>(a, o, b, L, gstep, xbase, s, tri_dyn);

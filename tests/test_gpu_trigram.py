@@ -188,3 +188,19 @@ def test_distance_of_a_batch_in_slices(order, V, C, B):
     with library_option(lb.OPT_FORCE_SOLO, 1):                 # the general kernels on the whole batch
         again = lb.last_shortest_distance(w, lengths, order=g_order)
     assert_dist_close(D.cpu().numpy()[:-2], again.cpu().numpy()[:-2])
+
+
+# clusters of 22 to 32 workgroups, the two directions of an item on two XCDs (up to four items); with more items both
+# directions on one XCD again
+@pytest.mark.parametrize("V,T,B", [(43, 6, 4), (51, 5, 3), (63, 4, 1), (64, 5, 4), (47, 4, 5), (64, 3, 9)])
+def test_directions_on_two_xcds(V, T, B):
+    announce("clustered trigram, directions apart", V, T, B)
+    cfg = workloads.dense(B=B, T=T, V=V, order=2, sigma=1.5, seed=300 + V, len_lo=1, len_hi=T)
+    check_posteriors(cfg, order=2)
+    check_path(cfg, order=2)
+    dist = lb.last_shortest_distance(dev(cfg["w"]), dev(cfg["lengths"]), order=2)
+    assert_dist_close(dist.cpu().numpy(), oracle.forward(cfg["w"], cfg["lengths"], 2)[1])
+
+
+def test_calls_on_several_streams_with_directions_on_two_xcds():
+    test_calls_on_several_streams_share_the_chip(60, 4)
