@@ -143,6 +143,21 @@ __global__ __launch_bounds__(256) void emb_prepare_kernel(EmbArgs a, size_t nf, 
     fill((const unsigned*)a.f, a.Ef, nf, nf);
 }
 
+typedef __amdgpu_buffer_rsrc_t em_buf;
+
+__device__ __forceinline__ em_buf em_make_buf(const void* p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float em_load(em_buf r, unsigned off)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void em_store(float x, em_buf r, unsigned voff, unsigned soff)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, x), r, (int)voff, (int)soff, 0);
+}
+
 // One workgroup: 32 states and a stretch of the frame list.  The rows of e^2e (64 KiB) and W (48 to 80 KiB) sit in LDS
 // in operand order; a wave takes four frames (three with five label tiles) at a time, so that each fragment of W serves
 // eight row tiles of 16, and never meets the others.  A operand: lane l holds hidden units 8 (l / 16) .. + 7 of a step
@@ -158,14 +173,33 @@ __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* 
     const int q0 = tile * kEmTile;
     const size_t fr = (size_t)a.C * V1;
     const int y = lane & 15;
-    for (int i = lo + FR * wave; i < hi; i += FR * kEwWaves) {
-        const float* fp[FR];
-        int row[FR];
+    const unsigned wOff = 4u * (unsigned)(4 * (lane >> 4) * V1 + y), wLast = 16 * (NT - 1) + y < V1 ? wOff : 0x80000000u;
+    // frames of the group that starts at list entry i (past the end: the last frame again)
+    auto rows_at = [&](int i, int (&row)[FR]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < FR; ++j) {
-            row[j] = __builtin_amdgcn_readfirstlane(a.frames[min(i + j, hi - 1)].x);
-            fp[j] = a.Ef + (size_t)row[j] * H + 8 * (lane >> 4);
-        }
+        for (int j = 0; j < FR; ++j) row[j] = a.frames[min(i + j, hi - 1)].x;
+    };
+    const unsigned foff = 8u * (lane >> 4);
+    auto request = [&](f32x4 (&x)[2], int row, int k) __attribute__((always_inline)) {
+        const float* p = a.Ef + (size_t)row * H + k;
+        x[0] = *(const f32x4*)(p + foff);
+        x[1] = *(const f32x4*)(p + foff + 4);
+    };
+    const int first = lo + FR * wave;
+    if (first >= hi) return;
+    int row[FR], next[FR];
+    f32x4 nx[FR][2];
+    rows_at(first, next);
+#pragma unroll
+    for (int j = 0; j < FR; ++j) {
+        next[j] = __builtin_amdgcn_readfirstlane(next[j]);
+        request(nx[j], next[j], 0);
+    }
+    for (int i = first; i < hi; i += FR * kEwWaves) {
+        int after[FR];
+        rows_at(i + FR * kEwWaves, after);
+#pragma unroll
+        for (int j = 0; j < FR; ++j) row[j] = next[j];
         f32x4 acc[2][FR][NT];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -173,12 +207,14 @@ __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* 
             for (int j = 0; j < FR; ++j)
 #pragma unroll
                 for (int n = 0; n < NT; ++n) acc[h][j][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        f32x4 nx[FR][2];
-#pragma unroll
-        for (int j = 0; j < FR; ++j) { nx[j][0] = *(const f32x4*)fp[j]; nx[j][1] = *(const f32x4*)(fp[j] + 4); }
 #pragma unroll 1
         for (int ks = 0; ks < KS; ++ks) {
-            const int kn = 32 * min(ks + 1, KS - 1);
+            // f of the next step, and in the last one of the next group's first step, is requested a step ahead
+            const bool last = ks + 1 == KS;
+            if (ks == 0) {
+#pragma unroll
+                for (int j = 0; j < FR; ++j) next[j] = __builtin_amdgcn_readfirstlane(after[j]);
+            }
             f32x4 ee[2][2];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -190,8 +226,7 @@ __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* 
 #pragma unroll
             for (int j = 0; j < FR; ++j) {
                 const f32x4 x[2] = {nx[j][0], nx[j][1]};
-                nx[j][0] = *(const f32x4*)(fp[j] + kn);
-                nx[j][1] = *(const f32x4*)(fp[j] + kn + 4);
+                request(nx[j], last ? next[j] : row[j], last ? 0 : 32 * (ks + 1));
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     u32x4 hv;
@@ -209,21 +244,17 @@ __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* 
                 if (NT > 3) __builtin_amdgcn_sched_barrier(0);            // (registers)
             }
         }
+        // states past the last one are past the end of the descriptor, labels past the last one get an offset that is
 #pragma unroll
         for (int j = 0; j < FR; ++j) {
-            if (i + j >= hi) break;
-            float* o = a.w + (size_t)row[j] * fr;
+            const em_buf o = em_make_buf(a.w + (size_t)row[j] * fr + (size_t)q0 * V1, i + j < hi ? 4u * (unsigned)((a.C - q0) * V1) : 0u);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int q = q0 + 16 * h + 4 * (lane >> 4) + r;
-                    if (q < a.C) {
+                for (int r = 0; r < 4; ++r)
 #pragma unroll
-                        for (int n = 0; n < NT; ++n)
-                            if (16 * n + y < V1) o[(size_t)q * V1 + 16 * n + y] = acc[h][j][n][r];
-                    }
-                }
+                    for (int n = 0; n < NT; ++n)
+                        em_store(acc[h][j][n][r], o, (n < NT - 1 ? wOff : wLast) + 64u * n, 4u * (unsigned)((16 * h + r) * V1));
         }
     }
 }
@@ -252,16 +283,6 @@ __global__ __launch_bounds__(64 * kEwWaves) __attribute__((amdgpu_waves_per_eu(2
 // ---- the gradient ---------------------------------------------------------------------------------
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __amdgpu_buffer_rsrc_t em_buf;
-
-__device__ __forceinline__ em_buf em_make_buf(const void* p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ float em_load(em_buf r, unsigned off)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
 __device__ __forceinline__ float em_exp(float x) { return __builtin_amdgcn_exp2f(x * (0.5f * kTwoLog2e)); }
 __device__ __forceinline__ void em_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
