@@ -1,14 +1,18 @@
-// Weights of the shared-embedding function for whole stretches of frames, laid out in memory
+// On-the-fly weights of the shared-embedding function for whole stretches of frames, laid out in memory
 //     w[t][q][y] = sum_k bf16(tanh(f[t][k] + e[q][k])) W[k][y]
-// for the recursions of trigram_kernels.hpp.  See emb.hpp.
+// for the recursions of trigram_kernels.hpp, and the gradients of f, e and W from the vectors that those leave.
 //
-// Nothing here is serial, so the hidden vectors, of which there are H / (V+1) for every arc, are formed at the
-// rate of the vector ALU, in the registers of the lane that feeds them to the matrix cores:
-//   tanh(f + e) = 1 - 2 / (1 + e^2f e^2e),
-// with e^2f and e^2e formed once per element of f and e, is a product and a sum in one instruction, one
-// reciprocal and one more instruction.  Both factors are held within e^+-80: where |f| or |e| is above 40 and
-// the other is below 30 the sum saturates just the same; where both f and e have values above 30 (no such sum need
-// saturate) the kernels take the exponential of each sum (`wide`).
+// The kernels of fused_kernels.hpp form the hidden vectors inside the chain of the recursion, three times, and send
+// them through LDS.  Here nothing but the recursion (2.1 us a frame) is serial: the hidden units, of which there are H / (V+1)
+// for every arc, are formed at the rate of the vector ALU by the whole chip, in the registers of the lane that feeds them to
+// the matrix cores, once for the weights and once for the gradients.  4 bytes an arc are written and read twice: 5 % of the
+// time.  16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 10.8 ms (weights 1.9, recursions 2.2,
+// gradients 6.1); distance of 4 items, 1000 frames, 64 labels 7.4 -> 3.95 ms (weights 2.3, recursions 1.6).
+//
+// In the weights tanh(f + e) = 1 - 2 / (1 + e^2f e^2e), with e^2f and e^2e formed once per element of f and e, is a product
+// and a sum in one instruction, one reciprocal and one more instruction.  Both factors are held within e^+-80: where |f| or
+// |e| is above 40 and the other is below 30 the sum saturates just the same; where both f and e have values above 30 (no such
+// sum need saturate) the exponential of each sum is taken (`wide`).
 #include <algorithm>
 #include <mutex>
 #include <set>
@@ -162,7 +166,9 @@ __device__ __forceinline__ void em_store(float x, em_buf r, unsigned voff, unsig
 // in operand order; a wave takes four frames (three with five label tiles) at a time, so that each fragment of W serves
 // eight row tiles of 16, and never meets the others.  A operand: lane l holds hidden units 8 (l / 16) .. + 7 of a step
 // of 32 for state l % 16.
-// Bound: vector ALU (per hidden unit two fused instructions, a reciprocal, half a conversion).
+// Bound: vector ALU (per hidden unit two fused instructions, a reciprocal of twice a plain instruction's time, half a
+// conversion: 1.2 of the 1.9 ms at 16 items, 1024 frames, 32 labels; matrix cores 0.35).  f is requested a step ahead, also
+// across groups of frames (2.04 -> 1.89 ms; with five label tiles 2.56 -> 2.32).  LDS operands a step ahead gained nothing.
 template <int NT, bool WIDE>
 __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* Es, const bf16x8* Ws, int tile, int lo, int hi)
 {
@@ -379,7 +385,11 @@ __global__ __launch_bounds__(256) void emb_cells_kernel(EmbArgs a, EmbNumArgs n)
 // transcendental instructions): 1 - h^2 of a unit that rounds the other way is off by up to 2^-7, and where one state holds
 // most of a frame's weight that is 1.6e-3 of an element of df.  (In the weights the same unit moves a sum of H
 // by 2^-9 W: there the product of exponentials does, at 2.9e-5.)
-// Sums over states and over frames leave as partial sums for emb_sum_kernel: no atomics.
+// Sums over states and over frames leave as partial sums for emb_sum_kernel.
+// Bound: vector ALU, 13 instructions and two transcendental ones a hidden unit, 4.0 of 6.1 ms at 16 items, 1024 frames, 32 labels,
+// 512 hidden units (matrix cores 0.9); two waves a SIMD (256 registers) leave the rest as waits for LDS.  Every load is issued on
+// every path, so that the waits are counted (with a condition around the cells' loads 6.9 ms); all LDS reads of a frame ahead
+// of the hidden units spilled (6.3 to 6.9).  Two frames between barriers up to 32 labels 6.2 -> 6.1.
 template <int NW, int KY>
 struct EmGradLds {
     static constexpr int S1 = 16 * KY + 8;         // row strides (bf16): 16-byte reads of 8 lanes fall on different banks

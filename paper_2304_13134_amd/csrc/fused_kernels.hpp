@@ -1,3 +1,8 @@
+// The kernels of the on-the-fly path that never hold more than the weights of a frame or two: for calls with
+// LAST_OPT_FUSED_KEEP_MARGINALS = 0, workspaces that hold no weights (the static one), items of more than 8 GiB of weights and
+// contexts of fewer than three labels.  Everything else lays the weights out in memory (emb_kernels.hip), which is 1.8 to 7
+// times faster.
+//
 // Trigram (context size 2) lattice with arc weights computed on the fly
 // (arXiv 2304.13134, Section 4.1: weights are produced frame by frame during
 // the topological visit and never stored), for the shared-embedding weight

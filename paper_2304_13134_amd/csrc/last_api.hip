@@ -878,7 +878,7 @@ last_status_t emb_run(const Shape& s, const last_weights_t* wt, const int* lengt
                       int* item_status, void* ws, hipStream_t st, const EmbNumArgs* num, hipEvent_t num_ready)
 {
     Shape sl;
-    emb_slice(s, wt, &sl);
+    if (!emb_slice(s, wt, &sl)) return LAST_ERR_WORKSPACE;      // (an option was changed since the workspace was looked at)
     const int per = sl.B;
     const EmbPlan p = emb_plan(sl.B, sl.T, sl.C, sl.V, wt->hidden);
     const TriPlan tp = tri_plan(sl, LAST_WEIGHTS_DENSE, false);
