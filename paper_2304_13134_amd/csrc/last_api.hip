@@ -664,9 +664,9 @@ TriPlan tri_plan(const Shape& s, int kind, bool trop)
     if (!best.ok) consider(1, Tri1());
     if (!best.ok) consider(2, Tri2());
     consider(3, Tri3());
-    // two labels a workgroup, one direction of an item on an XCD, against four, both directions on it: 2.3 to 4.3 against 3.1 to
-    // 5.2 us a frame with 45 to 60 labels (posteriors of 4 items, 60 labels, 200 frames 1043 -> 898 us, distance 389 -> 309),
-    // but half as many items at a time (8 items 1431 / 1754 us, 24 items of 64 labels, 100 frames 2494 / 2969)
+    // two labels a workgroup, one direction of an item on an XCD, against four, both directions on it: posteriors of 4 items, 60
+    // labels, 200 frames 898 / 1043 us, distance 309 / 389, of 2 items, 45 labels, 100 frames 121 / 173; but half as many items
+    // at a time: posteriors of 8 items 1754 / 1431 us, of 24 items, 64 labels, 100 frames 2969 / 2494
     if (!best.ok) consider(5, Tri5());
     if (!best.ok || best.dims == 5) consider(4, Tri4());
     return best;
