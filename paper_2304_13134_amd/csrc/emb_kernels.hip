@@ -6,8 +6,8 @@
 // them through LDS.  Here nothing but the recursion (2.1 us a frame) is serial: the hidden units, of which there are H / (V+1)
 // for every arc, are formed at the rate of the vector ALU by the whole chip, in the registers of the lane that feeds them to
 // the matrix cores, once for the weights and once for the gradients.  4 bytes an arc are written and read twice: 5 % of the
-// time.  16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 10.9 ms (weights 1.9, recursions 2.2,
-// gradients 6.1); distance of 4 items, 1000 frames, 64 labels 7.4 -> 3.94 ms (weights 2.3, recursions 1.6).
+// time.  16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 11.75 ms (weights 1.9, recursions 2.2,
+// gradients 7.0); distance of 4 items, 1000 frames, 64 labels 7.4 -> 3.94 ms (weights 2.3, recursions 1.6).
 //
 // In the weights tanh(f + e) = 1 - 2 / (1 + e^2f e^2e), with e^2f and e^2e formed once per element of f and e, is a product
 // and a sum in one instruction, one reciprocal and one more instruction.  Both factors are held within e^+-80: where |f| or
@@ -374,7 +374,9 @@ __global__ __launch_bounds__(256) void emb_cells_kernel(EmbArgs a, EmbNumArgs n)
 // Chain of the arc marginals through the weight function.  With h = bf16(tanh(f_t + e_q)) and g the marginals (minus
 // those of the intersected lattice),
 //   dW[k][y] += h[k] g[q][y],   d[q][k] = (sum_y g[q][y] W[k][y]) (1 - h[k]^2),   de[q] += d[q],   df[t] += sum_q d[q]
-// (the rounding of h is the identity when differentiating; g enters the matrix cores as two bf16 halves, 16 bits).
+// (the rounding of h is the identity when differentiating).  g enters the matrix cores as two bf16 parts, 16 bits, and as three,
+// all 24, where an intersected lattice is subtracted: its marginals are near 1 on a few arcs, so that 16 bits of them showed
+// (error of df five times that of float32 arithmetic).
 // One workgroup: 32 states, all hidden units (64 a wave), a stretch of the frame list.  d comes out of the matrix cores
 // with lane l holding hidden unit l % 32 for 16 of the 32 states; h is formed for just these, so e and de stay in
 // registers for all frames, f is one value a lane, and the same registers, read as an operand whose contraction runs
@@ -389,24 +391,27 @@ __global__ __launch_bounds__(256) void emb_cells_kernel(EmbArgs a, EmbNumArgs n)
 // Bound: vector ALU, 13 instructions and two transcendental ones a hidden unit, 4.0 of 6.1 ms at 16 items, 1024 frames, 32 labels,
 // 512 hidden units (matrix cores 0.9); two waves a SIMD (256 registers) leave the rest as waits for LDS.  Every load is issued on
 // every path, so that the waits are counted (with a condition around the cells' loads 6.9 ms); all LDS reads of a frame ahead
-// of the hidden units spilled (6.3 to 6.9).  Two frames between barriers up to 32 labels 6.2 -> 6.1.
-template <int NW, int KY>
+// of the hidden units spilled (6.3 to 6.9).  Two frames between barriers up to 32 labels 6.2 -> 6.1.  In a loss the third part
+// and de put away with dW cost 8 % of the call (10.85 -> 11.75 ms; 4x400 frames, 64 labels 6.6 -> 7.2); operands of the third
+// part read where they are used, or the small parts first, 11.85 to 11.95.
+template <int NW, int KY, bool NUM>
 struct EmGradLds {
+    static constexpr int P = NUM ? 3 : 2;          // bf16 parts of a marginal
     static constexpr int S1 = 16 * KY + 8;         // row strides (bf16): 16-byte reads of 8 lanes fall on different banks
     static constexpr int S2 = 40;
     static constexpr int NT = KY / 2;              // tiles of 32 labels
     static constexpr int FP = KY == 2 ? 2 : 1;     // frames between two barriers
-    __bf16 g1[2 * FP][2][32 * S1];                 // [buffer][half][state][label - 1]
-    __bf16 g2[2 * FP][2][32 * NT * S2];            // [buffer][half][label - 1][state in operand order]
+    __bf16 g1[2 * FP][P][32 * S1];                 // [buffer][part][state][label - 1]
+    __bf16 g2[2 * FP][P][32 * NT * S2];            // [buffer][part][label - 1][state in operand order]
     float g0[2 * FP][32];                          // empty label
-    float num[2 * FP][32 * (16 * KY + 1)];         // marginals of the intersected lattice [state][label]
+    float num[NUM ? 2 * FP : 1][32 * (16 * KY + 1)];   // marginals of the intersected lattice [state][label]
 };
 
 template <int NW, int KY, bool NUM>
-__device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArgs& g, EmGradLds<NW, KY>& s, int tile, int grp, int lo, int hi)
+__device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArgs& g, EmGradLds<NW, KY, NUM>& s, int tile, int grp, int lo, int hi)
 {
-    typedef EmGradLds<NW, KY> S;
-    constexpr int NT = S::NT, S1 = S::S1, S2 = S::S2, FP = S::FP;
+    typedef EmGradLds<NW, KY, NUM> S;
+    constexpr int NT = S::NT, S1 = S::S1, S2 = S::S2, FP = S::FP, P = S::P;
     constexpr int LPR = 2 * NW;                             // lanes of a row when the marginals are formed
     constexpr int NS = (16 * KY + 1 + LPR - 1) / LPR;       // labels of such a lane
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -494,11 +499,13 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
                 if (y == 0) {
                     s.g0[buf][gr] = v;
                 } else {
-                    const __bf16 hb = (__bf16)v, lb = (__bf16)(v - (float)hb);
-                    s.g1[buf][0][gr * S1 + y - 1] = hb;
-                    s.g1[buf][1][gr * S1 + y - 1] = lb;
-                    s.g2[buf][0][(y - 1) * S2 + pos] = hb;
-                    s.g2[buf][1][(y - 1) * S2 + pos] = lb;
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        const __bf16 part = (__bf16)v;
+                        v -= (float)part;
+                        s.g1[buf][p][gr * S1 + y - 1] = part;
+                        s.g2[buf][p][(y - 1) * S2 + pos] = part;
+                    }
                 }
             }
         }
@@ -547,16 +554,15 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
 #pragma unroll
             for (int ky = 0; ky < KY; ++ky)
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
+                for (int p = 0; p < P; ++p) {
                     const bf16x8 gv = *(const bf16x8*)&s.g1[buf][p][(lane & 31) * S1 + 16 * ky + 8 * half];
                     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gv, wt[kt][ky], d, 0, 0, 0);
                 }
-            bf16x8 g2v[4];
+            bf16x8 g2v[2 * P];                              // (d is on the matrix cores while h is formed)
             if (KY == 2) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) g2v[k] = *(const bf16x8*)&s.g2[buf][k & 1][(lane & 31) * S2 + 16 * (k >> 1) + 8 * half];
+                for (int k = 0; k < 2 * P; ++k) g2v[k] = *(const bf16x8*)&s.g2[buf][k % P][(lane & 31) * S2 + 16 * (k / P) + 8 * half];
             }
-                          // (d is on the matrix cores while h is formed)
             u32x4 hp[2];                                    // h of the 16 states, bf16, operand order
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
@@ -566,18 +572,17 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
                 const f32x2 p = {em_tanh(f[kt] + e0), em_tanh(f[kt] + e1)};
                 hp[r >> 3][(r & 7) >> 1] = __builtin_bit_cast(unsigned, __builtin_convertvector(p, bf16x2));
             }
-            
 #pragma unroll
             for (int n = 0; n < NT; ++n)
 #pragma unroll
                 for (int st = 0; st < 2; ++st)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const bf16x8 gv = KY == 2 ? g2v[2 * st + p] : *(const bf16x8*)&s.g2[buf][p][(32 * n + (lane & 31)) * S2 + 16 * st + 8 * half];
+                    for (int p = 0; p < P; ++p) {
+                        const bf16x8 gv = KY == 2 ? g2v[P * st + p] : *(const bf16x8*)&s.g2[buf][p][(32 * n + (lane & 31)) * S2 + 16 * st + 8 * half];
                         dw[kt][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, hp[st]), gv, dw[kt][n], 0, 0, 0);
                     }
-            
             cs[kt] = 0.f;
+            float h0 = 0.f;                                 // (a sum of its own: dw0 grows over many frames)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const unsigned pair = hp[r >> 3][(r & 7) >> 1];
@@ -585,11 +590,11 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
                 const float u = fmaf(-h, h, 1.f);
                 de[kt][r] = fmaf(d[r], u, de[kt][r]);
                 cs[kt] = fmaf(d[r], u, cs[kt]);
-                dw0[kt] = fmaf(h, z[r >> 2][r & 3], dw0[kt]);
+                h0 = fmaf(h, z[r >> 2][r & 3], h0);
             }
+            dw0[kt] += h0;
             // (the sums are not put off to the end of the frame, where h and d of both halves would still be needed)
             asm volatile("" : "+v"(de[kt]), "+v"(dw0[kt]), "+v"(cs[kt]));
-            
         }
         // sum over the 32 states: lanes of the other half hold the other 16; half 0 stores k0, half 1 k0 + 32
         const float send = half ? cs[0] : cs[1], keep = half ? cs[1] : cs[0];
@@ -597,7 +602,8 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         if (live) g.pdf[((size_t)tile * a.B * a.T + v.x) * H + k0 + 32 * half] = sum;
     };
 
-    // dW so far -> the partial sums of this workgroup
+    float* pde = g.pde + ((size_t)grp * a.tiles * kEmTile + q0 + 4 * half) * H + k0;
+    // dW so far, and de of a loss -> the partial sums of this workgroup
     auto flush = [&](bool first) __attribute__((always_inline)) {
         float* o = g.pdw + ((size_t)(grp * a.tiles + tile) * H + 64 * wave) * V1;
         // (no other workgroup adds to them; an addition in the L2 needs no register for the old value)
@@ -618,6 +624,11 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
             const float z0 = dw0[kt] + __shfl_xor(dw0[kt], 32);
             if (half == 0) add(o + (size_t)(32 * kt + lane) * V1, z0);
             dw0[kt] = 0.f;
+            if (NUM) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) add(pde + (size_t)((r & 3) + 8 * (r >> 2)) * H + 32 * kt, de[kt][r]);
+                de[kt] = f32x16{};
+            }
         }
     };
 
@@ -665,7 +676,7 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         em_lds_barrier();
         // the frames from i on are used; the marginals of those after them are formed, the requests for the next ones
         // go out and their cells are added up.  dW is put away every 64 frames: a sum over a thousand frames of values
-        // of which a few are near 1 and most near 1e-4 loses 2.4e-6 of it.
+        // of which a few are near 1 and most near 1e-4 loses 2.4e-6 of it.  So is de of a loss.
         for (int i = lo; i < hi;) {
             for (const int end = min(i + 64, hi); i < end; i += FP) {
                 const int cur = (i - lo) & FP ? FP : 0, nxt = FP - cur;
@@ -700,19 +711,20 @@ __device__ __forceinline__ void emb_grad_body(const EmbArgs& a, const EmbGradArg
         }
     }
     if (lo >= hi) flush(true);
+    if (NUM) return;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            g.pde[((size_t)grp * a.tiles * kEmTile + q0 + (r & 3) + 8 * (r >> 2) + 4 * half) * H + k0 + 32 * kt] = de[kt][r];
+        for (int r = 0; r < 16; ++r) pde[(size_t)((r & 3) + 8 * (r >> 2)) * H + 32 * kt] = de[kt][r];
 }
 
 template <int NW, int KY, bool NUM>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW > 4 ? 2 : 1, 2))) void emb_grad_kernel(EmbArgs a, EmbGradArgs g)
 {
     extern __shared__ __align__(16) unsigned char em_smem[];
-    EmGradLds<NW, KY>& s = *(EmGradLds<NW, KY>*)em_smem;
-    for (int i = threadIdx.x; i < (int)(sizeof(s) / 4); i += 64 * NW) ((int*)em_smem)[i] = 0;
+    typedef EmGradLds<NW, KY, NUM> S;
+    S& s = *(S*)em_smem;
+    for (int i = threadIdx.x; i < (int)(sizeof(S) / 4); i += 64 * NW) ((int*)em_smem)[i] = 0;
     const int tile = blockIdx.x % a.tiles, grp = blockIdx.x / a.tiles;
     const long long n = a.count[0];
     const int lo = (int)(n * grp / g.ngr), hi = (int)(n * (grp + 1) / g.ngr);
@@ -855,12 +867,19 @@ hipError_t emb_launch_gradient(const EmbArgs& a, const EmbGradArgs& g, hipStream
 {
     const size_t rows = (size_t)a.B * a.T;
     hipLaunchKernelGGL(emb_norm_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, a, g);
-    auto go = [&](auto NW, auto KY) {
+    hipError_t e = hipSuccess;
+    auto launch = [&](auto NW, auto KY, auto NUM) {
         constexpr int nw = decltype(NW)::value, ky = decltype(KY)::value;
-        constexpr size_t lds = sizeof(EmGradLds<nw, ky>);
-        static_assert(lds <= 64 * 1024, "no attribute needed");
-        if (g.pn) hipLaunchKernelGGL(HIP_KERNEL_NAME(emb_grad_kernel<nw, ky, true>), dim3(a.tiles * g.ngr), dim3(64 * nw), lds, st, a, g);
-        else hipLaunchKernelGGL(HIP_KERNEL_NAME(emb_grad_kernel<nw, ky, false>), dim3(a.tiles * g.ngr), dim3(64 * nw), lds, st, a, g);
+        constexpr bool num = decltype(NUM)::value;
+        constexpr size_t lds = sizeof(EmGradLds<nw, ky, num>);
+        static_assert(2 * lds <= 160 * 1024, "two workgroups of few waves a compute unit");
+        auto k = emb_grad_kernel<nw, ky, num>;
+        e = em_allow_lds((const void*)k, lds);
+        if (e == hipSuccess) hipLaunchKernelGGL(k, dim3(a.tiles * g.ngr), dim3(64 * nw), lds, st, a, g);
+    };
+    auto go = [&](auto NW, auto KY) {
+        if (g.pn) launch(NW, KY, std::true_type());
+        else launch(NW, KY, std::false_type());
     };
     auto steps = [&](auto NW) {
         if (grad_steps(a.V) == 2) go(NW, std::integral_constant<int, 2>());
@@ -872,6 +891,7 @@ hipError_t emb_launch_gradient(const EmbArgs& a, const EmbGradArgs& g, hipStream
     case 6: steps(std::integral_constant<int, 6>()); break;
     default: steps(std::integral_constant<int, 8>()); break;
     }
+    if (e != hipSuccess) return e;
     const unsigned nbf = (unsigned)((rows * (a.H / 4) + 255) / 256), nbe = (unsigned)(((size_t)a.C * (a.H / 4) + 255) / 256);
     const unsigned nbw = (unsigned)((a.H * (a.V + 1) + 31) / 32);
     hipLaunchKernelGGL(emb_sum_kernel, dim3(nbf + nbe + nbw), dim3(256), 0, st, a, g, (int)nbf, (int)nbe);
