@@ -132,7 +132,8 @@ __global__ __launch_bounds__(256) void emb_prepare_kernel(EmbArgs a, size_t nf, 
     if (blockIdx.x == 0 && threadIdx.x == 0) a.wide[0] = wide;
     auto value = [&](float x) __attribute__((always_inline)) {
         const float c = fminf(fmaxf(x, -kEmClamp), kEmClamp);
-        return wide || x != x ? x : __builtin_amdgcn_exp2f(c * kTwoLog2e);
+        // (rounded once: with the exponential of a rounded product the tanh of large f and e was off by 6e-7)
+        return wide || x != x ? x : (float)exp(2.0 * (double)c);
     };
     auto fill = [&](const unsigned* src, float* dst, size_t n, size_t n_pad) {
         for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_pad / 8; i += (size_t)gridDim.x * 256) {
@@ -386,7 +387,8 @@ __global__ __launch_bounds__(256) void emb_cells_kernel(EmbArgs a, EmbNumArgs n)
 // The hidden units are rounded here exactly as the numerator's kernels round theirs (em_tanh of the sum, two
 // transcendental instructions): 1 - h^2 of a unit that rounds the other way is off by up to 2^-7, and where one state holds
 // most of a frame's weight that is 1.6e-3 of an element of df.  (In the weights the same unit moves a sum of H
-// by 2^-9 W: there the product of exponentials does, at 2.9e-5.)
+// by 2^-9 W: there the product of exponentials does.  Of units above 2^-8, sigma 1 and 0.5, 2.7e-6 round the other way than in 64
+// bits, 2.9e-6 with the exponential of the sum; of the smaller ones 5e-5 and 2e-6.)
 // Sums over states and over frames leave as partial sums for emb_sum_kernel.
 // Bound: vector ALU, 13 instructions and two transcendental ones a hidden unit, 4.0 of 6.1 ms at 16 items, 1024 frames, 32 labels,
 // 512 hidden units (matrix cores 0.9); two waves a SIMD (256 registers) leave the rest as waits for LDS.  Every load is issued on

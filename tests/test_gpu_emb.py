@@ -47,6 +47,27 @@ def workloads_round(x):
     return oracle_float(workloads.to_bf16_bits(x.astype(np.float32)))
 
 
+def test_hidden_units_of_sums_that_cancel():
+    """tanh(f + e) of large f and e whose sum is 0.  e^2f and e^2e are rounded once each, so that their product is within
+    2^-23 of 1; 1 more is 2, or 2 - 2^-23, in float32, and the tanh 0 or -2^-24.  Weights are such tanh times 64, 128 times,
+    in every label but the empty one."""
+    announce("sums that cancel")
+    B, T, V, H = 16, 8, 3, 128
+    C = 1 + V + V * V
+    c = torch.linspace(2.5, 29.5, B, device="cuda").bfloat16()
+    worst = 0.0
+    for b in range(B):                                  # (e is shared by the items of a call)
+        f = c[b].expand(1, T, H).contiguous()
+        e = (-c[b]).expand(C, H).contiguous()
+        W = torch.full((H, V + 1), 64.0, device="cuda").bfloat16()
+        W[:, 0] = 0.0
+        dist, _ = lb.last_arc_posteriors(lb.SharedEmb(f, e, W), torch.tensor([T], dtype=torch.int32, device="cuda"), order=2)
+        worst = max(worst, abs(float(dist) / T - float(np.log(V + 1.0))))
+    print("worst", worst, flush=True)
+    # d log(1 + V e^w) = V / (V + 1) w for w = 64 H h
+    assert worst <= V / (V + 1.0) * 64 * H * 2.0 ** -24, worst
+
+
 def test_batch_in_slices_returns_what_its_items_return_alone():
     """Three items of which two fit the weights kept at a time: distances and df bit for bit those of calls with one
     item each, de and dW their sum."""
