@@ -60,7 +60,8 @@ __device__ __forceinline__ float em_tanh(float f, float e)
     return fmaf(-2.f, __builtin_amdgcn_rcpf(d), 1.f);
 }
 
-// f and e looked over for large values; W repacked as operand fragments, lane l of (ks, nt):
+// f (of the frames that exist: what lies behind an item's end has no part in the results) and e looked over for large
+// values; W repacked as operand fragments, lane l of (ks, nt):
 //   Wn[ks][nt][l] = W[32 ks + 8 (l / 16) + j][16 nt + l % 16],
 //   Wt[ht][ky][l] = W[32 ht + l % 32][16 ky + 8 (l / 32) + j + 1],       j = 0..7, zero outside W;
 // the list of the frames that exist (item by item)
@@ -69,16 +70,25 @@ __global__ __launch_bounds__(256) void emb_scan_kernel(EmbArgs a, size_t nf, siz
     __shared__ int s_or[4];
     __shared__ int s_sum[4];
     const int tid = threadIdx.x;
-    auto large = [&](const unsigned* p, size_t n) {
+    auto large = [&](const unsigned* p, size_t n, auto&& counts) {
         bool big = false;
+#pragma unroll 4
         for (size_t i = (size_t)blockIdx.x * 256 + tid; i < n; i += (size_t)kEmScan * 256) {
             const u32x4 v = ((const u32x4*)p)[i];
+            bool l = false;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) big = big || fabsf(bf_lo(v[j])) > kEmLarge || fabsf(bf_hi(v[j])) > kEmLarge;
+            for (int j = 0; j < 4; ++j) l = l | (fabsf(bf_lo(v[j])) > kEmLarge) | (fabsf(bf_hi(v[j])) > kEmLarge);
+            big = big | (l & counts((unsigned)i));           // (fewer than 2^32 pieces: 8 GiB hold the weights of their frames)
         }
         return big;
     };
-    const int flags = (large((const unsigned*)a.f, nf / 8) ? 1 : 0) | (large((const unsigned*)a.e, ne / 8) ? 2 : 0);
+    auto frame_exists = [&](unsigned i) {
+        const unsigned row = i / (unsigned)(a.H / 8), b = row / (unsigned)a.T;
+        const int L = a.len[b];
+        return L <= a.T && (int)(row - b * (unsigned)a.T) < L;
+    };
+    const int flags = (large((const unsigned*)a.f, nf / 8, frame_exists) ? 1 : 0)
+                      | (large((const unsigned*)a.e, ne / 8, [](unsigned) { return true; }) ? 2 : 0);
     const int any = (__any(flags & 1) ? 1 : 0) | (__any(flags & 2) ? 2 : 0);
     if ((tid & 63) == 0) s_or[tid >> 6] = any;
     const __bf16* W = (const __bf16*)a.W;

@@ -47,6 +47,28 @@ def workloads_round(x):
     return oracle_float(workloads.to_bf16_bits(x.astype(np.float32)))
 
 
+@pytest.mark.parametrize("fill", [50.0, float("inf")])
+def test_frames_past_the_end_have_no_part_in_the_results(fill):
+    """Large values of e, and large ones of f only behind the ends of the items: the same bits as with zeros there."""
+    announce("frames past the end", fill)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    B, T, V, H = 3, 40, 20, 128
+    C = 1 + V + V * V
+    f = torch.randn((B, T, H), generator=g, device="cuda")
+    e = 0.5 * torch.randn((C, H), generator=g, device="cuda")
+    e[:, ::8] = 35.0
+    W = (torch.randn((H, V + 1), generator=g, device="cuda") / H ** 0.5).bfloat16()
+    lengths = torch.tensor([T, 25, 0], dtype=torch.int32, device="cuda")
+    got = []
+    for x in (0.0, fill):
+        f[1, 25:], f[2] = x, x
+        dist, grads = lb.last_arc_posteriors(lb.SharedEmb(f.bfloat16(), e.bfloat16(), W), lengths, order=2)
+        got.append((dist, *grads))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 def test_hidden_units_of_sums_that_cancel():
     """tanh(f + e) of large f and e whose sum is 0.  e^2f and e^2e are rounded once each, so that their product is within
     2^-23 of 1; 1 more is 2, or 2 - 2^-23, in float32, and the tanh 0 or -2^-24.  Weights are such tanh times 64, 128 times,
