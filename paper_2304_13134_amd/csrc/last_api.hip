@@ -619,7 +619,7 @@ struct TriPlan {
 // workgroups of 8 waves, two of them exchanging (128 states a workgroup), or of 16 and four (256)
 typedef TriDims<8, 2, 2, 5> Tri0;       // up to 19 labels
 typedef TriDims<8, 2, 3, 9> Tri1;       // up to 35
-typedef TriDims<8, 2, 4, 11> Tri2;      // up to 42 (43: three labels a workgroup no longer fit)
+typedef TriDims<8, 2, 4, 11> Tri2;      // up to 42, 43 with two labels a workgroup instead of three
 typedef TriDims<16, 4, 3, 9> Tri3;      // up to 35
 typedef TriDims<16, 4, 6, 17> Tri4;     // up to 64
 typedef TriDims<8, 2, 6, 17> Tri5;      // up to 64, two labels a workgroup
@@ -664,11 +664,13 @@ TriPlan tri_plan(const Shape& s, int kind, bool trop)
     if (!best.ok) consider(1, Tri1());
     if (!best.ok) consider(2, Tri2());
     consider(3, Tri3());
-    // two labels a workgroup, one direction of an item on an XCD, against four, both directions on it: posteriors of 4 items, 60
-    // labels, 200 frames 898 / 1043 us, distance 309 / 389, of 2 items, 45 labels, 100 frames 121 / 173; but half as many items
-    // at a time: posteriors of 8 items 1754 / 1431 us, of 24 items, 64 labels, 100 frames 2969 / 2494
+    // two labels a workgroup (43 labels and more), one direction of an item on an XCD, against four, both directions on it:
+    // posteriors of 4 items, 60 labels, 200 frames 898 / 1043 us, distance 309 / 389, of 2 items, 45 labels, 100 frames 121 / 173;
+    // but half as many items at a time: posteriors of 8 items 1754 / 1431 us, of 24 items, 64 labels, 100 frames 2969 / 2494, of
+    // 8 items, 43 labels, 60 frames 305 / 252.  Shortest paths, 60 frames, where as many rounds are needed: 44 labels, 1 item
+    // 147 / 173 us, 8 items 150 / 176, 64 labels 200 / 213, 256 / 281; where more are, 43 labels, 9 items 221 / 174
     if (!best.ok) consider(5, Tri5());
-    if (!best.ok || best.dims == 5) consider(4, Tri4());
+    if (!best.ok || best.nb < 3) consider(4, Tri4());
     return best;
 }
 

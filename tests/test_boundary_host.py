@@ -57,6 +57,20 @@ def test_workspace_bytes_and_context_validation(lib):
     assert lb.last_workspace_bytes(_wt(), lb.LastContext(3, 3, 40), 0) == 0
 
 
+@pytest.mark.parametrize("V", range(36, 65))
+def test_eight_items_of_a_dense_trigram_go_through_at_once(lib, V):
+    """The exchange area of the cooperating workgroups holds two slots of V^2 + V states and at most 64 headers for each
+    direction of every item that is worked on at a time: no label count may take a batch of eight in two rounds."""
+    T, C = 10, 1 + V + V * V
+    for B in (8, 24):
+        total = lb.last_workspace_bytes(_wt(B=B, T=T), lb.context(V, 2), lb.OP_ARC_POSTERIORS)
+        up = lambda n: (n + 255) // 256 * 256
+        rows = B * (T + 1)
+        area = total - 2 * up(rows * C * 4) - 2 * up(rows * 8) - up(B * 8) - up(B * 4)
+        at_a_time = area / 8 / (2 * 2 * (V * V + V))
+        assert 8 <= at_a_time < 9, (B, at_a_time)
+
+
 def test_argument_errors_are_reported_before_any_launch(lib):
     cx = lb.context(3, 1)
     wt = _wt()

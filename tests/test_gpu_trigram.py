@@ -192,7 +192,7 @@ def test_distance_of_a_batch_in_slices(order, V, C, B):
 
 # clusters of 22 to 32 workgroups, the two directions of an item on two XCDs (up to four items); with more items both
 # directions on one XCD again
-@pytest.mark.parametrize("V,T,B", [(43, 6, 4), (51, 5, 3), (63, 4, 1), (64, 5, 4), (47, 4, 5), (64, 3, 9)])
+@pytest.mark.parametrize("V,T,B", [(43, 6, 4), (43, 4, 9), (51, 5, 3), (63, 4, 1), (64, 5, 4), (47, 4, 5), (64, 3, 9)])
 def test_directions_on_two_xcds(V, T, B):
     announce("clustered trigram, directions apart", V, T, B)
     cfg = workloads.dense(B=B, T=T, V=V, order=2, sigma=1.5, seed=300 + V, len_lo=1, len_hi=T)
