@@ -10,18 +10,21 @@ namespace last {
 
 constexpr int kEmTile = 32;          // states of a tile
 constexpr int kEmMaxLabelTiles = 5;  // V + 1 <= 80 in tiles of 16
-constexpr int kEmScan = 256;         // workgroups that look over f and e
+constexpr int kEmScan = 1024;        // workgroups that go over f and e
 
 struct EmbArgs {
     const void *f, *e, *W;           // bfloat16 [B][T][H], [C][H], [H][V+1]
     const int* len;
-    float *Ef, *Ee;                  // [B T][H], [tiles 32][H]: e^2f, e^2e (wide inputs: f, e themselves)
+    float *Ef, *Ee;                  // [B T][H], [tiles 32][H]: e^2f, e^2e
     void* Wn;                        // W as operand fragments of the weights
     void* Wt;                        // W transposed as operand fragments of the gradient
     int2* frames;                    // (row b T + t, item b) of the frames that exist, item by item
     int* count;                      // how many
-    int *big, *wide;                 // per scanning workgroup: large values in f (1), in e (2); 1: in both
+    int* big;                        // per such workgroup: large values in f (1), in e (2)
     float* w;                        // [B][T][C][V+1]
+    unsigned long long* x;           // exchange area and flags of the recursions, cleared on the way
+    size_t xwords;
+    int* fail;
     int B, T, C, V, H;
     int tiles;                       // ceil(C / 32)
     int nch;                         // stretches of frames of the weights kernel

@@ -60,25 +60,39 @@ __device__ __forceinline__ float em_tanh(float f, float e)
     return fmaf(-2.f, __builtin_amdgcn_rcpf(d), 1.f);
 }
 
-// f (of the frames that exist: what lies behind an item's end has no part in the results) and e looked over for large
-// values; W repacked as operand fragments, lane l of (ks, nt):
-//   Wn[ks][nt][l] = W[32 ks + 8 (l / 16) + j][16 nt + l % 16],
-//   Wt[ht][ky][l] = W[32 ht + l % 32][16 ky + 8 (l / 32) + j + 1],       j = 0..7, zero outside W;
-// the list of the frames that exist (item by item)
-__global__ __launch_bounds__(256) void emb_scan_kernel(EmbArgs a, size_t nf, size_t ne, int NT)
+// What the other kernels start from, in one launch (a call of a few frames is launches for the most part):
+//   e^2f, e^2e, and whether f (of the frames that exist: what lies behind an item's end has no part in the results) and e
+//   have large values;
+//   W repacked as operand fragments, lane l of (ks, nt):
+//     Wn[ks][nt][l] = W[32 ks + 8 (l / 16) + j][16 nt + l % 16],
+//     Wt[ht][ky][l] = W[32 ht + l % 32][16 ky + 8 (l / 32) + j + 1],       j = 0..7, zero outside W;
+//   the list of the frames that exist (item by item);
+//   the cleared exchange area and flags of the recursions.
+__global__ __launch_bounds__(256) void emb_prepare_kernel(EmbArgs a, size_t nf, size_t ne, size_t ne_pad, int NT)
 {
     __shared__ int s_or[4];
     __shared__ int s_sum[4];
     const int tid = threadIdx.x;
-    auto large = [&](const unsigned* p, size_t n, auto&& counts) {
+    for (size_t i = (size_t)blockIdx.x * 256 + tid; i < a.xwords; i += (size_t)kEmScan * 256) a.x[i] = ~0ull;
+    for (int i = blockIdx.x * 256 + tid; i < a.B; i += kEmScan * 256) a.fail[i] = 0;
+    auto value = [&](float x) __attribute__((always_inline)) {
+        const float c = fminf(fmaxf(x, -kEmClamp), kEmClamp);
+        // (rounded once: with the exponential of a rounded product the tanh of large f and e was off by 6e-7)
+        return x != x ? x : (float)exp(2.0 * (double)c);
+    };
+    auto fill = [&](const unsigned* src, float* dst, size_t n, size_t n_pad, auto&& counts) {
         bool big = false;
-#pragma unroll 4
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < n; i += (size_t)kEmScan * 256) {
-            const u32x4 v = ((const u32x4*)p)[i];
+#pragma unroll 2
+        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < n_pad / 8; i += (size_t)kEmScan * 256) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (8 * i < n) v = ((const u32x4*)src)[i];
             bool l = false;
 #pragma unroll
             for (int j = 0; j < 4; ++j) l = l | (fabsf(bf_lo(v[j])) > kEmLarge) | (fabsf(bf_hi(v[j])) > kEmLarge);
             big = big | (l & counts((unsigned)i));           // (fewer than 2^32 pieces: 8 GiB hold the weights of their frames)
+            float4* d = (float4*)(dst + 8 * i);
+            d[0] = make_float4(value(bf_lo(v[0])), value(bf_hi(v[0])), value(bf_lo(v[1])), value(bf_hi(v[1])));
+            d[1] = make_float4(value(bf_lo(v[2])), value(bf_hi(v[2])), value(bf_lo(v[3])), value(bf_hi(v[3])));
         }
         return big;
     };
@@ -87,9 +101,9 @@ __global__ __launch_bounds__(256) void emb_scan_kernel(EmbArgs a, size_t nf, siz
         const int L = a.len[b];
         return L <= a.T && (int)(row - b * (unsigned)a.T) < L;
     };
-    const int flags = (large((const unsigned*)a.f, nf / 8, frame_exists) ? 1 : 0)
-                      | (large((const unsigned*)a.e, ne / 8, [](unsigned) { return true; }) ? 2 : 0);
-    const int any = (__any(flags & 1) ? 1 : 0) | (__any(flags & 2) ? 2 : 0);
+    const bool le = fill((const unsigned*)a.e, a.Ee, ne, ne_pad, [](unsigned) { return true; });
+    const bool lf = fill((const unsigned*)a.f, a.Ef, nf, nf, frame_exists);
+    const int any = (__any(lf) ? 1 : 0) | (__any(le) ? 2 : 0);
     if ((tid & 63) == 0) s_or[tid >> 6] = any;
     const __bf16* W = (const __bf16*)a.W;
     const int V1 = a.V + 1, npack = (a.H / 32) * NT * 64;
@@ -133,31 +147,6 @@ __global__ __launch_bounds__(256) void emb_scan_kernel(EmbArgs a, size_t nf, siz
     if (tid == 0) a.big[blockIdx.x] = s_or[0] | s_or[1] | s_or[2] | s_or[3];
 }
 
-// Ef, Ee from f, e
-__global__ __launch_bounds__(256) void emb_prepare_kernel(EmbArgs a, size_t nf, size_t ne, size_t ne_pad)
-{
-    const int m = a.big[threadIdx.x];
-    const int any = (__syncthreads_or(m & 1) ? 1 : 0) | (__syncthreads_or(m & 2) ? 2 : 0);
-    const bool wide = any == 3;
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.wide[0] = wide;
-    auto value = [&](float x) __attribute__((always_inline)) {
-        const float c = fminf(fmaxf(x, -kEmClamp), kEmClamp);
-        // (rounded once: with the exponential of a rounded product the tanh of large f and e was off by 6e-7)
-        return wide || x != x ? x : (float)exp(2.0 * (double)c);
-    };
-    auto fill = [&](const unsigned* src, float* dst, size_t n, size_t n_pad) {
-        for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_pad / 8; i += (size_t)gridDim.x * 256) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (8 * i < n) v = ((const u32x4*)src)[i];
-            float4* d = (float4*)(dst + 8 * i);
-            d[0] = make_float4(value(bf_lo(v[0])), value(bf_hi(v[0])), value(bf_lo(v[1])), value(bf_hi(v[1])));
-            d[1] = make_float4(value(bf_lo(v[2])), value(bf_hi(v[2])), value(bf_lo(v[3])), value(bf_hi(v[3])));
-        }
-    };
-    fill((const unsigned*)a.e, a.Ee, ne, ne_pad);
-    fill((const unsigned*)a.f, a.Ef, nf, nf);
-}
-
 typedef __amdgpu_buffer_rsrc_t em_buf;
 
 __device__ __forceinline__ em_buf em_make_buf(const void* p, unsigned bytes)
@@ -198,6 +187,12 @@ __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* 
     };
     const unsigned foff = 8u * (lane >> 4);
     auto request = [&](f32x4 (&x)[2], int row, int k) __attribute__((always_inline)) {
+        if (WIDE) {
+            const u32x4 v = *(const u32x4*)((const unsigned short*)a.f + (size_t)row * H + k + foff);
+            x[0] = f32x4{bf_lo(v[0]), bf_hi(v[0]), bf_lo(v[1]), bf_hi(v[1])};
+            x[1] = f32x4{bf_lo(v[2]), bf_hi(v[2]), bf_lo(v[3]), bf_hi(v[3])};
+            return;
+        }
         const float* p = a.Ef + (size_t)row * H + k;
         x[0] = *(const f32x4*)(p + foff);
         x[1] = *(const f32x4*)(p + foff + 4);
@@ -287,14 +282,26 @@ __global__ __launch_bounds__(64 * kEwWaves) __attribute__((amdgpu_waves_per_eu(2
     const long long n = a.count[0];
     const int lo = (int)(n * ch / a.nch), hi = (int)(n * (ch + 1) / a.nch);
     if (lo >= hi) return;
+    static_assert(kEmScan == 2 * 64 * kEwWaves, "two words a thread");
+    const int large = a.big[threadIdx.x] | a.big[threadIdx.x + 64 * kEwWaves];
     for (int i = threadIdx.x; i < KS * 256; i += 64 * kEwWaves) {
         const int l = i & 63, g = (i >> 6) & 1, h = (i >> 7) & 1, ks = i >> 8;
         Es[i] = *(const f32x4*)(a.Ee + (size_t)(tile * kEmTile + 16 * h + (l & 15)) * H + 32 * ks + 8 * (l >> 4) + 4 * g);
     }
     for (int i = threadIdx.x; i < KS * NT * 64; i += 64 * kEwWaves) Ws[i] = ((const bf16x8*)a.Wn)[i];
+    const int in_f = __syncthreads_or(large & 1), in_e = __syncthreads_or(large & 2);
+    if (!in_f || !in_e) {
+        emb_weights_body<NT, false>(a, Es, Ws, tile, lo, hi);
+        return;
+    }
+    // both f and e have large values: e itself in the place of its exponentials
+    for (int i = threadIdx.x; i < KS * 256; i += 64 * kEwWaves) {
+        const int l = i & 63, g = (i >> 6) & 1, h = (i >> 7) & 1, ks = i >> 8, q = tile * kEmTile + 16 * h + (l & 15);
+        const unsigned* p = (const unsigned*)a.e + ((size_t)min(q, a.C - 1) * H + 32 * ks + 8 * (l >> 4) + 4 * g) / 2;
+        Es[i] = f32x4{bf_lo(p[0]), bf_hi(p[0]), bf_lo(p[1]), bf_hi(p[1])};
+    }
     __syncthreads();
-    if (a.wide[0]) emb_weights_body<NT, true>(a, Es, Ws, tile, lo, hi);
-    else emb_weights_body<NT, false>(a, Es, Ws, tile, lo, hi);
+    emb_weights_body<NT, true>(a, Es, Ws, tile, lo, hi);
 }
 
 // ---- the gradient ---------------------------------------------------------------------------------
@@ -856,12 +863,11 @@ hipError_t emb_launch_weights(const EmbArgs& a, const EmbPlan& p, hipStream_t st
 {
     const size_t nf = (size_t)a.B * a.T * a.H, ne = (size_t)a.C * a.H, ne_pad = (size_t)a.tiles * kEmTile * a.H;
     const int NT = label_tiles(a.V);
-    hipLaunchKernelGGL(emb_scan_kernel, dim3(kEmScan), dim3(256), 0, st, a, nf, ne, NT);
-    hipLaunchKernelGGL(emb_prepare_kernel, dim3(1024), dim3(256), 0, st, a, nf, ne, ne_pad);
+    hipLaunchKernelGGL(emb_prepare_kernel, dim3(kEmScan), dim3(256), 0, st, a, nf, ne, ne_pad, NT);
     hipError_t e = hipSuccess;
     em_label_tiles(NT, [&](auto N) {
         auto k = emb_weights_kernel<decltype(N)::value>;
-        e = em_allow_lds((const void*)k, 160 * 1024);
+        e = em_allow_lds((const void*)k, 159 * 1024);         // (the barrier's reduction takes a little static LDS)
         if (e == hipSuccess) hipLaunchKernelGGL(k, dim3(a.tiles * a.nch), dim3(64 * kEwWaves), p.lds, st, a);
     });
     return e != hipSuccess ? e : hipGetLastError();

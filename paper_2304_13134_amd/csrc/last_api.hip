@@ -708,9 +708,9 @@ Shape tri_slice(const Shape& s)
 }
 
 last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const float* w, const int* lengths,
-                         bool trop, bool keep, int* bp, hipStream_t st)
+                         bool trop, bool keep, int* bp, hipStream_t st, bool cleared = false)
 {
-    hipLaunchKernelGGL(tri_clear_kernel, dim3(64), dim3(256), 0, st, c.x, c.xwords, c.fail, s.B);
+    if (!cleared) hipLaunchKernelGGL(tri_clear_kernel, dim3(64), dim3(256), 0, st, c.x, c.xwords, c.fail, s.B);
     TriArgs a;
     a.w = w; a.len = lengths; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb;
     a.bp = bp; a.x = c.x; a.fail = c.fail;
@@ -840,8 +840,8 @@ EmbWs carve_emb(Carver& cv, const Shape& sl, const EmbPlan& p, const last_weight
     c.a.frames = cv.take<int2>(BT);
     c.a.count = cv.take<int>(1);
     c.a.big = cv.take<int>(kEmScan);
-    c.a.wide = cv.take<int>(1);
     c.tri = carve_tri(cv, sl, tri_plan(sl, LAST_WEIGHTS_DENSE, false), false, grads);
+    c.a.x = c.tri.x; c.a.xwords = c.tri.xwords; c.a.fail = c.tri.fail;
     if (grads) {
         c.g.alpha = c.tri.alpha; c.g.beta = c.tri.beta; c.g.offa = c.tri.offa; c.g.offb = c.tri.offb;
         c.g.norm = cv.take<EmbNorm>(BT);
@@ -897,7 +897,7 @@ last_status_t emb_run(const Shape& s, const last_weights_t* wt, const int* lengt
         c.a.W = wt->W;
         c.a.len = lengths + b0;
         last_status_t rc = hip(emb_launch_weights(c.a, p, st));
-        if (rc == LAST_OK) rc = launch_tri(sl, tp, c.tri, c.a.w, lengths + b0, false, out != nullptr, nullptr, st);
+        if (rc == LAST_OK) rc = launch_tri(sl, tp, c.tri, c.a.w, lengths + b0, false, out != nullptr, nullptr, st, true);
         if (rc != LAST_OK) return rc;
         launch_tri_join(sl, c.tri, c.a.w, lengths + b0, nullptr, dist + b0, item_status ? item_status + b0 : nullptr, st, out != nullptr);
         if (!out) continue;
