@@ -272,8 +272,8 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
  *     out in the workspace (and partial sums of the gradients, together at most 8 GiB at a time: larger batches
  *     go through in slices of items); 0 = it never holds more than the weights of a frame or two, in the kernels
  *     that single items of more than 8 GiB and contexts of fewer than three labels take, too.
- *     last_workspace_bytes follows the setting: ask again after changing it.  A call whose workspace only holds
- *     what the kernels without weights need takes these.
+ *     last_workspace_bytes follows the setting: ask again after changing it.  A call (distance, posteriors or
+ *     loss) whose workspace only holds what the kernels without weights need, the size asked for with 0, takes these.
  *   LAST_OPT_FUSED_FRAMES_PER_TILE (1 or 2, default 2): frames whose on-the-fly weights the forward
  *     kernel that holds no weights computes at a time (Section 5 discusses evaluating the weight
  *     function for several frames at once).  2 shares the rows of e and the phase barriers between

@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include <atomic>
+#include <cstdint>
 #include <cstdlib>
 #include <mutex>
 #include <set>
@@ -525,6 +526,19 @@ FusedWs carve_fused(Carver& cv, const Shape& s, const FusedPlan& p, bool keep_al
     f.xwords = (size_t)p.ncl * 2 * (s.V + 1) * p.XW;
     f.xb = cv.take<u64>(f.xwords);
     return f;
+}
+
+// Bytes of the kernels that hold no weights.  `most`: where it does not hold the planes of kept marginals, these are left out
+// of the plan (they are recomputed then).
+size_t fused_bytes(const Shape& s, FusedPlan& p, bool grads, size_t most)
+{
+    Carver cv(nullptr);
+    carve_fused(cv, s, p, grads);
+    if (!grads || !p.gamma_elems || cv.used <= most) return cv.used;
+    p.gamma_elems = 0;
+    Carver without(nullptr);
+    carve_fused(without, s, p, grads);
+    return without.used;
 }
 
 last_status_t launch_fused_forward(const Shape& s, const FusedPlan& p, const FusedWs& f,
@@ -1234,7 +1248,7 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
     if (check_common(weights, context, &s) != LAST_OK) return 0;
     Carver cv(nullptr);
     if (weights->kind == LAST_WEIGHTS_SHARED_EMB) {
-        const FusedPlan fp = fused_plan(s, weights);
+        FusedPlan fp = fused_plan(s, weights);
         if (op == LAST_OP_LOSS) {
             const size_t den = last_workspace_bytes(weights, context, LAST_OP_ARC_POSTERIORS, 0);
             const size_t num = last_workspace_bytes(weights, context, LAST_OP_INTERSECT_REFERENCE, Umax);
@@ -1248,13 +1262,9 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
             return cv.used;
         }
         if (!fp.ok) return 0;
-        if (op == LAST_OP_SHORTEST_DISTANCE) {
-            carve_fused(cv, s, fp, false);
-            return std::max(cv.used, emb_workspace(s, weights, false));
-        }
-        if (op != LAST_OP_ARC_POSTERIORS) return 0;
-        carve_fused(cv, s, fp, true);
-        return std::max(cv.used, emb_workspace(s, weights, true));
+        if (op != LAST_OP_SHORTEST_DISTANCE && op != LAST_OP_ARC_POSTERIORS) return 0;
+        const bool grads = op == LAST_OP_ARC_POSTERIORS;
+        return std::max(fused_bytes(s, fp, grads, SIZE_MAX), emb_workspace(s, weights, grads));
     }
     carve_table_flag(cv, s);
     const ClusterPlan plan = cluster_plan(s, weights->kind);
@@ -1318,17 +1328,15 @@ last_status_t last_shortest_distance(const last_weights_t* weights, const int32_
     if (semiring != LAST_LOG && semiring != LAST_TROPICAL) return LAST_ERR_SEMIRING;
     hipStream_t st = (hipStream_t)hip_stream;
     if (weights->kind == LAST_WEIGHTS_SHARED_EMB) {
-        const FusedPlan fp = fused_plan(s, weights);
+        FusedPlan fp = fused_plan(s, weights);
         if (!fp.ok || semiring != LAST_LOG) return LAST_ERR_UNSUPPORTED;
         const size_t need = emb_workspace(s, weights, false);
         if (need && check_ws(ws, ws_bytes, need) == LAST_OK)
             return emb_run(s, weights, lengths, dist, nullptr, item_status, ws, st, nullptr, nullptr);
         // a smaller workspace (the static one among them) holds what the kernels need that keep no weights
-        Carver cvf(nullptr);
-        carve_fused(cvf, s, fp, false);
-        rc = check_ws(ws, ws_bytes, cvf.used);
+        rc = check_ws(ws, ws_bytes, fused_bytes(s, fp, false, ws_bytes));
         if (rc != LAST_OK) return rc;
-        cvf = Carver(ws);
+        Carver cvf(ws);
         const FusedWs fw = carve_fused(cvf, s, fp, false);
         return launch_fused_forward(s, fp, fw, weights, lengths, dist, item_status, false, st);
     }
@@ -1429,17 +1437,15 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     if (rc != LAST_OK) return rc;
     if (!lengths || !dist || !out) return LAST_ERR_NULL;
     if (weights->kind == LAST_WEIGHTS_SHARED_EMB) {
-        const FusedPlan fp = fused_plan(s, weights);
+        FusedPlan fp = fused_plan(s, weights);
         if (!fp.ok) return LAST_ERR_UNSUPPORTED;
         if (!out->df || !out->de || !out->dW) return LAST_ERR_NULL;
         const size_t need = emb_workspace(s, weights, true);
         if (need && check_ws(ws, ws_bytes, need) == LAST_OK)
             return emb_run(s, weights, lengths, dist, out, item_status, ws, (hipStream_t)hip_stream, nullptr, nullptr);
-        Carver cvf(nullptr);
-        carve_fused(cvf, s, fp, true);
-        rc = check_ws(ws, ws_bytes, cvf.used);
+        rc = check_ws(ws, ws_bytes, fused_bytes(s, fp, true, ws_bytes));
         if (rc != LAST_OK) return rc;
-        cvf = Carver(ws);
+        Carver cvf(ws);
         const FusedWs fw = carve_fused(cvf, s, fp, true);
         rc = launch_fused_forward(s, fp, fw, weights, lengths, dist, item_status, true, (hipStream_t)hip_stream);
         if (rc != LAST_OK) return rc;
@@ -1774,12 +1780,12 @@ last_status_t last_globally_normalized_loss(const last_weights_t* weights, const
     check_common(weights, context, &s);
     // on-the-fly weights in memory: the numerator's gradient goes through the weight function with the denominator's
     EmbNumArgs num{};
-    bool emb = weights->kind == LAST_WEIGHTS_SHARED_EMB && emb_workspace(s, weights, true) != 0;
-    if (emb && check_ws(ws, ws_bytes, need_den + need_num + emb_cells_workspace(s, weights, Umax, nullptr, nullptr)) != LAST_OK) {
-        emb = false;                                // (a smaller workspace holds what the kernels need that keep no weights)
-        Carver cv(nullptr);
-        carve_fused(cv, s, fused_plan(s, weights), true);
-        need_den = cv.used;
+    const bool on_the_fly = weights->kind == LAST_WEIGHTS_SHARED_EMB;
+    const bool emb = on_the_fly && emb_workspace(s, weights, true) != 0
+                     && check_ws(ws, ws_bytes, need_den + need_num + emb_cells_workspace(s, weights, Umax, nullptr, nullptr)) == LAST_OK;
+    if (on_the_fly && !emb) {                       // (a smaller workspace holds what the kernels need that keep no weights)
+        FusedPlan fp = fused_plan(s, weights);
+        need_den = fused_bytes(s, fp, true, ws_bytes > need_num ? ws_bytes - need_num : 0);
     }
     last_status_t rc = check_ws(ws, ws_bytes, need_den + need_num);
     if (rc != LAST_OK) return rc;
@@ -1929,9 +1935,8 @@ last_status_t static_scratch(void** out)
 size_t smallest_distance_workspace(const Shape& s, const last_weights_t* wt, const last_context_t* cx)
 {
     if (wt->kind != LAST_WEIGHTS_SHARED_EMB) return last_workspace_bytes(wt, cx, LAST_OP_SHORTEST_DISTANCE, 0);
-    Carver cv(nullptr);
-    carve_fused(cv, s, fused_plan(s, wt), false);
-    return cv.used;
+    FusedPlan fp = fused_plan(s, wt);
+    return fused_bytes(s, fp, false, 0);
 }
 
 }  // namespace

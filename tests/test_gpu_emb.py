@@ -197,3 +197,46 @@ def test_lengths_labels_and_smaller_workspaces(V, lens):
             lb._stream()) == code
     torch.cuda.synchronize()
     assert_dist_close(dist2.cpu().numpy(), o["D"])
+
+
+@pytest.mark.parametrize("force_solo", [0, 1])
+@pytest.mark.parametrize("V,lens,U", [(2, [6, 3], 3), (3, [9, 0], 4), (33, [7, 6], 5)])
+def test_gradients_in_smaller_workspaces(V, lens, U, force_solo):
+    """Posteriors and loss take a workspace that only holds the kernels without weights, and without marginals kept between
+    two of them: the size asked for with LAST_OPT_FUSED_KEEP_MARGINALS = 0, used with 1; a byte less is refused."""
+    announce("gradients, smaller workspace", V, lens, U, force_solo)
+    B, H = 2, 256
+    s = workloads.shared_emb(B=B, T=max(lens), V=V, order=2, H=H, seed=V)
+    s["lengths"] = np.asarray(lens, dtype=np.int32)
+    s["refs"], s["ref_lengths"] = workloads.references(np.random.default_rng(V), B, V, U, 0, min(U, *lens))
+    se = fused_inputs(s)
+    lengths, refs, ulen = (torch.from_numpy(s[k]).cuda() for k in ("lengths", "refs", "ref_lengths"))
+    den = oracle.fused_forward_backward(s["f"], s["e"], s["W"], s["lengths"], 2, round_h=True, grads=True)
+    num = oracle.fused_numerator(s["f"], s["e"], s["W"], s["lengths"], s["refs"], s["ref_lengths"], 2)
+    wt, cx, _, _ = lb._weights_and_context(se, 2)
+    lib = lb.load_library()
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0):
+        least = lb.last_workspace_bytes(wt, cx, lb.OP_ARC_POSTERIORS)
+    beside = lb.last_workspace_bytes(wt, cx, lb.OP_INTERSECT_REFERENCE, U)
+    ws = torch.empty(least + beside, dtype=torch.uint8, device="cuda")
+    grads = [torch.empty(t.shape, dtype=torch.float32, device="cuda") for t in se]
+    g = lb.LastGrads(None, *(t.data_ptr() for t in grads), 0, 1.0)
+    dist, score = (torch.empty(B, dtype=torch.float32, device="cuda") for _ in range(2))
+    args = ctypes.byref(wt), lb._ptr(lengths), ctypes.byref(cx)
+    with library_option(lb.OPT_FORCE_SOLO, force_solo):
+        for nbytes, code in ((least - 1, 5), (least, 0)):
+            assert lib.last_arc_posteriors(*args, lb._ptr(dist), ctypes.byref(g), None, lb._ptr(ws), nbytes, lb._stream()) == code
+        torch.cuda.synchronize()
+        assert_dist_close(dist.cpu().numpy(), den["D"])
+        for name, got in zip(("df", "de", "dW"), grads):
+            assert_grad_close(name, got.cpu().numpy(), den[name])
+        for nbytes, code in ((least + beside - 1, 5), (least + beside, 0)):
+            assert lib.last_globally_normalized_loss(*args, lb._ptr(refs), lb._ptr(ulen), U, lb._ptr(dist), lb._ptr(score),
+                                                     ctypes.byref(g), None, lb._ptr(ws), nbytes, lb._stream()) == code
+        torch.cuda.synchronize()
+    assert_dist_close(dist.cpu().numpy(), den["D"])
+    assert_dist_close(score.cpu().numpy(), num["N"], "numerator")
+    for name, got in zip(("df", "de", "dW"), grads):
+        a, b = den[name].astype(np.float64), num[name].astype(np.float64)
+        tol = 1e-4 * max(1.0, np.max(np.abs(a)) + np.max(np.abs(b)))      # a difference of two such terms
+        assert np.max(np.abs(got.cpu().numpy() - (a - b))) <= tol, name
