@@ -71,6 +71,15 @@ def test_eight_items_of_a_dense_trigram_go_through_at_once(lib, V):
         assert 8 <= at_a_time < 9, (B, at_a_time)
 
 
+def test_slices_of_on_the_fly_weights_are_even(lib):
+    """Seven items of which six fit the weights in memory at a time go as four and three, and need what four need."""
+    def size(B, T=1000, V=64, H=512, op=lb.OP_ARC_POSTERIORS):
+        return lb.last_workspace_bytes(lb.LastWeights(lb.WEIGHTS_SHARED_EMB, B, T, None, 0x1000, 0x1000, 0x1000, H),
+                                       lb.context(V, 2), op)
+    assert size(7, op=lb.OP_SHORTEST_DISTANCE) == size(4, op=lb.OP_SHORTEST_DISTANCE) > 4 << 30
+    assert size(13, op=lb.OP_SHORTEST_DISTANCE) == size(5, op=lb.OP_SHORTEST_DISTANCE)
+
+
 def test_argument_errors_are_reported_before_any_launch(lib):
     cx = lb.context(3, 1)
     wt = _wt()
