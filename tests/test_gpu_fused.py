@@ -1,5 +1,7 @@
-"""GPU parity of the fused on-the-fly-weights path (trigram context, shared-embedding weight
-function) against the float64 oracle."""
+"""GPU parity of on-the-fly weights (trigram context, shared-embedding weight function) against the
+float64 oracle.  By default their weights are laid out in memory from three labels on (test_gpu_emb.py has the edges of
+that path); the kernels that hold the weights of a frame or two at most are reached here with
+LAST_OPT_FUSED_KEEP_MARGINALS = 0, those that keep the marginals between two of them with LAST_OPT_FORCE_SOLO = 1."""
 import numpy as np
 import pytest
 import torch
@@ -7,7 +9,7 @@ import torch
 import oracle
 from paper_2304_13134_amd import binding as lb
 from paper_2304_13134_amd import workloads
-from gpu_util import announce, assert_dist_close
+from gpu_util import announce, assert_dist_close, library_option
 
 pytestmark = pytest.mark.gpu
 
@@ -51,11 +53,10 @@ def test_fused_shortest_distance_config4_shape_short():
                                                 (2, 9, 20, 256, [9, 2], 13), (4, 12, 33, 384, [12, 11, 7, 3], 14),
                                                 (2, 7, 64, 512, [7, 6], 15)])
 def test_fused_frames_per_tile(B, T, V, H, lens, seed):
-    """Weights of one or of two frames at a time in the forward kernel (the library's
-    LAST_OPT_FUSED_FRAMES_PER_TILE): both against the oracle, odd and even lengths, a length of one
+    """Weights of one or of two frames at a time in the forward kernel that holds no more (the library's
+    LAST_OPT_FUSED_FRAMES_PER_TILE, with LAST_OPT_FUSED_KEEP_MARGINALS = 0): both against the oracle, odd and even lengths, a length of one
     and of zero, full-size tiles; the two settings give the same bits (each frame's weights and the
     recursion are computed by the same instructions, only their order in time differs)."""
-    from gpu_util import library_option
     announce("fused forward, frames per tile 1 and 2", B, T, V, H, lens)
     s = workloads.shared_emb(B=B, T=T, V=V, order=2, H=H, seed=seed)
     s["lengths"] = np.asarray(lens, dtype=np.int32)
@@ -63,7 +64,7 @@ def test_fused_frames_per_tile(B, T, V, H, lens, seed):
     o = oracle.fused_forward_backward(s["f"], s["e"], s["W"], s["lengths"], 2, round_h=True, grads=True)
     got = {}
     for frames in (1, 2):
-        with library_option(lb.OPT_FUSED_FRAMES_PER_TILE, frames):
+        with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0), library_option(lb.OPT_FUSED_FRAMES_PER_TILE, frames):
             st = torch.full((B,), -1, dtype=torch.int32, device="cuda")
             dist = lb.last_shortest_distance(se, lengths, order=2, item_status=st)
             dist2, grads = lb.last_arc_posteriors(se, lengths, order=2, item_status=st)
@@ -80,10 +81,9 @@ def test_fused_frames_per_tile(B, T, V, H, lens, seed):
 @pytest.mark.parametrize("keep", [0, 1])
 @pytest.mark.parametrize("B,T,V,H,seed", [(3, 9, 3, 128, 21), (2, 7, 17, 384, 22), (2, 6, 64, 512, 23)])
 def test_fused_gradients_with_and_without_kept_marginals(B, T, V, H, seed, keep):
-    """dW from the marginals the backward kernel kept in the workspace (LAST_OPT_FUSED_KEEP_MARGINALS = 1,
-    the default) and from marginals rebuilt with a third evaluation of the weights (0): both against the
-    oracle; the workspace the library asks for follows the setting."""
-    from gpu_util import library_option
+    """dW from the marginals the backward kernel kept in the workspace (LAST_OPT_FUSED_KEEP_MARGINALS = 1 where the
+    weights are not laid out in memory, as with LAST_OPT_FORCE_SOLO = 1) and from marginals rebuilt with a third evaluation
+    of the weights (0): both against the oracle; the workspace the library asks for follows the settings."""
     announce("fused gradients, kept marginals", keep, B, T, V, H)
     s = workloads.shared_emb(B=B, T=T, V=V, order=2, H=H, seed=seed, len_lo=max(1, T - 3), len_hi=T)
     se, lengths = fused_inputs(s), torch.from_numpy(s["lengths"]).cuda()
@@ -92,10 +92,10 @@ def test_fused_gradients_with_and_without_kept_marginals(B, T, V, H, seed, keep)
     cx = lb.context(V, 2)
     with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0):
         n0 = lb.last_workspace_bytes(wt, cx, lb.OP_ARC_POSTERIORS)
-    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 1):
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 1), library_option(lb.OPT_FORCE_SOLO, 1):
         n1 = lb.last_workspace_bytes(wt, cx, lb.OP_ARC_POSTERIORS)
     assert n1 >= n0 + B * T * V * (V + 2) * (V + 1) * 4
-    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, keep):
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, keep), library_option(lb.OPT_FORCE_SOLO, 1):
         st = torch.full((B,), -1, dtype=torch.int32, device="cuda")
         dist, grads = lb.last_arc_posteriors(se, lengths, order=2, item_status=st)
         torch.cuda.synchronize()
@@ -163,20 +163,23 @@ def test_fused_gradients_config4_shape_short():
     run_fused_grads(s)
 
 
-def test_fused_full_size_against_stored_oracle_results():
+@pytest.mark.parametrize("keep", [1, 0])
+def test_fused_full_size_against_stored_oracle_results(keep):
     """Config 4 at full size (B=4, T=1000, V=64, hidden 512), the launch configuration the
     benchmark times.  The float64 oracle needs about 20 core-minutes for it, so its results are
     stored: tests/golden/config4_fused.npz, written by tests/golden/make_config4_fused.py, which
-    calls only the oracle (D, dW whole, 4096 seeded samples each of df and de)."""
+    calls only the oracle (D, dW whole, 4096 seeded samples each of df and de).  keep = 0: the kernels that hold
+    no weights."""
     import os
-    announce("fused forward-backward, config 4 full size")
+    announce("fused forward-backward, config 4 full size, keep", keep)
     gold = np.load(os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "config4_fused.npz"))
     s = workloads.config(4)
     B = s["f"].shape[0]
     st = torch.full((B,), -1, dtype=torch.int32, device="cuda")
-    dist, (df, de, dW) = lb.last_arc_posteriors(fused_inputs(s), torch.from_numpy(s["lengths"]).cuda(),
-                                                order=2, item_status=st)
-    torch.cuda.synchronize()
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, keep):
+        dist, (df, de, dW) = lb.last_arc_posteriors(fused_inputs(s), torch.from_numpy(s["lengths"]).cuda(),
+                                                    order=2, item_status=st)
+        torch.cuda.synchronize()
     assert st.cpu().tolist() == [0] * B
     assert_dist_close(dist.cpu().numpy(), gold["D"])
     assert_grad_close("dW", dW.cpu().numpy(), gold["dW"])
@@ -283,16 +286,26 @@ def test_fused_numerator_table2_shape_two_items():
         assert_grad_close(name, got.cpu().numpy(), want)
 
 
-def test_table2_shape_full_loss_against_stored_oracle_results():
+@pytest.mark.parametrize("keep,calls", [(1, 2), (1, 1), (0, 2)])
+def test_table2_shape_full_loss_against_stored_oracle_results(keep, calls):
     """One training step at the shape of the paper's benchmark (Table 2), all 16 items: D, N and the
     gradient of D - N against tests/golden/table2_fused.npz, written by
     tests/golden/make_table2_fused.py, which calls only the oracle (D, N, dW whole, 4096 seeded
-    samples each of df and de)."""
+    samples each of df and de).  In two calls and in one; keep = 0: the kernels that hold no weights."""
     import os
-    announce("Table 2 shape, full loss, B=16 T=1024 V=32 U=256 hidden 512")
+    announce("Table 2 shape, full loss, B=16 T=1024 V=32 U=256 hidden 512; keep, calls", keep, calls)
     gold = np.load(os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "table2_fused.npz"))
     s = workloads.config(5)
-    D, N, (df, de, dW), st = run_fused_loss(s)
+    if calls == 2:
+        with library_option(lb.OPT_FUSED_KEEP_MARGINALS, keep):
+            D, N, (df, de, dW), st = run_fused_loss(s)
+    else:
+        refs, ulen = torch.from_numpy(s["refs"]).cuda(), torch.from_numpy(s["ref_lengths"]).cuda()
+        st = torch.full((len(s["lengths"]),), -1, dtype=torch.int32, device="cuda")
+        D, N, grads = lb.last_globally_normalized_loss(fused_inputs(s), torch.from_numpy(s["lengths"]).cuda(), refs, ulen,
+                                                       order=2, item_status=st)
+        D, N, st = (t.cpu().numpy() for t in (D, N, st))
+        df, de, dW = (t.cpu().numpy() for t in grads)
     assert np.all(st == 0)
     assert_dist_close(D, gold["D"])
     assert_dist_close(N, gold["N"], "numerator")
@@ -329,12 +342,12 @@ def test_fused_loss_in_one_call():
 
 @pytest.mark.parametrize("frames", [1, 2])
 def test_fused_bounded_waits_end_every_kernel_and_are_reported(frames):
-    """Spin limit of one poll on the fused kernels: every kernel ends, items that gave up carry status 5."""
-    from gpu_util import library_option
+    """Spin limit of one poll on the kernels that hold no weights: every kernel ends, items that gave up carry status 5."""
     announce("spin limit 1, fused forward-backward, frames per tile", frames)
     s = workloads.shared_emb(B=3, T=12, V=6, order=2, H=256, seed=77)
     se, lengths = fused_inputs(s), torch.from_numpy(s["lengths"]).cuda()
-    with library_option(lb.OPT_SPIN_LIMIT, 1), library_option(lb.OPT_FUSED_FRAMES_PER_TILE, frames):
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0), library_option(lb.OPT_SPIN_LIMIT, 1), \
+            library_option(lb.OPT_FUSED_FRAMES_PER_TILE, frames):
         st = torch.full((3,), -1, dtype=torch.int32, device="cuda")
         dist, grads = lb.last_arc_posteriors(se, lengths, order=2, item_status=st)
         torch.cuda.synchronize()
@@ -347,7 +360,8 @@ def test_fused_bounded_waits_end_every_kernel_and_are_reported(frames):
         else:
             assert torch.isnan(dist[b])
     st2 = torch.full((3,), -1, dtype=torch.int32, device="cuda")
-    dist2 = lb.last_shortest_distance(se, lengths, order=2, item_status=st2)
+    with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0), library_option(lb.OPT_FUSED_FRAMES_PER_TILE, frames):
+        dist2 = lb.last_shortest_distance(se, lengths, order=2, item_status=st2)
     torch.cuda.synchronize()
     assert st2.cpu().tolist() == [0, 0, 0]
     assert_dist_close(dist2.cpu().numpy(), o["D"])
