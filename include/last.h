@@ -154,6 +154,12 @@ typedef struct {
 size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t* context,
                             int32_t op, int32_t Umax);
 
+/* The least that a call of `op` takes: less than last_workspace_bytes where the weights of the frames are laid out in
+ * the workspace (shared_emb, see LAST_OPT_FUSED_KEEP_MARGINALS).  With a workspace between the two sizes the kernels
+ * without weights run, 2 to 7 times slower. */
+size_t last_least_workspace_bytes(const last_weights_t* weights, const last_context_t* context,
+                                  int32_t op, int32_t Umax);
+
 /* Shortest distance over the complete lattice (Section 2.1; Eq. 2 visited in
  * increasing t as in Section 4.1).  lengths: dev int32 [B].  dist: dev
  * float32 [B] = (+)-sum over all accepting paths (LAST_LOG) or the best path
@@ -273,7 +279,7 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
  *     go through in slices of items); 0 = it never holds more than the weights of a frame or two, in the kernels
  *     that single items of more than 8 GiB and contexts of fewer than three labels take, too.
  *     last_workspace_bytes follows the setting: ask again after changing it.  A call (distance, posteriors or
- *     loss) whose workspace only holds what the kernels without weights need, the size asked for with 0, takes these.
+ *     loss) whose workspace only holds what the kernels without weights need (last_least_workspace_bytes) takes these.
  *   LAST_OPT_FUSED_FRAMES_PER_TILE (1 or 2, default 2): frames whose on-the-fly weights the forward
  *     kernel that holds no weights computes at a time (Section 5 discusses evaluating the weight
  *     function for several frames at once).  2 shares the rows of e and the phase barriers between

@@ -27,7 +27,7 @@ EXPORTS = ["last_workspace_bytes", "last_shortest_distance", "last_arc_posterior
            "last_version", "last_kernel_variant", "last_hip_error_string",
            "last_shortest_distance_static", "last_set_option", "last_get_option",
            "last_local_log_likelihood", "last_probe_bandwidth", "last_globally_normalized_loss",
-           "last_verify_placement"]
+           "last_verify_placement", "last_least_workspace_bytes"]
 PROBE_READ, PROBE_COPY, PROBE_READ_ROWS, PROBE_READ_COLUMNS = 0, 1, 2, 3
 OPT_FORCE_SOLO, OPT_CLUSTER_GENERATION, OPT_CLUSTER_VITERBI, OPT_SPIN_LIMIT, OPT_FUSED_FRAMES_PER_TILE = 0, 1, 2, 3, 4
 OPT_FUSED_KEEP_MARGINALS = 5
@@ -72,6 +72,8 @@ def load_library():
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     lib.last_workspace_bytes.restype = sz
     lib.last_workspace_bytes.argtypes = [ctypes.POINTER(LastWeights), ctypes.POINTER(LastContext), i32, i32]
+    lib.last_least_workspace_bytes.restype = sz
+    lib.last_least_workspace_bytes.argtypes = lib.last_workspace_bytes.argtypes
     lib.last_shortest_distance.restype = i32
     lib.last_shortest_distance.argtypes = [ctypes.POINTER(LastWeights), vp, ctypes.POINTER(LastContext),
                                            i32, vp, vp, vp, sz, vp]
@@ -164,18 +166,39 @@ def verify_placement(device=None):
     return _placement[index]
 
 
-def workspace(nbytes, device):
+def workspace(nbytes, device, least=None):
     """A cached device scratch buffer (grown on demand, 256-byte aligned by the allocator), one per
-    device and stream: calls enqueued on different streams may overlap and must not share scratch."""
+    device and stream: calls enqueued on different streams may overlap and must not share scratch.  It is kept until
+    release_workspaces().  Where the card has no room for `nbytes`, one of `least()` bytes, which is not kept."""
     index = torch.device(device).index or 0
     if index not in _placement and not torch.cuda.is_current_stream_capturing():
         verify_placement(index)     # once per device, before the first kernel that relies on it
     key = (index, torch.cuda.current_stream().cuda_stream)
     buf = _workspaces.get(key)
     if buf is None or buf.numel() < nbytes:
-        buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        try:
+            buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            few = int(least()) if least is not None else int(nbytes)
+            if few >= nbytes:
+                raise
+            return buf if buf is not None and buf.numel() >= few else torch.empty(few, dtype=torch.uint8, device=device)
         _workspaces[key] = buf
     return buf
+
+
+def release_workspaces():
+    """Give the cached scratch buffers of all devices and streams back to the allocator (work that is enqueued on
+    them is not disturbed: the allocator hands memory out again in the order of the stream it was used on)."""
+    _workspaces.clear()
+
+
+def _scratch(wt, cx, op, device, Umax=0):
+    nbytes = last_workspace_bytes(wt, cx, op, Umax)
+    if nbytes == 0:
+        raise LastError(6, "combination not supported")
+    return workspace(nbytes, device, lambda: load_library().last_least_workspace_bytes(
+        ctypes.byref(wt), ctypes.byref(cx), op, Umax))
 
 
 def context(V, order):
@@ -268,10 +291,7 @@ def last_shortest_distance(w, lengths, order=1, semiring="log", item_status=None
     _dev_tensor(lengths, torch.int32, "lengths")
     dist = torch.empty(B, dtype=torch.float32, device=device)
     item_status = _status(item_status, B, device)
-    nbytes = last_workspace_bytes(wt, cx, OP_SHORTEST_DISTANCE)
-    if nbytes == 0:
-        raise LastError(6, "combination not supported")
-    ws = workspace(nbytes, device)
+    ws = _scratch(wt, cx, OP_SHORTEST_DISTANCE, device)
     sr = LAST_LOG if semiring == "log" else LAST_TROPICAL
     _check(lib.last_shortest_distance(ctypes.byref(wt), _ptr(lengths), ctypes.byref(cx), sr,
                                       _ptr(dist), _ptr(item_status), _ptr(ws), ws.numel(), _stream()))
@@ -314,10 +334,7 @@ def last_arc_posteriors(w, lengths, order=1, dw=None, scale=1.0, accumulate=Fals
         _dev_tensor(dw, torch.float32, "dw")
         g = LastGrads(dw.data_ptr(), None, None, None, int(bool(accumulate)), float(scale))
     item_status = _status(item_status, B, device)
-    nbytes = last_workspace_bytes(wt, cx, OP_ARC_POSTERIORS)
-    if nbytes == 0:
-        raise LastError(6, "combination not supported")
-    ws = workspace(nbytes, device)
+    ws = _scratch(wt, cx, OP_ARC_POSTERIORS, device)
     _check(lib.last_arc_posteriors(ctypes.byref(wt), _ptr(lengths), ctypes.byref(cx), _ptr(dist),
                                    ctypes.byref(g), _ptr(item_status), _ptr(ws), ws.numel(),
                                    _stream()))
@@ -342,10 +359,7 @@ def _intersect(entry, op, w, lengths, refs, ref_lengths, order, dw, scale, accum
     elif dw is not None:
         _dev_tensor(dw, torch.float32, "dw")
         g = LastGrads(dw.data_ptr(), None, None, None, int(bool(accumulate)), float(scale))
-    nbytes = last_workspace_bytes(wt, cx, op, Umax)
-    if nbytes == 0:
-        raise LastError(6, "combination not supported")
-    ws = workspace(nbytes, device)
+    ws = _scratch(wt, cx, op, device, Umax)
     _check(getattr(lib, entry)(ctypes.byref(wt), _ptr(lengths), ctypes.byref(cx),
                                _ptr(refs), _ptr(ref_lengths), Umax, _ptr(num),
                                ctypes.byref(g) if g is not None else None,
@@ -388,10 +402,7 @@ def last_globally_normalized_loss(w, lengths, refs, ref_lengths, order=1, dw=Non
             dw = torch.empty_like(w)
         _dev_tensor(dw, torch.float32, "dw")
         g = LastGrads(dw.data_ptr(), None, None, None, int(bool(accumulate)), float(scale))
-    nbytes = last_workspace_bytes(wt, cx, OP_LOSS, Umax)
-    if nbytes == 0:
-        raise LastError(6, "combination not supported")
-    ws = workspace(nbytes, device)
+    ws = _scratch(wt, cx, OP_LOSS, device, Umax)
     _check(lib.last_globally_normalized_loss(ctypes.byref(wt), _ptr(lengths), ctypes.byref(cx), _ptr(refs),
                                              _ptr(ref_lengths), Umax, _ptr(dist), _ptr(num), ctypes.byref(g),
                                              _ptr(item_status), _ptr(ws), ws.numel(), _stream()))
@@ -416,10 +427,7 @@ def last_shortest_path(w, lengths, order=1, item_status=None):
     states = torch.empty((B, T + 1), dtype=torch.int32, device=w.device)
     score = torch.empty(B, dtype=torch.float32, device=w.device)
     item_status = _status(item_status, B, w.device)
-    nbytes = last_workspace_bytes(wt, cx, OP_SHORTEST_PATH)
-    if nbytes == 0:
-        raise LastError(6, "combination not supported")
-    ws = workspace(nbytes, w.device)
+    ws = _scratch(wt, cx, OP_SHORTEST_PATH, w.device)
     _check(lib.last_shortest_path(ctypes.byref(wt), _ptr(lengths), ctypes.byref(cx), _ptr(labels),
                                   _ptr(states), _ptr(score), _ptr(item_status), _ptr(ws),
                                   ws.numel(), _stream()))

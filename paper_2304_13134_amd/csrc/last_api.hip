@@ -1267,7 +1267,8 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
         if (!fp.ok) return 0;
         if (op != LAST_OP_SHORTEST_DISTANCE && op != LAST_OP_ARC_POSTERIORS) return 0;
         const bool grads = op == LAST_OP_ARC_POSTERIORS;
-        return std::max(fused_bytes(s, fp, grads, SIZE_MAX), emb_workspace(s, weights, grads));
+        const size_t emb = emb_workspace(s, weights, grads);
+        return std::max(fused_bytes(s, fp, grads, emb ? 0 : SIZE_MAX), emb);
     }
     carve_table_flag(cv, s);
     const ClusterPlan plan = cluster_plan(s, weights->kind);
@@ -1317,6 +1318,18 @@ size_t last_workspace_bytes(const last_weights_t* weights, const last_context_t*
         return 0;
     }
     return cv.used;
+}
+
+size_t last_least_workspace_bytes(const last_weights_t* weights, const last_context_t* context,
+                                  int32_t op, int32_t Umax)
+{
+    Shape s;
+    const size_t usual = last_workspace_bytes(weights, context, op, Umax);
+    if (!usual || weights->kind != LAST_WEIGHTS_SHARED_EMB || op == LAST_OP_INTERSECT_REFERENCE) return usual;
+    check_common(weights, context, &s);
+    FusedPlan fp = fused_plan(s, weights);
+    const size_t least = fused_bytes(s, fp, op != LAST_OP_SHORTEST_DISTANCE, 0);
+    return op == LAST_OP_LOSS ? least + last_workspace_bytes(weights, context, LAST_OP_INTERSECT_REFERENCE, Umax) : least;
 }
 
 last_status_t last_shortest_distance(const last_weights_t* weights, const int32_t* lengths,
@@ -1935,13 +1948,6 @@ last_status_t static_scratch(void** out)
     return LAST_OK;
 }
 
-size_t smallest_distance_workspace(const Shape& s, const last_weights_t* wt, const last_context_t* cx)
-{
-    if (wt->kind != LAST_WEIGHTS_SHARED_EMB) return last_workspace_bytes(wt, cx, LAST_OP_SHORTEST_DISTANCE, 0);
-    FusedPlan fp = fused_plan(s, wt);
-    return fused_bytes(s, fp, false, 0);
-}
-
 }  // namespace
 
 extern "C" {
@@ -1956,7 +1962,7 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
     if (!lengths || !dist) return LAST_ERR_NULL;
     if (semiring != LAST_LOG && semiring != LAST_TROPICAL) return LAST_ERR_SEMIRING;
     if (last_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0) == 0) return LAST_ERR_UNSUPPORTED;
-    if (smallest_distance_workspace(s, weights, context) > (size_t)LAST_STATIC_SCRATCH_BYTES) return LAST_ERR_WORKSPACE;
+    if (last_least_workspace_bytes(weights, context, LAST_OP_SHORTEST_DISTANCE, 0) > (size_t)LAST_STATIC_SCRATCH_BYTES) return LAST_ERR_WORKSPACE;
     void* ws = nullptr;
     rc = static_scratch(&ws);
     if (rc != LAST_OK) return rc;

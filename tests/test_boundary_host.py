@@ -71,6 +71,22 @@ def test_eight_items_of_a_dense_trigram_go_through_at_once(lib, V):
         assert 8 <= at_a_time < 9, (B, at_a_time)
 
 
+def test_least_workspace(lib):
+    def sizes(wt, cx, op, U=0):
+        least = lib.last_least_workspace_bytes(ctypes.byref(wt), ctypes.byref(cx), op, U)
+        return least, lb.last_workspace_bytes(wt, cx, op, U)
+    for op in (lb.OP_SHORTEST_DISTANCE, lb.OP_ARC_POSTERIORS, lb.OP_SHORTEST_PATH, lb.OP_LOSS, lb.OP_INTERSECT_REFERENCE, 99):
+        least, usual = sizes(_wt(), lb.context(3, 1), op, 2)
+        assert least == usual and (usual > 0) == (op != 99)
+    wt = lb.LastWeights(lb.WEIGHTS_SHARED_EMB, 4, 1000, None, 0x1000, 0x1000, 0x1000, 512)
+    least, usual = sizes(wt, lb.context(64, 2), lb.OP_SHORTEST_DISTANCE)
+    assert 0 < least < 1 << 20 and usual > 4 << 30
+    least, usual = sizes(wt, lb.context(64, 2), lb.OP_LOSS, 100)
+    assert 0 < least < usual / 8
+    assert sizes(wt, lb.context(64, 2), lb.OP_SHORTEST_PATH) == (0, 0)
+    assert sizes(wt, lb.context(65, 2), lb.OP_SHORTEST_DISTANCE) == (0, 0)
+
+
 def test_slices_of_on_the_fly_weights_are_even(lib):
     """Seven items of which six fit the weights in memory at a time go as four and three, and need what four need."""
     def size(B, T=1000, V=64, H=512, op=lb.OP_ARC_POSTERIORS):

@@ -199,6 +199,36 @@ def test_lengths_labels_and_smaller_workspaces(V, lens):
     assert_dist_close(dist2.cpu().numpy(), o["D"])
 
 
+def test_calls_on_a_card_without_room_for_the_weights():
+    """The binding asks for 0.5 to 2.3 GiB of scratch where the allocator may give 300 MiB: the calls go through with the
+    kernels that hold no weights, and nothing of the smaller buffers is kept."""
+    announce("no room for the weights")
+    s = workloads.shared_emb(B=2, T=240, V=64, order=2, H=128, seed=4, len_lo=200, len_hi=240)
+    s["refs"], s["ref_lengths"] = workloads.references(np.random.default_rng(4), 2, 64, 30, 10, 30)
+    se = fused_inputs(s)
+    lengths, refs, ulen = (torch.from_numpy(s[k]).cuda() for k in ("lengths", "refs", "ref_lengths"))
+
+    def calls():
+        d0 = lb.last_shortest_distance(se, lengths, order=2)
+        d1, g1 = lb.last_arc_posteriors(se, lengths, order=2)
+        lb.check_item_status()
+        d2, n2, g2 = lb.last_globally_normalized_loss(se, lengths, refs, ulen, order=2)
+        lb.check_item_status()
+        return [t.cpu().numpy() for t in (d0, d1, *g1, d2, n2, *g2)]
+    want = calls()
+    lb.release_workspaces()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (300 << 20)) / total)
+    try:
+        got = calls()
+        assert not lb._workspaces
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    for a, b in zip(got, want):
+        assert_grad_close("one result", a, b)
+
+
 @pytest.mark.parametrize("force_solo", [0, 1])
 @pytest.mark.parametrize("V,lens,U", [(2, [6, 3], 3), (3, [9, 0], 4), (33, [7, 6], 5)])
 def test_gradients_in_smaller_workspaces(V, lens, U, force_solo):
@@ -218,6 +248,8 @@ def test_gradients_in_smaller_workspaces(V, lens, U, force_solo):
     with library_option(lb.OPT_FUSED_KEEP_MARGINALS, 0):
         least = lb.last_workspace_bytes(wt, cx, lb.OP_ARC_POSTERIORS)
     beside = lb.last_workspace_bytes(wt, cx, lb.OP_INTERSECT_REFERENCE, U)
+    assert lib.last_least_workspace_bytes(ctypes.byref(wt), ctypes.byref(cx), lb.OP_ARC_POSTERIORS, 0) == least
+    assert lib.last_least_workspace_bytes(ctypes.byref(wt), ctypes.byref(cx), lb.OP_LOSS, U) == least + beside
     ws = torch.empty(least + beside, dtype=torch.uint8, device="cuda")
     grads = [torch.empty(t.shape, dtype=torch.float32, device="cuda") for t in se]
     g = lb.LastGrads(None, *(t.data_ptr() for t in grads), 0, 1.0)
