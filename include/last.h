@@ -48,10 +48,12 @@
  *   the number of frames: numerator = -inf, its marginals are 0);
  *   5 the cooperating workgroups of an item timed out waiting for each other
  *   (results of that item are undefined).  Possible for dense bigrams of 97 to
- *   264 states and for shared_emb weights, where a launch wants all its
+ *   264 states and for shared_emb weights that are not laid out in the
+ *   workspace (LAST_OPT_FUSED_KEEP_MARGINALS), where a launch wants all its
  *   workgroups resident at once: not expected as long as no more than two
- *   such calls run on one GPU at a time (streams, threads, processes).  Dense
- *   trigrams of 3 to 64 labels wait for each other, too, but an item whose
+ *   such calls run on one GPU at a time (streams, threads, processes).
+ *   Trigrams of 3 to 64 labels on dense weights and on shared_emb weights laid
+ *   out in the workspace wait for each other, too, but an item whose
  *   waits ran out is computed by one workgroup afterwards: right, late, and
  *   with status 0.  LAST_OPT_FORCE_SOLO takes every dense call off the waits;
  *   6 the weights of the item span more dynamic range than the kernels for
@@ -121,8 +123,9 @@ enum { LAST_WEIGHTS_DENSE = 0, LAST_WEIGHTS_SHARED_EMB = 1 };
  * kind = shared_emb: f dev bf16 [B][T][hidden], e dev bf16 [C][hidden],
  * W dev bf16 [hidden][V+1] (bf16 = upper 16 bits of a float32); the hidden
  * vector tanh(f + e) is rounded to bf16 before the float32-accumulated
- * contraction with W; the weights are never stored (Section 4.1).  Supported
- * for context size 2, V <= 64, hidden a multiple of 128 up to 512, in
+ * contraction with W.  The caller never stores the weights; the library lays them
+ * out in the workspace, or holds those of a frame or two (Section 4.1; see
+ * LAST_OPT_FUSED_KEEP_MARGINALS).  Supported for context size 2, V <= 64, hidden a multiple of 128 up to 512, in
  * last_shortest_distance (LAST_LOG) and last_arc_posteriors; f, e, W must be
  * 16-byte aligned.  Other combinations return LAST_ERR_UNSUPPORTED. */
 typedef struct {
@@ -275,9 +278,12 @@ last_status_t last_shortest_distance_static(const last_weights_t* weights, const
  *     waiting for the others (the item then gets status 5 and dist = NaN, or is
  *     computed by one workgroup, see status 5; every kernel still ends).
  *   LAST_OPT_FUSED_KEEP_MARGINALS (0/1, default 1): 1 = the shared_emb path lays the weights of the frames
- *     out in the workspace (and partial sums of the gradients, together at most 8 GiB at a time: larger batches
- *     go through in slices of items); 0 = it never holds more than the weights of a frame or two, in the kernels
- *     that single items of more than 8 GiB and contexts of fewer than three labels take, too.
+ *     out in the workspace (with the state vectors, the exponentials of f and partial sums of df at most 8 GiB at a
+ *     time: larger batches go through in slices of items; partial sums of de and dW come beside them, up to
+ *     1.7 GiB); 0 = it never holds more than the weights of a frame or two, in the kernels
+ *     that single items of more than 8 GiB of weights and sums of df, contexts of fewer than three labels and calls
+ *     under LAST_OPT_FORCE_SOLO take, too (there 1 = the arc marginals, as long as they take at most 8 GiB, are kept
+ *     between two kernels instead of formed twice: the option's name).
  *     last_workspace_bytes follows the setting: ask again after changing it.  A call (distance, posteriors or
  *     loss) whose workspace only holds what the kernels without weights need (last_least_workspace_bytes) takes these.
  *   LAST_OPT_FUSED_FRAMES_PER_TILE (1 or 2, default 2): frames whose on-the-fly weights the forward

@@ -830,9 +830,11 @@ bool emb_slice(const Shape& s, const last_weights_t* wt, Shape* sl)
     const EmbPlan p = emb_plan(1, s.T, s.C, s.V, wt->hidden);
     const size_t item = (size_t)s.T * (p.row + (size_t)p.tiles * wt->hidden * sizeof(float));
     if (!p.ok || item > kFusedKeepBytes) return false;
+    // with the state vectors and e^2f, which are half of it where labels are few
+    const size_t whole = item + (size_t)s.T * ((size_t)s.C * 2 + wt->hidden) * sizeof(float);
     // as many slices as it takes, the items evenly over them (7 of 1000 frames, 64 labels go as 4 and 3: 6 and 1 took
     // as long for the one as for the six)
-    const int most = (int)std::min((size_t)s.B, kFusedKeepBytes / item), slices = (s.B + most - 1) / most;
+    const int most = (int)std::max((size_t)1, std::min((size_t)s.B, kFusedKeepBytes / whole)), slices = (s.B + most - 1) / most;
     sl->B = (s.B + slices - 1) / slices;
     return tri_plan(*sl, LAST_WEIGHTS_DENSE, false).ok;
 }

@@ -94,6 +94,11 @@ def test_slices_of_on_the_fly_weights_are_even(lib):
                                        lb.context(V, 2), op)
     assert size(7, op=lb.OP_SHORTEST_DISTANCE) == size(4, op=lb.OP_SHORTEST_DISTANCE) > 4 << 30
     assert size(13, op=lb.OP_SHORTEST_DISTANCE) == size(5, op=lb.OP_SHORTEST_DISTANCE)
+    # 8 GiB of weights, partial sums by frame, state vectors and exponentials; partial sums of de and dW and smaller things
+    # (64 bytes a frame) beside them
+    for B, T, V, H in ((60000, 500, 3, 128), (1000, 1000, 8, 512), (300, 300, 32, 256), (16, 1000, 64, 512)):
+        frames_of_a_slice = (8 << 30) // (4 * (1 + V + V * V) * (V + 3))
+        assert size(B, T, V, H) < (8 << 30) + (1800 << 20) + 64 * frames_of_a_slice, (B, T, V, H)
 
 
 def test_argument_errors_are_reported_before_any_launch(lib):
