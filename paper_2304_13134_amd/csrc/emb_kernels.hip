@@ -5,8 +5,9 @@
 // The kernels of fused_kernels.hpp form the hidden vectors inside the chain of the recursion, three times, and send
 // them through LDS.  Here nothing but the recursion (2.1 us a frame) is serial: the hidden units, of which there are H / (V+1)
 // for every arc, are formed at the rate of the vector ALU by the whole chip, in the registers of the lane that feeds them to
-// the matrix cores, once for the weights and once for the gradients.  4 bytes an arc are written and read twice: 5 % of the
-// time.  16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 11.75 ms (weights 1.9, recursions 2.2,
+// the matrix cores, once for the weights and once for the gradients.  4 bytes an arc are written once and read three times
+// (by both directions and for the gradients; once for a distance, whose directions meet in the middle): 1.35 of 11.75 ms.
+// 16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 11.75 ms (weights 1.9, recursions 2.2,
 // gradients 7.0); distance of 4 items, 1000 frames, 64 labels 7.4 -> 3.94 ms (weights 2.3, recursions 1.6).
 //
 // In the weights tanh(f + e) = 1 - 2 / (1 + e^2f e^2e), with e^2f and e^2e formed once per element of f and e, is a product
@@ -256,7 +257,8 @@ __device__ __forceinline__ void emb_weights_body(const EmbArgs& a, const f32x4* 
                 if (NT > 3) __builtin_amdgcn_sched_barrier(0);            // (registers)
             }
         }
-        // states past the last one are past the end of the descriptor, labels past the last one get an offset that is
+        // states past the last one are past the end of the descriptor (checked with the uniform part of the offset), labels
+        // past the last one get an offset that is so anywhere
 #pragma unroll
         for (int j = 0; j < FR; ++j) {
             const em_buf o = em_make_buf(a.w + (size_t)row[j] * fr + (size_t)q0 * V1, i + j < hi ? 4u * (unsigned)((a.C - q0) * V1) : 0u);
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(256) void emb_cells_kernel(EmbArgs a, EmbNumArgs n)
 // by 2^-9 W: there the product of exponentials does.  Of units above 2^-8, sigma 1 and 0.5, 2.7e-6 round the other way than in 64
 // bits, 2.9e-6 with the exponential of the sum; of the smaller ones 5e-5 and 2e-6.)
 // Sums over states and over frames leave as partial sums for emb_sum_kernel.
-// Bound: vector ALU, 13 instructions and two transcendental ones a hidden unit, 4.0 of 6.1 ms at 16 items, 1024 frames, 32 labels,
+// Bound (without the third part): vector ALU, 13 instructions and two transcendental ones a hidden unit, 4.0 of 6.1 ms at 16 items, 1024 frames, 32 labels,
 // 512 hidden units (matrix cores 0.9); two waves a SIMD (256 registers) leave the rest as waits for LDS.  Every load is issued on
 // every path, so that the waits are counted (with a condition around the cells' loads 6.9 ms); all LDS reads of a frame ahead
 // of the hidden units spilled (6.3 to 6.9).  Two frames between barriers up to 32 labels 6.2 -> 6.1.  In a loss the third part

@@ -1,6 +1,6 @@
 // The kernels of the on-the-fly path that never hold more than the weights of a frame or two: for calls with
-// LAST_OPT_FUSED_KEEP_MARGINALS = 0, workspaces that hold no weights (the static one), items of more than 8 GiB of weights and
-// contexts of fewer than three labels.  Everything else lays the weights out in memory (emb_kernels.hip), which is 1.8 to 7
+// LAST_OPT_FUSED_KEEP_MARGINALS = 0 or LAST_OPT_FORCE_SOLO = 1, workspaces that hold no weights (the static one), items of more
+// than 8 GiB of weights and contexts of fewer than three labels.  Everything else lays the weights out in memory (emb_kernels.hip), which is 1.8 to 7
 // times faster.
 //
 // Trigram (context size 2) lattice with arc weights computed on the fly

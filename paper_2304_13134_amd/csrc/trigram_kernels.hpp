@@ -31,7 +31,7 @@
 // forming them inside the recursion would put the stores on the chain to save
 // 4 of 16 bytes per arc.
 //
-// Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.68 ms against
+// Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.7 ms against
 // 34 ms with one workgroup per item (solo_kernels.hpp), 1.9 us a frame and
 // marginals in 0.11 ms; distance of 4 items, 1000 frames, 64 labels (weights in memory) 1.6 ms on 32 workgroups a direction,
 // 2.1 on 16 that own twice the labels; 6 items, 120 to 250 frames, 28 labels, shortest path 0.39
