@@ -61,8 +61,7 @@
  *   state vectors in scaled float32: entries more than 2^126 below the largest
  *   of a frame may be zero there): paths through such states may be missing
  *   from the marginals and from dist.  Never raised for weights within +-27;
- *   setting the environment variable LAST_FORCE_SOLO=1 selects the log-domain
- *   kernels, which have no such limit.  last_shortest_distance does not raise
+ *   LAST_OPT_FORCE_SOLO selects the log-domain kernels, which have no such limit.  last_shortest_distance does not raise
  *   it: up to 96 states it computes such items in the log domain (weights more
  *   than 1040 below the largest of their row count as absent arcs), from 97 to
  *   264 states dist may miss such paths.

@@ -759,13 +759,15 @@ __global__ __launch_bounds__(256) void emb_sum_kernel(EmbArgs a, EmbGradArgs g, 
     __shared__ float red[8][32];
     const int tid = threadIdx.x, H4 = a.H / 4;
     const size_t BT = (size_t)a.B * a.T;
-    auto write = [&](float4* p, float4 v, bool add) {
+    struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };      // (the caller's gradients lie anywhere)
+    auto write = [&](float* at, float4 v, bool add) {
+        F4* p = (F4*)at;
         v = make_float4(g.scale * v.x, g.scale * v.y, g.scale * v.z, g.scale * v.w);
         if (add) {
-            const float4 o = *p;
+            const F4 o = *p;
             v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
         }
-        *p = v;
+        *p = F4{v.x, v.y, v.z, v.w};
     };
     auto sum4 = [&](const float4* p, size_t stride, int n) {
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -784,11 +786,11 @@ __global__ __launch_bounds__(256) void emb_sum_kernel(EmbArgs a, EmbGradArgs g, 
         const int L = a.len[b];
         const bool live = L <= a.T && t < L;                // (L < 0: no frame)
         if (!live && g.acc_df) return;
-        write((float4*)g.df + i, live ? sum4((const float4*)g.pdf + i, BT * H4, a.tiles) : make_float4(0.f, 0.f, 0.f, 0.f), g.acc_df);
+        write(g.df + 4 * i, live ? sum4((const float4*)g.pdf + i, BT * H4, a.tiles) : make_float4(0.f, 0.f, 0.f, 0.f), g.acc_df);
     } else if (blk < nbf + nbe) {
         const size_t i = (size_t)(blk - nbf) * 256 + tid;
         if (i >= (size_t)a.C * H4) return;
-        write((float4*)g.de + i, sum4((const float4*)g.pde + i, (size_t)a.tiles * kEmTile * H4, g.ngr), g.acc_rest);
+        write(g.de + 4 * i, sum4((const float4*)g.pde + i, (size_t)a.tiles * kEmTile * H4, g.ngr), g.acc_rest);
     } else {
         const int n = a.H * (a.V + 1), e = (blk - nbf - nbe) * 32 + (tid & 31), grp = tid >> 5;
         float s = 0.f;

@@ -167,6 +167,22 @@ def test_loss_gradient_is_that_of_marginals_in_float32(B, T, V, H, U):
         assert sq[name] ** 0.5 <= most, (name, sq[name] ** 0.5)
 
 
+def test_gradients_at_addresses_of_single_floats():
+    """Only f, e and W have to lie on 16 bytes: gradients one float further on hold the same bits, and nothing beside them."""
+    announce("gradients on 4 bytes")
+    s = workloads.shared_emb(B=2, T=9, V=7, order=2, H=128, seed=12, len_lo=5, len_hi=9)
+    se, lengths = fused_inputs(s), torch.from_numpy(s["lengths"]).cuda()
+    for accumulate in (False, True):
+        want = [torch.full(t.shape, 2.0, dtype=torch.float32, device="cuda") for t in se]
+        flat = [torch.full((t.numel() + 2,), 2.0, dtype=torch.float32, device="cuda") for t in se]
+        got = [x[1:-1].view(t.shape) for x, t in zip(flat, se)]
+        assert all(x.data_ptr() % 16 == 4 for x in got)
+        for grads in (want, got):
+            lb.last_arc_posteriors(se, lengths, order=2, dw=tuple(grads), accumulate=accumulate)
+        for x, y, z in zip(want, got, flat):
+            assert torch.equal(x, y) and float(z[0]) == 2.0 and float(z[-1]) == 2.0
+
+
 def test_items_whose_waits_ran_out_have_their_gradient():
     announce("spin limit 1, weights in memory")
     with library_option(lb.OPT_SPIN_LIMIT, 1):
