@@ -19,6 +19,7 @@
 #include "trigram_kernels.hpp"
 #include "marginals_kernels.hpp"
 #include "bigram_kernels.hpp"
+#include "bigram_wave_kernels.hpp"
 #include "table_chain_kernels.hpp"
 #include "emb.hpp"
 #include <algorithm>
@@ -1010,6 +1011,9 @@ last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const in
     return rc;
 }
 
+// Up to 64 labels: the chain in one wavefront (bigram_wave_kernels.hpp).
+bool bw_ok(const Shape& s) { return s.V <= kBwMaxV; }
+
 constexpr size_t kBiBigLds = 2 * kBiMaxC * kBiMaxC * sizeof(float);
 last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep, int* bp,
                int* final_state, float* dist, int* item_status, hipStream_t st)
@@ -1033,10 +1037,24 @@ last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int
         else if (keep) launch(bigram_kernel<D, false, true>, 2);
         else launch(bigram_kernel<D, false, false>, 2);
     };
-    if (s.C <= 32) go(BiDims<8, 1, 4, 4, 8, 1, 2>());
-    else if (s.C <= 48) go(BiDims<16, 1, 4, 4, 12, 3, 2>());
-    else if (s.C <= 64) go(BiDims<16, 1, 4, 4, 16, 4, 2>());
-    else go(BiDims<32, 2, 8, 8, 12, 6, 1>());
+    auto wave = [&](auto DD) {
+        typedef decltype(DD) D;
+        constexpr size_t lds = 2 * D::G * sizeof(BwFrame<D>);
+        static_assert(lds <= 160 * 1024, "two groups of frames");
+        auto launch = [&](auto k, int roles) {
+            rc = allow_lds((const void*)k, lds);
+            if (rc == LAST_OK) hipLaunchKernelGGL(k, dim3(s.B, roles), dim3(kBwThreads), lds, st, a);
+        };
+        if (trop) launch(bigram_wave_kernel<D, true, false>, 1);
+        else if (keep) launch(bigram_wave_kernel<D, false, true>, 2);
+        else launch(bigram_wave_kernel<D, false, false>, 2);
+    };
+    if (!bw_ok(s)) go(BiDims<32, 2, 8, 8, 12, 6, 1>());
+    else if (s.V <= 8) wave(BwNarrow<1>());
+    else if (s.V <= 16) wave(BwNarrow<2>());
+    else if (s.V <= 32) wave(BwNarrow<4>());
+    else if (s.V <= 48) wave(BwWide<12>());
+    else wave(BwWide<16>());
     return rc;
 }
 
@@ -1908,8 +1926,12 @@ last_status_t last_shortest_path(const last_weights_t* weights, const int32_t* l
         hipLaunchKernelGGL(solo_viterbi, dim3(s.B), dim3(1024), l.lds_viterbi, st, weights->w, lengths,
                            c, s.T, l.CPAD, l.R, p.bp, p.final_state, score, item_status);
     const int cthreads = s.C < 256 ? (s.C + 63) / 64 * 64 : 256;
-    hipLaunchKernelGGL(backtrace_compose_kernel, dim3(p.nseg, s.B), dim3(cthreads), 0, st, (const int*)p.bp,
-                       lengths, s.C, s.V1, s.T, p.S, p.nseg, p.map);
+    if (bi && bw_ok(s))          // (the chain stored scores in the place of backpointers)
+        hipLaunchKernelGGL(bigram_bp_kernel, dim3(p.nseg, s.B), dim3(kBpWaves * kWave), 0, st, weights->w, lengths, s.C, s.T,
+                           p.S, p.nseg, p.bp, p.map);
+    else
+        hipLaunchKernelGGL(backtrace_compose_kernel, dim3(p.nseg, s.B), dim3(cthreads), 0, st, (const int*)p.bp,
+                           lengths, s.C, s.V1, s.T, p.S, p.nseg, p.map);
     hipLaunchKernelGGL(backtrace_boundaries_kernel, dim3((s.B + 63) / 64), dim3(64), 0, st, (const int*)p.map,
                        lengths, (const int*)p.final_state, s.B, s.C, s.T, p.S, p.nseg, p.bnd);
     hipLaunchKernelGGL(backtrace_emit_kernel, dim3(p.nseg, s.B), dim3(64), 0, st, (const int*)p.bp, lengths,

@@ -29,7 +29,7 @@ constexpr int kMgThreads = 256;
 constexpr float kMgRangeBits = 80.f;
 // difference of two logarithms of the partition sum that no rounding makes: this much, and per frame
 constexpr double kMgLostBits = 0.01, kMgLostBitsPerFrame = 1.0e-7;
-constexpr int kMgAlphaExp = 46, kMgBetaExp = 40;      // alpha is below 2^108, beta below 2^101: taken down for their product
+constexpr int kMgAlphaExp = 65, kMgBetaExp = 59;      // alpha is below 2^127, beta below 2^120: taken down for their product
 constexpr float kMgMax = 1.8e19f;            // 2^64: no marginal exceeds 1 but those of items that are flagged
 constexpr float kLog2eLow = 1.925963033500e-8f;      // log2 e - (float)log2 e
 constexpr int kMgChunk = 32768;              // arcs of a workgroup, about
