@@ -1557,6 +1557,15 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     return hip_status();
 }
 
+static void launch_num_check(const Shape& s, const int* lengths, const int* refs, const int* ref_lengths, int Umax, const NumWs& p,
+                             const int* flag, hipStream_t st)
+{
+    const bool table = s.order == 0 && (size_t)s.C * s.V <= (size_t)kNcTable;
+    const size_t lds = ((size_t)Umax + 1 + (table ? (size_t)s.C * s.V : 0)) * sizeof(int);
+    hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(kNcThreads), lds, st, lengths, refs, ref_lengths, make_ctx(s), s.T, Umax,
+                       p.status, p.ctxs, p.link, flag, (int)table);
+}
+
 // The (t,u) recursion with one wavefront per item and direction (references of up to 511 labels);
 // false when the shape needs the workgroup kernel.
 static bool launch_num_wave(const Shape& s, int Umax, const NumWs& p, const int* lengths, const int* ref_lengths,
@@ -1624,8 +1633,7 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
         const dim3 block(kFnWaves * kWave);
         const int ugrid = (U1 + kFnWaves - 1) / kFnWaves;
         if (prepare) {
-        hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(256), 0, st, lengths, refs, ref_lengths,
-                           c, s.T, Umax, p.status, p.ctxs, p.link, (const int*)nullptr);
+        launch_num_check(s, lengths, refs, ref_lengths, Umax, p, nullptr, st);
         hipLaunchKernelGGL(fnum_transpose_w_kernel, dim3((s.V1 * H + 255) / 256), dim3(256), 0, st,
                            (const __bf16*)weights->W, H, s.V1, Wt);
         if (s.T > 0)
@@ -1680,8 +1688,7 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
     };
     if (prepare) {
     if (flag) launch_table_check(s, flag, st);
-    hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(256), 0, st, lengths, refs, ref_lengths,
-                       c, s.T, Umax, p.status, p.ctxs, p.link, (const int*)flag);
+    launch_num_check(s, lengths, refs, ref_lengths, Umax, p, flag, st);
     if (s.T > 0) {
         if (local)
             with_pieces([&](auto QL) {
@@ -1715,7 +1722,7 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
         if (local)
             with_pieces([&](auto QL) {
                 auto k = num_scatter_local_kernel<decltype(QL)::value>;
-                const size_t need = (size_t)U1 * (sizeof(float2) + 3 * sizeof(int)) + (s.C <= kNsMaxC ? s.C : 0);
+                const size_t need = (size_t)U1 * (sizeof(float2) + 3 * sizeof(int)) + (s.C <= kNsMaxC ? s.C * sizeof(short) : 0);
                 if (need + 64 > kMaxLds) rc = allow_lds((const void*)k, kBigLds - 1024);
                 // eight workgroups a compute unit, as long as each still has 16 KiB of the frame to write, or 128 KiB where
                 // the frames alone are two a compute unit (800 frames of 601 labels 393 -> 333 us, of 131 labels 60 -> 64)

@@ -20,6 +20,7 @@
 // exponent that must be good to 1e-6); the transcendental part of each
 // log-add-exp has an O(1) argument and is evaluated in float32.
 #pragma once
+#include "cluster_kernels.hpp"
 #include "common.hpp"
 
 namespace last {
@@ -39,63 +40,88 @@ __device__ __forceinline__ int clamp_label(int y, int V) { return y < 1 ? 1 : (y
 // link [B][U1][2]: [0] = the next u' > u with the same context (-1: none), [1] = 1 when no
 // u' < u has the same context (u heads its chain).  Cells of one chain ride on the same rows
 // of the complete lattice.
-__global__ void num_check_kernel(const int* __restrict__ len, const int* __restrict__ refs,
+// Bound: latency (one workgroup an item, in front of the gather).  The contexts stay in LDS, a wave compares 64 of them at a time,
+// and a next-state table of up to kNcTable entries is walked in LDS: 150 labels 25 -> 9 us, 60 labels 13 -> 4.7 us, 80 labels through a table
+// of 585 x 8 entries 27 -> 12 us, against a thread per cell that looked through global memory and a walk of
+// dependent loads.  LDS: int[U1] contexts (fewer than 4096 labels), then int[C V] the table (table_lds).
+constexpr int kNcThreads = 1024;
+constexpr int kNcTable = 12032;         // 47 KiB, beside the 16 of the contexts
+__global__ __launch_bounds__(kNcThreads) void num_check_kernel(const int* __restrict__ len, const int* __restrict__ refs,
                                  const int* __restrict__ ulen, Ctx c, int T, int Umax,
                                  int* __restrict__ status, int* __restrict__ ctxs,
-                                 int* __restrict__ link, const int* __restrict__ badtab)
+                                 int* __restrict__ link, const int* __restrict__ badtab, int table_lds)
 {
+    extern __shared__ int nc_s[];
     __shared__ int bad;
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, tid = threadIdx.x;
     const int U1 = Umax + 1;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
+    if (tid == 0) bad = 0;
     const int L = len[b], U = ulen[b];
+    const bool wrong = badtab && badtab[0];
+    const int* r = refs + (size_t)b * Umax;
+    int* cx = ctxs + (size_t)b * U1;
+    int* q_s = nc_s;
+    int* nx_s = nc_s + U1;
+    if (table_lds)
+        for (int i = tid; i < c.C * c.V; i += kNcThreads) nx_s[i] = min((unsigned)c.nx[i], (unsigned)(c.C - 1));
     int code = kItemOk;
-    if (badtab && badtab[0]) code = kItemBadTable;
+    __syncthreads();
+    if (wrong) code = kItemBadTable;
     else if (L < 0 || L > T) code = kItemBadLength;
     else if (U < 0 || U > Umax) code = kItemBadRefLength;
     else {
-        for (int u = threadIdx.x; u < U; u += blockDim.x) {
-            const int y = refs[(size_t)b * Umax + u];
+        for (int u = tid; u < U; u += kNcThreads) {
+            const int y = r[u];
             if (y < 1 || y > c.V) atomicOr(&bad, 1);
+            else if (c.order == 0) q_s[u + 1] = y;        // (labels, until the walk comes by)
         }
     }
     __syncthreads();
     if (code == kItemOk && bad) code = kItemBadLabel;
     if (code == kItemOk && U > L) code = kItemInfeasible;
-    if (threadIdx.x == 0) status[b] = code;
-    int* cx = ctxs + (size_t)b * U1;
+    if (tid == 0) status[b] = code;
     if (code != kItemOk && code != kItemInfeasible) {
-        for (int u = threadIdx.x; u < U1; u += blockDim.x) cx[u] = -1;
+        for (int u = tid; u < U1; u += kNcThreads) cx[u] = -1;
         return;
     }
-    const int* r = refs + (size_t)b * Umax;
     if (c.order == 0) {
         // a general automaton has to be walked label by label
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             int q = 0;
-            cx[0] = 0;
-            for (int u = 1; u <= U; ++u) { q = ctx_next(c, q, r[u - 1]); cx[u] = q; }
+            q_s[0] = 0;
+            for (int u = 1; u <= U; ++u) {
+                const int y = q_s[u];
+                q = table_lds ? nx_s[q * c.V + y - 1] : ctx_next(c, q, y);
+                q_s[u] = q;
+            }
         }
-        for (int u = U + 1 + threadIdx.x; u < U1; u += blockDim.x) cx[u] = -1;
+        __syncthreads();
+        for (int u = tid; u <= U; u += kNcThreads) cx[u] = q_s[u];
     } else {
-        for (int u = threadIdx.x; u < U1; u += blockDim.x) cx[u] = u <= U ? ref_context(c, r, u) : -1;
+        for (int u = tid; u <= U; u += kNcThreads) {
+            const int q = ref_context(c, r, u);
+            q_s[u] = q;
+            cx[u] = q;
+        }
     }
+    for (int u = U + 1 + tid; u < U1; u += kNcThreads) cx[u] = -1;
     __syncthreads();
     int* lk = link + (size_t)b * U1 * 2;
-    for (int u = threadIdx.x; u < U1; u += blockDim.x) {
+    const int lane = tid & (kWave - 1);
+    for (int u = tid / kWave; u < U1; u += kNcThreads / kWave) {        // (uniform in a wave)
         int nxt = -1, head = 1;
         if (u <= U) {
-            const int q = cx[u];
-            for (int v = u + 1; v <= U; ++v)
-                if (cx[v] == q) { nxt = v; break; }
-            for (int v = u - 1; v >= 0; --v)
-                if (cx[v] == q) { head = 0; break; }
+            const int q = q_s[u];
+            for (int v0 = u + 1; v0 <= U; v0 += kWave) {
+                const unsigned long long same = __ballot(v0 + lane <= U && q_s[min(v0 + lane, U)] == q);
+                if (same) { nxt = v0 + __ffsll(same) - 1; break; }
+            }
+            for (int v0 = u - 1; v0 >= 0; v0 -= kWave)
+                if (__any(v0 - lane >= 0 && q_s[max(v0 - lane, 0)] == q)) { head = 0; break; }
         } else {
             head = 0;
         }
-        lk[2 * u] = nxt;
-        lk[2 * u + 1] = head;
+        if (lane < 2) lk[2 * u + lane] = lane == 0 ? nxt : head;
     }
 }
 
@@ -155,6 +181,35 @@ __device__ __forceinline__ NumRow<QL> num_load_row(const float* __restrict__ row
     return r;
 }
 
+// sum over the wave in float64, without LDS
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double num_shifted(double x)      // 0 where no lane is behind
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ double num_wave_sum(double x)
+{
+    x += num_shifted<0x111, 0xf>(x);
+    x += num_shifted<0x112, 0xf>(x);
+    x += num_shifted<0x114, 0xf>(x);
+    x += num_shifted<0x118, 0xf>(x);
+    x += num_shifted<0x142, 0xa>(x);
+    x += num_shifted<0x143, 0xc>(x);
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, 63), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), 63);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
+// e^x for x <= 0, the argument of exp2 reduced to [-1/2, 1/2] (its rounding would be the largest error)
+__device__ __forceinline__ float num_exp(float x)
+{
+    const float h = rintf(x * kLog2e), f = fmaf(x, 1.925963033500e-8f, fmaf(x, kLog2e, -h));       // log2 e - (float)log2 e
+    return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)fmaxf(h, -200.f));
+}
+
 // Locally normalised variant of the gather: a wavefront takes kNlFrames neighbouring frames of one u,
 //   lz[b][t][u] = log sum_y exp w[b][t][ctx(u)][y],  wd[b][t][u] = w - lz of the two arcs (float64).
 // Cells outside the cone that paths from (0,0) to (len, U) can visit get zeros without touching the
@@ -184,11 +239,7 @@ __global__ __launch_bounds__(256) void num_gather_local_kernel(
     bool in[kNlFrames];
     float m[kNlFrames], w0[kNlFrames], w1[kNlFrames];
     double s[kNlFrames];                         // the lanes' sums are added up in float64
-    auto lanes = [](double x) __attribute__((always_inline)) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
-        return x;
-    };
+    auto lanes = [](double x) __attribute__((always_inline)) { return num_wave_sum(x); };
     auto one = [&](int i) __attribute__((always_inline)) {
         const int t = min(t0 + i, L - 1);
         return row0 + (size_t)t * fr;
@@ -213,13 +264,13 @@ __global__ __launch_bounds__(256) void num_gather_local_kernel(
             for (int j = 0; j < Q; ++j)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) m[i] = fmaxf(m[i], r[i].w[j][k]);
-            m[i] = wave_max(m[i]);
+            m[i] = wave_max_dpp(m[i]);
             const float mm = m[i] == LAST_NEG_INF ? 0.f : m[i];
             float si = 0.f;
 #pragma unroll
             for (int j = 0; j < Q; ++j)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) si += k >= p.skip[j] ? expf(r[i].w[j][k] - mm) : 0.f;
+                for (int k = 0; k < 4; ++k) si += k >= p.skip[j] ? num_exp(r[i].w[j][k] - mm) : 0.f;
             s[i] = lanes((double)si);
         }
     } else if (c.V1 >= 4) {
@@ -246,11 +297,11 @@ __global__ __launch_bounds__(256) void num_gather_local_kernel(
             stretch(c0, [&](int i, float x, bool) __attribute__((always_inline)) { mi[i] = fmaxf(mi[i], x); });
 #pragma unroll
         for (int i = 0; i < kNlFrames; ++i) {
-            m[i] = wave_max(mi[i]);
+            m[i] = wave_max_dpp(mi[i]);
             mi[i] = m[i] == LAST_NEG_INF ? 0.f : m[i];
         }
         for (int c0 = 0; c0 < c.V1; c0 += 4 * kWave)
-            stretch(c0, [&](int i, float x, bool counts) __attribute__((always_inline)) { si[i] += counts ? expf(x - mi[i]) : 0.f; });
+            stretch(c0, [&](int i, float x, bool counts) __attribute__((always_inline)) { si[i] += counts ? num_exp(x - mi[i]) : 0.f; });
 #pragma unroll
         for (int i = 0; i < kNlFrames; ++i) s[i] = lanes((double)si[i]);
     } else {
@@ -259,7 +310,7 @@ __global__ __launch_bounds__(256) void num_gather_local_kernel(
             const float* row = one(in[i] ? i : 0);
             float mi = LAST_NEG_INF, si = 0.f;
             for (int y = lane; y < c.V1; y += kWave) mi = fmaxf(mi, row[y]);
-            mi = wave_max(mi);
+            mi = wave_max_dpp(mi);
             if (mi != LAST_NEG_INF)
                 for (int y = lane; y < c.V1; y += kWave) si += expf(row[y] - mi);
             m[i] = mi;
@@ -588,10 +639,12 @@ __global__ void num_scatter_kernel(const float2* __restrict__ wi, const int* __r
 // atomics are needed and the result does not depend on timing.  Rows that no path visits are zero (accumulate:
 // left alone) and are written by the same workgroup, every element of the tensor once.
 // Bound: HBM, the tensor written once and the visited rows read.  B=16, T=500, V=256, 50 to 150 labels: 1.19 -> 0.69 ms
-// against a fill of the whole tensor followed by a wavefront per chain whose cells were fetched one by one.
+// against a fill of the whole tensor followed by a wavefront per chain whose cells were fetched one by one.  Rows are
+// written in their order, zeros or not (0.705 -> 0.66 ms against the zeros of a frame first): what a frame's zeros leave out costs as much as what they write.  (The
+// zero rows alone, beside the recursion: 1.4 GB in 0.43 ms, while the whole 2.1 GB go in 0.33.)
 // zeroed: the tensor has been filled with zeros by another kernel (context sets too large for `seen`).
-// LDS: float2[U1] marginals | int[U1] heads of visited chains | int[U1] links | int[U1] labels |
-// unsigned char[C] visited (unless zeroed).
+// LDS: float2[U1] marginals | int[U1] heads of visited chains (zeroed) | int[U1] links | int[U1] labels |
+// short[C] head of the row's chain, -1: not visited (unless zeroed).
 constexpr int kNsThreads = 512;
 constexpr int kNsMaxC = 32768;
 template <int QL>
@@ -608,8 +661,9 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     int* heads = (int*)(nsl_p + U1);
     int* next = heads + U1;                     // next cell of the chain, -1: none
     int* label = next + U1;                     // label of the cell's label arc, -1: none
-    unsigned char* seen = (unsigned char*)(label + U1);
+    short* head = (short*)(label + U1);
     const bool zeros = !accumulate && !zeroed;  // rows no path visits are written here
+    const bool ordered = c.C <= kNsMaxC;        // (else zeroed, or added to what is there)
     const int b = blockIdx.y, t = blockIdx.x, tid = threadIdx.x, part = blockIdx.z, parts = gridDim.z;
     const int wv = tid / kWave, lane = tid & (kWave - 1);
     constexpr int NW = kNsThreads / kWave;
@@ -622,8 +676,8 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     const int* lk = link + (size_t)b * U1 * 2;
     const int* cx = ctxs + (size_t)b * U1;
     const size_t cell0 = ((size_t)b * T + t) * U1;
-    if (zeros)
-        for (int q = tid; q < c.C; q += kNsThreads) seen[q] = 0;
+    if (ordered)
+        for (int q = tid; q < c.C; q += kNsThreads) head[q] = -1;
     if (tid == 0) { count = 0; visited = 0; }
     if (live) {
         const double* at = a + ((size_t)b * (T + 1) + t) * U1;
@@ -654,9 +708,9 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             bool any = false;
             for (int v = u; v >= 0 && !any; v = next[v]) any = nsl_p[v].x >= 0.f;
             if (!any) continue;
-            if (u % parts == part) heads[atomicAdd(&count, 1)] = u;     // (the order of the rows does not matter)
             visited = 1;
-            if (zeros) seen[cx[u]] = 1;
+            if (ordered) head[cx[u]] = (short)u;                        // (fewer than 4096 labels)
+            else if (u % parts == part) heads[atomicAdd(&count, 1)] = u;     // (the order of the rows does not matter)
         }
     __syncthreads();
     const int n = live ? count : 0;
@@ -672,26 +726,10 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             for (int i = lead + 4 * n4 + tid; i < total; i += kNsThreads) g[i] = 0.f;
             return;
         }
-        for (int q = part * NW + wv; q < c.C; q += parts * NW) {
-            if (seen[q]) continue;
-            float* grow = g + (size_t)q * c.V1;
-            struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
-            for (int y = 4 * lane; y < c.V1; y += 4 * kWave)
-                if (c.V1 >= 4) *(f4*)(grow + min(y, c.V1 - 4)) = f4{{0.f, 0.f, 0.f, 0.f}};
-                else
-                    for (int k = y; k < c.V1; ++k) grow[k] = 0.f;
-        }
     }
     constexpr int Q = QL > 0 ? QL : 2;
     const NumPieces<Q> p(c.V1, lane);
-    auto row_of = [&](int i) __attribute__((always_inline)) { return fo + (size_t)cx[heads[min(i, n - 1)]] * c.V1; };
-    NumRow<Q> nx;
-    if (QL > 0 && n > 0) nx = num_load_row<Q>(w + row_of(wv), p);
-    for (int i = wv; i < n; i += NW) {
-        const int u = heads[i];
-        const size_t ro = fo + (size_t)cx[u] * c.V1;
-        const NumRow<Q> x = nx;
-        if (QL > 0) nx = num_load_row<Q>(w + row_of(i + NW), p);
+    auto row = [&](int u, size_t ro, const NumRow<Q>& x) __attribute__((always_inline)) {
         float occ = 0.f, pbs = 0.f, lab[Q][4];
         int first = -1;
         // the chain's label marginals by column, in chain order (deterministic), and once per row their sums
@@ -756,6 +794,48 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
                 const float o = grad(y, w[ro + y], l);
                 if (accumulate) grow[y] += o; else grow[y] = o;
             }
+        }
+    };
+    if (!ordered) {
+        auto row_of = [&](int i) __attribute__((always_inline)) { return fo + (size_t)cx[heads[min(i, n - 1)]] * c.V1; };
+        NumRow<Q> nx;
+        if (QL > 0 && n > 0) nx = num_load_row<Q>(w + row_of(wv), p);
+        for (int i = wv; i < n; i += NW) {
+            const NumRow<Q> x = nx;
+            if (QL > 0) nx = num_load_row<Q>(w + row_of(i + NW), p);
+            row(heads[i], row_of(i), x);
+        }
+        return;
+    }
+    // own rows first + step i; those of the next 64 that are visited as a mask, the weights of the next one requested while one
+    // is worked on
+    const int first = part * NW + wv, step = parts * NW;
+    for (int q0 = first; q0 < c.C; q0 += step * kWave) {
+        const int mine = q0 + step * lane, h = mine < c.C ? head[mine] : -1;
+        unsigned long long m = __ballot(h >= 0);
+        const int rows = min(kWave, (c.C - q0 + step - 1) / step);
+        NumRow<Q> nx;
+        auto request = [&](int i) __attribute__((always_inline)) {
+            if (QL > 0) nx = num_load_row<Q>(w + fo + (size_t)(q0 + step * i) * c.V1, p);
+        };
+        int at = m ? __ffsll(m) - 1 : kWave;
+        if (at < kWave) request(at);
+        for (int i = zeros ? 0 : at; i < rows; zeros ? ++i : i = at) {
+            const size_t ro = fo + (size_t)(q0 + step * i) * c.V1;
+            if (i == at) {
+                const NumRow<Q> x = nx;
+                m &= m - 1;
+                at = m ? __ffsll(m) - 1 : kWave;
+                request(min(at, rows - 1));
+                row(__builtin_amdgcn_readlane(h, i), ro, x);
+                continue;
+            }
+            float* grow = dw + ro;
+            struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
+            for (int y = 4 * lane; y < c.V1; y += 4 * kWave)
+                if (c.V1 >= 4) *(f4*)(grow + min(y, c.V1 - 4)) = f4{{0.f, 0.f, 0.f, 0.f}};
+                else
+                    for (int k = y; k < c.V1; ++k) grow[k] = 0.f;
         }
     }
 }
