@@ -638,6 +638,8 @@ typedef TriDims<8, 2, 4, 11> Tri2;      // up to 42, 43 with two labels a workgr
 typedef TriDims<16, 4, 3, 9> Tri3;      // up to 35
 typedef TriDims<16, 4, 6, 17> Tri4;     // up to 64
 typedef TriDims<8, 2, 6, 17> Tri5;      // up to 64, two labels a workgroup
+typedef TriDims<8, 2, 2, 5, false> Tri6;   // up to 11, a single workgroup (log semiring)
+typedef TriDims<16, 4, 3, 9, false> Tri7;  // up to 16, likewise
 
 constexpr size_t kTriRowBytes = (size_t)24 << 20;   // most that the rows of a call without marginals may take
 
@@ -658,6 +660,7 @@ TriPlan tri_plan(const Shape& s, int kind, bool trop)
         p.nb = (s.V + p.K - 1) / p.K;                       // evenly over the workgroups, each with at least one
         p.K = (s.V + p.nb - 1) / p.nb;
         if (p.K > 32 || p.K * D::NCM > kWave) return;
+        if (!trop && (p.K == 1) == D::Ahead && D::NR <= 4) return;
         p.across = p.roles * p.K > 32 ? 1 : 0;
         const int xcds = 8 >> p.across, each = p.K * (p.roles >> p.across);      // XCDs an item may start on, workgroups there
         p.ncl = std::min((s.B + xcds - 1) / xcds, 32 / each);
@@ -667,8 +670,9 @@ TriPlan tri_plan(const Shape& s, int kind, bool trop)
         if (p.nb * s.V1 + 1 > D::NP * D::CT / 4 || p.nb * s.V1 + 1 > D::States || p.nb >= 32) return;
         p.xs = s.V * s.V + s.V + p.K * D::NCM;
         p.grid = 8 * p.ncl * each;
-        const size_t fwd = (size_t)2 * kTriMaxG * 4 * cq;
-        const size_t bwd = (size_t)(p.nb + 1) * D::BtPitch + 3 + (size_t)s.V1 * 4 * cq + kTriPad;
+        const bool ahead = !trop && D::Ahead;
+        const size_t fwd = (size_t)kTriMaxG * (ahead ? 3 * D::Pitch : 2 * 4 * cq);
+        const size_t bwd = 2 * ((size_t)(p.nb + 1) * D::BtPitch + 3) + (ahead ? 2 : 1) * ((size_t)s.V1 * 4 * cq + kTriPad);
         p.lds = std::max(fwd, trop ? (size_t)0 : bwd) * sizeof(float);
         if (p.lds > kBigLds - 16384) return;
         p.ok = true;
@@ -676,9 +680,11 @@ TriPlan tri_plan(const Shape& s, int kind, bool trop)
         if (!best.ok || rounds < fewest) { best = p; fewest = rounds; }
     };
     consider(0, Tri0());
+    if (!best.ok && !trop) consider(6, Tri6());
     if (!best.ok) consider(1, Tri1());
     if (!best.ok) consider(2, Tri2());
     consider(3, Tri3());
+    if (!trop) consider(7, Tri7());
     // two labels a workgroup (43 labels and more), one direction of an item on an XCD, against four, both directions on it:
     // posteriors of 4 items, 60 labels, 200 frames 898 / 1043 us, distance 309 / 389, of 2 items, 45 labels, 100 frames 121 / 173;
     // but half as many items at a time: posteriors of 8 items 1754 / 1431 us, of 24 items, 64 labels, 100 frames 2969 / 2494, of
@@ -748,6 +754,8 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
     case 2: pick(Tri2()); break;
     case 3: pick(Tri3()); break;
     case 4: pick(Tri4()); break;
+    case 6: pick(Tri6()); break;
+    case 7: pick(Tri7()); break;
     default: pick(Tri5()); break;
     }
     return rc;

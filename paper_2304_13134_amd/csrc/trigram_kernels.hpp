@@ -21,8 +21,14 @@
 //
 // What bounds it: the chain of a frame.  Own rows -> partial sums (compute
 // waves) -> barrier -> combine and publish (exchange waves) -> L2 round trip
-// -> own states -> barrier.  Weights are requested four rows' worth at a time with
-// 16-byte loads two frames (backward: three) ahead by waves that never wait
+// -> own states -> barrier; a wave issues an instruction every five clocks or so, so that what is on this chain counts by
+// instructions.  In the log semiring (up to 43 labels) the compute waves therefore form e^(w - m) of the next frame while the
+// exchange is under way, m the largest weight of a thread's rows in a column (backward: of a row), and the exchange waves keep the
+// exponentials of the states beside the states: the sums are multiply-adds, the exchange waves have what the partial sums are
+// to be multiplied by before these are there, and rows are stored behind the barrier.  A sum that comes out below 2^-60 (weights or
+// states far apart) is taken again from the logarithms by the wave that has it, so there is still no limit on the range.
+// Weights are requested four rows' worth at a time with
+// 16-byte loads two frames (backward: up to four) ahead by waves that never wait
 // for an exchange; the exchange waves issue no weight loads, because a wave's
 // loads return in order and a look at the exchange would queue behind them.
 // Forward and backward pass run at the same time on different compute units.
@@ -31,12 +37,12 @@
 // forming them inside the recursion would put the stores on the chain to save
 // 4 of 16 bytes per arc.
 //
-// Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.7 ms against
-// 34 ms with one workgroup per item (solo_kernels.hpp), 1.9 us a frame and
+// Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.61 ms (0.70 with exponentials on the chain) against
+// 34 ms with one workgroup per item (solo_kernels.hpp), 1.5 us a frame (1.8) and
 // marginals in 0.11 ms; distance of 4 items, 1000 frames, 64 labels (weights in memory) 1.6 ms on 32 workgroups a direction,
-// 2.1 on 16 that own twice the labels; 6 items, 120 to 250 frames, 28 labels, shortest path 0.39
+// 2.1 on 16 that own twice the labels; 6 items, 120 to 250 frames, 28 labels, shortest path 0.36
 // against 3.7 ms.
-// What made the difference between 3.0 and 1.9 us a frame is that every weight
+// What made the difference between 3.0 and 1.9 us a frame, before that, is that every weight
 // request and store is issued on every path (the waits for the weights can then
 // be counted; a condition around one of them turns them into waits for all) and
 // that the exchange waves read all partial results in one batch.
@@ -75,7 +81,7 @@ constexpr int kTriMaxG = 12;     // row groups whose partial results the exchang
 
 // NW waves of which NCM exchange and the rest compute, nb V <= 64 NCM; NR: 16-byte pieces of a frame per
 // compute thread; EPL: elements of a row per lane in the backward direction (four lanes a row, two rows a lane)
-template <int NW_, int NCM_, int NR_, int EPL_>
+template <int NW_, int NCM_, int NR_, int EPL_, bool AHEAD_ = (NR_ <= 4)>
 struct TriDims {
     static constexpr int NW = NW_, NCM = NCM_, NR = NR_, EPL = EPL_;
     static constexpr int CT = (NW - NCM) * kWave;              // compute threads
@@ -83,6 +89,11 @@ struct TriDims {
     static constexpr int MaxV = 4 * EPL - 1 < kTriMaxV ? 4 * EPL - 1 : kTriMaxV;
     static constexpr int States = NCM * kWave + 32;            // own states, the start state
     static constexpr int BtPitch = (4 * EPL) | 1;              // odd: neighbouring labels start in other banks
+    static constexpr int Pitch = NCM * kWave + 32;             // forward, partial results of a row group: 4 CQ floats at most
+    // log: the exponentials of the weights are formed beside the exchange.  Not beyond 43 labels, where their registers are
+    // not there (64 labels 3.1 -> 4.2 us a frame, spilled), nor in a single workgroup, which has no exchange (8 labels 118 -> 133 us
+    // for 100 frames); at 32 labels 1.84 -> 1.47 us a frame
+    static constexpr bool Ahead = AHEAD_;
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -122,12 +133,31 @@ __device__ __forceinline__ float tri_quad_sum(float v)
     return v + tri_quad<0x4E>(v);
 }
 
+// largest float of the wave, the same in all lanes, in as few instructions as it takes
+__device__ __forceinline__ float tri_wave_max(float v)
+{
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:1 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 0"
+        : "+v"(v));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 // One look after the other at this lane's word (and, with HEAD, at one header word) until the tags are
-// right in every lane of the wave; false when the bound is reached.
+// right in every lane of the wave; false when the bound is reached.  The tropical waves look right after they have
+// published: a first look that leaves 256 clocks later (`later`: clusters of more than four workgroups) is answered when there
+// is something to see, one that leaves at once has to be sent again (28 labels, 7 workgroups 1.34 -> 1.25 us a frame; 16 labels,
+// 2 workgroups 132 -> 139 us for 100 frames; the others form their header word meanwhile, and are slower for any such
+// wait, 1.47 -> 1.60; with two looks under way both are slower).
 template <bool HEAD, bool TAG16>
 __device__ __forceinline__ bool tri_poll(const u64* wp, const u64* hp, bool act, unsigned tag, int limit,
-                                         u64& word, u64& head)
+                                         u64& word, u64& head, bool later = false)
 {
+    if (TAG16 && later) __builtin_amdgcn_s_sleep(4);
     for (int n = 0; n <= limit; ++n) {
         word = xload(wp);
         if (HEAD) head = xload(hp);
@@ -135,7 +165,7 @@ __device__ __forceinline__ bool tri_poll(const u64* wp, const u64* hp, bool act,
         ok = ok || !act;
         if (HEAD) ok = ok && (unsigned)(head >> 32) == tag;
         if (__all(ok)) return true;
-        __builtin_amdgcn_s_sleep(1);
+        if (!TAG16 || !later) __builtin_amdgcn_s_sleep(1);
     }
     return false;
 }
@@ -162,7 +192,10 @@ struct TriOwn {
 template <typename D>
 struct TriLds {
     float own[D::States + 32];                 // own states, [a nbk + i]; the start state at [rows]; then nbk times -inf
-    float bl[D::States];                       // forward: empty-label candidates; backward: the new states
+    float ex[D::States + 32];                  // log: their exponentials
+    float bl[D::States];                       // tropical: empty-label candidates; backward: the new states
+    float bw[2][D::States + 32];               // forward, log: weights of the empty label
+    int far[2];                                // log: a sum of the frame was taken the long way
     float strow[2][4 * 17 + 4];                // the start state's row of weights
     float xl[D::NCM * kWave + kTriMaxV];       // exchange of a single workgroup (K = 1)
     int xa[D::NCM * kWave];
@@ -176,6 +209,11 @@ struct TriLds {
 // the waits for prefetched weights can be counted
 constexpr unsigned kTriOut = 0xfffffff0u;
 
+// A sum of products e^x e^(w - m), both factors at most 1, is the sum it stands for as long as it is not below this: what both
+// factors have lost below 2^-126 is 2^-66 of it.  Smaller ones (weights far apart, states out of reach) are
+// taken from the logarithms themselves.
+constexpr float kTriFar = 8.6736174e-19f;      // 2^-60
+
 template <typename D, bool TROP>
 __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, int b, int L, unsigned& gstep,
                                             u64* xbase, TriLds<D>& s, float* dyn)
@@ -186,19 +224,26 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool comm = wave < NCM;
-    const int V = o.V, V1 = o.V1, nbk = o.nbk, P = 4 * o.CQ;
-    float* pm = dyn;                            // [kTriMaxG][P] partial maxima (tropical: scores)
-    float* ps = dyn + kTriMaxG * P;             // [kTriMaxG][P] partial sums   (tropical: source a, as int)
+    const int V = o.V, V1 = o.V1, nbk = o.nbk;
+    constexpr bool AHEAD = !TROP && D::Ahead;
+    const int P = AHEAD ? D::Pitch : 4 * o.CQ;
+    float* ps = dyn;                            // [kTriMaxG][P] partial sums   (tropical: source a, as int)
+    float* pm = dyn + kTriMaxG * P;             // [kTriMaxG][P] partial maxima (tropical: scores); log: two frames of them
+    const int pmz = AHEAD ? kTriMaxG * P : 0;
     const size_t fr = (size_t)o.V1 * a.C;
     const float* wi = a.w + (size_t)b * a.T * fr;
     const int steps = TROP || a.keep ? L : tri_meet(L, false);
 
-    for (int r = tid; r < D::States + 32; r += D::NW * kWave) s.own[r] = r == o.rows ? 0.f : LAST_NEG_INF;
+    for (int r = tid; r < D::States + 32; r += D::NW * kWave) {
+        s.own[r] = r == o.rows ? 0.f : LAST_NEG_INF;
+        s.ex[r] = r == o.rows ? 1.f : 0.f;
+    }
     for (int i = tid; i < kTriMaxG * P; i += D::NW * kWave) {      // groups that do not exist stay neutral
         pm[i] = LAST_NEG_INF;
+        if (AHEAD) pm[pmz + i] = LAST_NEG_INF;
         ps[i] = TROP ? __int_as_float(0xffff) : 0.f;
     }
-    if (tid == 0) { s.dead = 0; s.off = 0.0; }
+    if (tid == 0) { s.dead = 0; s.off = 0.0; s.far[0] = s.far[1] = 0; }
     __syncthreads();
 
     if (!comm) {
@@ -234,6 +279,12 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
             buf_store(s.own[rS], make_buf(a.alpha + row * a.C, on ? rowb : 0u), rq, 0);
             if (!TROP) nw_store64(s.off, make_buf(a.offa + row, on ? 8u : 0u), oq, 0);
         };
+        // the same in two: read before the exchange, stored beside it
+        auto store_read = [&](float x, double at, int t) __attribute__((always_inline)) {
+            const size_t row = a.keep ? (size_t)b * (a.T + 1) + t : (size_t)b;
+            buf_store(x, make_buf(a.alpha + row * a.C, a.keep ? rowb : 0u), rq, 0);
+            nw_store64(at, make_buf(a.offa + row, a.keep ? 8u : 0u), oq, 0);
+        };
         float4 wv[2][D::NR];
         float st[2] = {0.f, 0.f}, st64[2] = {0.f, 0.f};
         auto issue = [&](auto S, int t) __attribute__((always_inline)) {
@@ -251,16 +302,85 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 if (D::MaxV == 64) s.strow[Z][V] = st64[Z];
             }
         };
+        // log: e^(w - m) of a frame, m the largest weight of the thread's rows in a column, and what the exchange waves need
+        // of it before its sums; ahead of the chain.  z0: 1 where a small sum is of no account (a column without a weight, whose
+        // m says so, or of the empty label)
+        float E[AHEAD ? D::NR : 1][4], z0[4];
+        unsigned exOff[AHEAD ? D::NR : 1][4], bwOff[AHEAD ? D::NR : 1];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int n = 0; n < D::NR; ++n) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    exOff[n][c] = 4u * (unsigned)(base(n) + iC[c]);
+                    asm volatile("" : "+v"(exOff[n][c]));           // (an instruction less on the chain)
+                }
+                bwOff[n] = 4u * (unsigned)(base(n) + iB);
+            }
+        }
+        auto factors = [&](auto S) __attribute__((always_inline)) {
+            constexpr int Z = decltype(S)::value;
+            int at = hasB ? cB : -1;
+            asm volatile("" : "+v"(at));                        // (no masks kept in scalar registers for all frames)
+            float mw[4] = {LAST_NEG_INF, LAST_NEG_INF, LAST_NEG_INF, LAST_NEG_INF};
+#pragma unroll
+            for (int n = 0; n < D::NR; ++n) {
+                const float4 w4 = wv[Z][n];
+                const float wc[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) mw[c] = fmaxf(mw[c], wc[c]);
+                if (at >= 0) *(float*)((char*)s.bw[Z] + bwOff[AHEAD ? n : 0]) = at == 0 ? wc[0] : at == 1 ? wc[1] : at == 2 ? wc[2] : wc[3];
+            }
+            if (act) *(float4*)(pm + Z * pmz + g * P + 4 * cq) = make_float4(mw[0], mw[1], mw[2], mw[3]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bool none = mw[c] == LAST_NEG_INF;
+                z0[c] = none || c == at ? 1.f : 0.f;
+#pragma unroll
+                for (int n = 0; n < D::NR; ++n) {
+                    const float4 w4 = wv[Z][n];
+                    const float wc = c == 0 ? w4.x : c == 1 ? w4.y : c == 2 ? w4.z : w4.w;
+                    E[AHEAD ? n : 0][c] = tri_exp(wc - (none ? 0.f : mw[c]));
+                }
+            }
+        };
         if (steps > 0) {
             issue(std::integral_constant<int, 0>(), 0);
             issue(std::integral_constant<int, 1>(), 1);
             start_row(std::integral_constant<int, 0>());
+            if constexpr (AHEAD) factors(std::integral_constant<int, 0>());
         }
         __syncthreads();
         auto frame = [&](auto S, int t) __attribute__((always_inline)) {
             constexpr int Z = decltype(S)::value;
-            if (!TROP) store_row(t, a.keep);
-            else if (t > 0) buf_store(__int_as_float(s.flat[rS]), make_buf(a.bp + ((size_t)b * a.T + t - 1) * a.C, a.bp ? rowb : 0u), rq, 0);
+            float rowv = 0.f;
+            double rowo = 0.0;
+            if (TROP) {
+                if (t > 0) buf_store(__int_as_float(s.flat[rS]), make_buf(a.bp + ((size_t)b * a.T + t - 1) * a.C, a.bp ? rowb : 0u), rq, 0);
+            } else if (!AHEAD) {
+                store_row(t, a.keep);
+            }
+            bool far = !AHEAD;
+            if constexpr (AHEAD) {
+                float z[4] = {z0[0], z0[1], z0[2], z0[3]};
+                float x[D::NR][4];
+#pragma unroll
+                for (int n = 0; n < D::NR; ++n)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x[n][c] = *(const float*)((const char*)s.ex + exOff[n][c]);
+                rowv = s.own[rS];
+                rowo = s.off;
+#pragma unroll
+                for (int n = 0; n < D::NR; ++n)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) z[c] = fmaf(x[n][c], E[n][c], z[c]);
+                float least;
+                asm("v_min3_f32 %0, %1, %2, %3" : "=v"(least) : "v"(z[0]), "v"(z[1]), "v"(z[2]));
+                asm("v_min_f32 %0, %1, %2" : "=v"(least) : "v"(least), "v"(z[3]));
+                far = __any(least < kTriFar);
+                if (act) *(float4*)(ps + g * P + 4 * cq) = make_float4(z[0], z[1], z[2], z[3]);
+            }
+            if (__builtin_expect(far, !AHEAD)) {
             float m[4], z[4];
             int src[4];
 #pragma unroll
@@ -299,7 +419,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                         }
                     }
                     const int bs = base(n0 + n);
-                    if (hasB && bs <= o.rows) s.bl[bs + iB] = xB;
+                    if (!AHEAD && hasB && bs <= o.rows) s.bl[bs + iB] = xB;
                 }
                 if (!TROP) {
 #pragma unroll
@@ -313,15 +433,21 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 }
             }
             if (act) {
-                *(float4*)(pm + g * P + 4 * cq) = make_float4(m[0], m[1], m[2], m[3]);
+                *(float4*)(pm + Z * pmz + g * P + 4 * cq) = make_float4(m[0], m[1], m[2], m[3]);
                 if (TROP) *(int4*)(ps + g * P + 4 * cq) = make_int4(src[0], src[1], src[2], src[3]);
                 else *(float4*)(ps + g * P + 4 * cq) = make_float4(z[0], z[1], z[2], z[3]);
+            }
+            if (AHEAD) s.far[Z] = 1;
             }
             lds_only_barrier();                                                   // B
             if (a.K == 1) lds_only_barrier();
             // (the exchange is under way) start row of the next frame, weights of the frame after it
             start_row(std::integral_constant<int, Z ^ 1>());
             issue(S, t + 2);
+            if constexpr (AHEAD) {
+                store_read(rowv, rowo, t);
+                factors(std::integral_constant<int, Z ^ 1>());
+            }
             lds_only_barrier();                                                   // A
         };
         for (int t = 0; t < steps; t += 2) {
@@ -337,7 +463,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
         const bool act = lidx < nbk * V;
         const int pi = act ? lidx / V : 0, py = act ? lidx - pi * V + 1 : 1;
         const int col = pi * V1 + py;
-        const int slot = col + (col >= 4 * (o.CQ - 1) ? P - o.W : 0);
+        const int slot = col + (col >= 4 * (o.CQ - 1) ? 4 * o.CQ - o.W : 0);
         const int ga = act ? lidx / nbk + 1 : 1, gi = act ? lidx - (ga - 1) * nbk : 0;
         const int grow = ga * nbk + gi;                                           // own row of the gathered state
         const int gidx = (ga - 1) * V + (o.b0 - 1 + gi);
@@ -348,41 +474,85 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
         const unsigned oHead = tri_place(V * V + V + o.k * NCM + wave), oHeads = tri_place(V * V + V + (lane < nh ? lane : 0));
         bool dead = false;
         double A = 0.0;
+        float mine = LAST_NEG_INF, mine1 = LAST_NEG_INF;        // log: own states of this lane (the gathered one; with one label)
         __syncthreads();
         for (int t = 0; t < steps; ++t) {
             u64* xs = xbase + (size_t)(gstep & 1) * a.xs;
             const unsigned tag = gstep + 1;
             gstep += 1;
+            // log: what the partial sums will have to be multiplied by, while they are formed
+            float fz[AHEAD ? kTriMaxG : 1], top = LAST_NEG_INF;
+            if constexpr (AHEAD) {
+#pragma unroll
+                for (int g = 0; g < kTriMaxG; ++g) fz[g] = pm[(t & 1) * pmz + g * P + slot];
+#pragma unroll
+                for (int g = 0; g < kTriMaxG; ++g) top = fmaxf(top, fz[g]);
+                const float mm = top == LAST_NEG_INF ? 0.f : top;
+#pragma unroll
+                for (int g = 0; g < kTriMaxG; ++g) {
+                    fz[g] = tri_exp(fz[g] - mm);
+                    asm volatile("" : "+v"(fz[g]));             // (not put off behind the barrier)
+                }
+                asm volatile("" : "+v"(top));
+            }
+            float bwr = LAST_NEG_INF, u2 = LAST_NEG_INF;       // the empty label's candidate; histories of one label, the start state
+            if constexpr (AHEAD) {
+                bwr = act ? mine + s.bw[t & 1][grow] : LAST_NEG_INF;
+                const float w0 = s.strow[t & 1][single ? o.b0 + lane : 0], start = s.own[o.rows], kept = mine1 + s.bw[t & 1][single ? lane : 0];
+                u2 = tri_lse2(second ? __fadd_rn(start, w0) : LAST_NEG_INF, single ? kept : LAST_NEG_INF);
+                asm volatile("" : "+v"(bwr), "+v"(u2));
+            }
             lds_only_barrier();                                                   // B
             float val = LAST_NEG_INF, m[kTriMaxG], z[kTriMaxG];
             int src = 0xffff;
+            if (!AHEAD) {
 #pragma unroll
-            for (int g = 0; g < kTriMaxG; ++g) m[g] = pm[g * P + slot];
+                for (int g = 0; g < kTriMaxG; ++g) m[g] = pm[g * P + slot];
+            }
 #pragma unroll
             for (int g = 0; g < kTriMaxG; ++g) z[g] = ps[g * P + slot];
-            const float blr = s.bl[grow];
-            const float w0 = s.strow[t & 1][single ? o.b0 + lane : 0], start = s.own[o.rows], sbr = s.bl[single ? lane : 0];
+            const int far = AHEAD ? s.far[t & 1] : 0;
+            const float blr = AHEAD ? bwr : s.bl[grow];
+            const float w0 = AHEAD ? 0.f : s.strow[t & 1][single ? o.b0 + lane : 0], start = AHEAD ? 0.f : s.own[o.rows], sbr = AHEAD ? 0.f : s.bl[single ? lane : 0];
+            if (!AHEAD) {
 #pragma unroll
-            for (int g = 0; g < kTriMaxG; ++g) val = fmaxf(val, m[g]);
+                for (int g = 0; g < kTriMaxG; ++g) val = fmaxf(val, m[g]);
+            }
             if (TROP) {
 #pragma unroll
                 for (int g = 0; g < kTriMaxG; ++g) src = min(src, m[g] == val ? __float_as_int(z[g]) : 0xffff);
                 if (val == LAST_NEG_INF) src = 0xffff;
-            } else {
+            } else if (!AHEAD) {
                 const float mm = val == LAST_NEG_INF ? 0.f : val;
                 float zz = 0.f;
 #pragma unroll
                 for (int g = 0; g < kTriMaxG; ++g) zz += z[g] * tri_exp(m[g] - mm);
                 val = ln_sum(val, zz);
+            } else {
+                if (__builtin_expect(__builtin_amdgcn_readfirstlane(far), 0)) {
+                    top = LAST_NEG_INF;
+#pragma unroll
+                    for (int g = 0; g < kTriMaxG; ++g) { m[g] = pm[(t & 1) * pmz + g * P + slot]; top = fmaxf(top, m[g]); }
+                    const float mm = top == LAST_NEG_INF ? 0.f : top;
+#pragma unroll
+                    for (int g = 0; g < kTriMaxG; ++g) fz[AHEAD ? g : 0] = tri_exp(m[g] - mm);
+                }
+                float zz = 0.f, zy = 0.f;
+#pragma unroll
+                for (int g = 0; g < kTriMaxG; g += 2) {
+                    zz = fmaf(z[g], fz[AHEAD ? g : 0], zz);
+                    zy = fmaf(z[g + 1], fz[AHEAD ? g + 1 : 0], zy);
+                }
+                val = ln_sum(top, zz + zy);
             }
-            const float blg = act ? blr : LAST_NEG_INF;
+            const float blg = AHEAD || act ? blr : LAST_NEG_INF;
             // histories of one label: from the start state, or kept by the empty label; the start state: kept
-            const float sn = !second ? LAST_NEG_INF : __fadd_rn(start, w0);
-            const float sb = single ? sbr : LAST_NEG_INF;
+            const float sn = AHEAD || !second ? LAST_NEG_INF : __fadd_rn(start, w0);
+            const float sb = !AHEAD && single ? sbr : LAST_NEG_INF;
             float head = LAST_NEG_INF;
             u64 word = 0, hw = 0;
             if (a.K == 1) {
-                if (!TROP) head = wave_max_dpp(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), fmaxf(sn, sb)));
+                if (!TROP) head = tri_wave_max(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), AHEAD ? u2 : fmaxf(sn, sb)));
                 if (act) { s.xl[lidx] = val; s.xa[lidx] = src; }
                 if (lane == 0) s.hd[wave] = head;
                 lds_only_barrier();
@@ -394,10 +564,10 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 if (act) xpublish(tri_at(xs, oMine), TROP ? (u64)__float_as_uint(val) | ((u64)(unsigned)src << 32) | ((u64)(tag & 0xffffu) << 48)
                                              : pack_word(val, tag));
                 if (!TROP) {
-                    head = wave_max_dpp(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), fmaxf(sn, sb)));
+                    head = tri_wave_max(fmaxf(fmaxf(act ? val : LAST_NEG_INF, blg), AHEAD ? u2 : fmaxf(sn, sb)));
                     if (lane == 0) xpublish(tri_at(xs, oHead), pack_word(head, tag));
                 }
-                if (!dead) dead = !tri_poll<!TROP, TROP>(tri_at(xs, oGot), tri_at(xs, oHeads), act, tag, a.spin_limit, word, hw);
+                if (!dead) dead = !tri_poll<!TROP, TROP>(tri_at(xs, oGot), tri_at(xs, oHeads), act, tag, a.spin_limit, word, hw, a.K > 4);
                 val = __uint_as_float((unsigned)word);
                 src = (int)((word >> 32) & 0xffffu);
                 head = __uint_as_float((unsigned)hw);
@@ -419,12 +589,23 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 if (single) keep(sn, o.b0 + lane, sb, (o.b0 + lane) * V1, lane);
                 if (second && !single) keep(sn, 0, LAST_NEG_INF, 0, o.rows);
             } else {
-                float mx = wave_max_dpp(head);
+                float mx = tri_wave_max(head);
                 if (mx == LAST_NEG_INF) mx = 0.f;              // no state reachable: keep -inf everywhere
                 A += (double)mx;
-                if (act) s.own[grow] = tri_lse2(val, blg) - mx;
-                if (second) s.own[single ? lane : o.rows] = tri_lse2(sn, sb) - mx;
-                if (tid == 0) s.off = A;
+                if (act) {
+                    mine = tri_lse2(val, blg) - mx;
+                    if (AHEAD) s.ex[grow] = tri_exp(mine);
+                    s.own[grow] = mine;
+                }
+                if (second) {
+                    mine1 = (AHEAD ? u2 : tri_lse2(sn, sb)) - mx;
+                    if (AHEAD) s.ex[single ? lane : o.rows] = tri_exp(mine1);
+                    s.own[single ? lane : o.rows] = mine1;
+                }
+                if (tid == 0) {
+                    s.off = A;
+                    if (AHEAD) s.far[(t & 1) ^ 1] = 0;
+                }
             }
             if (dead) s.dead = 1;
             lds_only_barrier();                                                   // A
@@ -447,20 +628,29 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
     const bool comm = wave < NCM;
     const int V = o.V, V1 = o.V1, nbk = o.nbk, P = 4 * o.CQ;
     constexpr int BP = D::BtPitch;
+    constexpr bool AHEAD = D::Ahead;
     const int epl = (V1 + 3) / 4;
     float* bt = dyn;                              // [nbk + 1][BP] states (b0 + i, y) by i; [nbk]: histories of one label
-    float* tile = dyn + ((a.nb + 1) * BP + 3) / 4 * 4;   // [V + 1][P] weights of a frame
+    float* be = dyn + ((a.nb + 1) * BP + 3) / 4 * 4;     // their exponentials
+    float* tile = dyn + 2 * (((a.nb + 1) * BP + 3) / 4 * 4);   // [V + 1][P] weights of a frame, two of them
+    const int tilez = AHEAD ? V1 * P + kTriPad : 0;
     const size_t fr = (size_t)V1 * a.C;
     const float* wi = a.w + (size_t)b * a.T * fr;
     const int low = a.keep ? 1 : tri_meet(L, false);       // the last row this direction makes
     const int steps = max(L - low, 0);
     const int rows = o.rows + (o.k == 0 ? 1 : 0);          // the first workgroup also has the start state
 
-    for (int r = tid; r <= o.rows; r += D::NW * kWave) s.own[r] = 0.f;
+    for (int r = tid; r <= o.rows; r += D::NW * kWave) {
+        s.own[r] = 0.f;
+        s.ex[r] = 1.f;
+    }
     // (four lanes read at least V + 1 elements of a row; what they read past it counts for nothing)
-    for (int i = tid; i < (nbk + 1) * BP; i += D::NW * kWave) bt[i] = i % BP < V1 ? 0.f : LAST_NEG_INF;
-    for (int i = tid; i < V1 * P + kTriPad; i += D::NW * kWave) tile[i] = 0.f;
-    if (tid < 72) s.strow[0][tid] = 0.f;
+    for (int i = tid; i < (nbk + 1) * BP; i += D::NW * kWave) {
+        bt[i] = i % BP < V1 ? 0.f : LAST_NEG_INF;
+        be[i] = i % BP < V1 ? 1.f : 0.f;
+    }
+    for (int i = tid; i < (AHEAD ? 2 : 1) * (V1 * P + kTriPad); i += D::NW * kWave) tile[i] = 0.f;
+    if (tid < 72) s.strow[0][tid] = s.strow[1][tid] = 0.f;
     if (tid == 0) { s.dead = 0; s.off = 0.0; }
     __syncthreads();
 
@@ -500,48 +690,104 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
 #pragma unroll
             for (int x = 0; x < D::NR; ++x)
                 if (act && g + o.G * x <= V) {
-                    float* d = tile + (g + o.G * x) * P + col0;
+                    float* d = tile + Z * tilez + (g + o.G * x) * P + col0;
                     const float4 v = wv[Z][x];
                     if (col0 & 3) { d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w; }
                     else *(float4*)d = v;
                 }
             if (wave == D::NW - 1) {
-                if (lane <= V) s.strow[0][lane] = st[Z];
-                if (D::MaxV == 64) s.strow[0][V] = st64[Z];
+                if (lane <= V) s.strow[AHEAD ? Z : 0][lane] = st[Z];
+                if (D::MaxV == 64) s.strow[AHEAD ? Z : 0][V] = st64[Z];
             }
         };
         // four lanes a row: elements y = l epl .. l epl + epl - 1
         const int l = ct & 3;
         const float* rowP[D::NP];
         const float* btP[D::NP];
-        int rP[D::NP];
+        int rP[D::NP], rowZ[D::NP];
 #pragma unroll
         for (int p = 0; p < D::NP; ++p) {
             rP[p] = min((ct >> 2) + p * (D::CT / 4), rows - 1);
             const int ra = rP[p] / nbk, ri = rP[p] - ra * nbk;
             rowP[p] = (rP[p] == o.rows ? s.strow[0] : tile + ra * P + ri * V1) + l * epl;
+            rowZ[p] = !AHEAD ? 0 : rP[p] == o.rows ? (int)(sizeof(s.strow[0]) / sizeof(float)) : tilez;
             btP[p] = bt + (rP[p] == o.rows ? nbk : ri) * BP + l * epl;
         }
+        const int beOff = (int)(be - bt);
+        // e^(w - m) of a frame's rows, m a row's largest weight; ahead of the chain
+        float E[AHEAD ? D::NP : 1][D::EPL], mr[D::NP];
+        const int count = max(0, min(epl, V1 - l * epl));       // elements of the row in this lane
+        auto factors = [&](auto S) __attribute__((always_inline)) {
+            constexpr int Z = decltype(S)::value;
+            int have = count;
+            asm volatile("" : "+v"(have));                      // (no masks kept in scalar registers for all frames)
+#pragma unroll
+            for (int p = 0; p < (AHEAD ? D::NP : 1); ++p) {
+                const float* row = rowP[p] + Z * rowZ[p];
+                mr[p] = LAST_NEG_INF;
+#pragma unroll
+                for (int e = 0; e < D::EPL; ++e) {
+                    E[p][e] = e < have ? row[e] : LAST_NEG_INF;
+                    mr[p] = fmaxf(mr[p], E[p][e]);
+                }
+                mr[p] = tri_quad_max(mr[p]);
+                const float mm = mr[p] == LAST_NEG_INF ? 0.f : mr[p];
+#pragma unroll
+                for (int e = 0; e < D::EPL; ++e) E[p][e] = tri_exp(E[p][e] - mm);
+            }
+        };
         if (steps > 0) {
             issue(std::integral_constant<int, 0>(), 0);
             issue(std::integral_constant<int, 1>(), 1);
             spread(std::integral_constant<int, 0>());
             issue(std::integral_constant<int, 0>(), 2);
+            if (AHEAD) {
+                spread(std::integral_constant<int, 1>());
+                issue(std::integral_constant<int, 1>(), 3);
+            }
         }
         __syncthreads();
+        if constexpr (AHEAD)
+            if (steps > 0) factors(std::integral_constant<int, 0>());
         auto frame = [&](auto S, int n) __attribute__((always_inline)) {
             constexpr int Z = decltype(S)::value;
+            bool far = !AHEAD;
+            float rowv = 0.f;
+            double rowo = 0.0;
+            if constexpr (AHEAD) {
+                rowv = s.own[rS];
+                rowo = s.off;
+#pragma unroll
+                for (int p = 0; p < D::NP; ++p) {
+                    const int r = (ct >> 2) + p * (D::CT / 4);
+                    if (__builtin_amdgcn_readfirstlane(ct >> 2) + p * (D::CT / 4) >= rows) break;      // (no row for this wave)
+                    float z = 0.f, z1 = 0.f;
+#pragma unroll
+                    for (int e = 0; e < D::EPL; ++e) {
+                        float x = btP[p][beOff + e];
+                        if (e == 0) x = l == 0 ? s.ex[rP[p]] : x;                  // the empty label keeps the state
+                        if (e & 1) z1 = fmaf(E[p][e], x, z1);
+                        else z = fmaf(E[p][e], x, z);
+                    }
+                    z = tri_quad_sum(z + z1);
+                    far = far || (!(z >= kTriFar) && mr[p] != LAST_NEG_INF);
+                    if (l == 0 && r < rows) s.bl[r] = ln_sum(mr[p], z);
+                }
+                far = __any(far);
+            }
+            if (__builtin_expect(far, !AHEAD))
 #pragma unroll
             for (int p = 0; p < D::NP; ++p) {
                 const int r = (ct >> 2) + p * (D::CT / 4);
                 if (r < rows) {
+                    const float* row = rowP[p] + Z * rowZ[p];
                     float v[D::EPL], x[D::EPL], m = LAST_NEG_INF;
                     const float keep = s.own[r];                                   // the empty label keeps the state
                     constexpr int EH = D::EPL > 11 ? 9 : D::EPL;                   // (registers)
 #pragma unroll
                     for (int e0 = 0; e0 < D::EPL; e0 += EH) {
 #pragma unroll
-                        for (int e = e0; e < e0 + EH && e < D::EPL; ++e) { x[e] = rowP[p][e]; v[e] = btP[p][e]; }
+                        for (int e = e0; e < e0 + EH && e < D::EPL; ++e) { x[e] = row[e]; v[e] = btP[p][e]; }
                         if (e0 == 0) v[0] = l == 0 ? keep : v[0];
 #pragma unroll
                         for (int e = e0; e < e0 + EH && e < D::EPL; ++e) {
@@ -560,12 +806,22 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
                 }
                 if (D::EPL > 11) __builtin_amdgcn_sched_barrier(0);                // (one row's elements in registers at a time)
             }
-            store_row(L - n, a.keep);
+            if (!AHEAD) store_row(L - n, a.keep);
             lds_only_barrier();                                                    // B
             if (a.K == 1) lds_only_barrier();
-            // (the exchange is under way) the next frame into the tile, the requests for the frame two after it
-            spread(std::integral_constant<int, Z ^ 1>());
-            issue(std::integral_constant<int, Z ^ 1>(), n + 3);
+            // (the exchange is under way) the next frame into the tile, the requests for the frame two after it; or the factors of
+            // the next frame, the one after it into its tile, the requests for the frame two after that
+            if constexpr (AHEAD) {
+                const size_t row = a.keep ? (size_t)b * (a.T + 1) + (L - n) : (size_t)b;
+                buf_store(rowv, make_buf(a.beta + row * a.C, a.keep ? rowb : 0u), rq, 0);
+                nw_store64(rowo, make_buf(a.offb + row, a.keep ? 8u : 0u), oq, 0);
+                factors(std::integral_constant<int, Z ^ 1>());
+                spread(S);
+                issue(S, n + 4);
+            } else {
+                spread(std::integral_constant<int, Z ^ 1>());
+                issue(std::integral_constant<int, Z ^ 1>(), n + 3);
+            }
             lds_only_barrier();                                                    // A
         };
         for (int n = 0; n < steps; n += 2) {
@@ -600,7 +856,7 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
             u64 word = 0, hw = 0;
             float got, gots = LAST_NEG_INF;
             if (a.K == 1) {
-                head = wave_max_dpp(fmaxf(val, sv));
+                head = tri_wave_max(fmaxf(val, sv));
                 if (act) s.xl[(pa - 1) * V + pi] = val;
                 if (single) s.xl[V * V + lane] = sv;
                 if (lane == 0) s.hd[wave] = head;
@@ -611,7 +867,7 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
             } else {
                 if (act) xpublish(tri_at(xs, oMine), pack_word(val, tag));
                 if (single) xpublish(tri_at(xs, oSingle), pack_word(sv, tag));
-                head = wave_max_dpp(fmaxf(val, sv));
+                head = tri_wave_max(fmaxf(val, sv));
                 if (lane == 0) xpublish(tri_at(xs, oHead), pack_word(head, tag));
                 if (!dead) dead = !tri_poll<true, false>(tri_at(xs, oGot), tri_at(xs, oHeads), act, tag,
                                                          a.spin_limit, word, hw);
@@ -623,15 +879,23 @@ __device__ __forceinline__ void tri_backward(const TriArgs& a, const TriOwn& o, 
                     gots = __uint_as_float((unsigned)word);
                 }
             }
-            float mx = wave_max_dpp(head);
+            float mx = tri_wave_max(head);
             if (mx == LAST_NEG_INF) mx = 0.f;
             A += (double)mx;
             if (act) {
                 bt[gi * BP + gy] = got - mx;
+                if (AHEAD) be[gi * BP + gy] = tri_exp(got - mx);
                 s.own[prow] = val - mx;
+                if (AHEAD) s.ex[prow] = tri_exp(val - mx);
             }
-            if (starter && lane < V) bt[nbk * BP + 1 + lane] = gots - mx;
-            if (second && (single || o.k == 0)) s.own[single ? lane : o.rows] = sv - mx;
+            if (starter && lane < V) {
+                bt[nbk * BP + 1 + lane] = gots - mx;
+                if (AHEAD) be[nbk * BP + 1 + lane] = tri_exp(gots - mx);
+            }
+            if (second && (single || o.k == 0)) {
+                s.own[single ? lane : o.rows] = sv - mx;
+                if (AHEAD) s.ex[single ? lane : o.rows] = tri_exp(sv - mx);
+            }
             if (tid == 0) s.off = A;
             if (dead) s.dead = 1;
             lds_only_barrier();                                                    // A
