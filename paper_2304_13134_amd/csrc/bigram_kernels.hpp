@@ -1,5 +1,7 @@
-// Full 1-gram contexts of 5 (tropical: 4) to 96 states with dense weights: one
+// Full 1-gram contexts of 66 to 96 states with dense weights: one
 // workgroup per item and direction, no exchange between compute units.
+// (Up to 65 states the chain of frames runs in one wavefront, bigram_wave_kernels.hpp, with the arithmetic and the
+// joining kernel that are described here.)
 //
 // A frame is a C x C matrix; at these sizes one compute unit can stream it and
 // the recursions (Eq. 2 of arXiv 2304.13134, both directions, and the tropical
@@ -38,9 +40,7 @@
 // instead of 84 us.  The producers are the longer half of a frame.)
 // Marginals are formed afterwards from the stored vectors (marginals_kernels.hpp).
 //
-// Measured: last_arc_posteriors at B=8, T=200, V=32 0.15 ms (0.72 us a frame)
-// against 0.52 ms on the clustered kernel, the shortest path of one utterance
-// at T=150, V=47 0.10 against 0.26 ms.  Loops over a wave's rows run
+// Measured: figures beside bi_ok in last_api.hip.  Loops over a wave's rows run
 // over all RC of them: with a test per row the compiler kept every row's state alive
 // along every path and spilled by the thousand.
 #pragma once

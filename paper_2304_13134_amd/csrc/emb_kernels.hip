@@ -3,12 +3,12 @@
 // for the recursions of trigram_kernels.hpp, and the gradients of f, e and W from the vectors that those leave.
 //
 // The kernels of fused_kernels.hpp form the hidden vectors inside the chain of the recursion, three times, and send
-// them through LDS.  Here nothing but the recursion (2.1 us a frame) is serial: the hidden units, of which there are H / (V+1)
+// them through LDS.  Here nothing but the recursion (2.0 us a frame) is serial: the hidden units, of which there are H / (V+1)
 // for every arc, are formed at the rate of the vector ALU by the whole chip, in the registers of the lane that feeds them to
 // the matrix cores, once for the weights and once for the gradients.  4 bytes an arc are written once and read three times
-// (by both directions and for the gradients; once for a distance, whose directions meet in the middle): 1.35 of 11.75 ms.
-// 16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 11.75 ms (weights 1.9, recursions 2.2,
-// gradients 7.0); distance of 4 items, 1000 frames, 64 labels 7.4 -> 3.94 ms (weights 2.3, recursions 1.6).
+// (by both directions and for the gradients; once for a distance, whose directions meet in the middle): 1.35 of 11.0 ms.
+// 16 items, 1024 frames, 32 labels, 512 hidden units: loss with gradients 42.3 -> 11.0 ms (weights 1.75, recursions 2.0,
+// gradients 6.9); distance of 4 items, 1000 frames, 64 labels 7.4 -> 3.94 ms (weights 2.4, recursions 1.6).
 //
 // In the weights tanh(f + e) = 1 - 2 / (1 + e^2f e^2e), with e^2f and e^2e formed once per element of f and e, is a product
 // and a sum in one instruction, one reciprocal and one more instruction.  Both factors are held within e^+-80: where |f| or

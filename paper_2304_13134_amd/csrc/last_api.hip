@@ -971,7 +971,8 @@ struct BiWs {
     int* wide;           // call without marginals
 };
 
-// Full 1-gram contexts, one workgroup per item and direction (bigram_kernels.hpp), against the cluster at 96 states,
+// Full 1-gram contexts without an exchange between compute units: one wavefront's chain up to 65 states (bw_ok,
+// bigram_wave_kernels.hpp), one workgroup per item and direction above (bigram_kernels.hpp).  The latter against the cluster at 96 states,
 // the most the tiles hold, 75 to 100 frames, B=1 / 16 / 64 / 128, us: marginals 184 / 223 / 279 / 384 against
 // 247 / 285 / 667 / 1346, distance 102 / 125 / 126 / 164 against 114 / 133 / 311 / 761, path 148 / 168 / 171 / 175 against
 // 170 / 193 / 195 / 397.  With tiles for 101 states the registers no longer hold the pieces in flight: 16 items of 200 frames
@@ -1584,12 +1585,16 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     return hip_status();
 }
 
+// Beside the clusters of a bigram's denominator (beside) two waves: the check of references of up to 512 labels is hidden there
+// however long it takes, and the sooner the gather reads the same weights, the more the clusters lose.  Loss of 16 items, 500 frames, 256 labels
+// 1.532 ms with 128 threads, 1.540 with 256 or 1024; small denominators wait for their numerator.
 static void launch_num_check(const Shape& s, const int* lengths, const int* refs, const int* ref_lengths, int Umax, const NumWs& p,
-                             const int* flag, hipStream_t st)
+                             const int* flag, bool beside, hipStream_t st)
 {
+    const int threads = beside && s.order == 1 && s.C > kBiMaxC && Umax <= 512 ? 2 * kWave : kNcThreads;
     const bool table = s.order == 0 && (size_t)s.C * s.V <= (size_t)kNcTable;
     const size_t lds = ((size_t)Umax + 1 + (table ? (size_t)s.C * s.V : 0)) * sizeof(int);
-    hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(kNcThreads), lds, st, lengths, refs, ref_lengths, make_ctx(s), s.T, Umax,
+    hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(threads), lds, st, lengths, refs, ref_lengths, make_ctx(s), s.T, Umax,
                        p.status, p.ctxs, p.link, flag, (int)table);
 }
 
@@ -1660,7 +1665,7 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
         const dim3 block(kFnWaves * kWave);
         const int ugrid = (U1 + kFnWaves - 1) / kFnWaves;
         if (prepare) {
-        launch_num_check(s, lengths, refs, ref_lengths, Umax, p, nullptr, st);
+        launch_num_check(s, lengths, refs, ref_lengths, Umax, p, nullptr, false, st);
         hipLaunchKernelGGL(fnum_transpose_w_kernel, dim3((s.V1 * H + 255) / 256), dim3(256), 0, st,
                            (const __bf16*)weights->W, H, s.V1, Wt);
         if (s.T > 0)
@@ -1715,7 +1720,7 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
     };
     if (prepare) {
     if (flag) launch_table_check(s, flag, st);
-    launch_num_check(s, lengths, refs, ref_lengths, Umax, p, flag, st);
+    launch_num_check(s, lengths, refs, ref_lengths, Umax, p, flag, phases == kNumPrepare, st);
     if (s.T > 0) {
         if (local)
             with_pieces([&](auto QL) {

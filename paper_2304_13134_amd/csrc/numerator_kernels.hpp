@@ -44,7 +44,7 @@ __device__ __forceinline__ int clamp_label(int y, int V) { return y < 1 ? 1 : (y
 // and a next-state table of up to kNcTable entries is walked in LDS: 150 labels 25 -> 9 us, 60 labels 13 -> 4.7 us, 80 labels through a table
 // of 585 x 8 entries 27 -> 12 us, against a thread per cell that looked through global memory and a walk of
 // dependent loads.  LDS: int[U1] contexts (fewer than 4096 labels), then int[C V] the table (table_lds).
-constexpr int kNcThreads = 1024;
+constexpr int kNcThreads = 1024;        // at most; whole waves
 constexpr int kNcTable = 12032;         // 47 KiB, beside the 16 of the contexts
 __global__ __launch_bounds__(kNcThreads) void num_check_kernel(const int* __restrict__ len, const int* __restrict__ refs,
                                  const int* __restrict__ ulen, Ctx c, int T, int Umax,
@@ -63,14 +63,14 @@ __global__ __launch_bounds__(kNcThreads) void num_check_kernel(const int* __rest
     int* q_s = nc_s;
     int* nx_s = nc_s + U1;
     if (table_lds)
-        for (int i = tid; i < c.C * c.V; i += kNcThreads) nx_s[i] = min((unsigned)c.nx[i], (unsigned)(c.C - 1));
+        for (int i = tid; i < c.C * c.V; i += blockDim.x) nx_s[i] = min((unsigned)c.nx[i], (unsigned)(c.C - 1));
     int code = kItemOk;
     __syncthreads();
     if (wrong) code = kItemBadTable;
     else if (L < 0 || L > T) code = kItemBadLength;
     else if (U < 0 || U > Umax) code = kItemBadRefLength;
     else {
-        for (int u = tid; u < U; u += kNcThreads) {
+        for (int u = tid; u < U; u += blockDim.x) {
             const int y = r[u];
             if (y < 1 || y > c.V) atomicOr(&bad, 1);
             else if (c.order == 0) q_s[u + 1] = y;        // (labels, until the walk comes by)
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kNcThreads) void num_check_kernel(const int* __rest
     if (code == kItemOk && U > L) code = kItemInfeasible;
     if (tid == 0) status[b] = code;
     if (code != kItemOk && code != kItemInfeasible) {
-        for (int u = tid; u < U1; u += kNcThreads) cx[u] = -1;
+        for (int u = tid; u < U1; u += blockDim.x) cx[u] = -1;
         return;
     }
     if (c.order == 0) {
@@ -96,19 +96,19 @@ __global__ __launch_bounds__(kNcThreads) void num_check_kernel(const int* __rest
             }
         }
         __syncthreads();
-        for (int u = tid; u <= U; u += kNcThreads) cx[u] = q_s[u];
+        for (int u = tid; u <= U; u += blockDim.x) cx[u] = q_s[u];
     } else {
-        for (int u = tid; u <= U; u += kNcThreads) {
+        for (int u = tid; u <= U; u += blockDim.x) {
             const int q = ref_context(c, r, u);
             q_s[u] = q;
             cx[u] = q;
         }
     }
-    for (int u = U + 1 + tid; u < U1; u += kNcThreads) cx[u] = -1;
+    for (int u = U + 1 + tid; u < U1; u += blockDim.x) cx[u] = -1;
     __syncthreads();
     int* lk = link + (size_t)b * U1 * 2;
     const int lane = tid & (kWave - 1);
-    for (int u = tid / kWave; u < U1; u += kNcThreads / kWave) {        // (uniform in a wave)
+    for (int u = tid / kWave; u < U1; u += blockDim.x / kWave) {        // (uniform in a wave)
         int nxt = -1, head = 1;
         if (u <= U) {
             const int q = q_s[u];

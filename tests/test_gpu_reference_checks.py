@@ -54,3 +54,21 @@ def test_tables_in_and_out_of_lds(C, V):
     lb.check_item_status()
     assert np.max(np.abs(ll.cpu().numpy() - o["N"]) / np.maximum(1, np.abs(o["N"]))) < 1e-5
     assert np.max(np.abs(g.cpu().numpy() - o["grad"])) < 1e-5
+
+
+# beside the clusters of a denominator the check runs on two waves for references of up to 512 labels
+@pytest.mark.parametrize("U", [1, 130, 512, 513])
+def test_check_beside_a_clustered_denominator(U):
+    announce("reference check beside a clustered denominator: labels, reference length", 100, U)
+    rng = np.random.default_rng(U)
+    B, T, V = 2, U + 4, 100
+    w = rng.normal(size=(B, T, V + 1, V + 1)).astype(np.float32)
+    refs = rng.integers(1, V + 1, size=(B, U)).astype(np.int32)
+    refs[1, ::2] = 7
+    args = dev(w), dev(np.array([T, T - 2], np.int32)), dev(refs), dev(np.array([U, max(U - 3, 0)], np.int32))
+    _, N, g = lb.last_globally_normalized_loss(*args, order=1)
+    lb.check_item_status()
+    g2 = torch.empty_like(g)
+    lb.last_arc_posteriors(*args[:2], order=1, dw=g2)
+    assert torch.equal(N, lb.last_intersect_reference(*args, order=1, dw=g2, scale=-1.0, accumulate=True))
+    assert float((g - g2).abs().max()) < 2e-5
