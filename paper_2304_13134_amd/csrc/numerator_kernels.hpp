@@ -203,11 +203,16 @@ __device__ __forceinline__ double num_wave_sum(double x)
     return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
 }
 
-// e^x for x <= 0, the argument of exp2 reduced to [-1/2, 1/2] (its rounding would be the largest error)
+// e^x for x <= 0, with the error of expf (2.6e-8 rms, 8e-8 at most): the argument of exp2 is reduced to [-1/2, 1/2] and what
+// the product with log2 e is rounded by goes with it.  Below -150 it is 0: the reduction does not hold for masks of -1e10 (what a
+// product is rounded by is no small number there), lowest values (the product is not finite) and -inf.  NaN stays NaN.
 __device__ __forceinline__ float num_exp(float x)
 {
-    const float h = rintf(x * kLog2e), f = fmaf(x, 1.925963033500e-8f, fmaf(x, kLog2e, -h));       // log2 e - (float)log2 e
-    return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)fmaxf(h, -200.f));
+#pragma clang fp contract(off)
+    const float y = x < -150.f ? -150.f : x;
+    const float p = y * kLog2e, h = rintf(p);
+    const float f = (p - h) + fmaf(y, 1.925963033500e-8f, fmaf(y, kLog2e, -p));      // log2 e - (float)log2 e
+    return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)h);
 }
 
 // Locally normalised variant of the gather: a wavefront takes kNlFrames neighbouring frames of one u,

@@ -57,3 +57,36 @@ def test_long_rows_and_chains(V, C):
     base = torch.full_like(w, 0.25)
     lb.last_local_log_likelihood(w, lengths, r, n, order=g0, dw=base, scale=-2.0, accumulate=True)
     assert torch.max(torch.abs(base - (0.25 - 2.0 * g))).item() < 1e-6
+
+
+# arcs that do not exist and masks: lowest values, and some whose product with log2 e leaves float32 or its whole numbers; rows of one or
+# two pieces a lane, of more, and of less than one.  The weights of what the reference reads stay, so that the likelihood is finite.
+@pytest.mark.parametrize("V", [3, 4, 255, 256, 511, 512, 799])
+@pytest.mark.parametrize("mask", [-np.inf, float(np.finfo(np.float32).min), -1.0e30, -1.3e10])
+def test_missing_and_masked_arcs(V, mask):
+    announce("local rows: masked arcs: V, mask", V, mask)
+    T, U = 7, 4
+    cfg = workloads.config(3, B=3, T=T, V=V, order=1, Umax=U, u_lo=1, u_hi=U)
+    cfg["lengths"] = np.array([T, T - 1, 5], np.int32)
+    cfg["ref_lengths"] = np.array([U, 2, 0], np.int32)
+    shape = cfg["w"].shape
+    hide = np.random.default_rng(V).random(shape) < 0.4
+    hide[:, :, :, 0] = False
+    for b in range(3):
+        for r in cfg["refs"][b]:
+            hide[b, :, :, r] = False
+    cfg["w"][hide] = mask
+    unread = np.setdiff1d(np.arange(1, V + 1), cfg["refs"][0])
+    if unread.size:
+        cfg["w"][0, :, unread[0]] = mask                        # a row that no path visits has none at all
+    w, lengths, refs, ulen = (dev(cfg[k]) for k in ("w", "lengths", "refs", "ref_lengths"))
+    lo = oracle.numerator_local(cfg["w"], cfg["lengths"], cfg["refs"], cfg["ref_lengths"], 1)
+    assert np.all(np.isfinite(lo["N"])) and np.all(np.isfinite(lo["grad"]))
+    g = torch.full_like(w, 7.0)
+    ll = lb.last_local_log_likelihood(w, lengths, refs, ulen, order=1, dw=g)
+    lb.check_item_status()
+    assert_dist_close(ll.cpu().numpy(), lo["N"])
+    assert np.max(np.abs(g.cpu().numpy() - lo["grad"])) <= TOL_POST_ABS
+    base = torch.full_like(w, 0.25)
+    lb.last_local_log_likelihood(w, lengths, refs, ulen, order=1, dw=base, accumulate=True)
+    assert np.max(np.abs(base.cpu().numpy() - 0.25 - lo["grad"])) <= TOL_POST_ABS
