@@ -26,7 +26,7 @@ constexpr int kTpPieces = kTpMaxArcs / 4 / kTpThreads;
 __host__ __device__ inline size_t tp_lds(int C, int V1)
 {
     const size_t n = (size_t)C * V1, pad = (n + 8) & ~(size_t)3;
-    return (2 * pad + n + 2 * ((size_t)C + 1) + 2 * (size_t)C + 2 + 64) * sizeof(float);
+    return (2 * pad + n + 2 * (size_t)C + 2 * (size_t)C + 2 + 64) * sizeof(float);
 }
 
 // over the LPR lanes of a row
@@ -49,7 +49,7 @@ __device__ __forceinline__ void table_pull(const TabArgs& a, const Ctx& c)
     constexpr int NT = kTpThreads, NW = NT / kWave, NQ = kTpPieces;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int C = c.C, V1 = c.V1, n = C * V1, pad = (n + 8) & ~3, CP = C + 1;
+    const int C = c.C, V1 = c.V1, n = C * V1, pad = (n + 8) & ~3;
     const int L = a.len[b];
     const bool badtab = a.bad && a.bad[0] != 0;
     if (L < 0 || L > a.T || badtab) {
@@ -65,8 +65,8 @@ __device__ __forceinline__ void table_pull(const TabArgs& a, const Ctx& c)
     const float* wi = a.w + (size_t)b * a.T * n;
     float* const tile = tp_s;                               // [2][pad] weights; [n]: a weight that is none
     unsigned* const list = (unsigned*)(tile + 2 * pad);     // [n] arc | other state << 16, by state
-    float* const vec = (float*)(list + n);                  // [2][CP] states; [C]: one that cannot be reached
-    int* const start = (int*)(vec + 2 * CP);                // [C + 1] first arc of a state
+    float* const vec = (float*)(list + n);                  // [2][C]
+    int* const start = (int*)(vec + 2 * C);                 // [C + 1] first arc of a state
     int* const cnt = start + C + 1;                         // [C]
     float* const red = (float*)(cnt + C + 1);               // [2][NW]
     __shared__ int sums[NW];
@@ -153,21 +153,19 @@ __device__ __forceinline__ void table_pull(const TabArgs& a, const Ctx& c)
         }
     }
     for (int d = tid; d < C; d += NT) vec[d] = back || d == 0 ? 0.f : LAST_NEG_INF;
-    if (tid < 2) vec[tid * CP + C] = LAST_NEG_INF;
     __syncthreads();
     if (tid < 8) {
         if (n + tid < pad) tile[n + tid] = tile[pad + n + tid] = LAST_NEG_INF;
     }
 
-    // this lane's share of its row; what it has not is the weight that is none from the state that cannot be reached (a real
-    // state may be NaN, where weights of no account are)
+    // this lane's share of its row
     const int lpr = a.lpr, l = tid & (lpr - 1), row = tid / lpr;
     const bool mine = row < C;
     const int first = mine ? start[row] + l : 0, last = mine ? start[row + 1] : 0;
     unsigned wOff[kTpArcs], oOff[kTpArcs];                  // bytes
 #pragma unroll
     for (int i = 0; i < kTpArcs; ++i) {
-        const unsigned e = first + lpr * i < last ? list[first + lpr * i] : (unsigned)n | (unsigned)C << 16;
+        const unsigned e = first + lpr * i < last ? list[first + lpr * i] : (unsigned)n;
         wOff[i] = 4u * (e & 0xffffu);
         oOff[i] = 4u * (e >> 16);
     }
@@ -192,8 +190,8 @@ __device__ __forceinline__ void table_pull(const TabArgs& a, const Ctx& c)
     auto frame = [&](auto S, int k) __attribute__((always_inline)) {
         constexpr int Z = decltype(S)::value;
         const float* const w = tile + Z * pad;
-        const float* const old = vec + Z * CP;
-        float* const now = vec + (Z ^ 1) * CP;
+        const float* const old = vec + Z * C;
+        float* const now = vec + (Z ^ 1) * C;
         // the largest entry of the vector at hand
         if (k > 0) {
             float x = red[Z * NW];
@@ -253,7 +251,7 @@ __device__ __forceinline__ void table_pull(const TabArgs& a, const Ctx& c)
         frame(I0(), k);
         frame(I1(), k + 1);
     }
-    const float* const end = vec + (steps & 1) * CP;
+    const float* const end = vec + (steps & 1) * C;
     if (!a.keep) {
         if (steps > 0) put(back ? a.beta : a.alpha, back ? a.offb : a.offa, 0, end);
         return;

@@ -78,25 +78,3 @@ def test_status_and_a_bad_table():
     table[3, 3] = C
     D, g = lb.last_arc_posteriors(dev(w), dev(lengths), order=dev(table), item_status=status)
     assert status.cpu().tolist() == [7] * 4 and torch.isnan(D).all()
-
-
-# 4 to 64 lanes have places that hold no arc; state 0 is left after the first frame, and NaN on half of its arcs from then on counts nowhere
-@pytest.mark.parametrize("C,V", [(1024, 6), (300, 15), (61, 60), (50, 63)])
-def test_weights_of_a_state_that_is_left(C, V):
-    announce("table lists: NaN on the arcs of a state that is left: states, labels", C, V)
-    T = 98
-    rng = np.random.default_rng(C)
-    table = np.maximum(workloads.random_table(C, V, 4), 1)
-    w = rng.normal(size=(2, T, C, V + 1)).astype(np.float32)
-    w[:, 0, 0, 0] = -np.inf
-    lengths = np.array([T, T - 1], np.int32)
-    oracle.set_next_table(table)
-    want = oracle.forward(w, lengths, 0)[1]
-    grad = oracle.posteriors(w, lengths, 0)
-    w[:, 1:, 0, ::2] = np.nan
-    wd, ld, td = dev(w), dev(lengths), dev(table)
-    D, g = lb.last_arc_posteriors(wd, ld, order=td)
-    lb.check_item_status()
-    assert_dist_close(D.cpu().numpy(), want)
-    g[:, 0, 0, 0] = 0.0                                       # (-inf on the arc into the very state whose scores are NaN)
-    assert np.max(np.abs(g.cpu().numpy() - grad)) <= TOL_POST_ABS
