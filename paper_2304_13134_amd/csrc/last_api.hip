@@ -21,7 +21,6 @@
 #include "bigram_kernels.hpp"
 #include "bigram_wave_kernels.hpp"
 #include "table_chain_kernels.hpp"
-#include "table_pull_kernels.hpp"
 #include "emb.hpp"
 #include <algorithm>
 
@@ -1006,20 +1005,6 @@ last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const in
     a.w = w; a.len = lengths; a.bad = flag; a.alpha = c.alpha; a.beta = c.beta; a.offa = c.offa; a.offb = c.offb;
     a.D2 = c.D2; a.dist = dist; a.item_status = item_status; a.bp = bp; a.final_state = final_state;
     a.T = s.T; a.keep = keep;
-    // lists of arcs instead of atomics, where arcs are many (a thread of table_chain_kernel then has more than three) and frames pay for
-    // the lists (some 10 us an item).  Marginals of 4 items: 48 frames, 150 states, 20 labels 122 -> 103 us, 60 frames, 400
-    // states, 9 labels 150 -> 133, 1000 states, 6 labels 181 -> 166, 150 states, 40 labels 204 -> 162, of 8 items of 200 frames, 585
-    // states, 8 labels 538 -> 381, distance of 96 frames, 120 states, 60 labels 159 -> 152; but 48 frames, 400 states, 5 labels
-    // 92 -> 102, 100 frames, 150 states, 12 labels 171 -> 173, 20 frames, 24 states, 60 labels 46 -> 53
-    const size_t arcs = (size_t)s.C * s.V1;
-    if (!trop && s.C <= kTpMaxStates && arcs >= (size_t)kTpMinArcs && arcs <= (size_t)kTpMaxArcs && (keep ? s.T : s.T / 2) >= kTpMinFrames) {
-        a.lpr = 1;                               // a row's lanes: about four arcs each, as long as all rows have theirs
-        while (a.lpr < 64 && a.lpr * 2 * s.C <= kTpThreads && a.lpr * 4 < s.V1) a.lpr *= 2;
-        const size_t lds = tp_lds(s.C, s.V1);
-        const last_status_t rc = allow_lds((const void*)table_pull_kernel, kBigLds - 1024);
-        if (rc == LAST_OK) hipLaunchKernelGGL(table_pull_kernel, dim3(s.B, 2), dim3(kTpThreads), lds, st, a, make_ctx(s));
-        return rc;
-    }
     a.lpr = 1;                                   // lanes per row: as many as the workgroup has for its rows
     while (a.lpr < 64 && a.lpr * 2 * s.C <= 2 * kTabThreads && a.lpr * 4 < s.V1) a.lpr *= 2;
     const size_t lds = tab_lds(s.C, s.V1, trop);
