@@ -149,10 +149,11 @@ __device__ __forceinline__ float tri_wave_max(float v)
 
 // One look after the other at this lane's word (and, with HEAD, at one header word) until the tags are
 // right in every lane of the wave; false when the bound is reached.  The tropical waves look right after they have
-// published: a first look that leaves 256 clocks later (`later`: clusters of more than four workgroups) is answered when there
-// is something to see, one that leaves at once has to be sent again (28 labels, 7 workgroups 1.34 -> 1.25 us a frame; 16 labels,
-// 2 workgroups 132 -> 139 us for 100 frames; the others form their header word meanwhile, and are slower for any such
-// wait, 1.47 -> 1.60; with two looks under way both are slower).
+// published: in clusters of more than four workgroups (`later`) a first look that leaves 256 clocks later is answered when there
+// is something to see, one that leaves at once has to be sent again.  Paths of 200 frames, 1 and 4 items, without and with the delay:
+// 22 labels on 5 workgroups 291 / 274 us, 28 labels on 7 304 / 287; but 16 labels on 2, 100 frames, 132 / 139.  The others
+// form their header word meanwhile, and are slower for any such wait (1.47 -> 1.60 us a frame).  With two looks under
+// way both are slower; so are later looks without the pause between them (28 labels 287 -> 289).
 template <bool HEAD, bool TAG16>
 __device__ __forceinline__ bool tri_poll(const u64* wp, const u64* hp, bool act, unsigned tag, int limit,
                                          u64& word, u64& head, bool later = false)
@@ -165,7 +166,7 @@ __device__ __forceinline__ bool tri_poll(const u64* wp, const u64* hp, bool act,
         ok = ok || !act;
         if (HEAD) ok = ok && (unsigned)(head >> 32) == tag;
         if (__all(ok)) return true;
-        if (!TAG16 || !later) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_s_sleep(1);
     }
     return false;
 }
@@ -236,7 +237,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
 
     for (int r = tid; r < D::States + 32; r += D::NW * kWave) {
         s.own[r] = r == o.rows ? 0.f : LAST_NEG_INF;
-        s.ex[r] = r == o.rows ? 1.f : 0.f;
+        if (AHEAD) s.ex[r] = r == o.rows ? 1.f : 0.f;
     }
     for (int i = tid; i < kTriMaxG * P; i += D::NW * kWave) {      // groups that do not exist stay neutral
         pm[i] = LAST_NEG_INF;
