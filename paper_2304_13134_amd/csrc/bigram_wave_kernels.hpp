@@ -733,8 +733,11 @@ __global__ __launch_bounds__(kBpWaves * kWave) void bigram_bp_kernel(const float
             const int y = min(lane + 1, C - 1);                 // this lane's state (the start state: lane 0 too)
             const float s0 = __int_as_float(bp[row * C]), sy = __int_as_float(bp[row * C + y]);
             const float wb = wt[(size_t)y * C], w00 = wt[0];
-            float best = __fadd_rn(s0, wt[y]);
-            int src = best == LAST_NEG_INF ? -1 : 0;
+            // (what is no number, an arc out of a state that no path is in, is no candidate: the chain's maxima pass over it)
+            const float x0 = __fadd_rn(s0, wt[y]);
+            const bool any = x0 > LAST_NEG_INF;
+            float best = any ? x0 : LAST_NEG_INF;
+            int src = any ? 0 : -1;
             constexpr int UN = 8;
             for (int k0 = 1; k0 < C; k0 += UN) {
                 float v[UN];
@@ -750,7 +753,7 @@ __global__ __launch_bounds__(kBpWaves * kWave) void bigram_bp_kernel(const float
                     src = up ? k : src;
                 }
             }
-            const float xb = __fadd_rn(sy, wb), xs = __fadd_rn(s0, w00);
+            const float xk = __fadd_rn(sy, wb), xb = xk > LAST_NEG_INF ? xk : LAST_NEG_INF, xs = __fadd_rn(s0, w00);
             const int fl = best == LAST_NEG_INF ? 0x7fffffff : src * C + y, fb = xb == LAST_NEG_INF ? 0x7fffffff : y * C;
             const bool label = best > xb || (best == xb && fl < fb);
             const int flat = label ? fl : fb, arc = flat == 0x7fffffff ? -1 : flat;
@@ -759,7 +762,7 @@ __global__ __launch_bounds__(kBpWaves * kWave) void bigram_bp_kernel(const float
                 prev[t - lo][y] = (unsigned char)bt_prev_state(arc, C, C);
             }
             if (lane == 0) {
-                bp[row * C] = xs == LAST_NEG_INF ? -1 : 0;
+                bp[row * C] = xs > LAST_NEG_INF ? 0 : -1;
                 prev[t - lo][0] = 0;
             }
         }

@@ -57,3 +57,22 @@ def test_paths_of_many_segments(V):
     w = rng.integers(-2, 3, size=(2, T, C, C)).astype(np.float32)          # (ties everywhere)
     w[rng.random(w.shape) < 0.2] = -np.inf
     check_path(dict(w=w, lengths=np.array([T, 1111], np.int32), B=2))
+
+
+@pytest.mark.parametrize("V", [3, 8, 31, 48, 64])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_paths_past_weights_that_count_nowhere(V, value):
+    announce("one-wave bigram, paths, weights of states that no path is in: V, value", V, value)
+    rng = np.random.default_rng(V)
+    B, T, C = 3, 41, V + 1
+    for kind in range(3):
+        w = rng.normal(size=(B, T, C, C)).astype(np.float32)
+        if kind == 2:
+            w[:, 0, 0, 0] = -np.inf                          # the start state is left at once
+        nowhere = w[:, 1:, 0] if kind == 2 else w[:, 0, 1:]
+        lengths = np.array([T, T - 1, 7], np.int32)
+        want = oracle.viterbi(w, lengths, 1, "f32")
+        nowhere[rng.random(nowhere.shape) < (0.4 if kind == 0 else 1.0)] = value
+        got = lb.last_shortest_path(dev(w), dev(lengths))
+        for g, x in zip(got, want):
+            assert np.array_equal(g.cpu().numpy(), x)
