@@ -576,7 +576,7 @@ __global__ __launch_bounds__(kBwThreads) void bigram_wave_kernel(BiArgs a)
                 A += (double)rel;
             };
             // what a distance alone notes (see bigram_kernels.hpp)
-            bool was_thin = false, unburied = false, unburied_small = false;
+            bool was_thin = false, unburied = false, unburied_small = false, none = false;      // none: a score is no number, nor is the sum then
             const float not_thin = mine ? 0.f : __builtin_inff();
             const unsigned not_small = mine ? 0u : ~0u;
             unsigned small = ~0u, small0 = ~0u;
@@ -647,6 +647,7 @@ __global__ __launch_bounds__(kBwThreads) void bigram_wave_kernel(BiArgs a)
                     if (!KEEP) look(v, v0, M);
                 }, [&](int t0, int nf) __attribute__((always_inline)) { ended((size_t)b * (a.T + 1) + t0, nf, false); });
                 put_row(v, v0, steps, A);
+                none = __any(v != v) || v0 != v0;
                 if (KEEP) {
                     // all states of the last frame are final with weight 0
                     double z = single ? (double)v : 0.0;
@@ -695,9 +696,10 @@ __global__ __launch_bounds__(kBwThreads) void bigram_wave_kernel(BiArgs a)
                     }
                 }, [&](int n0, int nf) __attribute__((always_inline)) { ended((size_t)b * (a.T + 1) + (L - 1 - n0), nf, true); });
                 if (!KEEP && steps > 0) put_row(x, x0, L - steps, A);
+                none = __any(x != x) || x0 != x0;
             }
             if (!KEEP) {
-                const int f = (unburied ? 1 : 0) | (unburied_small ? 2 : 0);
+                const int f = none ? 0 : (unburied ? 1 : 0) | (unburied_small ? 2 : 0);
                 if (lane == 0) a.wide[(size_t)b * 2 + (BACK ? 1 : 0)] = f;
             }
         }

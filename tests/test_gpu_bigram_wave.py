@@ -76,3 +76,17 @@ def test_paths_past_weights_that_count_nowhere(V, value):
         got = lb.last_shortest_path(dev(w), dev(lengths))
         for g, x in zip(got, want):
             assert np.array_equal(g.cpu().numpy(), x)
+
+
+@pytest.mark.parametrize("V", [4, 9, 32, 47, 64])
+def test_distance_of_weights_that_are_no_number(V):
+    announce("one-wave bigram, distance, NaN on the arcs of a state that is left: V", V)
+    rng = np.random.default_rng(V)
+    B, T, C = 3, 31, V + 1
+    w = rng.normal(size=(B, T, C, C)).astype(np.float32)
+    w[:2, 0, 0, 0] = -np.inf
+    w[:2, 1:, 0] = np.nan
+    lengths = np.array([T, T - 1, T], np.int32)
+    got = lb.last_shortest_distance(dev(w), dev(lengths)).cpu().numpy()
+    assert np.isnan(got[:2]).all()                           # (0 times NaN: never a number that looks like a distance)
+    assert_dist_close(got[2:], oracle.forward(w[2:], lengths[2:], 1)[1])
