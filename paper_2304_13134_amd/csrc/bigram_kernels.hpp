@@ -1,7 +1,7 @@
 // Full 1-gram contexts of 66 to 96 states with dense weights: one
 // workgroup per item and direction, no exchange between compute units.
 // (Up to 65 states the chain of frames runs in one wavefront, bigram_wave_kernels.hpp, with the arithmetic and the
-// joining kernel that are described here.)
+// joining kernel that are described here; paths and distances of many items stay here, see bw_ok in last_api.hip.)
 //
 // A frame is a C x C matrix; at these sizes one compute unit can stream it and
 // the recursions (Eq. 2 of arXiv 2304.13134, both directions, and the tropical

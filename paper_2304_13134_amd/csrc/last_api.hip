@@ -1024,8 +1024,24 @@ last_status_t launch_tab(const Shape& s, const BiWs& c, const float* w, const in
     return rc;
 }
 
-// Up to 64 labels: the chain in one wavefront (bigram_wave_kernels.hpp).
-bool bw_ok(const Shape& s) { return s.V <= kBwMaxV; }
+// Up to 64 labels: the chain in one wavefront (bigram_wave_kernels.hpp), as long as its workgroups, of which a compute unit holds one,
+// are not so many that bigram_kernel's, of which it holds up to eight, are through sooner, and for paths (bp) as long as the
+// weights, which are read a second time for the sources, are not what counts.  100 frames, bigram_kernel / one wave, us:
+//   path      16 labels  256 items 62 / 50, 512 76 / 85;  28 labels 224 items 62 / 59, 256 62 / 62, 31 labels 256 items 62 / 63;
+//             47 labels 96 items 74 / 72, 112 74 / 76, 63 labels 64 items 82 / 79, 80 82 / 84;  64 labels 192 items 172 / 137, 256 175 / 180
+//   best score alone  33 labels 256 items 75 / 48, 512 items 0.98 times as fast, 1024 0.87; 47 labels 1.47, 0.93, 1.08
+//   distance  16 labels 256 items 36.5 / 34.9, 512 60 / 67;  31 labels 128 items 35 / 25, 160 36.0 / 36.3, 512 60 / 73;
+//             40 labels 512 items 107 / 107, 1024 193 / 212;  63 labels 192 items 76 / 72, 256 81 / 85, 512 162 / 189
+// With 32 and with 64 labels bigram_kernel has the tiles of 48 and 96 states and is 1.2 to 2.6 times slower at any number of items
+// (distance); marginals, most of their call, 0.99 to 3 times as fast with one wave for all of 4 to 64 labels, 32 to 1024 items.
+bool bw_ok(const Shape& s, bool trop, bool keep, bool bp)
+{
+    if (s.V > kBwMaxV) return false;
+    if (keep) return true;
+    if (bp) return s.V == 64 ? s.B <= 192 : s.B <= 256 && (size_t)s.B * s.C * s.C <= 220000;
+    if (trop) return s.V <= 32 || s.V == 64 || s.B <= 256;
+    return s.B <= (s.V <= 16 ? 256 : s.V <= 31 ? 128 : s.V == 32 || s.V == 64 ? INT32_MAX : s.V <= 56 ? 512 : 192);
+}
 
 constexpr size_t kBiBigLds = 2 * kBiMaxC * kBiMaxC * sizeof(float);
 last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int* lengths, bool trop, bool keep, int* bp,
@@ -1047,8 +1063,10 @@ last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int
             if (rc == LAST_OK) hipLaunchKernelGGL(k, dim3(s.B, roles), dim3((D::NC + D::NP) * kWave), lds, st, a);
         };
         if (trop) launch(bigram_kernel<D, true, false>, 1);
-        else if (keep) launch(bigram_kernel<D, false, true>, 2);
-        else launch(bigram_kernel<D, false, false>, 2);
+        else if constexpr (D::N > 64) {
+            if (keep) launch(bigram_kernel<D, false, true>, 2);
+            else launch(bigram_kernel<D, false, false>, 2);
+        } else launch(bigram_kernel<D, false, false>, 2);            // (keep: one wave)
     };
     auto wave = [&](auto DD) {
         typedef decltype(DD) D;
@@ -1062,7 +1080,12 @@ last_status_t launch_bi(const Shape& s, const BiWs& c, const float* w, const int
         else if (keep) launch(bigram_wave_kernel<D, false, true>, 2);
         else launch(bigram_wave_kernel<D, false, false>, 2);
     };
-    if (!bw_ok(s)) go(BiDims<32, 2, 8, 8, 12, 6, 1>());
+    if (!bw_ok(s, trop, keep, bp != nullptr)) {
+        if (s.C > 64) go(BiDims<32, 2, 8, 8, 12, 6, 1>());
+        else if (s.C > 48) go(BiDims<16, 1, 4, 4, 16, 4, 2>());
+        else if (s.C > 32) go(BiDims<16, 1, 4, 4, 12, 3, 2>());
+        else go(BiDims<8, 1, 4, 4, 8, 1, 2>());
+    }
     else if (s.V <= 8) wave(BwNarrow<1>());
     else if (s.V <= 16) wave(BwNarrow<2>());
     else if (s.V <= 32) wave(BwNarrow<4>());
@@ -1968,7 +1991,7 @@ last_status_t last_shortest_path(const last_weights_t* weights, const int32_t* l
         hipLaunchKernelGGL(solo_viterbi, dim3(s.B), dim3(1024), l.lds_viterbi, st, weights->w, lengths,
                            c, s.T, l.CPAD, l.R, p.bp, p.final_state, score, item_status);
     const int cthreads = s.C < 256 ? (s.C + 63) / 64 * 64 : 256;
-    if (bi && bw_ok(s))          // (the chain stored scores in the place of backpointers)
+    if (bi && bw_ok(s, true, false, true))          // (the chain stored scores in the place of backpointers)
         hipLaunchKernelGGL(bigram_bp_kernel, dim3(p.nseg, s.B), dim3(kBpWaves * kWave), 0, st, weights->w, lengths, s.C, s.T,
                            p.S, p.nseg, p.bp, p.map);
     else

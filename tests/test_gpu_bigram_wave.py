@@ -90,3 +90,28 @@ def test_distance_of_weights_that_are_no_number(V):
     got = lb.last_shortest_distance(dev(w), dev(lengths)).cpu().numpy()
     assert np.isnan(got[:2]).all()                           # (0 times NaN: never a number that looks like a distance)
     assert_dist_close(got[2:], oracle.forward(w[2:], lengths[2:], 1)[1])
+
+
+# (labels, most items on one wave) of paths, best scores and distances: both sides of where other kernels take over
+@pytest.mark.parametrize("call,V,B", [("path", 3, 256), ("path", 16, 256), ("path", 20, 256), ("path", 31, 214), ("path", 32, 202), ("path", 47, 95),
+                                      ("path", 48, 91), ("path", 63, 53), ("path", 64, 192), ("score", 33, 256), ("score", 63, 256),
+                                      ("distance", 4, 256), ("distance", 16, 256), ("distance", 17, 128), ("distance", 31, 128),
+                                      ("distance", 33, 512), ("distance", 56, 512), ("distance", 57, 192), ("distance", 63, 192)])
+def test_batches_on_both_sides_of_the_rule(call, V, B):
+    announce("one-wave bigram and more items than it is taken for:", call, V, B)
+    rng = np.random.default_rng(V)
+    T, C = 9, V + 1
+    w = rng.normal(size=(B + 1, T, C, C)).astype(np.float32)
+    w[::2] = np.round(w[::2])                                # (ties)
+    w[rng.random(w.shape) < 0.1] = -np.inf
+    lengths = rng.integers(0, T + 1, size=B + 1).astype(np.int32)
+    for n in (B, B + 1):
+        wd, ld = dev(w[:n]), dev(lengths[:n])
+        if call == "path":
+            for g, x in zip(lb.last_shortest_path(wd, ld), oracle.viterbi(w[:n], lengths[:n], 1, "f32")):
+                assert np.array_equal(g.cpu().numpy(), x)
+        elif call == "score":
+            got = lb.last_shortest_distance(wd, ld, semiring="tropical")
+            assert np.array_equal(got.cpu().numpy(), oracle.viterbi(w[:n], lengths[:n], 1, "f32")[2])
+        else:
+            assert_dist_close(lb.last_shortest_distance(wd, ld).cpu().numpy(), oracle.forward(w[:n], lengths[:n], 1)[1])
