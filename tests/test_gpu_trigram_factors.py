@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2304_13134_amd import binding as lb
 from paper_2304_13134_amd import workloads
-from gpu_util import announce, assert_dist_close, dev
+from gpu_util import announce, assert_dist_close, dev, library_option
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +45,73 @@ def test_weights_far_apart(kind, V):
     # an exponent is a sum of scores of the size of `most`, each rounded to 2^-24 of it: a handful of such errors
     most = max(16.0, float(np.max(np.abs(np.where(np.isfinite(w) & (np.abs(w) < 9.0e3), w, 0.0)))))
     assert np.max(np.abs(g.cpu().numpy() - g_o)) <= max(1.0e-5, 8.0 * T * most * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("V", [12, 20, 36])
+@pytest.mark.parametrize("sigma", [1.0, 3.0, 5.0, 10.0])
+def test_as_precise_as_sums_of_differences(sigma, V):
+    """Marginals where both factors have large arguments: no further from the oracle than those of the general kernel, which takes the
+    exponential of each score's distance from the largest, and to neither side of it."""
+    announce("trigram factors: precision:", sigma, V)
+    B, T, C = 8, 24, workloads.num_states(V, 2)
+    errors, sides = [], []
+    for seed in range(2 if V == 36 else 4):
+        cfg = workloads.dense(B=B, T=T, V=V, order=2, sigma=sigma, seed=10 * V + seed, C=C)
+        want = torch.from_numpy(np.asarray(oracle.posteriors(cfg["w"], cfg["lengths"], 2))).cuda()
+        w, lengths = dev(cfg["w"]), dev(cfg["lengths"])
+
+        def far():
+            off = lb.last_arc_posteriors(w, lengths, order=2)[1].double() - want
+            side = off.sum((1, 2, 3)) / want.sum((1, 2, 3))
+            return (off.flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)).mean().item(), side.mean().item()
+        new = far()
+        with library_option(lb.OPT_FORCE_SOLO, 1):
+            old = far()
+        errors.append((new[0], old[0]))
+        sides.append(new[1])
+    (new, old), side = np.mean(errors, axis=0), np.mean(sides)
+    print("error %.2e / %.2e, mean of the signed errors %+.1e" % (new, old, side), flush=True)
+    assert new <= 0.9 * old
+    # roundings go both ways; a constant that is off (log2 e by 1.3e-8 of itself, for arguments of some 2 sigma) does not
+    assert abs(side) <= 1.0e-7
+
+
+@pytest.mark.parametrize("V", [4, 12, 20, 33, 36, 43])
+@pytest.mark.parametrize("mask", [-7.1e5, -1.0e9, -1.0e10, -3.0e38, float(np.finfo(np.float32).min), -np.inf])
+def test_masks_as_largest_weights(mask, V):
+    """Labels that nothing may emit and histories that nothing may leave: the largest weight of a column or of a row is the mask."""
+    announce("trigram factors: masks:", mask, V)
+    rng = np.random.default_rng(V)
+    B, T, C = 3, 9, workloads.num_states(V, 2)
+    w = rng.normal(size=(B, T, C, V + 1)).astype(np.float32)
+    w[:, :, :, V // 2 + 1] = mask                                    # a label
+    w[:, 1:, 1 + V:1 + V + V // 2] = mask                            # histories (1, 1) to (1, V / 2)
+    w[0, 4, :, 1 + V // 3] = mask                                    # a label in one frame
+    w[1, 3, 2] = mask
+    lengths = np.array([T, T - 1, 4], np.int32)
+    wd, ld = dev(w), dev(lengths)
+    D, g = lb.last_arc_posteriors(wd, ld, order=2)
+    lb.check_item_status()
+    _, D_o = oracle.forward(w, lengths, 2)
+    assert_dist_close(D.cpu().numpy(), D_o)
+    assert_dist_close(lb.last_shortest_distance(wd, ld, order=2).cpu().numpy(), D_o)
+    assert np.max(np.abs(g.cpu().numpy() - oracle.posteriors(w, lengths, 2))) <= 1.0e-5
+
+
+@pytest.mark.parametrize("level", [-3.0e38, -1.0e10, -1.0e9, -6.0e5, 6.0e5, 1.0e9, 2.0e9, 1.0e30])
+@pytest.mark.parametrize("V", [12, 20, 36])
+def test_levels_of_frames(V, level):
+    """One frame all of whose weights are far from the others': the distance is still the sum of both."""
+    announce("trigram factors: levels:", level, V)
+    rng = np.random.default_rng(V)
+    B, T, C = 2, 7, workloads.num_states(V, 2)
+    w = rng.normal(size=(B, T, C, V + 1)).astype(np.float32)
+    w[:, 3] += np.float32(level)
+    lengths = np.array([T, T - 2], np.int32)
+    wd, ld = dev(w), dev(lengths)
+    D, g = lb.last_arc_posteriors(wd, ld, order=2)
+    lb.check_item_status()
+    _, D_o = oracle.forward(w, lengths, 2)
+    assert_dist_close(D.cpu().numpy(), D_o)
+    assert_dist_close(lb.last_shortest_distance(wd, ld, order=2).cpu().numpy(), D_o)
+    assert not np.isnan(g.cpu().numpy()).any()
