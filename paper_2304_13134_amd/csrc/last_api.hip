@@ -1761,8 +1761,17 @@ static last_status_t intersect_impl(const last_weights_t* weights, const int32_t
         }
         if (local)
             with_pieces([&](auto QL) {
-                auto k = num_scatter_local_kernel<decltype(QL)::value>;
-                const size_t need = (size_t)U1 * (sizeof(float2) + 3 * sizeof(int)) + (s.C <= kNsMaxC ? s.C * sizeof(short) : 0);
+                // rows in their order, zeros or not, where the tensor does not stay in the last cache and references visit a good part of the
+                // rows, or nearly all.  Zeros of a frame first / rows in order, us: 16 items, 500 frames, 256 labels, 150 reference labels
+                // 1071 / 1027, 60 811 / 816 (added to what is there 506 / 496); 64 items, 200 frames, 128 labels, 40 457 / 420; 16 items, 200
+                // frames, 32 labels, 60 111 / 108; but 4 items, 200 frames, 255 labels (210 MB), 120 111 / 124; 64 items, 200 frames, 256
+                // labels, 8 added 190 / 209; two-label contexts of 32 labels, 16 items, 200 frames, 40 218 / 253; 20000 states of a table, 5
+                // labels, 8 items, 100 frames, 40 582 / 743.  (Two instantiations: in one kernel either was up to 8 % slower.)
+                const bool ordered = s.C <= kNsMaxC && (U1 >= s.C || ((size_t)5 * U1 >= (size_t)s.C
+                                                                      && (size_t)s.B * s.T * s.C * s.V1 * sizeof(float) >= (size_t)256 << 20));
+                auto k = ordered ? num_scatter_local_kernel<decltype(QL)::value, true> : num_scatter_local_kernel<decltype(QL)::value, false>;
+                const size_t need = (size_t)U1 * (sizeof(float2) + 2 * sizeof(int))
+                                    + (ordered ? s.C * sizeof(short) : U1 * sizeof(int) + (zeroed || out->accumulate ? 0 : s.C));
                 if (need + 64 > kMaxLds) rc = allow_lds((const void*)k, kBigLds - 1024);
                 // eight workgroups a compute unit, as long as each still has 16 KiB of the frame to write, or 128 KiB where
                 // the frames alone are two a compute unit (800 frames of 601 labels 393 -> 333 us, of 131 labels 60 -> 64)

@@ -644,15 +644,15 @@ __global__ void num_scatter_kernel(const float2* __restrict__ wi, const int* __r
 // atomics are needed and the result does not depend on timing.  Rows that no path visits are zero (accumulate:
 // left alone) and are written by the same workgroup, every element of the tensor once.
 // Bound: HBM, the tensor written once and the visited rows read.  B=16, T=500, V=256, 50 to 150 labels: 1.19 -> 0.69 ms
-// against a fill of the whole tensor followed by a wavefront per chain whose cells were fetched one by one.  Rows are
+// against a fill of the whole tensor followed by a wavefront per chain whose cells were fetched one by one.  ORDERED: rows are
 // written in their order, zeros or not (0.705 -> 0.66 ms against the zeros of a frame first): what a frame's zeros leave out costs as much as what they write.  (The
 // zero rows alone, beside the recursion: 1.4 GB in 0.43 ms, while the whole 2.1 GB go in 0.33.)
 // zeroed: the tensor has been filled with zeros by another kernel (context sets too large for `seen`).
-// LDS: float2[U1] marginals | int[U1] heads of visited chains (zeroed) | int[U1] links | int[U1] labels |
-// short[C] head of the row's chain, -1: not visited (unless zeroed).
+// LDS: float2[U1] marginals | int[U1] links | int[U1] labels | ORDERED: short[C] head of the row's chain, -1: not visited; else
+// int[U1] heads of visited chains | unsigned char[C] visited (unless zeroed or accumulated).
 constexpr int kNsThreads = 512;
 constexpr int kNsMaxC = 32768;
-template <int QL>
+template <int QL, bool ORDERED>
 __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     const float* __restrict__ w, const double2* __restrict__ wd, const double* __restrict__ lz,
     const int* __restrict__ len, const int* __restrict__ refs, const int* __restrict__ ulen,
@@ -663,12 +663,12 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     extern __shared__ float2 nsl_p[];
     __shared__ int count, visited;
     const int U1 = Umax + 1;
-    int* heads = (int*)(nsl_p + U1);
-    int* next = heads + U1;                     // next cell of the chain, -1: none
+    int* next = (int*)(nsl_p + U1);             // next cell of the chain, -1: none
     int* label = next + U1;                     // label of the cell's label arc, -1: none
     short* head = (short*)(label + U1);
+    int* heads = label + U1;
+    unsigned char* seen = (unsigned char*)(heads + U1);
     const bool zeros = !accumulate && !zeroed;  // rows no path visits are written here
-    const bool ordered = c.C <= kNsMaxC;        // (else zeroed, or added to what is there)
     const int b = blockIdx.y, t = blockIdx.x, tid = threadIdx.x, part = blockIdx.z, parts = gridDim.z;
     const int wv = tid / kWave, lane = tid & (kWave - 1);
     constexpr int NW = kNsThreads / kWave;
@@ -681,8 +681,11 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
     const int* lk = link + (size_t)b * U1 * 2;
     const int* cx = ctxs + (size_t)b * U1;
     const size_t cell0 = ((size_t)b * T + t) * U1;
-    if (ordered)
+    if constexpr (ORDERED) {
         for (int q = tid; q < c.C; q += kNsThreads) head[q] = -1;
+    } else if (zeros) {
+        for (int q = tid; q < c.C; q += kNsThreads) seen[q] = 0;
+    }
     if (tid == 0) { count = 0; visited = 0; }
     if (live) {
         const double* at = a + ((size_t)b * (T + 1) + t) * U1;
@@ -714,8 +717,12 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             for (int v = u; v >= 0 && !any; v = next[v]) any = nsl_p[v].x >= 0.f;
             if (!any) continue;
             visited = 1;
-            if (ordered) head[cx[u]] = (short)u;                        // (fewer than 4096 labels)
-            else if (u % parts == part) heads[atomicAdd(&count, 1)] = u;     // (the order of the rows does not matter)
+            if constexpr (ORDERED) {
+                head[cx[u]] = (short)u;                                 // (fewer than 4096 labels)
+                continue;
+            }
+            if (u % parts == part) heads[atomicAdd(&count, 1)] = u;     // (the order of the rows does not matter)
+            if (zeros) seen[cx[u]] = 1;
         }
     __syncthreads();
     const int n = live ? count : 0;
@@ -732,6 +739,13 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             return;
         }
     }
+    auto zero_row = [&](float* grow) __attribute__((always_inline)) {
+        struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
+        for (int y = 4 * lane; y < c.V1; y += 4 * kWave)
+            if (c.V1 >= 4) *(f4*)(grow + min(y, c.V1 - 4)) = f4{{0.f, 0.f, 0.f, 0.f}};
+            else
+                for (int k = y; k < c.V1; ++k) grow[k] = 0.f;
+    };
     constexpr int Q = QL > 0 ? QL : 2;
     const NumPieces<Q> p(c.V1, lane);
     auto row = [&](int u, size_t ro, const NumRow<Q>& x) __attribute__((always_inline)) {
@@ -801,7 +815,10 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             }
         }
     };
-    if (!ordered) {
+    if constexpr (!ORDERED) {
+        if (zeros)
+            for (int q = part * NW + wv; q < c.C; q += parts * NW)
+                if (!seen[q]) zero_row(dw + fo + (size_t)q * c.V1);
         auto row_of = [&](int i) __attribute__((always_inline)) { return fo + (size_t)cx[heads[min(i, n - 1)]] * c.V1; };
         NumRow<Q> nx;
         if (QL > 0 && n > 0) nx = num_load_row<Q>(w + row_of(wv), p);
@@ -810,37 +827,32 @@ __global__ __launch_bounds__(kNsThreads) void num_scatter_local_kernel(
             if (QL > 0) nx = num_load_row<Q>(w + row_of(i + NW), p);
             row(heads[i], row_of(i), x);
         }
-        return;
-    }
-    // own rows first + step i; those of the next 64 that are visited as a mask, the weights of the next one requested while one
-    // is worked on
-    const int first = part * NW + wv, step = parts * NW;
-    for (int q0 = first; q0 < c.C; q0 += step * kWave) {
-        const int mine = q0 + step * lane, h = mine < c.C ? head[mine] : -1;
-        unsigned long long m = __ballot(h >= 0);
-        const int rows = min(kWave, (c.C - q0 + step - 1) / step);
-        NumRow<Q> nx;
-        auto request = [&](int i) __attribute__((always_inline)) {
-            if (QL > 0) nx = num_load_row<Q>(w + fo + (size_t)(q0 + step * i) * c.V1, p);
-        };
-        int at = m ? __ffsll(m) - 1 : kWave;
-        if (at < kWave) request(at);
-        for (int i = zeros ? 0 : at; i < rows; zeros ? ++i : i = at) {
-            const size_t ro = fo + (size_t)(q0 + step * i) * c.V1;
-            if (i == at) {
-                const NumRow<Q> x = nx;
-                m &= m - 1;
-                at = m ? __ffsll(m) - 1 : kWave;
-                request(min(at, rows - 1));
-                row(__builtin_amdgcn_readlane(h, i), ro, x);
-                continue;
+    } else {
+        // own rows first + step i; those of the next 64 that are visited as a mask, the weights of the next one requested while one
+        // is worked on
+        const int first = part * NW + wv, step = parts * NW;
+        for (int q0 = first; q0 < c.C; q0 += step * kWave) {
+            const int mine = q0 + step * lane, h = mine < c.C ? head[mine] : -1;
+            unsigned long long m = __ballot(h >= 0);
+            const int rows = min(kWave, (c.C - q0 + step - 1) / step);
+            NumRow<Q> nx;
+            auto request = [&](int i) __attribute__((always_inline)) {
+                if (QL > 0) nx = num_load_row<Q>(w + fo + (size_t)(q0 + step * i) * c.V1, p);
+            };
+            int at = m ? __ffsll(m) - 1 : kWave;
+            if (at < kWave) request(at);
+            for (int i = zeros ? 0 : at; i < rows; zeros ? ++i : i = at) {
+                const size_t ro = fo + (size_t)(q0 + step * i) * c.V1;
+                if (i == at) {
+                    const NumRow<Q> x = nx;
+                    m &= m - 1;
+                    at = m ? __ffsll(m) - 1 : kWave;
+                    request(min(at, rows - 1));
+                    row(__builtin_amdgcn_readlane(h, i), ro, x);
+                    continue;
+                }
+                zero_row(dw + ro);
             }
-            float* grow = dw + ro;
-            struct __attribute__((packed, aligned(4))) f4 { float v[4]; };
-            for (int y = 4 * lane; y < c.V1; y += 4 * kWave)
-                if (c.V1 >= 4) *(f4*)(grow + min(y, c.V1 - 4)) = f4{{0.f, 0.f, 0.f, 0.f}};
-                else
-                    for (int k = y; k < c.V1; ++k) grow[k] = 0.f;
         }
     }
 }

@@ -59,6 +59,28 @@ def test_long_rows_and_chains(V, C):
     assert torch.max(torch.abs(base - (0.25 - 2.0 * g))).item() < 1e-6
 
 
+# rows in order or zeros of a frame first: as many reference labels as rows, one fewer and one more; a frame's rows by several workgroups
+# (300 labels); a tensor of 272 MB with references of a fifth of its rows, and of one label less
+@pytest.mark.parametrize("B,T,V,U", [(3, 12, 3, 2), (3, 12, 3, 3), (3, 12, 3, 4), (2, 40, 32, 31), (2, 40, 32, 32), (2, 40, 32, 33),
+                                     (1, 310, 300, 299), (1, 310, 300, 300), (2, 520, 255, 51), (2, 520, 255, 50)])
+def test_order_of_rows(B, T, V, U):
+    announce("local rows: in order or not: B, T, V, U", B, T, V, U)
+    cfg = workloads.config(3, B=B, T=T, V=V, order=1, Umax=U, u_lo=1, u_hi=U)
+    cfg["lengths"] = np.array([T, T - 1, T - 2][:B], np.int32)
+    cfg["ref_lengths"] = np.array([U, U // 2, 0][:B], np.int32)
+    w, lengths, refs, ulen = (dev(cfg[k]) for k in ("w", "lengths", "refs", "ref_lengths"))
+    lo = oracle.numerator_local(cfg["w"], cfg["lengths"], cfg["refs"], cfg["ref_lengths"], 1)
+    want = torch.from_numpy(lo["grad"]).cuda()
+    g = torch.full_like(w, 7.0)
+    ll = lb.last_local_log_likelihood(w, lengths, refs, ulen, order=1, dw=g)
+    lb.check_item_status()
+    assert_dist_close(ll.cpu().numpy(), lo["N"])
+    assert torch.max(torch.abs(g - want)).item() <= TOL_POST_ABS
+    base = torch.full_like(w, 0.25)
+    lb.last_local_log_likelihood(w, lengths, refs, ulen, order=1, dw=base, accumulate=True)
+    assert torch.max(torch.abs(base - 0.25 - want)).item() <= TOL_POST_ABS
+
+
 # arcs that do not exist and masks: lowest values, and some whose product with log2 e leaves float32 or its whole numbers; rows of one or
 # two pieces a lane, of more, and of less than one.  The weights of what the reference reads stay, so that the likelihood is finite.
 @pytest.mark.parametrize("V", [3, 4, 255, 256, 511, 512, 799])
