@@ -1593,13 +1593,15 @@ last_status_t last_arc_posteriors(const last_weights_t* weights, const int32_t* 
     return hip_status();
 }
 
-// Beside the clusters of a bigram's denominator (beside) two waves: the check of references of up to 512 labels is hidden there
-// however long it takes, and the sooner the gather reads the same weights, the more the clusters lose.  Loss of 16 items, 500 frames, 256 labels
-// 1.532 ms with 128 threads, 1.540 with 256 or 1024; small denominators wait for their numerator.
+// Beside the clusters of a bigram's denominator (beside) a wave for 64 reference labels, two at least: the check is hidden there, and its
+// waves and the gather that follows take from the clusters.  Loss with 1024 / 256 / 128 threads: 16 items, 500 frames, 256 labels, 150
+// reference labels 1554 / 1547 / 1542 us, 32 items 3084 / 3083 / 3072; but 32 items, 600 frames, 128 labels, 500 reference labels 2655 /
+// 2666 / 2740; one item of 20 to 500 frames, 8 of 500, 16 of 100 and 20 of 400 the same with all.  Smaller denominators wait for their
+// numerator: 4 items, 300 frames, 40 labels, 250 reference labels 159 / 176 (256); alone, 16 items, 500 frames, 256 labels 191 / 205.
 static void launch_num_check(const Shape& s, const int* lengths, const int* refs, const int* ref_lengths, int Umax, const NumWs& p,
                              const int* flag, bool beside, hipStream_t st)
 {
-    const int threads = beside && s.order == 1 && s.C > kBiMaxC && Umax <= 512 ? 2 * kWave : kNcThreads;
+    const int threads = beside && s.order == 1 && s.C > kBiMaxC ? std::clamp(Umax / kWave + 1, 2, kNcThreads / kWave) * kWave : kNcThreads;
     const bool table = s.order == 0 && (size_t)s.C * s.V <= (size_t)kNcTable;
     const size_t lds = ((size_t)Umax + 1 + (table ? (size_t)s.C * s.V : 0)) * sizeof(int);
     hipLaunchKernelGGL(num_check_kernel, dim3(s.B), dim3(threads), lds, st, lengths, refs, ref_lengths, make_ctx(s), s.T, Umax,
