@@ -349,7 +349,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
         // waves need of it before its sums; ahead of the chain.  z0: 1 where a small sum is of no account (a column without a weight,
         // whose reference says so, or of the empty label)
         float E[AHEAD ? D::NR : 1][4], z0[4];
-        unsigned exOff[AHEAD ? D::NR : 1][4], bwOff[AHEAD ? D::NR : 1];
+        unsigned exOff[AHEAD ? D::NR : 1][4];
         if constexpr (AHEAD) {
 #pragma unroll
             for (int n = 0; n < D::NR; ++n) {
@@ -358,7 +358,6 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                     exOff[n][c] = 4u * (unsigned)(base(n) + iC[c]);
                     asm volatile("" : "+v"(exOff[n][c]));           // (an instruction less on the chain)
                 }
-                bwOff[n] = 4u * (unsigned)(base(n) + iB);
             }
         }
         auto factors = [&](auto S) __attribute__((always_inline)) {
@@ -372,8 +371,20 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 const float wc[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) mw[c] = fmaxf(mw[c], wc[c]);
-                if (at >= 0) *(float*)((char*)s.bw[Z] + bwOff[AHEAD ? n : 0]) = at == 0 ? wc[0] : at == 1 ? wc[1] : at == 2 ? wc[2] : wc[3];
             }
+            // The empty label's weights, at the places of the states that they are added to.  (Through the states' own offsets: with offsets
+            // of their own the kernel of up to 35 labels took 113 registers.  One gets eight more than 112, and beside two workgroups of it
+            // a SIMD then has no room for a wave of the numerator's gather, beside one for four instead of five: loss on on-the-fly
+            // weights, 16 items, 1024 frames, 32 labels, 512 hidden units 11.25 -> 11.12 ms.)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (at == c) {
+#pragma unroll
+                    for (int n = 0; n < D::NR; ++n) {
+                        const float4 w4 = wv[Z][n];
+                        *(float*)((char*)s.bw[Z] + exOff[AHEAD ? n : 0][c]) = c == 0 ? w4.x : c == 1 ? w4.y : c == 2 ? w4.z : w4.w;
+                    }
+                }
             unsigned large = ~0u;
 #pragma unroll
             for (int c = 0; c < 4; ++c) large = min(large, tri_large(mw[c]));
