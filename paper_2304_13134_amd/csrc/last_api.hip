@@ -746,8 +746,13 @@ last_status_t launch_tri(const Shape& s, const TriPlan& p, const TriWs& c, const
     };
     auto pick = [&](auto DD) {
         typedef decltype(DD) D;
-        if (trop) go(trigram_kernel<D, true>, D::NW * kWave);
-        else go(trigram_kernel<D, false>, D::NW * kWave);
+        if constexpr (D::Ahead || D::NR > 4) {       // (Tri6, Tri7: log semiring)
+            if (trop) {
+                go(trigram_kernel<D, true>, D::NW * kWave);
+                return;
+            }
+        }
+        go(trigram_kernel<D, false>, D::NW * kWave);
     };
     switch (p.dims) {
     case 0: pick(Tri0()); break;

@@ -38,9 +38,9 @@
 // 4 of 16 bytes per arc.
 //
 // Measured: 8 items, 200 to 300 frames, 32 labels, loss with gradient 0.61 ms (0.70 with exponentials on the chain) against
-// 34 ms with one workgroup per item (solo_kernels.hpp), 1.5 us a frame (1.8) and
+// 34 ms with one workgroup per item (solo_kernels.hpp), 1.6 us a frame (1.8) and
 // marginals in 0.11 ms; distance of 4 items, 1000 frames, 64 labels (weights in memory) 1.6 ms on 32 workgroups a direction,
-// 2.1 on 16 that own twice the labels; 6 items, 120 to 250 frames, 28 labels, shortest path 0.36
+// 2.1 on 16 that own twice the labels; 6 items, 120 to 250 frames, 28 labels, shortest path 0.38
 // against 3.7 ms.
 // What made the difference between 3.0 and 1.9 us a frame, before that, is that every weight
 // request and store is issued on every path (the waits for the weights can then

@@ -1,6 +1,6 @@
 """The trigram recursions whose sums are products of exponentials formed ahead of the chain (trigram_kernels.hpp), where those products
-do not hold: weights of a column or row so far apart, or states so far behind, that a sum falls below 2^-60, so that the
-workgroup takes the logarithms.  Against the float64 oracle; distances 1e-5 relative."""
+do not hold: weights of a column or row so far apart, or states so far behind, that a sum falls below 2^-92, so that the
+wave takes the logarithms.  Against the float64 oracle; distances 1e-5 relative."""
 import numpy as np
 import pytest
 import torch
