@@ -249,7 +249,8 @@ constexpr unsigned kTriOut = 0xfffffff0u;
 
 // A sum of products e^x e^(w - m), both factors at most 1, is the sum it stands for as long as it is not below this: what both
 // factors have lost below 2^-126 is 2^-30 of it at most.  Smaller ones (weights far apart, states out of reach) are
-// taken from the logarithms themselves.  A sum of states that no path is in is -0, which stands for itself: their exponentials are -0.
+// taken from the logarithms themselves.  A sum of states that no path is in is -0, which stands for itself: their exponentials are -0;
+// its weights are no reference for the sums of others.
 constexpr float kTriFar = 2.0194839e-28f;      // 2^-92
 // A wave that had one takes the logarithms at once for the next kTriSkip - 1 frames.  Against sums of differences in all frames, 100
 // frames of one item and 60 of eight, without / with that: normal weights, 12 to 40 labels 0.84 to 0.94 / 0.85 to 0.97 of the time,
@@ -284,7 +285,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
     for (int i = tid; i < kTriMaxG * P; i += D::NW * kWave) {      // groups that do not exist stay neutral
         pm[i] = LAST_NEG_INF;
         if (AHEAD) pm[pmz + i] = LAST_NEG_INF;
-        ps[i] = TROP ? __int_as_float(0xffff) : 0.f;
+        ps[i] = TROP ? __int_as_float(0xffff) : AHEAD ? -0.f : 0.f;
     }
     if (tid == 0) { s.dead = 0; s.off = 0.0; s.far[0] = s.far[1] = 0; }
     __syncthreads();
@@ -346,8 +347,8 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
             }
         };
         // log: exponentials of a frame's weights relative to the largest of the thread's rows in a column (tri_ref), and what the exchange
-        // waves need of it before its sums; ahead of the chain.  z0: 1 where a small sum is of no account (a column without a weight,
-        // whose reference says so, or of the empty label)
+        // waves need of it before its sums; ahead of the chain.  z0: negative where a small sum is of no account (a column without a
+        // weight, whose reference makes it -0, or of the empty label)
         float E[AHEAD ? D::NR : 1][4], z0[4];
         unsigned exOff[AHEAD ? D::NR : 1][4];
         if constexpr (AHEAD) {
@@ -413,7 +414,7 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                         E[AHEAD ? n : 0][c] = tri_factor(wc, down);
                     }
                 }
-                z0[c] = m == LAST_NEG_INF || c == at ? 1.f : -0.f;
+                z0[c] = m == LAST_NEG_INF || c == at ? -1.0e30f : -0.f;
             }
             if (act) *(float4*)(pm + Z * pmz + g * P + 4 * cq) = make_float4(mw[0], mw[1], mw[2], mw[3]);
         };
@@ -579,11 +580,11 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
             gstep += 1;
             // log: what the partial sums will have to be multiplied by, while they are formed
             float fz[AHEAD ? kTriMaxG : 1], top = LAST_NEG_INF;
-            auto scales = [&]() __attribute__((always_inline)) {
+            auto scales = [&](auto&& counts) __attribute__((always_inline)) {
                 const float* r = pm + (t & 1) * pmz + slot;
                 top = LAST_NEG_INF;
 #pragma unroll
-                for (int g = 0; g < kTriMaxG; ++g) fz[AHEAD ? g : 0] = r[g * P];
+                for (int g = 0; g < kTriMaxG; ++g) fz[AHEAD ? g : 0] = counts(r[g * P], g);
 #pragma unroll
                 for (int g = 0; g < kTriMaxG; ++g) top = fmaxf(top, fz[AHEAD ? g : 0]);
                 const float mm = fmaxf(top, kTriLeast);
@@ -593,8 +594,9 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                     fz[AHEAD ? g : 0] = fast_exp2(d + d);
                 }
             };
+            auto all = [](float k, int) __attribute__((always_inline)) { return k; };
             if constexpr (AHEAD) {
-                scales();
+                scales(all);
 #pragma unroll
                 for (int g = 0; g < kTriMaxG; ++g) asm volatile("" : "+v"(fz[g]));        // (not put off behind the barrier)
                 asm volatile("" : "+v"(top));
@@ -634,15 +636,25 @@ __device__ __forceinline__ void tri_forward(const TriArgs& a, const TriOwn& o, i
                 val = ln_sum(val, zz);
             } else {
                 if (__builtin_expect(__builtin_amdgcn_readfirstlane(far), 0)) {
-                    scales();
+                    scales(all);
                 }
-                float zz = 0.f, zy = 0.f;
+                auto total = [&]() __attribute__((always_inline)) {
+                    float zz = -0.f, zy = -0.f;
 #pragma unroll
-                for (int g = 0; g < kTriMaxG; g += 2) {
-                    zz = fmaf(z[g], fz[AHEAD ? g : 0], zz);
-                    zy = fmaf(z[g + 1], fz[AHEAD ? g + 1 : 0], zy);
+                    for (int g = 0; g < kTriMaxG; g += 2) {
+                        zz = fmaf(z[g], fz[AHEAD ? g : 0], zz);
+                        zy = fmaf(z[g + 1], fz[AHEAD ? g + 1 : 0], zy);
+                    }
+                    return zz + zy;
+                };
+                float sum = total();
+                // The group with the largest weights may have no state that a path is in, and the others may then be nothing beside them.
+                // (-0: there is no such state at all.)
+                if (__builtin_expect(__any(__float_as_uint(sum) < __builtin_bit_cast(unsigned, kTriFar)), 0)) {
+                    scales([&](float k, int g) __attribute__((always_inline)) { return z[g] <= 0.f ? LAST_NEG_INF : k; });
+                    sum = total();
                 }
-                val = tri_ln(top, zz + zy);
+                val = tri_ln(top, sum);
             }
             const float blg = AHEAD || act ? blr : LAST_NEG_INF;
             // histories of one label: from the start state, or kept by the empty label; the start state: kept

@@ -115,3 +115,31 @@ def test_levels_of_frames(V, level):
     assert_dist_close(D.cpu().numpy(), D_o)
     assert_dist_close(lb.last_shortest_distance(wd, ld, order=2).cpu().numpy(), D_o)
     assert not np.isnan(g.cpu().numpy()).any()
+
+
+# the largest weights of a column belong to histories that no path is in: at the item's start, and where nothing may lead there
+@pytest.mark.parametrize("V", [4, 12, 17, 20, 35, 36, 43])
+@pytest.mark.parametrize("kind", ["start", "label"])
+def test_large_weights_of_histories_that_no_path_is_in(kind, V):
+    announce("trigram factors: weights of histories that no path is in:", kind, V)
+    rng = np.random.default_rng(V)
+    B, T, C = 3, 9, workloads.num_states(V, 2)
+    w = rng.normal(size=(B, T, C, V + 1)).astype(np.float32)
+    if kind == "start":                                      # one label after one frame, two after two
+        w[:, 1, :1 + V] -= 150.0
+        w[:, 1, 1 + V:] += 150.0
+    else:                                                    # histories (a, b) are 1 + V + (a - 1) V + b - 1
+        y = V // 2
+        w[:, :, :, y] = -np.inf
+        w[:, :, 1 + V:] -= 100.0
+        w[:, :, 1 + V + (y - 1) * V:1 + V + y * V] += 300.0
+        w[:, 3, 1 + V + (y - 1) * V] = 600.0
+    lengths = np.array([T, T - 1, 4], np.int32)
+    wd, ld = dev(w), dev(lengths)
+    D, g = lb.last_arc_posteriors(wd, ld, order=2)
+    lb.check_item_status()
+    _, D_o = oracle.forward(w, lengths, 2)
+    assert_dist_close(D.cpu().numpy(), D_o)
+    assert_dist_close(lb.last_shortest_distance(wd, ld, order=2).cpu().numpy(), D_o)
+    # scores of up to 300 T (one is 600), each rounded to 2^-24 of it
+    assert np.max(np.abs(g.cpu().numpy() - oracle.posteriors(w, lengths, 2))) <= 8.0 * T * 300.0 * 2.0 ** -24
